@@ -94,7 +94,12 @@ extern "C" {
 #define THEMIS_PROFILE_EQ1 1 /* coefficients (a,k,q,p,o,d)                      */
 
 /* themis_problem_t.prune: ways of doing less work for the same results; the
-   two may be combined (THEMIS_PRUNE_DOMINATED | THEMIS_PRUNE_STEPS) */
+   two may be combined (THEMIS_PRUNE_DOMINATED | THEMIS_PRUNE_STEPS).  They say
+   what the stage calls do.  The whole-solve entry points solve pipelines of up
+   to 64 models with one wavefront per instance and the recurrence over the
+   total cost instead of the budget, which takes neither tables nor rows, so
+   there the option makes no difference; longer pipelines go through the three
+   stages in the form it names. */
 #define THEMIS_PRUNE_NONE 0      /* every feasible candidate enters the recurrence,
                                     which combines it with every budget          */
 #define THEMIS_PRUNE_DOMINATED 1 /* candidates that another candidate of the same
@@ -154,7 +159,8 @@ int themis_check_problem(const themis_problem_t *p);
  * Bytes of device workspace the solve and stage calls need for `p`
  * (0 if `p` is not acceptable).  The workspace holds the candidate tables
  * (Section 4.4, the per-candidate l, q, h evaluation hoisted out of the
- * budget loop), the DP rows of every model, and one word per instance.
+ * budget loop), the DP rows of every model, and one word per instance; after a
+ * whole solve of up to 64 models per pipeline, its inputs and results instead.
  * It must be 256-byte aligned.  Contents need not be initialised.
  */
 size_t themis_workspace_bytes(const themis_problem_t *p);
@@ -169,7 +175,11 @@ size_t themis_workspace_bytes(const themis_problem_t *p);
  *   d_cost    int32 [N]   total cores, -1 unless solved
  *   d_ticks   int32 [N]   total latency in ticks, -1 unless solved
  *   d_cfg     int32 [N][S][3] = (c, b, n) per model, zeros unless solved
- * Runs the three stages below back to back on `stream`.
+ * The results are those of the three stages below run back to back on `stream`
+ * (see themis_problem_t.prune for how they are computed), and
+ * themis_export_candidates, themis_count_relaxations and themis_stage_backtrack
+ * work on the workspace afterwards as they do after the stages;
+ * themis_stage_minplus needs a themis_stage_candidates first, as always.
  */
 int themis_solve_joint(const themis_problem_t *p, const int32_t *d_coef,
                        const int32_t *d_lambda, const int32_t *d_slo_us,
@@ -372,7 +382,9 @@ int themis_stage_backtrack(const themis_problem_t *p, int32_t *d_status,
  * d_lt, d_cost int32 [N][S][K], K = c_max*n_batch; infeasible entries are -1
  * in both (under THEMIS_PRUNE_DOMINATED the dropped candidates too: what is
  * left is the cost/latency staircase of each row).  The replica count of a
- * feasible entry is cost / c.
+ * feasible entry is cost / c.  After a whole solve that formed no tables they are
+ * built first, in the workspace (`d_workspace` is const for the sake of the
+ * interface only).
  */
 int themis_export_candidates(const themis_problem_t *p, const void *d_workspace,
                              size_t workspace_bytes, int32_t *d_lt, int32_t *d_cost,
@@ -380,7 +392,7 @@ int themis_export_candidates(const themis_problem_t *p, const void *d_workspace,
 
 /*
  * Number of min-plus relaxations stage 2 executes for the tables currently
- * in the workspace, summed over all instances, written to d_count[0]
+ * in the workspace (built first where a whole solve formed none), summed over all instances, written to d_count[0]
  * (d_count: uint64 [3], device): for every valid instance, model and feasible candidate,
  * T + 1 - lt, except for two models that take no relaxations when they
  * have candidates enough to make it pay: the one the recurrence starts with

@@ -21,7 +21,8 @@ LIB_PATH = os.path.join(HERE, "libthemis_hip.so")
 PROBE_LIB_PATH = os.path.join(HERE, "libthemis_probe.so")
 SOURCES = ["themis_api.hip", "k1_candidates.hip", "k2_minplus.hip", "k2_steps.hip",
            "k3_backtrack.hip",
-           "k4_fallback.hip", "k5_stability.hip", "k6_memo.hip"]
+           "k4_fallback.hip", "k5_stability.hip", "k6_memo.hip",
+           "cost_solve.hip"]
 PROBE_SOURCES = [os.path.join(HERE, "probe", "lds_probe.hip")]
 
 HIPCC_FLAGS = [

@@ -21,50 +21,12 @@
 // carry lambda, or when lt exceeds the instance's budget T.
 #include "candidate_eval.h"
 #include "themis_internal.h"
+#include "wave_ops.h"
 
 #include <type_traits>
 
 namespace themis {
 namespace {
-
-
-// Orders the LDS traffic of one wavefront: what its lanes wrote before is
-// visible to all its lanes after (a wavefront's LDS operations complete in
-// order; this only keeps the compiler from moving them across).
-__device__ __forceinline__ void wave_lds_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Inclusive prefix sums (MIN = false) or running minima (MIN = true) over segments
-// of `width` consecutive lanes (a power of two; q = lane within its segment), with
-// the data-parallel primitives instead of LDS permutes: shifts by 1, 2, 4, 8 inside
-// each row of 16 lanes (a lane whose source lies outside its row, or its segment,
-// takes the identity), then the last lane of a row of 16 broadcast to the next row
-// (32-lane segments: rows 1 and 3) and lane 31 to rows 2 and 3 (64).
-template <bool MIN, int CTRL, int ROWS>
-__device__ __forceinline__ uint32_t scan_step(uint32_t x, bool keep)
-{
-    uint32_t t = (uint32_t)__builtin_amdgcn_update_dpp(MIN ? -1 : 0, (int)x, CTRL, ROWS, 0xF, false);
-    if (!keep) t = MIN ? 0xFFFFFFFFu : 0u;
-    return MIN ? (t < x ? t : x) : x + t;
-}
-
-template <bool MIN>
-__device__ __forceinline__ uint32_t segmented_scan(uint32_t x, uint32_t q, uint32_t width)
-{
-    // segments shorter than a row of 16: a shift must not reach into the segment before
-    const bool narrow = width < 16u;
-    if (width > 1u) x = scan_step<MIN, 0x111, 0xF>(x, !narrow || q >= 1u);
-    if (width > 2u) x = scan_step<MIN, 0x112, 0xF>(x, !narrow || q >= 2u);
-    if (width > 4u) x = scan_step<MIN, 0x114, 0xF>(x, !narrow || q >= 4u);
-    if (width > 8u) x = scan_step<MIN, 0x118, 0xF>(x, true);
-    if (width > 16u) x = scan_step<MIN, 0x142 /* row_bcast:15 */, 0xA>(x, true);
-    if (width > 32u) x = scan_step<MIN, 0x143 /* row_bcast:31 */, 0xC>(x, true);
-    return x;
-}
 
 __device__ __forceinline__ int in_range(int32_t v, int32_t lo, int32_t hi)
 {
@@ -147,10 +109,31 @@ __global__ __launch_bounds__(VALIDATE_THREADS) void k1_validate(
     if (cls >= 0) order[(size_t)cls * N + list_base[cls] + within] = (int32_t)i;
 }
 
-// ctrl[0..N_CLS) = instances per class, ctrl[N_CLS..2 N_CLS) = queue cursors
+// ctrl[0..N_CLS) = instances per class, ctrl[N_CLS..2 N_CLS) = queue cursors, then
+// the state word
 __global__ void k1_reset_ctrl(int32_t* ctrl)
 {
-    if (threadIdx.x < 2 * N_CLS) ctrl[threadIdx.x] = 0;
+    if (threadIdx.x <= STATE_WORD) ctrl[threadIdx.x] = 0;
+}
+
+// What a whole solve left in the table region moves to the row region, so that the
+// tables can be built from it (see STATE_WORD).
+__global__ __launch_bounds__(256) void k1_keep_move(const int32_t* __restrict__ ctrl,
+                                                    const int32_t* __restrict__ from,
+                                                    int32_t* __restrict__ to, uint32_t words)
+{
+    if (!(ctrl[STATE_WORD] & STATE_KEPT_IN_TABLE)) return;
+    for (uint32_t x = blockIdx.x * 256u + threadIdx.x; x < words; x += gridDim.x * 256u)
+        to[x] = from[x];
+}
+
+// ... after which the state says that, and whether the launches that follow build.
+__global__ void k1_keep_state(int32_t* ctrl)
+{
+    const int32_t s = ctrl[STATE_WORD];
+    ctrl[STATE_WORD] = (s & STATE_KEPT_IN_TABLE)
+                           ? (s & STATE_GIVEN) | STATE_KEPT_IN_ROWS | STATE_REBUILD
+                           : s & ~STATE_REBUILD;
 }
 
 // The same check for a small batch, by one workgroup that owns the class lists:
@@ -179,6 +162,7 @@ __global__ __launch_bounds__(VALIDATE_SINGLE_THREADS) void k1_validate_single(
         ctrl[threadIdx.x] = listed[threadIdx.x];
         ctrl[N_CLS + threadIdx.x] = 0;
     }
+    if (threadIdx.x == 0) ctrl[STATE_WORD] = 0;
 }
 
 // Candidate evaluation plus a counting sort of each row by bucket.
@@ -284,9 +268,11 @@ __global__ __launch_bounds__(64 * K1_WAVES) __attribute__((amdgpu_waves_per_eu(4
     uint32_t S, uint32_t Kp, uint32_t c_max, uint32_t r_max, uint32_t tick, double rtick,
     int coef_shared, uint32_t lpr_log2, uint32_t split_log2, uint32_t nb, uint32_t nbs,
     uint64_t class_map, int sparse, uint32_t c_all, uint32_t cs, uint32_t s_magic,
-    uint32_t n_groups)
+    uint32_t n_groups, const int32_t* __restrict__ gate, int32_t gate_want)
 {
     extern __shared__ uint32_t smem[];
+    // (after a whole solve) only where there are tables to build, and in this form
+    if (gate && (*gate & (STATE_REBUILD | STATE_GIVEN)) != gate_want) return;
     const uint32_t nbat = (uint32_t)bl.n;
     static_assert(!(PRUNE && ME > 0) && ME % 2 == 0, "pruning works on parked singles");
     const K1Row R = k1_row(Kp, c_max, nbat, nb, ME > 0);
@@ -707,35 +693,19 @@ __global__ __launch_bounds__(256) void k_count_relax(const StepEntry* __restrict
 
 }  // namespace
 
-hipError_t launch_candidates(const themis_problem_t& p, const Layout& L,
-                             const int32_t* d_coef, const int32_t* d_lambda,
-                             const int32_t* d_slo_us, const int32_t* d_r_fixed,
-                             char* ws, hipStream_t st, const PassOpts& opts)
+// The table launch of launch_candidates().  `gate`: null, or a word in device memory
+// that says whether there is anything to do (see STATE_WORD).
+static hipError_t launch_tables(const themis_problem_t& p, const Layout& L, const int32_t* d_coef,
+                                int coef_shared, const int32_t* d_lambda, const int32_t* d_slo_us,
+                                const int32_t* d_r_fixed, const int32_t* c_fixed, int c_all,
+                                int sparse, char* ws, hipStream_t st, const int32_t* gate,
+                                int32_t gate_want)
 {
     BatchList bl{};
     bl.n = p.n_batch;
     for (int j = 0; j < p.n_batch; ++j) bl.b[j] = p.batch_sizes[j];
     const uint32_t cs = p.profile_form == THEMIS_PROFILE_EQ1 ? 6u : 5u;
-    int32_t* tmeta = (int32_t*)(ws + L.tmeta_off);
-    int32_t* ctrl = (int32_t*)(ws + L.ctrl_off);
     const MinplusPlan plan = make_plan(L);
-    if ((uint32_t)L.N <= VALIDATE_SINGLE_MAX) {
-        hipLaunchKernelGGL(k1_validate_single, dim3(1), dim3(VALIDATE_SINGLE_THREADS), 0, st,
-                           d_coef, d_lambda, d_slo_us, d_r_fixed, opts.c_fixed, tmeta,
-                           (int32_t*)(ws + L.ans_off), (int32_t*)(ws + L.order_off), ctrl,
-                           (uint32_t)L.N, (uint32_t)L.S, p.r_max, p.c_max, (uint32_t)p.tick_us,
-                           p.slo_max_us, p.coef_shared, cs);
-    } else {
-        hipLaunchKernelGGL(k1_reset_ctrl, dim3(1), dim3(64), 0, st, ctrl);
-        hipLaunchKernelGGL(k1_validate, dim3((L.N + VALIDATE_THREADS - 1) / VALIDATE_THREADS),
-                           dim3(VALIDATE_THREADS), 0, st, d_coef, d_lambda, d_slo_us, d_r_fixed,
-                           opts.c_fixed, tmeta, (int32_t*)(ws + L.ans_off),
-                           (int32_t*)(ws + L.order_off), ctrl, (uint32_t)L.N, (uint32_t)L.S,
-                           p.r_max, p.c_max, (uint32_t)p.tick_us, p.slo_max_us, p.coef_shared, cs);
-    }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-
     const bool prune = (p.prune & THEMIS_PRUNE_DOMINATED) != 0;
     // Lanes per row: enough to give every batch size a lane, and beyond that enough
     // to leave a lane about sixteen candidates.  Fewer lanes per row spread the
@@ -789,13 +759,14 @@ hipError_t launch_candidates(const themis_problem_t& p, const Layout& L,
                                              hipFuncAttributeMaxDynamicSharedMemorySize, 152 * 1024);
         if (err != hipSuccess) return err;
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * waves), lds, st, d_coef,
-                           d_lambda, d_slo_us, d_r_fixed, opts.c_fixed, (const int32_t*)tmeta,
+                           d_lambda, d_slo_us, d_r_fixed, c_fixed,
+                           (const int32_t*)(ws + L.tmeta_off),
                            (StepEntry*)(ws + L.step_off), (uint16_t*)(ws + L.bcum_off), bl, rows,
                            (uint32_t)L.S, (uint32_t)L.Kp, (uint32_t)p.c_max,
                            (uint32_t)p.r_max, (uint32_t)p.tick_us,
-                           (1.0 / (double)p.tick_us) * (1.0 - 0x1p-45), p.coef_shared, lpr_log2,
+                           (1.0 / (double)p.tick_us) * (1.0 - 0x1p-45), coef_shared, lpr_log2,
                            split_log2, (uint32_t)L.nb, (uint32_t)L.nbs, plan.class_map,
-                           opts.sparse, (uint32_t)opts.c_all, cs, s_magic, n_groups);
+                           sparse, (uint32_t)c_all, cs, s_magic, n_groups, gate, gate_want);
         return hipGetLastError();
     };
     const bool derive = d_r_fixed == nullptr;
@@ -819,6 +790,58 @@ hipError_t launch_candidates(const themis_problem_t& p, const Layout& L,
         return by_replicas(std::integral_constant<int, THEMIS_QUEUE_WORST_CASE>{});
     default: return hipErrorInvalidValue;
     }
+}
+
+hipError_t launch_candidates(const themis_problem_t& p, const Layout& L,
+                             const int32_t* d_coef, const int32_t* d_lambda,
+                             const int32_t* d_slo_us, const int32_t* d_r_fixed,
+                             char* ws, hipStream_t st, const PassOpts& opts)
+{
+    const uint32_t cs = p.profile_form == THEMIS_PROFILE_EQ1 ? 6u : 5u;
+    int32_t* tmeta = (int32_t*)(ws + L.tmeta_off);
+    int32_t* ctrl = (int32_t*)(ws + L.ctrl_off);
+    if ((uint32_t)L.N <= VALIDATE_SINGLE_MAX) {
+        hipLaunchKernelGGL(k1_validate_single, dim3(1), dim3(VALIDATE_SINGLE_THREADS), 0, st,
+                           d_coef, d_lambda, d_slo_us, d_r_fixed, opts.c_fixed, tmeta,
+                           (int32_t*)(ws + L.ans_off), (int32_t*)(ws + L.order_off), ctrl,
+                           (uint32_t)L.N, (uint32_t)L.S, p.r_max, p.c_max, (uint32_t)p.tick_us,
+                           p.slo_max_us, p.coef_shared, cs);
+    } else {
+        hipLaunchKernelGGL(k1_reset_ctrl, dim3(1), dim3(64), 0, st, ctrl);
+        hipLaunchKernelGGL(k1_validate, dim3((L.N + VALIDATE_THREADS - 1) / VALIDATE_THREADS),
+                           dim3(VALIDATE_THREADS), 0, st, d_coef, d_lambda, d_slo_us, d_r_fixed,
+                           opts.c_fixed, tmeta, (int32_t*)(ws + L.ans_off),
+                           (int32_t*)(ws + L.order_off), ctrl, (uint32_t)L.N, (uint32_t)L.S,
+                           p.r_max, p.c_max, (uint32_t)p.tick_us, p.slo_max_us, p.coef_shared, cs);
+    }
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+
+    return launch_tables(p, L, d_coef, p.coef_shared, d_lambda, d_slo_us, d_r_fixed, opts.c_fixed,
+                         opts.c_all, opts.sparse, ws, st, nullptr, 0);
+}
+
+hipError_t launch_tables_after_solve(const themis_problem_t& p, const Layout& L, char* ws,
+                                     hipStream_t st)
+{
+    if (!cost_solve_serves(L)) return hipSuccess;  // the three stages did it: tables are there
+    int32_t* const ctrl = (int32_t*)(ws + L.ctrl_off);
+    int32_t* const rows = (int32_t*)(ws + L.frow_off);
+    const KeepLayout k = make_keep_layout(p, L);
+    const uint32_t blocks = (k.words + 255u) / 256u;
+    hipLaunchKernelGGL(k1_keep_move, dim3(blocks < 4096u ? blocks : 4096u), dim3(256), 0, st,
+                       (const int32_t*)ctrl, (const int32_t*)(ws + L.step_off), rows, k.words);
+    hipLaunchKernelGGL(k1_keep_state, dim3(1), dim3(1), 0, st, ctrl);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    // instances that failed the input check have a budget of -1 in tmeta
+    for (int given = 0; given < 2; ++given) {
+        e = launch_tables(p, L, rows + k.coef, 0, rows + k.lam, rows + k.slo,
+                          given ? rows + k.given : nullptr, rows + k.only, 0, 0, ws, st,
+                          ctrl + STATE_WORD, STATE_REBUILD | (given ? STATE_GIVEN : 0));
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_export_candidates(const Layout& L, const char* ws, int32_t* d_lt,

@@ -1092,15 +1092,6 @@ __global__ __launch_bounds__(NAR_NW * 64) void k2_minplus_narrow(
     }
 }
 
-int cu_count()
-{
-    int dev = 0, n = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 256;
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1)
-        return 256;
-    return n;
-}
-
 constexpr size_t LDS_PER_CU = 160 * 1024;
 
 inline size_t wide_lds_bytes(int waves, int cand_buf)
@@ -1159,10 +1150,19 @@ hipError_t launch_wide_class(const Layout& L_, char* ws, hipStream_t st, int c, 
 
 }  // namespace
 
+int compute_units()
+{
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 256;
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1)
+        return 256;
+    return n;
+}
+
 MinplusPlan make_plan(const Layout& L_)
 {
     MinplusPlan pl{};
-    pl.cus = cu_count();
+    pl.cus = compute_units();
     pl.top = class_of_budget(L_.t_max);
     pl.top_wide = pl.top == NARROW_CLS ? N_WIDE_CLS - 1 : pl.top;
     // A batch that fills less than half of the chip even with workgroups of twice

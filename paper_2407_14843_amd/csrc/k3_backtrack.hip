@@ -27,7 +27,7 @@ __global__ __launch_bounds__(256) void k3_backtrack(
     int32_t* __restrict__ status,
     int32_t* __restrict__ cost_out, int32_t* __restrict__ ticks_out, int32_t* __restrict__ cfg,
     BatchList bl, int N, int S, int Kp, int nbs, int row_stride, uint64_t class_map,
-    int sparse)
+    int sparse, const int32_t* __restrict__ state, KeepLayout kept)
 {
     static_assert(LANES == 8 || LANES == 16 || LANES == 32 || LANES == 64, "a power-of-two part of a wavefront");
     const int lane = threadIdx.x & (LANES - 1);
@@ -36,6 +36,20 @@ __global__ __launch_bounds__(256) void k3_backtrack(
     if (i >= N) return;
 
     int32_t* my_cfg = cfg + (size_t)i * S * 3;
+    const int32_t kind = *state;
+    if (kind & (STATE_KEPT_IN_TABLE | STATE_KEPT_IN_ROWS)) {
+        // no rows here: the workspace holds the results of a whole solve
+        const int32_t* const kp = (kind & STATE_KEPT_IN_TABLE)
+                                      ? reinterpret_cast<const int32_t*>(step_tab)
+                                      : reinterpret_cast<const int32_t*>(frow);
+        for (int x = lane; x < S * 3; x += LANES) my_cfg[x] = kp[kept.cfg + (size_t)i * S * 3 + x];
+        if (lane == 0) {
+            status[i] = kp[kept.status + i];
+            cost_out[i] = kp[kept.cost + i];
+            ticks_out[i] = kp[kept.ticks + i];
+        }
+        return;
+    }
 
     const int T = tmeta[i];
     const int ans_cost = ans[2 * i], ans_t = ans[2 * i + 1];  // set for every instance by stage 1
@@ -185,7 +199,9 @@ hipError_t launch_backtrack(const themis_problem_t& p, const Layout& L, int32_t*
                            (const StepEntry*)(ws + L.step_off), (const uint16_t*)(ws + L.bcum_off),
                            (const int32_t*)(ws + L.tmeta_off), (const uint16_t*)(ws + L.frow_off),
                            (const int32_t*)(ws + L.ans_off), d_status, d_cost, d_ticks, d_cfg, bl,
-                           L.N, L.S, L.Kp, L.nbs, L.row_stride, plan.class_map, opts.sparse);
+                           L.N, L.S, L.Kp, L.nbs, L.row_stride, plan.class_map, opts.sparse,
+                           (const int32_t*)(ws + L.ctrl_off) + STATE_WORD,
+                           make_keep_layout(p, L));
         return hipGetLastError();
     };
     if (lanes == 8) return launch(&k3_backtrack<8>, 32);

@@ -55,12 +55,18 @@ int check_ws(const themis_problem_t* p, const void* ws, size_t bytes, Layout* L)
     return THEMIS_OK;
 }
 
-// one pass of the three stages
+// one solve of every instance: by the one-wavefront solve where it serves the
+// problem, else by the three stages
 int pass(const themis_problem_t& p, const Layout& L, const int32_t* d_coef,
          const int32_t* d_lambda, const int32_t* d_slo_us, const int32_t* d_r_fixed,
          int32_t* d_status, int32_t* d_cost, int32_t* d_ticks, int32_t* d_cfg, char* w,
          hipStream_t st, const PassOpts& opts)
 {
+    if (cost_solve_serves(L))
+        return launch_cost_solve(p, L, d_coef, d_lambda, d_slo_us, d_r_fixed, d_status, d_cost,
+                                 d_ticks, d_cfg, w, st, opts) == hipSuccess
+                   ? THEMIS_OK
+                   : THEMIS_ERR_LAUNCH;
     if (launch_candidates(p, L, d_coef, d_lambda, d_slo_us, d_r_fixed, w, st, opts) != hipSuccess)
         return THEMIS_ERR_LAUNCH;
     if (launch_minplus(p, L, w, st) != hipSuccess) return THEMIS_ERR_LAUNCH;
@@ -140,8 +146,10 @@ int themis_solve_joint_static(const themis_problem_t* p, const int32_t* d_coef,
     void* ws = nullptr;
     rc = static_scratch(&ws);
     if (rc != THEMIS_OK) return rc;
+    PassOpts opts;
+    opts.inspectable = false;
     return pass(*p, L, d_coef, d_lambda, d_slo_us, nullptr, d_status, d_cost, d_ticks, d_cfg,
-                static_cast<char*>(ws), static_cast<hipStream_t>(stream), PassOpts());
+                static_cast<char*>(ws), static_cast<hipStream_t>(stream), opts);
 }
 
 int themis_solve_vertical(const themis_problem_t* p, const int32_t* d_coef,
@@ -349,6 +357,11 @@ int themis_export_candidates(const themis_problem_t* p, const void* d_workspace,
     Layout L;
     int rc = check_ws(p, d_workspace, workspace_bytes, &L);
     if (rc != THEMIS_OK) return rc;
+    // after a whole solve the tables are built first (the workspace is the caller's
+    // device memory, whatever the pointer's type says)
+    if (launch_tables_after_solve(*p, L, static_cast<char*>(const_cast<void*>(d_workspace)),
+                                  static_cast<hipStream_t>(stream)) != hipSuccess)
+        return THEMIS_ERR_LAUNCH;
     return launch_export_candidates(L, static_cast<const char*>(d_workspace), d_lt, d_cost,
                                     static_cast<hipStream_t>(stream)) == hipSuccess
                ? THEMIS_OK
@@ -362,6 +375,11 @@ int themis_count_relaxations(const themis_problem_t* p, const void* d_workspace,
     Layout L;
     int rc = check_ws(p, d_workspace, workspace_bytes, &L);
     if (rc != THEMIS_OK) return rc;
+    // after a whole solve the tables are built first (the workspace is the caller's
+    // device memory, whatever the pointer's type says)
+    if (launch_tables_after_solve(*p, L, static_cast<char*>(const_cast<void*>(d_workspace)),
+                                  static_cast<hipStream_t>(stream)) != hipSuccess)
+        return THEMIS_ERR_LAUNCH;
     return launch_count_relaxations(*p, L, static_cast<const char*>(d_workspace), d_count,
                                     static_cast<hipStream_t>(stream)) == hipSuccess
                ? THEMIS_OK

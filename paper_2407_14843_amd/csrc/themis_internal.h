@@ -162,7 +162,8 @@ MinplusPlan make_plan(const Layout& L);
 //   ans    int32 [N][2]        least cost and least latency attaining it, where stage 2
 //                              finds them itself; latency -1 = stage 3 reads them off row 0
 //   order  int32 [N_CLS][N]    instance ids grouped by work class
-//   ctrl   int32 [2][N_CLS]    per class: number of instances, queue cursor
+//   ctrl   int32 [2][N_CLS]    per class: number of instances, queue cursor; then the
+//                              state word, see STATE_WORD (the region is 256 bytes)
 struct Layout {
     size_t step_off, bcum_off, frow_off, tmeta_off, ans_off, order_off, ctrl_off, total;
     int32_t N, S, K, Kp, t_max, row_stride, nb, nbs;
@@ -200,6 +201,43 @@ inline Layout make_layout(const themis_problem_t& p)
     return L;
 }
 
+// ---- what a whole solve leaves in the workspace ----------------------------------
+// The one-wavefront solve (cost_solve.hip) forms neither tables nor rows.  For the
+// calls that look at the workspace after a solve it leaves its inputs and results
+// instead (at most 52 bytes per row and 12 per instance, of the 64 a row of the
+// table region has at least) and says so in the state word:
+//   0                     tables (and rows) of the stage calls
+//   STATE_KEPT_IN_TABLE   inputs and results in the table region; no tables
+//   STATE_KEPT_IN_ROWS    the same in the row region; tables built from them
+// Export and count first build the tables where there are none (launch_tables_after_solve);
+// the backtrack call then hands out the results.  Budgets are in tmeta in every state.
+constexpr int STATE_WORD = 2 * N_CLS;
+constexpr int STATE_KEPT_IN_TABLE = 1, STATE_KEPT_IN_ROWS = 2;
+constexpr int STATE_GIVEN = 4;    // the replicas were given
+constexpr int STATE_REBUILD = 8;  // the candidate launches that follow have work to do
+
+struct KeepLayout {  // in int32 words from the start of the region
+    uint32_t coef, given, only, lam, slo, status, cost, ticks, cfg, words;
+};
+
+inline KeepLayout make_keep_layout(const themis_problem_t& p, const Layout& L)
+{
+    KeepLayout k{};
+    const uint32_t n = (uint32_t)L.N, rows = n * (uint32_t)L.S;  // rows * Kp < 2^31, Kp >= 8
+    uint32_t at = 0;
+    k.coef = at;   at += rows * (p.profile_form == THEMIS_PROFILE_EQ1 ? 6u : 5u);
+    k.given = at;  at += rows;
+    k.only = at;   at += rows;
+    k.lam = at;    at += n;
+    k.slo = at;    at += n;
+    k.status = at; at += n;
+    k.cost = at;   at += n;
+    k.ticks = at;  at += n;
+    k.cfg = at;    at += 3u * rows;
+    k.words = at;
+    return k;
+}
+
 struct BatchList {
     int32_t n;
     int32_t b[THEMIS_MAX_BATCH];
@@ -213,11 +251,27 @@ struct BatchList {
 //            (no table rows, no outputs written) instead of being reported;
 //            used by multi-pass solves that switch instances off by handing
 //            them an arrival rate of zero
+//   inspectable  see STATE_WORD
 struct PassOpts {
     const int32_t* c_fixed = nullptr;
     int c_all = 0;  // nonzero and c_fixed null: these cores for every model
     int sparse = 0;
+    bool inspectable = true;  // the caller can look at the workspace afterwards
 };
+
+// The one-wavefront solve: three stages' worth of results in one or two launches.
+constexpr int COST_MAX_STAGES = 64;  // a lane per model
+bool cost_solve_serves(const Layout& L);
+hipError_t launch_cost_solve(const themis_problem_t& p, const Layout& L, const int32_t* d_coef,
+                             const int32_t* d_lambda, const int32_t* d_slo_us,
+                             const int32_t* d_r_fixed, int32_t* d_status, int32_t* d_cost,
+                             int32_t* d_ticks, int32_t* d_cfg, char* ws, hipStream_t st,
+                             const PassOpts& opts);
+// The candidate tables of the last whole solve on this workspace, where it left none;
+// nothing otherwise (decided on the device).
+hipError_t launch_tables_after_solve(const themis_problem_t& p, const Layout& L, char* ws,
+                                     hipStream_t st);
+int compute_units();  // of the current device
 
 // kernel launchers (one per stage), defined next to their kernels
 hipError_t launch_candidates(const themis_problem_t& p, const Layout& L,

@@ -1,0 +1,134 @@
+"""GPU parity of the one-wavefront solve where its branches meet, and the calls that
+look at the workspace after a solve.  Whole numbers: no tolerance."""
+
+import numpy as np
+import pytest
+
+from cost_families import families, over_base
+from paper_2407_14843_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+NAMES = ("status", "cost", "ticks", "cfg")
+
+
+@pytest.fixture(scope="module")
+def T():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    from paper_2407_14843_amd import themis
+    themis.lib()
+    return themis
+
+
+def same(got, want):
+    for n, g, x in zip(NAMES, got, want):
+        bad = np.nonzero((g != x).reshape(len(x), -1).any(axis=1))[0]
+        assert bad.size == 0, f"{n} differs at {bad[:8]}: got {g[bad[:2]]}, want {x[bad[:2]]}"
+
+
+# 300 instances are solved by one launch, 1500 by one with a window of 64 cells and a
+# second one for what that leaves over
+@pytest.mark.parametrize("n", [1, 300, 1500])
+@pytest.mark.parametrize("name", list(families(1)))
+def test_windows(T, oracle, name, n):
+    w = families(n)[name]
+    want = oracle.solve(w, threads=8)
+    print(f"[case] {name} N={n}", flush=True)
+    b = T.DeviceBatch(w)
+    b.solve()
+    same(b.results(), want)
+
+
+def test_windows_are_met(oracle):
+    """The batches above reach every branch: nothing over the least cost, inside and on
+    both sides of the end of the first window, wider ones, and beyond any in LDS."""
+    x = np.concatenate([over_base(w, oracle, oracle.solve(w, threads=8))
+                        for w in families(1500).values()])
+    for lo, hi in ((0, 0), (1, 62), (63, 63), (64, 64), (65, 255), (256, 1023), (8192, 32767)):
+        assert ((x >= lo) & (x <= hi)).any(), (lo, hi)
+
+
+@pytest.mark.parametrize("n_stage", [1, 2, 63, 64, 65])
+def test_model_counts(T, oracle, n_stage):
+    """A lane per model up to 64; more take the three stages."""
+    rng = np.random.default_rng(n_stage)
+    n = 37
+    coef = wl._draw_coef(rng, (n, n_stage), a=(1000, 9000), k=(100, 1000), q=(0, 10), p=(1, 3),
+                         o=(1, 500))
+    w = wl.Workload("models", wl.JOINT, n, n_stage, 3, [1, 2, 3], 20, 1000, 900_000, False, coef,
+                    rng.integers(1, 900, n).astype(np.int32),
+                    rng.integers(0, 900_001, n).astype(np.int32))
+    b = T.DeviceBatch(w)
+    b.solve()
+    want = oracle.solve(w, threads=8)
+    same(b.results(), want)
+    assert (want[0] == 0).any()
+
+
+def staged(T, w, prune):
+    """tables and counts after the candidate stage"""
+    b = T.DeviceBatch(w, prune=prune)
+    T.themis_stage_candidates(b.p, b.coef, b.lam, b.slo_us, b.r_fixed, b.workspace)
+    return inspect(T, b)
+
+
+def inspect(T, b):
+    import torch
+    shape = (b.p.n_inst, b.p.n_stage, b.w.n_cand)
+    lt = torch.empty(shape, dtype=torch.int32, device=b.device)
+    co = torch.empty(shape, dtype=torch.int32, device=b.device)
+    cnt = torch.empty(3, dtype=torch.int64, device=b.device)
+    T.themis_export_candidates(b.p, b.workspace, lt, co)
+    T.themis_count_relaxations(b.p, b.workspace, cnt)
+    torch.cuda.synchronize()
+    return lt.cpu().numpy(), co.cpu().numpy(), cnt.cpu().numpy()
+
+
+def backtrack(T, b):
+    out = T.alloc_outputs(b.p, b.device)
+    T.themis_stage_backtrack(b.p, *out, b.workspace)
+    return tuple(o.cpu().numpy() for o in out)
+
+
+@pytest.mark.parametrize("prune", [0, 1])
+@pytest.mark.parametrize("idx,n", [(0, 64), (2, 70), (3, 1100), (4, 1030)])
+def test_workspace_after_a_solve(T, oracle, idx, n, prune):
+    """Tables, counts and results can be had from the workspace after a solve as after
+    the stage calls, in any order, and the stage calls work on it afterwards."""
+    w = wl.workload(idx, n)
+    w.lam[3] = 0  # an invalid instance
+    print(f"[case] inspect workload {idx} N={n} prune={prune}", flush=True)
+    lt_w, co_w, cnt_w = staged(T, w, prune)
+    want = oracle.solve(w, threads=8)
+    b = T.DeviceBatch(w, prune=prune)
+    for order in ("tables first", "results first"):
+        b.solve()
+        same(b.results(), want)
+        if order == "results first":
+            same(backtrack(T, b), want)
+        for _ in range(2):
+            lt, co, cnt = inspect(T, b)
+            assert (lt == lt_w).all() and (co == co_w).all() and (cnt == cnt_w).all()
+            T.themis_stage_minplus(b.p, b.workspace)  # nothing is listed: no effect
+            same(backtrack(T, b), want)
+    T.themis_stage_candidates(b.p, b.coef, b.lam, b.slo_us, b.r_fixed, b.workspace)
+    T.themis_stage_minplus(b.p, b.workspace)
+    same(backtrack(T, b), want)
+
+
+def test_workspace_after_a_horizontal_solve(T, oracle):
+    w = wl.workload(1, 50)
+    rng = np.random.default_rng(1)
+    cores = rng.integers(1, w.c_max + 1, (w.n_inst, w.n_stage)).astype(np.int32)
+    b = T.DeviceBatch(w)
+    b.solve_horizontal(cores)
+    want = oracle.solve(w, threads=8, c_fixed=cores)
+    same(b.results(), want)
+    lt, co, _ = inspect(T, b)
+    lt_o, co_o, _ = oracle.candidates(w)
+    c = np.arange(w.n_cand) // len(w.batch_sizes) + 1
+    mine = c[None, None] == cores[..., None]
+    assert (lt == np.where(mine, lt_o, -1)).all()
+    assert (co == np.where(mine & (lt_o >= 0), co_o, -1)).all()
+    same(backtrack(T, b), want)
