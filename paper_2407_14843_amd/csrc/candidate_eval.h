@@ -94,19 +94,21 @@ struct Eval {
 // (vertical, h.n_given), or N_EITHER (h.n_given decides at run time).
 constexpr int N_EITHER = 0, N_DERIVED = 1, N_GIVEN = 2;
 
+// The candidate's own part of the arithmetic is in eval_parts(): num = a + k b + q b^2
+// and fixed = d b + o are the same for all cores of a batch size.
 template <int QUEUE, bool SMALL, int NMODE>
-__device__ __forceinline__ Eval eval_candidate_rd(const RowHdr& h, const BatchHdr& bh, double d,
-                                                  double rd, double r_max, double tick,
-                                                  double rtick)
+__device__ __forceinline__ Eval eval_parts(const RowHdr& h, const BatchHdr& bh, double num,
+                                           double fixed, double rd, double r_max, double tick,
+                                           double rtick)
 {
     // Straight-line: every test only clears a bit of `ok`, so the lanes of a
     // wavefront stay together.  A candidate that fails an early test may push
     // later intermediates past 2^53; they are then inexact but never used.
-    const double num = __builtin_fma(h.q, bh.b2, __builtin_fma(h.k, bh.b, h.a));  // < 2^41
-    const double proc = ceil_div_small(num, rd) + __builtin_fma(h.d, bh.b, h.o);
+    const double proc = ceil_div_small(num, rd) + fixed;  // num < 2^41
     // anything slower than the SLO also exceeds T ticks; cutting it here keeps
     // every later product of a surviving candidate below 2^53
-    int ok = (int)(proc <= h.slo);
+    // (under SMALL the last division shows it too, see above)
+    int ok = SMALL && QUEUE != THEMIS_QUEUE_WORST_CASE ? 1 : (int)(proc <= h.slo);
     const double lp = h.lam * proc;  // < 2^51
     const bool derive = NMODE == N_DERIVED || (NMODE == N_EITHER && h.n_given <= 0.0);
     // least n with lambda <= n * b / proc; at least 1 since lambda * proc >= 1
@@ -139,6 +141,16 @@ __device__ __forceinline__ Eval eval_candidate_rd(const RowHdr& h, const BatchHd
     }
     ok &= (int)(lt <= h.T);
     return Eval{ok ? (int32_t)lt : -1, ok ? (int32_t)n : 0};
+}
+
+template <int QUEUE, bool SMALL, int NMODE>
+__device__ __forceinline__ Eval eval_candidate_rd(const RowHdr& h, const BatchHdr& bh, double d,
+                                                  double rd, double r_max, double tick,
+                                                  double rtick)
+{
+    const double num = __builtin_fma(h.q, bh.b2, __builtin_fma(h.k, bh.b, h.a));
+    const double fixed = __builtin_fma(h.d, bh.b, h.o);
+    return eval_parts<QUEUE, SMALL, NMODE>(h, bh, num, fixed, rd, r_max, tick, rtick);
 }
 
 template <int QUEUE>

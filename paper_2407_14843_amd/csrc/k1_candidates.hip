@@ -120,10 +120,10 @@ __global__ void k1_reset_ctrl(int32_t* ctrl)
 // tables can be built from it (see STATE_WORD).
 __global__ __launch_bounds__(256) void k1_keep_move(const int32_t* __restrict__ ctrl,
                                                     const int32_t* __restrict__ from,
-                                                    int32_t* __restrict__ to, uint32_t words)
+                                                    int32_t* __restrict__ to, size_t words)
 {
     if (!(ctrl[STATE_WORD] & STATE_KEPT_IN_TABLE)) return;
-    for (uint32_t x = blockIdx.x * 256u + threadIdx.x; x < words; x += gridDim.x * 256u)
+    for (size_t x = blockIdx.x * 256u + threadIdx.x; x < words; x += gridDim.x * 256u)
         to[x] = from[x];
 }
 
@@ -132,7 +132,7 @@ __global__ void k1_keep_state(int32_t* ctrl)
 {
     const int32_t s = ctrl[STATE_WORD];
     ctrl[STATE_WORD] = (s & STATE_KEPT_IN_TABLE)
-                           ? (s & STATE_GIVEN) | STATE_KEPT_IN_ROWS | STATE_REBUILD
+                           ? (s & ~STATE_KEPT_IN_TABLE) | STATE_KEPT_IN_ROWS | STATE_REBUILD
                            : s & ~STATE_REBUILD;
 }
 
@@ -268,11 +268,16 @@ __global__ __launch_bounds__(64 * K1_WAVES) __attribute__((amdgpu_waves_per_eu(4
     uint32_t S, uint32_t Kp, uint32_t c_max, uint32_t r_max, uint32_t tick, double rtick,
     int coef_shared, uint32_t lpr_log2, uint32_t split_log2, uint32_t nb, uint32_t nbs,
     uint64_t class_map, int sparse, uint32_t c_all, uint32_t cs, uint32_t s_magic,
-    uint32_t n_groups, const int32_t* __restrict__ gate, int32_t gate_want)
+    uint32_t n_groups, const int32_t* __restrict__ gate, int32_t gate_want,
+    uint32_t record)
 {
     extern __shared__ uint32_t smem[];
     // (after a whole solve) only where there are tables to build, and in this form
-    if (gate && (*gate & (STATE_REBUILD | STATE_GIVEN)) != gate_want) return;
+    if (gate) {
+        const int32_t state = *gate;
+        if ((state & (STATE_REBUILD | STATE_GIVEN)) != gate_want) return;
+        if (!(state & STATE_ONLY)) c_fixed = nullptr, c_all = (uint32_t)state >> STATE_C_ALL;
+    }
     const uint32_t nbat = (uint32_t)bl.n;
     static_assert(!(PRUNE && ME > 0) && ME % 2 == 0, "pruning works on parked singles");
     const K1Row R = k1_row(Kp, c_max, nbat, nb, ME > 0);
@@ -307,11 +312,14 @@ __global__ __launch_bounds__(64 * K1_WAVES) __attribute__((amdgpu_waves_per_eu(4
         const uint32_t s = row - i * S;
         K1RowIn in;
         in.T = tmeta[i];
-        in.lam = lambda[i];
-        in.slo = slo_us[i];
-        in.n_given = DERIVE ? 0 : r_fixed[row];
-        in.only = c_fixed ? c_fixed[row] : (int32_t)c_all;
-        const int32_t* cf = coef + (coef_shared ? 0 : (size_t)i * S * cs) + s * cs;
+        // one array each, or `record` words per instance with everything in them
+        const size_t at = (size_t)i * (record ? record : 1u);
+        const size_t at_s = record ? at + s : row;
+        in.lam = lambda[at];
+        in.slo = slo_us[at];
+        in.n_given = DERIVE ? 0 : r_fixed[at_s];
+        in.only = c_fixed ? c_fixed[at_s] : (int32_t)c_all;
+        const int32_t* cf = coef + (coef_shared ? 0 : record ? at : (size_t)i * S * cs) + s * cs;
 #pragma unroll
         for (int x = 0; x < 5; ++x) in.cf[x] = cf[x];
         in.cf[5] = cs == 6 ? cf[5] : 0;
@@ -699,7 +707,7 @@ static hipError_t launch_tables(const themis_problem_t& p, const Layout& L, cons
                                 int coef_shared, const int32_t* d_lambda, const int32_t* d_slo_us,
                                 const int32_t* d_r_fixed, const int32_t* c_fixed, int c_all,
                                 int sparse, char* ws, hipStream_t st, const int32_t* gate,
-                                int32_t gate_want)
+                                int32_t gate_want, uint32_t record)
 {
     BatchList bl{};
     bl.n = p.n_batch;
@@ -766,7 +774,7 @@ static hipError_t launch_tables(const themis_problem_t& p, const Layout& L, cons
                            (uint32_t)p.r_max, (uint32_t)p.tick_us,
                            (1.0 / (double)p.tick_us) * (1.0 - 0x1p-45), coef_shared, lpr_log2,
                            split_log2, (uint32_t)L.nb, (uint32_t)L.nbs, plan.class_map,
-                           sparse, (uint32_t)c_all, cs, s_magic, n_groups, gate, gate_want);
+                           sparse, (uint32_t)c_all, cs, s_magic, n_groups, gate, gate_want, record);
         return hipGetLastError();
     };
     const bool derive = d_r_fixed == nullptr;
@@ -818,7 +826,7 @@ hipError_t launch_candidates(const themis_problem_t& p, const Layout& L,
     if (e != hipSuccess) return e;
 
     return launch_tables(p, L, d_coef, p.coef_shared, d_lambda, d_slo_us, d_r_fixed, opts.c_fixed,
-                         opts.c_all, opts.sparse, ws, st, nullptr, 0);
+                         opts.c_all, opts.sparse, ws, st, nullptr, 0, 0u);
 }
 
 hipError_t launch_tables_after_solve(const themis_problem_t& p, const Layout& L, char* ws,
@@ -827,18 +835,18 @@ hipError_t launch_tables_after_solve(const themis_problem_t& p, const Layout& L,
     if (!cost_solve_serves(L)) return hipSuccess;  // the three stages did it: tables are there
     int32_t* const ctrl = (int32_t*)(ws + L.ctrl_off);
     int32_t* const rows = (int32_t*)(ws + L.frow_off);
-    const KeepLayout k = make_keep_layout(p, L);
-    const uint32_t blocks = (k.words + 255u) / 256u;
-    hipLaunchKernelGGL(k1_keep_move, dim3(blocks < 4096u ? blocks : 4096u), dim3(256), 0, st,
-                       (const int32_t*)ctrl, (const int32_t*)(ws + L.step_off), rows, k.words);
+    const KeepLayout k = make_keep_layout(p);
+    const size_t words = (size_t)L.N * k.words, blocks = (words + 255u) / 256u;
+    hipLaunchKernelGGL(k1_keep_move, dim3((unsigned)(blocks < 4096u ? blocks : 4096u)), dim3(256), 0,
+                       st, (const int32_t*)ctrl, (const int32_t*)(ws + L.step_off), rows, words);
     hipLaunchKernelGGL(k1_keep_state, dim3(1), dim3(1), 0, st, ctrl);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     // instances that failed the input check have a budget of -1 in tmeta
     for (int given = 0; given < 2; ++given) {
-        e = launch_tables(p, L, rows + k.coef, 0, rows + k.lam, rows + k.slo,
+        e = launch_tables(p, L, rows + k.coef, p.coef_shared, rows + KEEP_LAM, rows + KEEP_SLO,
                           given ? rows + k.given : nullptr, rows + k.only, 0, 0, ws, st,
-                          ctrl + STATE_WORD, STATE_REBUILD | (given ? STATE_GIVEN : 0));
+                          ctrl + STATE_WORD, STATE_REBUILD | (given ? STATE_GIVEN : 0), k.words);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

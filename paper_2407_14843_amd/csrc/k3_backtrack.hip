@@ -39,14 +39,15 @@ __global__ __launch_bounds__(256) void k3_backtrack(
     const int32_t kind = *state;
     if (kind & (STATE_KEPT_IN_TABLE | STATE_KEPT_IN_ROWS)) {
         // no rows here: the workspace holds the results of a whole solve
-        const int32_t* const kp = (kind & STATE_KEPT_IN_TABLE)
-                                      ? reinterpret_cast<const int32_t*>(step_tab)
-                                      : reinterpret_cast<const int32_t*>(frow);
-        for (int x = lane; x < S * 3; x += LANES) my_cfg[x] = kp[kept.cfg + (size_t)i * S * 3 + x];
+        const int32_t* const kp = ((kind & STATE_KEPT_IN_TABLE)
+                                       ? reinterpret_cast<const int32_t*>(step_tab)
+                                       : reinterpret_cast<const int32_t*>(frow)) +
+                                  (size_t)i * kept.words;
+        for (int x = lane; x < S * 3; x += LANES) my_cfg[x] = kp[kept.cfg + x];
         if (lane == 0) {
-            status[i] = kp[kept.status + i];
-            cost_out[i] = kp[kept.cost + i];
-            ticks_out[i] = kp[kept.ticks + i];
+            status[i] = kp[KEEP_STATUS];
+            cost_out[i] = kp[KEEP_COST];
+            ticks_out[i] = kp[KEEP_TICKS];
         }
         return;
     }
@@ -201,7 +202,7 @@ hipError_t launch_backtrack(const themis_problem_t& p, const Layout& L, int32_t*
                            (const int32_t*)(ws + L.ans_off), d_status, d_cost, d_ticks, d_cfg, bl,
                            L.N, L.S, L.Kp, L.nbs, L.row_stride, plan.class_map, opts.sparse,
                            (const int32_t*)(ws + L.ctrl_off) + STATE_WORD,
-                           make_keep_layout(p, L));
+                           make_keep_layout(p));
         return hipGetLastError();
     };
     if (lanes == 8) return launch(&k3_backtrack<8>, 32);

@@ -204,37 +204,36 @@ inline Layout make_layout(const themis_problem_t& p)
 // ---- what a whole solve leaves in the workspace ----------------------------------
 // The one-wavefront solve (cost_solve.hip) forms neither tables nor rows.  For the
 // calls that look at the workspace after a solve it leaves its inputs and results
-// instead (at most 52 bytes per row and 12 per instance, of the 64 a row of the
-// table region has at least) and says so in the state word:
+// instead, a record per instance (at most 5 + 11 words per model, of the sixteen per
+// model that the table region has at least), and says so in the state word:
 //   0                     tables (and rows) of the stage calls
-//   STATE_KEPT_IN_TABLE   inputs and results in the table region; no tables
-//   STATE_KEPT_IN_ROWS    the same in the row region; tables built from them
+//   STATE_KEPT_IN_TABLE   records in the table region; no tables
+//   STATE_KEPT_IN_ROWS    records in the row region; tables built from them
 // Export and count first build the tables where there are none (launch_tables_after_solve);
 // the backtrack call then hands out the results.  Budgets are in tmeta in every state.
 constexpr int STATE_WORD = 2 * N_CLS;
 constexpr int STATE_KEPT_IN_TABLE = 1, STATE_KEPT_IN_ROWS = 2;
 constexpr int STATE_GIVEN = 4;    // the replicas were given
 constexpr int STATE_REBUILD = 8;  // the candidate launches that follow have work to do
+constexpr int STATE_ONLY = 16;    // the cores were given, per model
+constexpr int STATE_C_ALL = 8;    // from this bit up: the same cores for every model, or 0
 
-struct KeepLayout {  // in int32 words from the start of the region
-    uint32_t coef, given, only, lam, slo, status, cost, ticks, cfg, words;
+// first words of a record
+enum { KEEP_LAM = 0, KEEP_SLO, KEEP_STATUS, KEEP_COST, KEEP_TICKS, KEEP_HEAD };
+// offsets of the rest, and words per record; shared coefficients are in the first only
+struct KeepLayout {
+    uint32_t coef, given, only, cfg, words;
 };
 
-inline KeepLayout make_keep_layout(const themis_problem_t& p, const Layout& L)
+inline KeepLayout make_keep_layout(const themis_problem_t& p)
 {
     KeepLayout k{};
-    const uint32_t n = (uint32_t)L.N, rows = n * (uint32_t)L.S;  // rows * Kp < 2^31, Kp >= 8
-    uint32_t at = 0;
-    k.coef = at;   at += rows * (p.profile_form == THEMIS_PROFILE_EQ1 ? 6u : 5u);
-    k.given = at;  at += rows;
-    k.only = at;   at += rows;
-    k.lam = at;    at += n;
-    k.slo = at;    at += n;
-    k.status = at; at += n;
-    k.cost = at;   at += n;
-    k.ticks = at;  at += n;
-    k.cfg = at;    at += 3u * rows;
-    k.words = at;
+    const uint32_t S = (uint32_t)p.n_stage;
+    k.coef = KEEP_HEAD;
+    k.given = k.coef + S * (p.profile_form == THEMIS_PROFILE_EQ1 ? 6u : 5u);
+    k.only = k.given + S;
+    k.cfg = k.only + S;
+    k.words = k.cfg + 3u * S;
     return k;
 }
 
