@@ -22,7 +22,7 @@ PROBE_LIB_PATH = os.path.join(HERE, "libthemis_probe.so")
 SOURCES = ["themis_api.hip", "k1_candidates.hip", "k2_minplus.hip", "k2_steps.hip",
            "k3_backtrack.hip",
            "k4_fallback.hip", "k5_stability.hip", "k6_memo.hip",
-           "cost_solve.hip"]
+           "cost_solve.hip", "cost_multi.hip"]
 PROBE_SOURCES = [os.path.join(HERE, "probe", "lds_probe.hip")]
 
 HIPCC_FLAGS = [

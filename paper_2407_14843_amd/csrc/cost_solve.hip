@@ -53,994 +53,34 @@
 // by the three stages (dense / with dominated candidates pruned) against this one, in
 // microseconds: 65536 x 8 models 25900 / 3890 -> 94, 16384 x 8 with replicas given
 // 3360 -> 24, 86400 x 6 2790 -> 55, 4096 x 5 178 -> 12.6, 64 x 3 27.5 -> 9.7.
-#include "candidate_eval.h"
-#include "instance_queue.h"
-#include "themis_internal.h"
-#include "wave_ops.h"
-
-#include <type_traits>
+#include "cost_solver.h"
 
 namespace themis {
 namespace {
 
-constexpr uint32_t LT_NONE = 1u << 22;       // "no candidate": above any sum of 64 budgets
-constexpr uint32_t EMPTY = 0xFFFFFFFFu;      // empty cell of the (lt, index) table
-constexpr int INDEX_BITS = 13;               // candidate indices are below 8192
-constexpr int FIRST_WINDOWS = 256;           // widest window of the first launch
-constexpr uint32_t G_INF = 0x8000u;          // row cell beyond any budget
-
-// a batch size b, and recip_below(b * 1e6)
-struct __attribute__((aligned(16))) BatchConst {
-    double b, rM;
-};
-
-struct CostArgs {
-    const int32_t *coef, *lambda, *slo_us, *r_fixed, *c_fixed;
-    int32_t *status, *cost, *ticks, *cfg;
-    int32_t* tmeta;     // budgets, for calls that inspect the workspace afterwards
-    int32_t* hard;      // per instance: left to the launch with the large window
-    int32_t* ctrl;
-    uint16_t* frow;     // rows of step D
-    int32_t* keep;      // inputs and results for such calls, or null
-    KeepLayout kept;
-    BatchConst bc[THEMIS_MAX_BATCH];
-    int32_t n_batch;
-    int32_t N, S, cs, c_max, r_max, tick, slo_max, coef_shared, c_all, sparse, row_stride;
-    int32_t window;     // cells of the largest window, a multiple of 64
-    int32_t tried;      // cells of the largest one tried before (0: none)
-    uint32_t nb_magic;  // ceil(2^16 / n_batch): x / n_batch = x * nb_magic >> 16 for x < 1024
-    uint32_t k_magic;   // ceil(2^20 / n_batch): the same with 20 for x < 8192
-    double rtick;
-};
-
-// LDS words of one wavefront.  From `tab` on, step B takes 32 words per model, a table
-// and rows of sixteen words; the window of 64 cells a table of 64 words per model and
-// S + 1 rows of 16-bit cells, each with a guard cell (and one of padding) in front; wider
-// windows a table of one model and such rows.
-struct CostLds {
-    int best, key, fast, tab, rows, words;
-};
-__host__ __device__ inline CostLds cost_lds(int S, int window)
-{
-    CostLds l;
-    l.best = 0;  // two words per model
-    l.key = 2 * S;
-    l.fast = l.key + S;
-    l.tab = (l.fast + S + 3) & ~3;
-    l.rows = l.tab + window;
-    const int c = l.rows + (S + 1) * (window + 2) / 2, b = l.tab + 64 * S + (S + 1) * 33;
-    l.words = ((c > b ? c : b) + 3) & ~3;
-    return l;
-}
-
-// lo <= v <= hi, 0 <= lo
-__device__ __forceinline__ bool in_range(int32_t v, int32_t lo, int32_t hi)
-{
-    return (uint32_t)v - (uint32_t)lo <= (uint32_t)(hi - lo);
-}
-
-// four consecutive words on a word boundary
-typedef int32_t words4 __attribute__((ext_vector_type(4), aligned(4)));
-
-// The launch's arguments where they lie, for code that takes them by address: in the
-// constant address space, so that uniform reads stay scalar loads.
-typedef const __attribute__((address_space(4))) CostArgs* ArgsPtr;
-
-extern __shared__ uint32_t cost_smem[];
-
-// The value D lanes down within the rows of sixteen that `ROWS` names; `fill` where
-// there is none, x itself in the other rows.
-template <int D, int ROWS = 0xF>
-__device__ __forceinline__ uint32_t row_shifted(uint32_t x, uint32_t fill)
-{
-    const uint32_t old = ROWS == 0xF ? fill : x;
-    return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)x, 0x110 | D, ROWS, 0xF, false);
-}
-
-__device__ __forceinline__ uint32_t least(uint32_t a, uint32_t b) { return a < b ? a : b; }
-
-// The least of the four lanes that have the same place in the rows of sixteen, in all
-// of them.
-__device__ __forceinline__ uint32_t least_of_rows(uint32_t x)
-{
-    typedef uint32_t two __attribute__((ext_vector_type(2)));
-    const two h = __builtin_amdgcn_permlane32_swap(x, x, false, false);
-    x = least(h.x, h.y);
-    const two q = __builtin_amdgcn_permlane16_swap(x, x, false, false);
-    return least(q.x, q.y);
-}
-
-template <int QUEUE, bool DERIVE, bool LAST>
-__device__ __attribute__((noinline)) bool solve_further(uint64_t args, int i, int T, int32_t lam,
-                                                        int32_t slo);
-
-// One wavefront's view of the instance it works on.  ONE: its (model, batch size)
-// pairs fit the lanes, so every lane keeps its own from step A on.
-template <int QUEUE, bool DERIVE, bool ONE>
-struct Solver {
-    const __attribute__((address_space(4))) CostArgs& a;
-    uint32_t* const lds;  // the wavefront's words: a workgroup is one wavefront
-    const CostLds L;
-    const int lane;
-
-    // the instance
-    int i, T;
-    int32_t lam, slo;
-    int32_t lane_b;  // lane j: batch size j
-
-    __device__ __forceinline__ explicit Solver(ArgsPtr args)
-        : a(*args), lds(cost_smem), L(cost_lds(args->S, args->window)),
-          lane(threadIdx.x)
-    {
-    }
-
-    // What a lane works on: one model and one batch size, cores lo .. last.
-    struct Pair {
-        RowHdr h;
-        BatchHdr bh;
-        double num, fixed;  // numerator of the division by the cores; what they do not shrink
-        double lam_per_M;   // at most lambda / (b 1e6)
-        uint32_t s, j, lo, last, pcap;
-        bool there, valid;
-    };
-
-    __device__ __forceinline__ Pair pair_of(uint32_t s, uint32_t j, bool there) const
-    {
-        Pair p;
-        p.there = there;
-        p.s = there ? s : 0u;
-        p.j = there ? j : 0u;
-        const double b = a.bc[p.j].b;
-        const double rM = a.bc[p.j].rM;
-        const size_t row0 = (size_t)i * a.S;
-        const int32_t* const cf = a.coef + (a.coef_shared ? 0 : row0 * a.cs) + p.s * (uint32_t)a.cs;
-        const words4 c4 = *reinterpret_cast<const words4*>(cf);
-        int32_t v[6] = {c4.x, c4.y, c4.z, c4.w, cf[4], 0};
-        if (a.cs == 6) v[5] = cf[5];
-        const int32_t given = DERIVE ? 0 : (a.r_fixed + row0)[p.s];
-        const int32_t only = a.c_fixed ? (a.c_fixed + row0)[p.s] : a.c_all;
-        // a, k, q, d in 0 .. max, p >= 1, o in 1 .. max
-        uint32_t top = (uint32_t)v[0] > (uint32_t)v[1] ? (uint32_t)v[0] : (uint32_t)v[1];
-        top = (uint32_t)v[2] > top ? (uint32_t)v[2] : top;
-        top = (uint32_t)v[5] > top ? (uint32_t)v[5] : top;
-        p.valid = top <= (uint32_t)THEMIS_VALUE_MAX && v[3] >= 1 && in_range(v[4], 1, THEMIS_VALUE_MAX);
-        if (!DERIVE) p.valid = p.valid && in_range(given, 1, a.r_max);
-        if (a.c_fixed) p.valid = p.valid && in_range(only, 1, a.c_max);
-        p.h = make_row_hdr(v, 6u, lam, slo, T, (uint32_t)a.tick, given);
-        p.bh.b = b;
-        p.bh.b2 = b * b;
-        p.bh.M = b * 1.0e6;
-        p.bh.rM = rM;
-        p.bh.w = p.bh.M - 1.0e6;
-        p.pcap = (uint32_t)v[3];
-        p.lo = only > 0 ? (uint32_t)only : 1u;
-        const uint32_t hi = only > 0 ? (uint32_t)only : (uint32_t)a.c_max;
-        // beyond the cap a candidate has the cap's latency and costs more
-        const uint32_t reach = p.pcap > p.lo ? p.pcap : p.lo;
-        p.last = hi < reach ? hi : reach;
-        p.num = __builtin_fma(p.h.q, p.bh.b2, __builtin_fma(p.h.k, p.bh.b, p.h.a));
-        p.fixed = __builtin_fma(p.h.d, p.bh.b, p.h.o);
-        p.lam_per_M = p.h.lam * p.bh.rM * (1.0 - 0x1p-40);
-        return p;
-    }
-
-    // this lane's pair of the round that starts with pair r
-    __device__ __forceinline__ Pair pair_of_round(uint32_t r) const
-    {
-        const uint32_t x = r + (uint32_t)lane;
-        const uint32_t s = (x * a.nb_magic) >> 16;
-        return pair_of(s, x - s * (uint32_t)a.n_batch, x < (uint32_t)(a.S * a.n_batch));
-    }
-
-    // Calls f(pair) for this lane's pair of every round of 64; lanes without one get a
-    // pair with `there` unset.  `mine`: the pair, where there is one round only.
-    template <typename F>
-    __device__ __forceinline__ void for_pairs(const Pair& mine, F f) const
-    {
-        if constexpr (ONE) {
-            f(mine);
-        } else {
-            for (uint32_t r = 0; r < (uint32_t)(a.S * a.n_batch); r += 64u) f(pair_of_round(r));
-        }
-    }
-
-    // Reciprocals of the core counts, for loops over them: lane l holds that of l + 1, a
-    // lane fetches the one it needs (three instructions instead of nine).
-    struct Recips {
-        double mine;
-        bool held;
-    };
-    __device__ __forceinline__ Recips recips() const
-    {
-        return Recips{recip_below((double)(lane + 1)), a.c_max <= 64};
-    }
-    __device__ __forceinline__ double recip(const Recips& r, uint32_t d) const
-    {
-        return r.held ? __shfl(r.mine, (int)d - 1, 64) : recip_below((double)d);
-    }
-
-    // rd: recip_below() of the cores, or of the cap beyond it
-    template <bool SMALL>
-    __device__ __forceinline__ Eval eval(const Pair& p, double rd) const
-    {
-        return eval_parts<QUEUE, SMALL, DERIVE ? N_DERIVED : N_GIVEN>(
-            p.h, p.bh, p.num, p.fixed, rd, (double)a.r_max, (double)a.tick, a.rtick);
-    }
-
-    static __device__ __forceinline__ uint32_t speed(const Pair& p, uint32_t c)
-    {
-        return c < p.pcap ? c : p.pcap;
-    }
-
-    // No candidate of the pair with fewer cores than this is feasible (last + 1: none
-    // is): its processing time alone, num / c + fixed, would exceed what the budget,
-    // less the least queueing delay that goes with it, and the throughput with the
-    // most replicas leave.  Single precision; every term is rounded to the safe side
-    // by more than its error (some units in 2^-24).
-    __device__ __forceinline__ uint32_t first_core(const Pair& p) const
-    {
-        constexpr float UP = 1.00001f, DOWN = 0.99999f;
-        const float room = (float)((double)T * (double)a.tick) * UP;
-        const float rl = __builtin_amdgcn_rcpf((float)lam);
-        const float b = (float)p.bh.b;
-        const float n_max = DERIVE ? (float)a.r_max : (float)p.h.n_given;
-        float most = n_max * (float)p.bh.M * rl * UP;
-        float wait = (float)p.bh.w * rl * DOWN;
-        if (QUEUE == THEMIS_QUEUE_PER_REPLICA && !DERIVE) wait *= n_max;
-        most = room - wait < most ? room - wait : most;
-        if (QUEUE == THEMIS_QUEUE_PER_REPLICA && DERIVE) {
-            // n >= lambda proc / (b 1e6), so the queue is at least (b - 1) / b proc
-            const float both = room * b * __builtin_amdgcn_rcpf(2.0f * b - 1.0f) * UP;
-            most = both < most ? both : most;
-        }
-        const float left = most - (float)p.fixed * DOWN;
-        const float c = (float)p.num * __builtin_amdgcn_rcpf(left) * DOWN;
-        if (!(left > 0.0f) || c > (float)p.last) return p.last + 1u;
-        const uint32_t c0 = (uint32_t)__builtin_ceilf(c);
-        return c0 > p.lo ? c0 : p.lo;
-    }
-
-    // Whether a candidate of the pair with c cores or more can cost as little as
-    // `limit`: n >= 1 and n >= lambda (num / c + fixed) / (b 1e6).
-    __device__ __forceinline__ bool may_cost(const Pair& p, uint32_t c, uint32_t limit) const
-    {
-        if (!DERIVE) return (double)c * p.h.n_given <= (double)limit;
-        return c <= limit &&
-               __builtin_fma((double)c, p.fixed, p.num) * p.lam_per_M <= (double)limit;
-    }
-
-    // per model: cost << 15 | lt of the best candidate met so far; the same with the
-    // index below it, complete after step A; lt of the fastest candidate
-    __device__ __forceinline__ uint32_t* keys() const { return lds + L.key; }
-    __device__ __forceinline__ unsigned long long* bests() const
-    {
-        return reinterpret_cast<unsigned long long*>(lds + L.best);
-    }
-    __device__ __forceinline__ uint32_t* fastest() const { return lds + L.fast; }
-
-    // Sum over the lanes below S of values that are zero elsewhere, as a uniform value.
-    __device__ __forceinline__ uint32_t sum_models(uint32_t x) const
-    {
-        if (a.S <= 16) return lane_value(segmented_scan<false>(x, 0u, 16u), 15);
-        return wave_sum(x);
-    }
-
-    // ---- results -----------------------------------------------------------------
-    // this instance's record for the calls that look at the workspace afterwards
-    __device__ __forceinline__ int32_t* record() const { return a.keep + (size_t)i * a.kept.words; }
-
-    __device__ __forceinline__ void put(int32_t status, int32_t cost, int32_t ticks) const
-    {
-        if (lane != 0) return;
-        a.status[i] = status;
-        a.cost[i] = cost;
-        a.ticks[i] = ticks;
-        if (a.keep) {
-            int32_t* const kp = record();
-            kp[KEEP_STATUS] = status;
-            kp[KEEP_COST] = cost;
-            kp[KEEP_TICKS] = ticks;
-        }
-    }
-
-    __device__ __forceinline__ void put_none(int32_t status) const
-    {
-        put(status, -1, -1);
-        const int words = 3 * a.S;
-        int32_t* const out = a.cfg + (size_t)i * words;
-        for (int x = lane; x < words; x += 64) {
-            out[x] = 0;
-            if (a.keep) record()[a.kept.cfg + x] = 0;
-        }
-    }
-
-    // lane s < S: index and cost of model s's candidate
-    __device__ __forceinline__ void put_choice(uint32_t k, uint32_t cost) const
-    {
-        const uint32_t q = (k * a.k_magic) >> 20;
-        const uint32_t c = q + 1u;
-        const int32_t b = __shfl(lane_b, (int)(k - q * (uint32_t)a.n_batch), 64);
-        if (lane >= a.S) return;
-        // cost / c: the exact quotient is a whole number up to 32767, half of 1 / c away
-        // from where the truncation would go wrong
-        const uint32_t n = (uint32_t)(((float)cost + 0.5f) * __builtin_amdgcn_rcpf((float)c));
-        const uint32_t off = 3u * (uint32_t)lane;
-        int32_t* const out = a.cfg + (size_t)i * a.S * 3;
-        out[off] = (int32_t)c;
-        out[off + 1u] = b;
-        out[off + 2u] = (int32_t)n;
-        if (a.keep) {
-            int32_t* const kp = record() + a.kept.cfg;
-            kp[off] = (int32_t)c;
-            kp[off + 1u] = b;
-            kp[off + 2u] = (int32_t)n;
-        }
-    }
-
-    // The instance's inputs into its record, see STATE_WORD.  `word`: word `lane` of the
-    // coefficients, loaded with the rest of the inputs.
-    __device__ __forceinline__ bool keeps_coef() const
-    {
-        return a.keep && (!a.coef_shared || i == 0);  // shared: the first record has them
-    }
-    __device__ __forceinline__ void keep_inputs(bool valid, int32_t word) const
-    {
-        if (!a.keep) return;
-        int32_t* const kp = record();
-        if (keeps_coef()) {
-            const int words = a.S * a.cs;
-            if (lane < words) (kp + a.kept.coef)[lane] = word;
-            for (int x = lane + 64; x < words; x += 64)
-                (kp + a.kept.coef)[x] = (a.coef + (size_t)i * words)[x];
-        }
-        if (!DERIVE && lane < a.S)
-            (kp + a.kept.given)[lane] = (a.r_fixed + (size_t)i * a.S)[lane];
-        if (a.c_fixed && lane < a.S)
-            (kp + a.kept.only)[lane] = (a.c_fixed + (size_t)i * a.S)[lane];
-        if (lane == 0) {
-            kp[KEEP_LAM] = valid ? lam : 0;
-            kp[KEEP_SLO] = slo;
-        }
-    }
-
-    // ---- step A ------------------------------------------------------------------
-    template <bool SMALL>
-    __device__ __forceinline__ void least_costs(const Pair& first) const
-    {
-        for_pairs(first, [&](const Pair& p) {
-            uint32_t best = EMPTY, best_c = 0;
-            auto meet = [&](uint32_t c, double rd) {
-                const Eval ev = eval<SMALL>(p, rd);
-                if (ev.lt >= 0) {
-                    const uint32_t key = (__umul24((uint32_t)ev.n, c) << 15) | (uint32_t)ev.lt;
-                    // (cores ascend: of equal keys the first one met has the smaller index)
-                    if (key < best) best = key, best_c = c;
-                    atomicMin(&keys()[p.s], key);
-                }
-            };
-            auto goes_on = [&](uint32_t c) {
-                return c <= p.last && may_cost(p, c, keys()[p.s] >> 15);
-            };
-            // most pipelines at low rates are done with the first core count
-            uint32_t c = p.lo;
-            if (p.there) meet(c, recip_below((double)speed(p, c)));
-            wave_lds_fence();
-            ++c;
-            bool go = p.there && goes_on(c);
-            if (__ballot(go) != 0ull) {
-                const uint32_t c0 = first_core(p);
-                c = c0 > c ? c0 : c;
-                const Recips rc = recips();
-                for (;;) {
-                    go = go && goes_on(c);
-                    if (__ballot(go) == 0ull) break;
-                    const double rd = recip(rc, go ? speed(p, c) : 1u);
-                    if (go) meet(c++, rd);
-                    wave_lds_fence();
-                }
-            }
-            if (best != EMPTY)
-                atomicMin(&bests()[p.s],
-                          ((unsigned long long)best << INDEX_BITS) |
-                              ((best_c - 1u) * (uint32_t)a.n_batch + p.j));
-        });
-        wave_lds_fence();
-    }
-
-    // ---- step F ------------------------------------------------------------------
-    template <bool SMALL>
-    __device__ __forceinline__ uint32_t fastest_ticks(const Pair& first) const
-    {
-        if (lane < a.S) fastest()[lane] = LT_NONE;
-        wave_lds_fence();
-        for_pairs(first, [&](const Pair& p) {
-            if (!p.there) return;
-            const Eval ev = eval<SMALL>(p, recip_below((double)speed(p, p.last)));
-            if (ev.lt >= 0) atomicMin(&fastest()[p.s], (uint32_t)ev.lt);
-        });
-        wave_lds_fence();
-        return sum_models(lane < a.S ? fastest()[lane] : 0u);
-    }
-
-    // ---- step B ------------------------------------------------------------------
-    static __device__ __forceinline__ uint32_t entry(const Eval& ev, uint32_t k)
-    {
-        return ((uint32_t)ev.lt << INDEX_BITS) | k;
-    }
-
-    // The table of (lt, index) by cost over base, W cells per model.
-    template <bool SMALL, int W>
-    __device__ __forceinline__ void fill_all(const Pair& first) const
-    {
-        uint32_t* const tab = lds + L.tab;
-        for (int x = lane; x < a.S * W; x += 64) tab[x] = EMPTY;
-        const Recips rc = recips();
-        wave_lds_fence();
-        for_pairs(first, [&](const Pair& p) {
-            const uint32_t base = keys()[p.s] >> 15;
-            const uint32_t top = base + (uint32_t)W - 1u;
-            uint32_t* const mine = tab + p.s * (uint32_t)W;
-            auto enter = [&](const Eval& ev, uint32_t c) {
-                const uint32_t cost = __umul24((uint32_t)ev.n, c);
-                if (ev.lt >= 0 && cost <= top)
-                    atomicMin(&mine[cost - base], entry(ev, (c - 1u) * (uint32_t)a.n_batch + p.j));
-            };
-            // two at a time: their chains of dependent operations fill each other's waits
-            uint32_t c = first_core(p);
-            for (;;) {
-                const bool go = p.there && c <= p.last && may_cost(p, c, top);
-                if (__ballot(go) == 0ull) break;
-                const uint32_t c1 = c < p.last ? c + 1u : c;
-                const double r0 = recip(rc, go ? speed(p, c) : 1u);
-                const double r1 = recip(rc, go ? speed(p, c1) : 1u);
-                if (go) {
-                    const Eval e0 = eval<SMALL>(p, r0), e1 = eval<SMALL>(p, r1);
-                    enter(e0, c);
-                    enter(e1, c1);
-                    c += 2u;
-                }
-            }
-        });
-        wave_lds_fence();
-    }
-
-    // Forward over the models, with the table of W <= 64 cells per model: the smallest
-    // index among the candidates that continue an optimum of x cells over base and
-    // `ticks`.  rest(s, y): cell y of row s + 1; lane s: base of model s.
-    template <int W, typename F>
-    __device__ __forceinline__ void read_out(uint32_t total, uint32_t ticks, int x,
-                                             uint32_t my_base, F rest) const
-    {
-        constexpr uint32_t INDEX = (1u << INDEX_BITS) - 1u;
-        const uint32_t* const tab = lds + L.tab;
-        uint32_t t = ticks, my_k = 0, my_cost = my_base;
-        const int d = lane & (W - 1);
-        uint32_t e = tab[d];
-        for (int s = 0; s < a.S; ++s) {
-            const bool more_models = s + 1 < a.S;
-            const uint32_t r = more_models ? rest(s, x >= d ? x - d : 0) : 0u;
-            const uint32_t e_next = more_models ? tab[(s + 1) * W + d] : 0u;
-            unsigned long long who = __ballot(d <= x && (e >> INDEX_BITS) + r == t);
-            if (W < 64) who &= (1ull << (W & 63)) - 1ull;
-            if (who == 0ull) {  // never expected
-                put_none(THEMIS_INTERNAL);
-                return;
-            }
-            int l = __builtin_ctzll(who);
-            uint32_t el = lane_value(e, l);
-            for (unsigned long long more = who & (who - 1ull); more; more &= more - 1ull) {
-                const int l2 = __builtin_ctzll(more);
-                const uint32_t e2 = lane_value(e, l2);
-                if ((e2 & INDEX) < (el & INDEX)) l = l2, el = e2;
-            }
-            if (lane == s) my_k = el & INDEX, my_cost += (uint32_t)l;
-            t -= el >> INDEX_BITS;
-            x -= l;
-            e = e_next;
-        }
-        put(THEMIS_SOLVED, (int32_t)total, (int32_t)ticks);
-        put_choice(my_k, my_cost);
-    }
-
-    // The recurrence over 16 cells.  Every row of sixteen lanes holds g[s+1][0..15]; row r
-    // takes the table's costs 4 q + r, so its copy is first shifted by r and then by 4 q,
-    // both operand modifiers, and the four rows' minima are combined.  (What does not beat
-    // everything cheaper does no harm.)  `base_sum`: the sum of the models' least costs.
-    __device__ __forceinline__ bool solve_sixteen(uint32_t base_sum, uint32_t my_base) const
-    {
-        const uint32_t* const tab = lds + L.tab;
-        uint32_t* const rows = lds + L.tab + 16 * a.S;
-        uint32_t g = 0u;  // g[S]: nothing left to run
-        const int at = lane >> 4;
-        for (int s = a.S - 1; s >= 0; --s) {
-            const uint32_t* const mine = tab + s * 16 + at;
-            uint32_t v[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = mine[4 * q] >> INDEX_BITS;  // EMPTY: 2^19 - 1
-            uint32_t h = row_shifted<1, 0x2>(g, LT_NONE);
-            // the lanes a shift leaves without a source keep their own value: mark them
-            h = row_shifted<2, 0x4>(h, LT_NONE);
-            h = row_shifted<3, 0x8>(h, LT_NONE);
-            h = (lane & 15) < at ? LT_NONE : h;
-            uint32_t acc = h + v[0];
-            acc = least(acc, row_shifted<4>(h, LT_NONE) + v[1]);
-            acc = least(acc, row_shifted<8>(h, LT_NONE) + v[2]);
-            acc = least(acc, row_shifted<12>(h, LT_NONE) + v[3]);
-            g = least_of_rows(acc);
-            if (lane < 16) rows[s * 16 + lane] = g;
-        }
-        const uint32_t m = (uint32_t)__ballot(g <= (uint32_t)T) & 0xFFFFu;
-        if (m == 0u) return false;
-        const int x = __builtin_ctz(m);
-        const uint32_t ticks = lane_value(g, x);
-        const uint32_t total = base_sum + (uint32_t)x;
-        wave_lds_fence();
-        read_out<16>(total, ticks, x, my_base, [&](int s, int y) { return rows[(s + 1) * 16 + y]; });
-        return true;
-    }
-
-    // ---- step C ------------------------------------------------------------------
-    // The recurrence over 64 cells, lane = cell, the table of all models in LDS.
-    __device__ __forceinline__ bool solve_sixtyfour() const
-    {
-        const uint32_t* const tab = lds + L.tab;
-        // rows of 16-bit cells, a guard cell (and one of padding) in front of each
-        uint16_t* const rows = reinterpret_cast<uint16_t*>(lds + L.tab + 64 * a.S);
-        auto row_of = [&](int s) { return rows + s * 66 + 2; };
-        for (int x = lane; x <= a.S; x += 64) row_of(x)[-1] = (uint16_t)G_INF;
-        row_of(a.S)[lane] = 0;
-        uint32_t acc = 0;
-        uint32_t lt = tab[(a.S - 1) * 64 + lane] >> INDEX_BITS;
-        wave_lds_fence();
-        for (int s = a.S - 1; s >= 0; --s) {
-            const uint16_t* const next = row_of(s + 1);
-            // what beats everything cheaper
-            const bool on = lt < from_lane_below(wave_scan<true>(lt), LT_NONE) && lt < G_INF;
-            const uint32_t lt_next = s > 0 ? tab[(s - 1) * 64 + lane] >> INDEX_BITS : 0u;
-            acc = G_INF;
-            unsigned long long m = __ballot(on);
-            while (m) {  // four entries at a time: independent reads
-                uint32_t v[4];
-#pragma unroll
-                for (int z = 0; z < 4; ++z) {
-                    const int d = m ? __builtin_ctzll(m) : 64;
-                    const uint32_t l = m ? lane_value(lt, d & 63) : 0u;
-                    m &= m - 1ull;
-                    const int y = lane - d;
-                    v[z] = (uint32_t)next[y < -1 ? -1 : y] + l;
-                }
-                acc = least(least(acc, v[0]), least(v[1], least(v[2], v[3])));
-            }
-            row_of(s)[lane] = (uint16_t)acc;
-            wave_lds_fence();
-            lt = lt_next;
-        }
-        const unsigned long long m = __ballot(acc <= (uint32_t)T);
-        if (m == 0ull) return false;
-        const int x = __builtin_ctzll(m);
-        const uint32_t my_base = lane < a.S ? keys()[lane] >> 15 : 0u;
-        read_out<64>(sum_models(my_base) + (uint32_t)x, lane_value(acc, x), x, my_base,
-                     [&](int s, int y) { return (uint32_t)row_of(s + 1)[y]; });
-        return true;
-    }
-
-    // The table of one model, W cells.  All lanes work on it: lane = (part, batch size),
-    // the parts take the cores in turn.
-    __device__ __forceinline__ void fill_model(int s, int W) const
-    {
-        uint32_t* const tab = lds + L.tab;
-        for (int x = lane; x < W; x += 64) tab[x] = EMPTY;
-        const uint32_t nb = (uint32_t)a.n_batch;
-        const uint32_t parts = (64u * a.nb_magic) >> 16;
-        const uint32_t part = ((uint32_t)lane * a.nb_magic) >> 16;
-        const Pair p = pair_of((uint32_t)s, (uint32_t)lane - part * nb, part < parts);
-        const uint32_t base = keys()[s] >> 15;
-        const uint32_t top = base + (uint32_t)W - 1u;
-        wave_lds_fence();
-        if (part < parts) {
-            for (uint32_t c = first_core(p) + part; c <= p.last && may_cost(p, c, top); c += parts) {
-                const Eval ev = eval<false>(p, recip_below((double)speed(p, c)));
-                const uint32_t cost = __umul24((uint32_t)ev.n, c);
-                if (ev.lt >= 0 && cost <= top)
-                    atomicMin(&tab[cost - base], entry(ev, (c - 1u) * nb + (uint32_t)(lane - part * nb)));
-            }
-        }
-        wave_lds_fence();
-    }
-
-    // The recurrence over W cells (a multiple of 64) and, where it ends within the budget,
-    // the answer.
-    __device__ __forceinline__ bool solve_window(int W) const
-    {
-        uint32_t* const tab = lds + L.tab;
-        uint16_t* const rows = reinterpret_cast<uint16_t*>(lds + L.rows);
-        auto row_of = [&](int s) { return rows + s * (W + 2) + 2; };  // cell -1 is the guard
-        for (int x = lane; x <= a.S; x += 64) row_of(x)[-1] = (uint16_t)G_INF;
-        for (int x = lane; x < W; x += 64) row_of(a.S)[x] = 0;
-        for (int s = a.S - 1; s >= 0; --s) {
-            fill_model(s, W);
-            // what beats everything cheaper, as a list in the table's own place: cost over
-            // base and lt of entry n at n, never beyond the cells already read
-            uint32_t low = LT_NONE;
-            int n = 0;
-            for (int x0 = 0; x0 < W; x0 += 64) {
-                const uint32_t lt = tab[x0 + lane] >> INDEX_BITS;
-                const uint32_t incl = least(wave_scan<true>(lt), low);
-                const bool on = lt < from_lane_below(incl, low) && lt < G_INF;
-                low = lane_value(incl, 63);
-                const unsigned long long m = __ballot(on);
-                if (on)
-                    tab[n + (int)__builtin_popcountll(m & ((1ull << lane) - 1ull))] =
-                        (uint32_t)(x0 + lane) << 16 | lt;
-                n += (int)__builtin_popcountll(m);
-                wave_lds_fence();
-            }
-            // entries beyond the list that never apply, so that it can be read in pairs
-            if (lane < 2 && n + lane < W) tab[n + lane] = 0xFFFFu << 16;
-            wave_lds_fence();
-            const uint16_t* const next = row_of(s + 1);
-            uint16_t* const row = row_of(s);
-            for (int x0 = 0; x0 < W; x0 += 256) {
-                uint32_t acc[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) acc[q] = G_INF;
-                const int end = x0 + 255;
-                for (int e = 0; e < n; e += 2) {
-                    const uint32_t w0 = tab[e], w1 = tab[e + 1 < W ? e + 1 : e];
-                    if (__builtin_amdgcn_readfirstlane((int)(w0 >> 16)) > end) break;
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int x = x0 + 64 * q + lane;
-                        if (x0 + 64 * q < W) {
-                            const int y0 = x - (int)(w0 >> 16), y1 = x - (int)(w1 >> 16);
-                            const uint32_t a0 = next[y0 < -1 ? -1 : y0] + (w0 & 0xFFFFu);
-                            const uint32_t a1 = next[y1 < -1 ? -1 : y1] + (w1 & 0xFFFFu);
-                            acc[q] = least(acc[q], least(a0, a1));
-                        }
-                    }
-                }
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    if (x0 + 64 * q < W) row[x0 + 64 * q + lane] = (uint16_t)acc[q];
-            }
-            wave_lds_fence();
-        }
-        int x = -1;
-        uint32_t ticks = 0;
-        for (int x0 = 0; x0 < W && x < 0; x0 += 64) {
-            const uint32_t v = row_of(0)[x0 + lane];
-            const unsigned long long m = __ballot(v <= (uint32_t)T);
-            if (m) {
-                const int l = __builtin_ctzll(m);
-                x = x0 + l;
-                ticks = lane_value(v, l);
-            }
-        }
-        if (x < 0) return false;
-
-        // forward: the smallest index among the candidates that continue an optimum
-        uint32_t total = (uint32_t)x, t = ticks, my_k = 0, my_cost = 0;
-        for (int s = 0; s < a.S; ++s) {
-            fill_model(s, W);
-            const uint16_t* const next = row_of(s + 1);
-            uint32_t key = EMPTY, key_lt = 0;
-            int key_d = 0;
-            for (int d0 = 0; d0 <= x; d0 += 64) {
-                const int d = d0 + lane;
-                const uint32_t e = d <= x ? tab[d] : EMPTY;
-                const uint32_t rest = next[d <= x ? x - d : 0];
-                unsigned long long m = __ballot(e != EMPTY && (e >> INDEX_BITS) + rest == t);
-                while (m) {
-                    const int l = __builtin_ctzll(m);
-                    m &= m - 1ull;
-                    const uint32_t el = lane_value(e, l);
-                    const uint32_t k = el & ((1u << INDEX_BITS) - 1u);
-                    if (k < key) key = k, key_lt = el >> INDEX_BITS, key_d = d0 + l;
-                }
-            }
-            if (key == EMPTY) {  // never expected
-                put_none(THEMIS_INTERNAL);
-                return true;
-            }
-            const uint32_t base = keys()[s] >> 15;
-            total += base;
-            if (lane == s) my_k = key, my_cost = base + (uint32_t)key_d;
-            t -= key_lt;
-            x -= key_d;
-            wave_lds_fence();
-        }
-        put(THEMIS_SOLVED, (int32_t)total, (int32_t)ticks);
-        put_choice(my_k, my_cost);
-        return true;
-    }
-
-    // ---- step D ---------------------------------------------------------------------
-    // Candidate number x of model s in index order (64 at a time, one per lane).
-    __device__ __forceinline__ Eval candidate(int s, uint32_t x, uint32_t count, uint32_t& cost,
-                                              uint32_t& k) const
-    {
-        const uint32_t q = (x * a.k_magic) >> 20;
-        const Pair p = pair_of((uint32_t)s, x - q * (uint32_t)a.n_batch, true);
-        const uint32_t c = p.lo + (x < count ? q : 0u);
-        Eval ev = eval<false>(p, recip_below((double)speed(p, c)));
-        if (x >= count) ev.lt = -1;
-        cost = __umul24((uint32_t)ev.n, c);
-        k = (c - 1u) * (uint32_t)a.n_batch + p.j;
-        return ev;
-    }
-
-    // Rows over the budget, in this instance's part of the row region.  Candidates are
-    // first entered into a table of least latencies by cost (as many costs per bin as
-    // it takes) so that only those faster than everything in a cheaper bin are swept.
-    __device__ __forceinline__ void solve_by_budget(int W) const
-    {
-        const int bins = W;
-        uint32_t* const tab = lds + L.tab;
-        uint32_t* const list = lds + L.rows;  // lt | cost << 16
-        const int cap = a.S * W / 2;          // entries of the list (the rows have room)
-        uint16_t* const rows = a.frow + (size_t)i * a.S * a.row_stride;
-        const uint32_t nbat = (uint32_t)a.n_batch;
-        for (int s = a.S - 1; s >= 0; --s) {
-            uint16_t* const out = rows + (size_t)s * a.row_stride;
-            const uint16_t* const next = out + a.row_stride;
-            const bool first_model = s == a.S - 1;
-            const Pair p0 = pair_of((uint32_t)s, 0u, true);
-            const uint32_t count = (p0.last - p0.lo + 1u) * nbat;
-            const uint32_t base = keys()[s] >> 15;
-            int sh = 0;
-            while ((a.r_max * a.c_max >> sh) >= bins) ++sh;
-            for (int x = lane; x < bins; x += 64) tab[x] = LT_NONE;
-            wave_lds_fence();
-            for (uint32_t x0 = 0; x0 < count; x0 += 64u) {
-                const uint32_t x = x0 + (uint32_t)lane;
-                uint32_t cost, k;
-                const Eval ev = candidate(s, x, count, cost, k);
-                if (ev.lt >= 0) atomicMin(&tab[(cost - base) >> sh], (uint32_t)ev.lt);
-            }
-            wave_lds_fence();
-            uint32_t low = LT_NONE;
-            for (int x0 = 0; x0 < bins; x0 += 64) {
-                const int x = x0 + lane;
-                uint32_t incl = wave_scan<true>(tab[x]);
-                incl = incl < low ? incl : low;
-                tab[x] = from_lane_below(incl, low);  // least of all cheaper bins
-                low = lane_value(incl, 63);
-            }
-            wave_lds_fence();
-            for (int t = lane; t <= T; t += 64) out[t] = (uint16_t)F_INF;
-            int n = 0;
-            auto sweep = [&]() {
-                wave_lds_fence();
-                for (int t = lane; t - lane <= T; t += 64) {
-                    uint32_t acc = t <= T ? (uint32_t)out[t] : F_INF;
-                    for (int e = 0; e < n; ++e) {
-                        const uint32_t w = list[e];
-                        const int y = t - (int)(w & 0xFFFFu);
-                        uint32_t v = F_INF;
-                        if (y >= 0 && t <= T) v = (w >> 16) + (first_model ? 0u : (uint32_t)next[y]);
-                        acc = v < acc ? v : acc;
-                    }
-                    if (t <= T) out[t] = (uint16_t)acc;
-                }
-                n = 0;
-                wave_lds_fence();
-            };
-            for (uint32_t x0 = 0; x0 < count; x0 += 64u) {
-                const uint32_t x = x0 + (uint32_t)lane;
-                uint32_t cost, k;
-                const Eval ev = candidate(s, x, count, cost, k);
-                const bool use =
-                    ev.lt >= 0 && tab[(cost - base) >> sh] > (uint32_t)ev.lt;
-                const unsigned long long m = __ballot(use);
-                if (n + (int)__builtin_popcountll(m) > cap) sweep();
-                // (a list shorter than a wavefront takes its lanes in portions)
-                unsigned long long todo = m;
-                while (todo) {
-                    const int rank = (int)__builtin_popcountll(todo & ((1ull << lane) - 1ull));
-                    const bool in = ((todo >> lane) & 1ull) && n + rank < cap;
-                    if (in) list[n + rank] = (uint32_t)ev.lt | (cost << 16);
-                    const unsigned long long took = __ballot(in);
-                    n += (int)__builtin_popcountll(took);
-                    todo &= ~took;
-                    if (todo) sweep();
-                }
-            }
-            sweep();
-            // the next model reads what other lanes wrote
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-        }
-        const uint32_t best = rows[T];
-        int t = T;
-        for (int t0 = 0; t0 <= T; t0 += 64) {
-            const unsigned long long m = __ballot(t0 + lane <= T && rows[t0 + lane <= T ? t0 + lane : T] == best);
-            if (m) {
-                t = t0 + __builtin_ctzll(m);
-                break;
-            }
-        }
-        const int t_star = t;
-        uint32_t my_k = 0, my_cost = 0, target = best;
-        for (int s = 0; s < a.S; ++s) {
-            const uint16_t* const next = rows + (size_t)(s + 1) * a.row_stride;
-            const Pair p0 = pair_of((uint32_t)s, 0u, true);
-            const uint32_t count = (p0.last - p0.lo + 1u) * nbat;
-            bool found = false;
-            for (uint32_t x0 = 0; x0 < count && !found; x0 += 64u) {
-                const uint32_t x = x0 + (uint32_t)lane;
-                uint32_t cost, k;
-                const Eval ev = candidate(s, x, count, cost, k);
-                uint32_t rest = F_INF;
-                if (ev.lt >= 0 && ev.lt <= t) rest = s + 1 < a.S ? (uint32_t)next[t - ev.lt] : 0u;
-                const unsigned long long m = __ballot(rest < F_INF && cost + rest == target);
-                if (m) {  // candidates are in index order: the first is the smallest
-                    const int l = __builtin_ctzll(m);
-                    const uint32_t ck = lane_value(k, l), cc = lane_value(cost, l);
-                    if (lane == s) my_k = ck, my_cost = cc;
-                    target -= cc;
-                    t -= (int)lane_value((uint32_t)ev.lt, l);
-                    found = true;
-                }
-            }
-            if (!found) {  // never expected
-                put_none(THEMIS_INTERNAL);
-                return;
-            }
-        }
-        put(THEMIS_SOLVED, (int32_t)best, t_star);
-        put_choice(my_k, my_cost);
-    }
-
-    // Steps A, F and B (MARKED: B has been tried before).
-    template <bool SMALL, bool MARKED>
-    __device__ __forceinline__ bool solve_valid(const Pair& first) const
-    {
-        least_costs<SMALL>(first);
-        uint32_t key = 0, k = 0, lt = 0;
-        if (lane < a.S) {
-            const unsigned long long best = bests()[lane];
-            key = (uint32_t)(best >> INDEX_BITS);
-            k = (uint32_t)best & ((1u << INDEX_BITS) - 1u);
-            lt = key == EMPTY ? LT_NONE : key & 0x7FFFu;
-        }
-        const uint32_t ticks = sum_models(lt);
-        if (ticks <= (uint32_t)T) {
-            put(THEMIS_SOLVED, (int32_t)sum_models(key >> 15), (int32_t)ticks);
-            put_choice(k, key >> 15);
-            return true;
-        }
-        if (ticks >= LT_NONE || fastest_ticks<SMALL>(first) > (uint32_t)T) {
-            put_none(THEMIS_INFEASIBLE);
-            return true;
-        }
-        if (!MARKED) {
-            fill_all<SMALL, 16>(first);
-            if (solve_sixteen(sum_models(key >> 15), key >> 15)) return true;
-            wave_lds_fence();
-        }
-        return false;
-    }
-
-    // Steps C and, LAST, D.
-    template <bool LAST>
-    __device__ __forceinline__ bool further(int inst, int budget, int32_t rate, int32_t objective)
-    {
-        i = inst, T = budget, lam = rate, slo = objective;
-        lane_b = lane < a.n_batch ? (int32_t)a.bc[lane].b : 0;
-        if (a.tried == 0) {
-            fill_all<false, 64>(Pair());
-            if (solve_sixtyfour()) return true;
-            wave_lds_fence();
-        }
-        for (int W = a.tried > 64 ? a.tried : 64; W < a.window;) {
-            W = 2 * W < a.window ? 2 * W : a.window;
-            if (solve_window(W)) return true;
-            wave_lds_fence();
-        }
-        if (!LAST) return false;
-        solve_by_budget(a.window);
-        return true;
-    }
-
-    // Solves instance i.  LAST: whatever it takes; else false when the first windows
-    // do not suffice.  MARKED: they have been tried.
-    template <bool LAST, bool MARKED>
-    __device__ __forceinline__ bool solve(int inst)
-    {
-        i = inst;
-        lam = a.lambda[i];
-        slo = a.slo_us[i];
-        if (lane < a.S) {
-            keys()[lane] = EMPTY;
-            bests()[lane] = ~0ull;
-        }
-        const bool rates = in_range(lam, 1, THEMIS_VALUE_MAX) && in_range(slo, 0, a.slo_max);
-        // floor(slo / tick): the quotient lies at least half of 1 / tick above any whole
-        // number below it, which the reciprocal's error (2^-44 relative) does not reach
-        T = __builtin_amdgcn_readfirstlane((int)(((double)slo + 0.5) * a.rtick));
-        int32_t word = 0;
-        if (keeps_coef() && lane < a.S * a.cs) word = (a.coef + (size_t)i * (a.S * a.cs))[lane];
-        const Pair first = pair_of_round(0u);
-        lane_b = (int32_t)first.bh.b;  // the first n_batch lanes have the first model's pairs
-        bool fine = rates;
-        for_pairs(first, [&](const Pair& p) { fine = fine && (!p.there || p.valid); });
-        const bool valid = __ballot(!fine) == 0ull;
-        keep_inputs(valid, word);
-        if (lane == 0) a.tmeta[i] = valid ? T : -1;
-        if (!valid) {
-            if (!a.sparse) put_none(THEMIS_INVALID);
-            return true;
-        }
-        wave_lds_fence();
-        bool done;
-        // row_is_small(), which is the same for all models of an instance
-        if (__builtin_amdgcn_readfirstlane((int)((double)lam * (double)slo <= 0x1p42)))
-            done = solve_valid<true, MARKED>(first);
-        else
-            done = solve_valid<false, MARKED>(first);
-        if (__builtin_amdgcn_readfirstlane((int)done)) return true;
-        return solve_further<QUEUE, DERIVE, LAST>((uint64_t)(uintptr_t)&a, i, T, lam, slo);
-    }
-};
-
-// Out of line, so that its registers do not weigh on the allocation of the steps
-// that nearly every instance ends with.
-template <int QUEUE, bool DERIVE, bool LAST>
-__device__ __attribute__((noinline)) bool solve_further(uint64_t args, int i, int T, int32_t lam,
-                                                        int32_t slo)
-{
-    auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
-    const uint64_t lo = (uint32_t)uniform((int)(uint32_t)args);
-    const uint64_t hi = (uint32_t)uniform((int)(uint32_t)(args >> 32));
-    Solver<QUEUE, DERIVE, false> sv((ArgsPtr)(uintptr_t)(hi << 32 | lo));
-    return uniform((int)sv.template further<LAST>(uniform(i), uniform(T), uniform(lam),
-                                                  uniform(slo))) != 0;
-}
-
-// FIRST: instance by workgroup; what the first windows do not solve is marked in
-// `hard`.  REST: the marked instances.  ALL: instance by workgroup, to the end.
-// (The arguments are read where they lie, see ArgsPtr.)
-enum { FIRST, REST, ALL };
 template <int QUEUE, bool DERIVE, bool ONE, int PART>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8, 8))) void kc_solve(CostArgs)
 {
-    const ArgsPtr args = (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
-    const __attribute__((address_space(4))) CostArgs& a = *args;
-    const int me = (int)blockIdx.x, all = (int)gridDim.x;
-    if constexpr (PART != REST) {
-        // what the class lists and the state word say about this workspace from now on:
-        // no tables, the inputs and results in the table region
-        if (me == 0 && (int)threadIdx.x <= STATE_WORD)
-            a.ctrl[threadIdx.x] = (int)threadIdx.x < STATE_WORD || !a.keep
-                                      ? 0
-                                      : STATE_KEPT_IN_TABLE | (DERIVE ? 0 : STATE_GIVEN) |
-                                            (a.c_fixed ? STATE_ONLY : 0) | a.c_all << STATE_C_ALL;
-        Solver<QUEUE, DERIVE, ONE> sv(args);
-        const bool done = sv.template solve<PART == ALL, false>(me);
-        if (PART == FIRST && threadIdx.x == 0) a.hard[me] = done ? 0 : 1;
-    } else {
-        // lane l of a wavefront looks at every all-th instance: the marked ones spread
-        // over the wavefronts whatever their order
-        for (long long i0 = me; i0 < a.N; i0 += 64ll * all) {
-            const long long mine_i = i0 + (long long)threadIdx.x * all;
-            unsigned long long m = __ballot(mine_i < a.N && a.hard[mine_i < a.N ? mine_i : 0] != 0);
-            while (m) {
-                const int l = __builtin_ctzll(m);
-                m &= m - 1ull;
-                Solver<QUEUE, DERIVE, ONE> sv(args);
-                sv.template solve<true, true>((int)(i0 + (long long)l * all));
-                wave_lds_fence();
-            }
-        }
-    }
+    const ArgsPtr args = kernel_args();
+    if (PART != REST)
+        mark_workspace(args, STATE_KEPT_IN_TABLE | (DERIVE ? 0 : STATE_GIVEN) |
+                                 (args->c_fixed ? STATE_ONLY : 0) | args->c_all << STATE_C_ALL);
+    for_instances<PART>(args, [&](int i) {
+        return solve_instance<QUEUE, DERIVE, ONE, PLAIN, PART != FIRST, PART == REST>(
+                   args, i, args->lambda[i]) != UNFINISHED;
+    });
 }
 
-constexpr size_t LDS_PER_CU = 160 * 1024;
+typedef void (*CostKernel)(CostArgs);
 
-constexpr int MAX_WINDOW = 8192;
-
-// Batches of up to this many instances per compute unit take one launch whose
-// wavefronts finish whatever they take: a second launch costs some four microseconds.
-constexpr int SINGLE_LAUNCH_PER_CU = 32;
+template <int QUEUE, bool DERIVE>
+CostKernel solve_kernel(int part, bool one)
+{
+    if (part == REST) return &kc_solve<QUEUE, DERIVE, false, REST>;
+    if (part == ALL)
+        return one ? &kc_solve<QUEUE, DERIVE, true, ALL> : &kc_solve<QUEUE, DERIVE, false, ALL>;
+    return one ? &kc_solve<QUEUE, DERIVE, true, FIRST> : &kc_solve<QUEUE, DERIVE, false, FIRST>;
+}
 
 }  // namespace
 
@@ -1052,92 +92,21 @@ hipError_t launch_cost_solve(const themis_problem_t& p, const Layout& L, const i
                              int32_t* d_ticks, int32_t* d_cfg, char* ws, hipStream_t st,
                              const PassOpts& opts)
 {
-    CostArgs a{};
-    a.coef = d_coef;
-    a.lambda = d_lambda;
-    a.slo_us = d_slo_us;
-    a.r_fixed = d_r_fixed;
-    a.c_fixed = opts.c_fixed;
-    a.status = d_status;
-    a.cost = d_cost;
-    a.ticks = d_ticks;
-    a.cfg = d_cfg;
-    a.tmeta = (int32_t*)(ws + L.tmeta_off);
-    a.hard = (int32_t*)(ws + L.ans_off);
-    a.ctrl = (int32_t*)(ws + L.ctrl_off);
-    a.frow = (uint16_t*)(ws + L.frow_off);
-    a.kept = make_keep_layout(p);
-    a.keep = opts.inspectable ? (int32_t*)(ws + L.step_off) : nullptr;
-    a.n_batch = p.n_batch;
-    for (int j = 0; j < p.n_batch; ++j)
-        a.bc[j] = {(double)p.batch_sizes[j], (1.0 / (1.0e6 * p.batch_sizes[j])) * (1.0 - 0x1p-45)};
-    a.N = L.N;
-    a.S = L.S;
-    a.cs = p.profile_form == THEMIS_PROFILE_EQ1 ? 6 : 5;
-    a.c_max = p.c_max;
-    a.r_max = p.r_max;
-    a.tick = p.tick_us;
-    a.slo_max = p.slo_max_us;
-    a.coef_shared = p.coef_shared;
-    a.c_all = opts.c_all;
-    a.sparse = opts.sparse;
-    a.row_stride = L.row_stride;
-    a.nb_magic = (65536u + (uint32_t)p.n_batch - 1u) / (uint32_t)p.n_batch;
-    a.k_magic = ((1u << 20) + (uint32_t)p.n_batch - 1u) / (uint32_t)p.n_batch;
-    a.rtick = (1.0 / (double)p.tick_us) * (1.0 - 0x1p-45);
-
-    auto lds_for = [&](int waves, int window) {
-        return (size_t)waves * cost_lds(L.S, window).words * sizeof(uint32_t);
-    };
-    // the largest window that leaves `per_cu` wavefronts on a compute unit, no larger
-    // than the costs of a pipeline can spread
-    auto widest = [&](int per_cu, int most) {
-        int w = 64;
-        while (w + 64 <= most && w < L.S * p.r_max * p.c_max &&
-               lds_for(1, w + 64) <= LDS_PER_CU / per_cu)
-            w += 64;
-        return w;
-    };
-    auto launch = [&](auto kernel, int grid, size_t lds) -> hipError_t {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)(LDS_PER_CU - 1024));
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64), lds, st, a);
-        return hipGetLastError();
-    };
-    const int cus = compute_units();
-    auto run = [&](auto q_tag, auto d_tag, auto one_tag) -> hipError_t {
-        constexpr int Q = decltype(q_tag)::value;
-        constexpr bool D = decltype(d_tag)::value, ONE = decltype(one_tag)::value;
-        if (L.N <= SINGLE_LAUNCH_PER_CU * cus) {
-            // one launch, with whatever window they leave each other on a compute unit
-            const int per_cu = (L.N + cus - 1) / cus;
-            a.hard = nullptr;
-            a.window = widest(per_cu < 4 ? 4 : per_cu, MAX_WINDOW);
-            return launch(&kc_solve<Q, D, ONE, ALL>, L.N, lds_for(1, a.window));
+    CostArgs a = cost_args(p, L, d_coef, d_lambda, d_slo_us, d_r_fixed, d_status, d_cost, d_ticks,
+                           d_cfg, ws, opts);
+    return launch_parts(p, L, a, st, [&](int part, bool one) {
+        switch (p.queue_model) {
+        case THEMIS_QUEUE_SHARED:
+            return d_r_fixed ? solve_kernel<THEMIS_QUEUE_SHARED, false>(part, one)
+                             : solve_kernel<THEMIS_QUEUE_SHARED, true>(part, one);
+        case THEMIS_QUEUE_WORST_CASE:
+            return d_r_fixed ? solve_kernel<THEMIS_QUEUE_WORST_CASE, false>(part, one)
+                             : solve_kernel<THEMIS_QUEUE_WORST_CASE, true>(part, one);
+        default:
+            return d_r_fixed ? solve_kernel<THEMIS_QUEUE_PER_REPLICA, false>(part, one)
+                             : solve_kernel<THEMIS_QUEUE_PER_REPLICA, true>(part, one);
         }
-        a.window = widest(32, FIRST_WINDOWS);
-        hipError_t e = launch(&kc_solve<Q, D, ONE, FIRST>, L.N, lds_for(1, a.window));
-        if (e != hipSuccess) return e;
-        a.tried = a.window;
-        a.window = widest(4, MAX_WINDOW);
-        return launch(&kc_solve<Q, D, false, REST>, 4 * cus, lds_for(1, a.window));
-    };
-    auto by_pairs = [&](auto q_tag, auto d_tag) -> hipError_t {
-        return L.S * p.n_batch <= 64 ? run(q_tag, d_tag, std::true_type{})
-                                     : run(q_tag, d_tag, std::false_type{});
-    };
-    auto by_replicas = [&](auto q_tag) -> hipError_t {
-        return d_r_fixed ? by_pairs(q_tag, std::false_type{}) : by_pairs(q_tag, std::true_type{});
-    };
-    switch (p.queue_model) {
-    case THEMIS_QUEUE_SHARED:
-        return by_replicas(std::integral_constant<int, THEMIS_QUEUE_SHARED>{});
-    case THEMIS_QUEUE_WORST_CASE:
-        return by_replicas(std::integral_constant<int, THEMIS_QUEUE_WORST_CASE>{});
-    default: return by_replicas(std::integral_constant<int, THEMIS_QUEUE_PER_REPLICA>{});
-    }
+    });
 }
 
 }  // namespace themis

@@ -205,6 +205,11 @@ int themis_solve_vertical_fallback(const themis_problem_t* p, const int32_t* d_c
     const FallbackOut out{d_status, d_cost,     d_ticks, d_cfg,    d_lambda_v,
                           d_status_h, d_cost_h, d_ticks_h, d_cfg_h};
 
+    if (cost_solve_serves(L))
+        return launch_cost_fallback(*p, L, d_coef, d_lambda, d_slo_us, d_r_fixed, out, w, st) ==
+                       hipSuccess
+                   ? THEMIS_OK
+                   : THEMIS_ERR_LAUNCH;
     // the plain vertical solve, reported for every instance
     rc = pass(*p, L, d_coef, d_lambda, d_slo_us, d_r_fixed, d_status, d_cost, d_ticks, d_cfg, w,
               st, PassOpts());
@@ -293,6 +298,12 @@ int themis_check_stability(const themis_problem_t* p, const int32_t* d_coef,
     PassOpts opts;
     opts.c_fixed = d_cores;
     opts.c_all = d_cores ? 0 : 1;
+    if (cost_solve_serves(L))
+        return launch_cost_stability(*p, L, B, d_coef, d_lambda_now, d_lambda_pred, d_slo_us,
+                                     d_stable, d_status, d_cost, d_ticks, d_cfg, w, st,
+                                     opts) == hipSuccess
+                   ? THEMIS_OK
+                   : THEMIS_ERR_LAUNCH;
     int32_t* status_p = (int32_t*)(w + B.status_off);
     int32_t* cfg_p = (int32_t*)(w + B.cfg_off);
     rc = pass(*p, L, d_coef, d_lambda_pred, d_slo_us, nullptr, status_p,

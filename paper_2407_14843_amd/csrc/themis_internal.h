@@ -331,26 +331,6 @@ hipError_t launch_fallback_search(const themis_problem_t& p, const Layout& L,
 hipError_t launch_fallback_finish(const Layout& L, const FallbackLayout& F,
                                   const int32_t* d_lambda, const FallbackOut& out, char* ws,
                                   hipStream_t st);
-// Results of the solve at the predicted rate, appended to the workspace after
-// Layout::total for the stability test: status, cost, ticks int32 [N] each and
-// cfg int32 [N][S][3].
-struct StabilityLayout {
-    size_t status_off, cost_off, ticks_off, cfg_off, total;
-};
-
-inline StabilityLayout make_stability_layout(const Layout& L)
-{
-    StabilityLayout B{};
-    size_t at = L.total;
-    const size_t n4 = (size_t)L.N * sizeof(int32_t);
-    B.status_off = at; at = align256(at + n4);
-    B.cost_off = at;   at = align256(at + n4);
-    B.ticks_off = at;  at = align256(at + n4);
-    B.cfg_off = at;    at = align256(at + n4 * L.S * 3);
-    B.total = at;
-    return B;
-}
-
 // State of the solve that handles every distinct instance once, appended to
 // the workspace after Layout::total:
 //   rep    int32 [N]      index of the instance that stands for this one's inputs
@@ -374,6 +354,39 @@ inline MemoLayout make_memo_layout(const Layout& L)
     M.total = at;
     return M;
 }
+
+// Results of the solve at the predicted rate, appended to the workspace after
+// Layout::total for the stability test: status, cost, ticks int32 [N] each and
+// cfg int32 [N][S][3].
+struct StabilityLayout {
+    size_t status_off, cost_off, ticks_off, cfg_off, total;
+};
+
+inline StabilityLayout make_stability_layout(const Layout& L)
+{
+    StabilityLayout B{};
+    size_t at = L.total;
+    const size_t n4 = (size_t)L.N * sizeof(int32_t);
+    B.status_off = at; at = align256(at + n4);
+    B.cost_off = at;   at = align256(at + n4);
+    B.ticks_off = at;  at = align256(at + n4);
+    B.cfg_off = at;    at = align256(at + n4 * L.S * 3);
+    B.total = at;
+    return B;
+}
+
+// The entry points that solve an instance more than once, an instance's solves by one
+// wavefront (cost_multi.hip); for problems that cost_solve_serves().
+hipError_t launch_cost_fallback(const themis_problem_t& p, const Layout& L, const int32_t* d_coef,
+                                const int32_t* d_lambda, const int32_t* d_slo_us,
+                                const int32_t* d_r_fixed, const FallbackOut& out, char* ws,
+                                hipStream_t st);
+hipError_t launch_cost_stability(const themis_problem_t& p, const Layout& L,
+                                 const StabilityLayout& B, const int32_t* d_coef,
+                                 const int32_t* d_lambda_now, const int32_t* d_lambda_pred,
+                                 const int32_t* d_slo_us, int32_t* d_stable, int32_t* d_status,
+                                 int32_t* d_cost, int32_t* d_ticks, int32_t* d_cfg, char* ws,
+                                 hipStream_t st, const PassOpts& opts);
 
 hipError_t launch_memo_dedupe(const themis_problem_t& p, const Layout& L, const MemoLayout& M,
                               const int32_t* d_coef, const int32_t* d_lambda,

@@ -132,3 +132,50 @@ def test_workspace_after_a_horizontal_solve(T, oracle):
     assert (lt == np.where(mine, lt_o, -1)).all()
     assert (co == np.where(mine & (lt_o >= 0), co_o, -1)).all()
     same(backtrack(T, b), want)
+
+
+@pytest.mark.parametrize("idx,n", [(2, 60), (4, 9000)])
+def test_fallback_and_stability_in_one_wavefront(T, oracle, idx, n):
+    """The multi-solve entry points on one launch and on two, with overload, rates equal to
+    the prediction and a prediction out of range."""
+    w = wl.workload(idx, n)
+    rng = np.random.default_rng(idx)
+    if idx == 4:
+        w = w.with_r_fixed(rng.integers(1, 5, (w.n_inst, w.n_stage)))
+    w.lam = np.minimum(w.lam.astype(np.int64) * rng.integers(1, 6, n), 1 << 20).astype(np.int32)
+    w.lam[1] = -5
+    b = T.DeviceBatch(w)
+    b.solve_vertical_fallback()
+    got, want = b.fallback_results(), oracle.vertical_fallback(w, threads=8)
+    for k in want:
+        assert (got[k] == want[k]).all(), k
+    assert ((want["lambda_v"] > 0) & (want["lambda_v"] < w.lam)).any()  # searched and split
+    pred = np.where(rng.random(n) < 0.5, w.lam, w.lam + rng.integers(-2, 30, n)).astype(np.int32)
+    pred[2] = 0
+    stable = b.check_stability(pred)
+    want = oracle.stability(w, pred)
+    assert (stable.cpu().numpy() == want[0]).all()
+    same(b.results(), want[1:])
+    assert 0 < want[0].mean() < 1
+
+
+def test_workspace_after_multi_solves(T, oracle):
+    """After a multi-solve call the workspace shows its last solve: instances that one was
+    not given have no tables and read as invalid."""
+    w = wl.workload(4, 1100)
+    w = w.take(np.arange(1100) % 400)
+    b = T.DeviceBatch(w)
+    b.workspace = __import__("torch").empty(T.memo_workspace_bytes(b.p), dtype=b.workspace.dtype,
+                                            device=b.device)
+    b.memo_workspace = b.workspace
+    b.solve_distinct()
+    want = oracle.solve(w, threads=8)
+    same(b.results(), want)
+    lt, _, _ = inspect(T, b)
+    lt_o, _, _ = oracle.candidates(w)
+    solved_here = (lt >= 0).any(axis=(1, 2))
+    assert 0 < solved_here.sum() < w.n_inst
+    assert (lt[solved_here] == lt_o[solved_here]).all()
+    got = backtrack(T, b)
+    same(tuple(g[solved_here] for g in got), tuple(x[solved_here] for x in want))
+    assert (got[0][~solved_here] == 2).all() and (got[3][~solved_here] == 0).all()
