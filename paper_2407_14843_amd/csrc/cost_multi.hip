@@ -82,12 +82,8 @@ __device__ __forceinline__ bool fallback_instance(ArgsPtr args, int i)
     wave_lds_fence();
     if (rest == 0) {
         // nothing to solve; for calls that look at the workspace afterwards the instance
-        // is one that the last solve was not given (shared coefficients are in the first
-        // record all the same)
-        bool valid;
-        if (nw.a.coef_shared && nw.keeps_coef()) nw.begin(i, 0, valid);
+        // is one that the last solve was not given
         nw.put_none(solved ? THEMIS_SOLVED : THEMIS_INVALID, solved ? 0 : -1);
-        nw.record_none(THEMIS_INVALID);
         if (nw.lane == 0) args->tmeta[i] = -1;
         return true;
     }

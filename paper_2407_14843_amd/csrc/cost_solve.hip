@@ -66,8 +66,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8, 8))) void
         mark_workspace(args, STATE_KEPT_IN_TABLE | (DERIVE ? 0 : STATE_GIVEN) |
                                  (args->c_fixed ? STATE_ONLY : 0) | args->c_all << STATE_C_ALL);
     for_instances<PART>(args, [&](int i) {
+        ArgsPtr again = args;
+        // a loop over instances starts each from the arguments again: what could be kept of
+        // them from one to the next would cost registers that the steps need
+        if (PART == LISTED || PART == REST) asm volatile("" : "+s"(again));
         return solve_instance<QUEUE, DERIVE, ONE, PLAIN, PART != FIRST, PART == REST>(
-                   args, i, args->lambda[i]) != UNFINISHED;
+                   again, i, again->lambda[i]) != UNFINISHED;
     });
 }
 
@@ -77,6 +81,8 @@ template <int QUEUE, bool DERIVE>
 CostKernel solve_kernel(int part, bool one)
 {
     if (part == REST) return &kc_solve<QUEUE, DERIVE, false, REST>;
+    if (part == LISTED)
+        return one ? &kc_solve<QUEUE, DERIVE, true, LISTED> : &kc_solve<QUEUE, DERIVE, false, LISTED>;
     if (part == ALL)
         return one ? &kc_solve<QUEUE, DERIVE, true, ALL> : &kc_solve<QUEUE, DERIVE, false, ALL>;
     return one ? &kc_solve<QUEUE, DERIVE, true, FIRST> : &kc_solve<QUEUE, DERIVE, false, FIRST>;

@@ -31,13 +31,14 @@ struct CostArgs {
     int32_t *lambda_v, *stable;
     int32_t* tmeta;     // budgets, for calls that inspect the workspace afterwards
     int32_t* hard;      // per instance: left to the launch with the large window
+    const int32_t* list;  // the instances to solve (LISTED)
     int32_t* ctrl;
     uint16_t* frow;     // rows of step D
     int32_t* keep;      // inputs and results for such calls, or null
     KeepLayout kept;
     BatchConst bc[THEMIS_MAX_BATCH];
     int32_t n_batch;
-    int32_t N, S, cs, c_max, r_max, tick, slo_max, coef_shared, c_all, sparse, row_stride;
+    int32_t N, S, cs, c_max, r_max, tick, slo_max, coef_shared, c_all, row_stride;
     int32_t window;     // cells of the largest window, a multiple of 64
     int32_t tried;      // cells of the largest one tried before (0: none)
     uint32_t nb_magic;  // ceil(2^16 / n_batch): x / n_batch = x * nb_magic >> 16 for x < 1024
@@ -334,20 +335,15 @@ struct Solver {
         record_result(status, cost, ticks);
     }
 
-    __device__ __forceinline__ void record_none(int32_t status) const
-    {
-        record_result(status, -1, -1);
-        if (records())
-            for (int x = lane; x < 3 * a.S; x += 64) record()[a.kept.cfg + x] = 0;
-    }
-
     // `amount`: what the result says for cost and ticks
     __device__ __forceinline__ void put_none(int32_t status, int32_t amount = -1) const
     {
         put(status, amount, amount);
         int32_t* const out = config();
-        for (int x = lane; x < 3 * a.S; x += 64) out[x] = 0;
-        record_none(status);
+        for (int x = lane; x < 3 * a.S; x += 64) {
+            out[x] = 0;
+            if (records()) record()[a.kept.cfg + x] = 0;
+        }
     }
 
     // lane s < S: index and cost of model s's candidate
@@ -377,7 +373,7 @@ struct Solver {
     // coefficients, loaded with the rest of the inputs.
     __device__ __forceinline__ bool keeps_coef() const
     {
-        return records() && (!a.coef_shared || i == 0);  // shared: the first record has them
+        return records() && !a.coef_shared;  // shared: see mark_workspace()
     }
     __device__ __forceinline__ void keep_inputs(bool valid, int32_t word) const
     {
@@ -1002,11 +998,7 @@ __device__ __forceinline__ int solve_instance(ArgsPtr args, int inst, int32_t ra
     bool valid;
     const auto first = sv.begin(inst, rate, valid);
     if (!valid) {
-        // switched off in this pass: results stay as they are
-        if (ROLE == PLAIN && args->sparse)
-            sv.record_none(THEMIS_INVALID);
-        else
-            sv.put_none(THEMIS_INVALID);
+        sv.put_none(THEMIS_INVALID);
         return THEMIS_INVALID;
     }
     const int status = sv.template solve<LAST, MARKED>(first);
@@ -1015,17 +1007,23 @@ __device__ __forceinline__ int solve_instance(ArgsPtr args, int inst, int32_t ra
 }
 
 // What the class lists and the state word say about the workspace after a solve: no
-// tables, the inputs and results in the table region.
+// tables, the inputs and results in the table region.  Shared coefficients are in the
+// first record, whether or not that instance is solved.
 __device__ __forceinline__ void mark_workspace(ArgsPtr args, int state)
 {
-    if (blockIdx.x == 0 && (int)threadIdx.x <= STATE_WORD)
+    if (blockIdx.x != 0) return;
+    if ((int)threadIdx.x <= STATE_WORD)
         args->ctrl[threadIdx.x] = (int)threadIdx.x < STATE_WORD || !args->keep ? 0 : state;
+    if (args->keep && args->coef_shared)
+        for (int x = (int)threadIdx.x; x < args->S * args->cs; x += 64)
+            (args->keep + args->kept.coef)[x] = args->coef[x];
 }
 
 // A launch's share of the instances.  FIRST: instance by workgroup, `f` returns false
 // for those the first windows do not solve, which are marked in `hard`.  REST: the
-// marked instances.  ALL: instance by workgroup, to the end.
-enum { FIRST, REST, ALL };
+// marked instances.  ALL: instance by workgroup, to the end.  LISTED: the same for the
+// instances of a list.
+enum { FIRST, REST, ALL, LISTED };
 template <int PART, typename F>
 __device__ __forceinline__ void for_instances(ArgsPtr args, F f)
 {
@@ -1035,6 +1033,12 @@ __device__ __forceinline__ void for_instances(ArgsPtr args, F f)
         if (threadIdx.x == 0) args->hard[me] = done ? 0 : 1;
     } else if constexpr (PART == ALL) {
         f(me);
+    } else if constexpr (PART == LISTED) {
+        const int n = args->ctrl[LIST_WORD];
+        for (int k = me; k < n; k += all) {
+            f(__builtin_amdgcn_readfirstlane(args->list[k]));
+            wave_lds_fence();
+        }
     } else {
         // lane l of a wavefront looks at every all-th instance: the marked ones spread
         // over the wavefronts whatever their order
@@ -1104,7 +1108,7 @@ inline CostArgs cost_args(const themis_problem_t& p, const Layout& L, const int3
     a.slo_max = p.slo_max_us;
     a.coef_shared = p.coef_shared;
     a.c_all = opts.c_all;
-    a.sparse = opts.sparse;
+    a.list = opts.list;
     a.row_stride = L.row_stride;
     a.nb_magic = (65536u + (uint32_t)p.n_batch - 1u) / (uint32_t)p.n_batch;
     a.k_magic = ((1u << 20) + (uint32_t)p.n_batch - 1u) / (uint32_t)p.n_batch;
@@ -1130,16 +1134,21 @@ hipError_t launch_parts(const themis_problem_t& p, const Layout& L, CostArgs& a,
             w += 64;
         return w;
     };
+    // (at most 40 KB, which a kernel may have without asking)
     auto launch = [&](auto kernel, int grid, size_t lds) -> hipError_t {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)(LDS_PER_CU - 1024));
-        if (e != hipSuccess) return e;
         hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64), lds, st, a);
         return hipGetLastError();
     };
     const int cus = compute_units();
     const bool one = L.S * p.n_batch <= 64;
+    if (a.list) {
+        // the host does not know how many: as many workgroups as stay resident walk the list
+        const int grid = L.N < 32 * cus ? L.N : 32 * cus;
+        const int per_cu = (grid + cus - 1) / cus;
+        a.hard = nullptr;
+        a.window = widest(per_cu < 4 ? 4 : per_cu, MAX_WINDOW);
+        return launch(kernel(LISTED, one), grid, lds_for(1, a.window));
+    }
     if (L.N <= SINGLE_LAUNCH_PER_CU * cus) {
         // one launch, with whatever window they leave each other on a compute unit
         const int per_cu = (L.N + cus - 1) / cus;

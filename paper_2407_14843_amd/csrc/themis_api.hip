@@ -259,12 +259,16 @@ int themis_solve_distinct(const themis_problem_t* p, const int32_t* d_coef,
     if (launch_memo_dedupe(*p, L, M, d_coef, d_lambda, d_slo_us, d_r_fixed, d_status, d_cost,
                            d_ticks, d_cfg, w, st) != hipSuccess)
         return THEMIS_ERR_LAUNCH;
-    // one pass over the instances that stand for themselves; the others carry a
-    // rate of zero, which switches them off
+    // one pass over the instances that stand for themselves; for the three stages the
+    // others carry a rate of zero, which switches them off
     PassOpts only_distinct;
-    only_distinct.sparse = 1;
-    rc = pass(*p, L, d_coef, (const int32_t*)(w + M.lam_off), d_slo_us, d_r_fixed, d_status, d_cost,
-              d_ticks, d_cfg, w, st, only_distinct);
+    const int32_t* const selected = (const int32_t*)(w + M.pass_off);
+    if (cost_solve_serves(L))
+        only_distinct.list = selected;
+    else
+        only_distinct.sparse = 1;
+    rc = pass(*p, L, d_coef, only_distinct.list ? d_lambda : selected, d_slo_us, d_r_fixed, d_status,
+              d_cost, d_ticks, d_cfg, w, st, only_distinct);
     if (rc != THEMIS_OK) return rc;
     return launch_memo_scatter(L, M, d_status, d_cost, d_ticks, d_cfg, w, st) == hipSuccess
                ? THEMIS_OK

@@ -212,6 +212,7 @@ inline Layout make_layout(const themis_problem_t& p)
 // Export and count first build the tables where there are none (launch_tables_after_solve);
 // the backtrack call then hands out the results.  Budgets are in tmeta in every state.
 constexpr int STATE_WORD = 2 * N_CLS;
+constexpr int LIST_WORD = STATE_WORD + 1;  // instances in the list of a listed solve
 constexpr int STATE_KEPT_IN_TABLE = 1, STATE_KEPT_IN_ROWS = 2;
 constexpr int STATE_GIVEN = 4;    // the replicas were given
 constexpr int STATE_REBUILD = 8;  // the candidate launches that follow have work to do
@@ -256,6 +257,8 @@ struct PassOpts {
     int c_all = 0;  // nonzero and c_fixed null: these cores for every model
     int sparse = 0;
     bool inspectable = true;  // the caller can look at the workspace afterwards
+    const int32_t* list = nullptr;  // one-wavefront solve: the instances to solve,
+                                    // their number in the control word LIST_WORD
 };
 
 // The one-wavefront solve: three stages' worth of results in one or two launches.
@@ -334,10 +337,11 @@ hipError_t launch_fallback_finish(const Layout& L, const FallbackLayout& F,
 // State of the solve that handles every distinct instance once, appended to
 // the workspace after Layout::total:
 //   rep    int32 [N]      index of the instance that stands for this one's inputs
-//   lam    int32 [N]      arrival rates of the pass: 0 unless the instance stands for itself
+//   pass   int32 [N]      the instances that stand for themselves (or, for the three stages,
+//                         the arrival rates of the pass: 0 unless the instance does)
 //   table  int32 [slots]  hash table of instance indices, slots = power of two >= 2 N
 struct MemoLayout {
-    size_t rep_off, lam_off, table_off, total;
+    size_t rep_off, pass_off, table_off, total;
     uint32_t slots;
 };
 
@@ -349,7 +353,7 @@ inline MemoLayout make_memo_layout(const Layout& L)
     M.slots = 256u;
     while (M.slots < 2u * (uint32_t)L.N) M.slots <<= 1;
     M.rep_off = at;   at = align256(at + n4);
-    M.lam_off = at;   at = align256(at + n4);
+    M.pass_off = at;  at = align256(at + n4);
     M.table_off = at; at = align256(at + (size_t)M.slots * sizeof(int32_t));
     M.total = at;
     return M;
