@@ -42,8 +42,8 @@ __device__ __forceinline__ int32_t search_rate(Solver<QUEUE, false, ONE, QUIET>&
     return lo;
 }
 
-template <int QUEUE, bool ONE, bool LAST, bool MARKED>
-__device__ __forceinline__ bool fallback_instance(ArgsPtr args, int i)
+template <int QUEUE, bool ONE>
+__device__ __forceinline__ void fallback_instance(ArgsPtr args, int i)
 {
     Solver<QUEUE, false, ONE, QUIET> sv(args);
     const int32_t lambda = args->lambda[i];
@@ -54,8 +54,7 @@ __device__ __forceinline__ bool fallback_instance(ArgsPtr args, int i)
         auto first = sv.begin(i, lambda, valid);
         status = valid ? THEMIS_INFEASIBLE : THEMIS_INVALID;
         for (bool searched = false; valid; searched = true) {
-            status = sv.template solve<LAST, MARKED>(first);
-            if (status == UNFINISHED) return false;
+            status = sv.solve(first);
             if (searched || status != THEMIS_INFEASIBLE) break;
             // (lambda is the largest rate met, so the short divisions stay allowed)
             if (__builtin_amdgcn_readfirstlane((int)((double)lambda * (double)sv.slo <= 0x1p42)))
@@ -85,38 +84,29 @@ __device__ __forceinline__ bool fallback_instance(ArgsPtr args, int i)
         // is one that the last solve was not given
         nw.put_none(solved ? THEMIS_SOLVED : THEMIS_INVALID, solved ? 0 : -1);
         if (nw.lane == 0) args->tmeta[i] = -1;
-        return true;
+        return;
     }
     bool valid;
     const auto first = nw.begin(i, rest, valid);
-    status = nw.template solve<LAST, MARKED>(first);
-    if (status == UNFINISHED) return false;
-    if (status == THEMIS_INFEASIBLE) nw.put_none(THEMIS_INFEASIBLE);
-    return true;
+    if (nw.solve(first) == THEMIS_INFEASIBLE) nw.put_none(THEMIS_INFEASIBLE);
 }
 
-template <int QUEUE, bool ONE, int PART>
+template <int QUEUE, bool ONE>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6, 8))) void kc_fallback(CostArgs)
 {
     const ArgsPtr args = kernel_args();
-    if (PART != REST) mark_workspace(args, STATE_KEPT_IN_TABLE | STATE_ONLY);
-    for_instances<PART>(args, [&](int i) {
-        return fallback_instance<QUEUE, ONE, PART != FIRST, PART == REST>(args, i);
-    });
+    mark_workspace(args, STATE_KEPT_IN_TABLE | STATE_ONLY);
+    fallback_instance<QUEUE, ONE>(args, (int)blockIdx.x);
 }
 
-template <int QUEUE, bool ONE, bool LAST, bool MARKED>
-__device__ __forceinline__ bool stability_instance(ArgsPtr args, int i)
+template <int QUEUE, bool ONE>
+__device__ __forceinline__ void stability_instance(ArgsPtr args, int i)
 {
     const int32_t now = args->lambda[i], pred = args->lambda2[i];
-    const int status = solve_instance<QUEUE, true, ONE, PLAIN, LAST, MARKED>(args, i, now);
-    if (status == UNFINISHED) return false;
-    bool stable = status == THEMIS_SOLVED;
+    bool stable = solve_instance<QUEUE, true, ONE, PLAIN>(args, i, now) == THEMIS_SOLVED;
     wave_lds_fence();
     if (stable && pred != now) {
-        const int other = solve_instance<QUEUE, true, ONE, SECOND, LAST, MARKED>(args, i, pred);
-        if (other == UNFINISHED) return false;
-        stable = other == THEMIS_SOLVED;
+        stable = solve_instance<QUEUE, true, ONE, SECOND>(args, i, pred) == THEMIS_SOLVED;
         if (stable) {
             bool same = true;
             if ((int)threadIdx.x < args->S) {
@@ -129,38 +119,27 @@ __device__ __forceinline__ bool stability_instance(ArgsPtr args, int i)
         }
     }
     if (threadIdx.x == 0) args->stable[i] = stable ? 1 : 0;
-    return true;
 }
 
-template <int QUEUE, bool ONE, int PART>
+template <int QUEUE, bool ONE>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8, 8))) void kc_stability(CostArgs)
 {
     const ArgsPtr args = kernel_args();
-    if (PART != REST)
-        mark_workspace(args, STATE_KEPT_IN_TABLE | (args->c_fixed ? STATE_ONLY : 0) |
-                                 args->c_all << STATE_C_ALL);
-    for_instances<PART>(args, [&](int i) {
-        return stability_instance<QUEUE, ONE, PART != FIRST, PART == REST>(args, i);
-    });
-}
-
-typedef void (*CostKernel)(CostArgs);
-
-template <int QUEUE>
-CostKernel fallback_kernel(int part, bool one)
-{
-    if (part == REST) return &kc_fallback<QUEUE, false, REST>;
-    if (part == ALL) return one ? &kc_fallback<QUEUE, true, ALL> : &kc_fallback<QUEUE, false, ALL>;
-    return one ? &kc_fallback<QUEUE, true, FIRST> : &kc_fallback<QUEUE, false, FIRST>;
+    mark_workspace(args, STATE_KEPT_IN_TABLE | (args->c_fixed ? STATE_ONLY : 0) |
+                             args->c_all << STATE_C_ALL);
+    stability_instance<QUEUE, ONE>(args, (int)blockIdx.x);
 }
 
 template <int QUEUE>
-CostKernel stability_kernel(int part, bool one)
+CostKernel fallback_kernel(bool one)
 {
-    if (part == REST) return &kc_stability<QUEUE, false, REST>;
-    if (part == ALL)
-        return one ? &kc_stability<QUEUE, true, ALL> : &kc_stability<QUEUE, false, ALL>;
-    return one ? &kc_stability<QUEUE, true, FIRST> : &kc_stability<QUEUE, false, FIRST>;
+    return one ? &kc_fallback<QUEUE, true> : &kc_fallback<QUEUE, false>;
+}
+
+template <int QUEUE>
+CostKernel stability_kernel(bool one)
+{
+    return one ? &kc_stability<QUEUE, true> : &kc_stability<QUEUE, false>;
 }
 
 }  // namespace
@@ -177,11 +156,11 @@ hipError_t launch_cost_fallback(const themis_problem_t& p, const Layout& L, cons
     a.ticks2 = out.ticks_h;
     a.cfg2 = out.cfg_h;
     a.lambda_v = out.lambda_v;
-    return launch_parts(p, L, a, st, [&](int part, bool one) {
+    return launch_per_instance(p, L, a, st, false, [&](bool one) {
         switch (p.queue_model) {
-        case THEMIS_QUEUE_SHARED: return fallback_kernel<THEMIS_QUEUE_SHARED>(part, one);
-        case THEMIS_QUEUE_WORST_CASE: return fallback_kernel<THEMIS_QUEUE_WORST_CASE>(part, one);
-        default: return fallback_kernel<THEMIS_QUEUE_PER_REPLICA>(part, one);
+        case THEMIS_QUEUE_SHARED: return fallback_kernel<THEMIS_QUEUE_SHARED>(one);
+        case THEMIS_QUEUE_WORST_CASE: return fallback_kernel<THEMIS_QUEUE_WORST_CASE>(one);
+        default: return fallback_kernel<THEMIS_QUEUE_PER_REPLICA>(one);
         }
     });
 }
@@ -201,11 +180,11 @@ hipError_t launch_cost_stability(const themis_problem_t& p, const Layout& L,
     a.cost2 = (int32_t*)(ws + B.cost_off);
     a.ticks2 = (int32_t*)(ws + B.ticks_off);
     a.cfg2 = (int32_t*)(ws + B.cfg_off);
-    return launch_parts(p, L, a, st, [&](int part, bool one) {
+    return launch_per_instance(p, L, a, st, false, [&](bool one) {
         switch (p.queue_model) {
-        case THEMIS_QUEUE_SHARED: return stability_kernel<THEMIS_QUEUE_SHARED>(part, one);
-        case THEMIS_QUEUE_WORST_CASE: return stability_kernel<THEMIS_QUEUE_WORST_CASE>(part, one);
-        default: return stability_kernel<THEMIS_QUEUE_PER_REPLICA>(part, one);
+        case THEMIS_QUEUE_SHARED: return stability_kernel<THEMIS_QUEUE_SHARED>(one);
+        case THEMIS_QUEUE_WORST_CASE: return stability_kernel<THEMIS_QUEUE_WORST_CASE>(one);
+        default: return stability_kernel<THEMIS_QUEUE_PER_REPLICA>(one);
         }
     });
 }

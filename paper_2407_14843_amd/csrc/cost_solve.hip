@@ -58,34 +58,36 @@
 namespace themis {
 namespace {
 
-template <int QUEUE, bool DERIVE, bool ONE, int PART>
+// LISTED: the instances of a list, each workgroup some of them; else one per workgroup.
+template <int QUEUE, bool DERIVE, bool ONE, bool LISTED>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8, 8))) void kc_solve(CostArgs)
 {
     const ArgsPtr args = kernel_args();
-    if (PART != REST)
-        mark_workspace(args, STATE_KEPT_IN_TABLE | (DERIVE ? 0 : STATE_GIVEN) |
-                                 (args->c_fixed ? STATE_ONLY : 0) | args->c_all << STATE_C_ALL);
-    for_instances<PART>(args, [&](int i) {
+    mark_workspace(args, STATE_KEPT_IN_TABLE | (DERIVE ? 0 : STATE_GIVEN) |
+                             (args->c_fixed ? STATE_ONLY : 0) | args->c_all << STATE_C_ALL);
+    if (!LISTED) {
+        const int i = (int)blockIdx.x;
+        solve_instance<QUEUE, DERIVE, ONE, PLAIN>(args, i, args->lambda[i]);
+        return;
+    }
+    const int n = args->ctrl[LIST_WORD];
+    for (int k = (int)blockIdx.x; k < n; k += (int)gridDim.x) {
+        // every instance starts from the arguments again: what could be kept of them from
+        // one to the next would cost registers that the steps need
         ArgsPtr again = args;
-        // a loop over instances starts each from the arguments again: what could be kept of
-        // them from one to the next would cost registers that the steps need
-        if (PART == LISTED || PART == REST) asm volatile("" : "+s"(again));
-        return solve_instance<QUEUE, DERIVE, ONE, PLAIN, PART != FIRST, PART == REST>(
-                   again, i, again->lambda[i]) != UNFINISHED;
-    });
+        asm volatile("" : "+s"(again));
+        const int i = __builtin_amdgcn_readfirstlane(again->list[k]);
+        solve_instance<QUEUE, DERIVE, ONE, PLAIN>(again, i, again->lambda[i]);
+        wave_lds_fence();
+    }
 }
 
-typedef void (*CostKernel)(CostArgs);
-
 template <int QUEUE, bool DERIVE>
-CostKernel solve_kernel(int part, bool one)
+CostKernel solve_kernel(bool listed, bool one)
 {
-    if (part == REST) return &kc_solve<QUEUE, DERIVE, false, REST>;
-    if (part == LISTED)
-        return one ? &kc_solve<QUEUE, DERIVE, true, LISTED> : &kc_solve<QUEUE, DERIVE, false, LISTED>;
-    if (part == ALL)
-        return one ? &kc_solve<QUEUE, DERIVE, true, ALL> : &kc_solve<QUEUE, DERIVE, false, ALL>;
-    return one ? &kc_solve<QUEUE, DERIVE, true, FIRST> : &kc_solve<QUEUE, DERIVE, false, FIRST>;
+    if (listed)
+        return one ? &kc_solve<QUEUE, DERIVE, true, true> : &kc_solve<QUEUE, DERIVE, false, true>;
+    return one ? &kc_solve<QUEUE, DERIVE, true, false> : &kc_solve<QUEUE, DERIVE, false, false>;
 }
 
 }  // namespace
@@ -100,17 +102,18 @@ hipError_t launch_cost_solve(const themis_problem_t& p, const Layout& L, const i
 {
     CostArgs a = cost_args(p, L, d_coef, d_lambda, d_slo_us, d_r_fixed, d_status, d_cost, d_ticks,
                            d_cfg, ws, opts);
-    return launch_parts(p, L, a, st, [&](int part, bool one) {
+    const bool listed = opts.list != nullptr;
+    return launch_per_instance(p, L, a, st, listed, [&](bool one) {
         switch (p.queue_model) {
         case THEMIS_QUEUE_SHARED:
-            return d_r_fixed ? solve_kernel<THEMIS_QUEUE_SHARED, false>(part, one)
-                             : solve_kernel<THEMIS_QUEUE_SHARED, true>(part, one);
+            return d_r_fixed ? solve_kernel<THEMIS_QUEUE_SHARED, false>(listed, one)
+                             : solve_kernel<THEMIS_QUEUE_SHARED, true>(listed, one);
         case THEMIS_QUEUE_WORST_CASE:
-            return d_r_fixed ? solve_kernel<THEMIS_QUEUE_WORST_CASE, false>(part, one)
-                             : solve_kernel<THEMIS_QUEUE_WORST_CASE, true>(part, one);
+            return d_r_fixed ? solve_kernel<THEMIS_QUEUE_WORST_CASE, false>(listed, one)
+                             : solve_kernel<THEMIS_QUEUE_WORST_CASE, true>(listed, one);
         default:
-            return d_r_fixed ? solve_kernel<THEMIS_QUEUE_PER_REPLICA, false>(part, one)
-                             : solve_kernel<THEMIS_QUEUE_PER_REPLICA, true>(part, one);
+            return d_r_fixed ? solve_kernel<THEMIS_QUEUE_PER_REPLICA, false>(listed, one)
+                             : solve_kernel<THEMIS_QUEUE_PER_REPLICA, true>(listed, one);
         }
     });
 }

@@ -15,7 +15,6 @@ namespace {
 constexpr uint32_t LT_NONE = 1u << 22;       // "no candidate": above any sum of 64 budgets
 constexpr uint32_t EMPTY = 0xFFFFFFFFu;      // empty cell of the (lt, index) table
 constexpr int INDEX_BITS = 13;               // candidate indices are below 8192
-constexpr int FIRST_WINDOWS = 256;           // widest window of the first launch
 constexpr uint32_t G_INF = 0x8000u;          // row cell beyond any budget
 
 // a batch size b, and recip_below(b * 1e6)
@@ -30,17 +29,16 @@ struct CostArgs {
     int32_t *status2, *cost2, *ticks2, *cfg2;  // results of the second kind, see ROLE
     int32_t *lambda_v, *stable;
     int32_t* tmeta;     // budgets, for calls that inspect the workspace afterwards
-    int32_t* hard;      // per instance: left to the launch with the large window
     const int32_t* list;  // the instances to solve (LISTED)
     int32_t* ctrl;
-    uint16_t* frow;     // rows of step D
+    uint16_t* frow;     // rows of steps C and D
     int32_t* keep;      // inputs and results for such calls, or null
     KeepLayout kept;
     BatchConst bc[THEMIS_MAX_BATCH];
     int32_t n_batch;
     int32_t N, S, cs, c_max, r_max, tick, slo_max, coef_shared, c_all, row_stride;
-    int32_t window;     // cells of the largest window, a multiple of 64
-    int32_t tried;      // cells of the largest one tried before (0: none)
+    int32_t window;     // cells of the largest window with rows in LDS, a multiple of 64
+    int32_t window_hbm; // and in HBM (no larger than the other: none)
     uint32_t nb_magic;  // ceil(2^16 / n_batch): x / n_batch = x * nb_magic >> 16 for x < 1024
     uint32_t k_magic;   // ceil(2^20 / n_batch): the same with 20 for x < 8192
     double rtick;
@@ -108,10 +106,10 @@ __device__ __forceinline__ uint32_t least_of_rows(uint32_t x)
 // the record; QUIET, the same without the record; SECOND, the second set of results;
 // PINNED, the second set and the record, with the cores of every model taken from LDS.
 enum { PLAIN, QUIET, SECOND, PINNED };
-// Besides the status of an instance: the first windows did not suffice.
+// Besides the status of an instance: the steps so far did not suffice.
 constexpr int UNFINISHED = -1;
 
-template <int QUEUE, bool DERIVE, int ROLE, bool LAST>
+template <int QUEUE, bool DERIVE, int ROLE>
 __device__ __attribute__((noinline)) int solve_further(uint64_t args, int i, int T, int32_t lam,
                                                        int32_t slo);
 
@@ -642,14 +640,24 @@ struct Solver {
     }
 
     // The recurrence over W cells (a multiple of 64) and, where it ends within the budget,
-    // the answer.
+    // the answer.  HBM: the rows are in this instance's part of the row region.
+    template <bool HBM>
     __device__ __forceinline__ int solve_window(int W) const
     {
         uint32_t* const tab = lds + L.tab;
-        uint16_t* const rows = reinterpret_cast<uint16_t*>(lds + L.rows);
+        uint16_t* const rows = HBM ? a.frow + (size_t)i * a.S * a.row_stride
+                                   : reinterpret_cast<uint16_t*>(lds + L.rows);
+        // a row's lanes read what others wrote
+        auto rows_fence = [] {
+            if (HBM)
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+            else
+                wave_lds_fence();
+        };
         auto row_of = [&](int s) { return rows + s * (W + 2) + 2; };  // cell -1 is the guard
         for (int x = lane; x <= a.S; x += 64) row_of(x)[-1] = (uint16_t)G_INF;
         for (int x = lane; x < W; x += 64) row_of(a.S)[x] = 0;
+        rows_fence();
         for (int s = a.S - 1; s >= 0; --s) {
             fill_model(s, W);
             // what beats everything cheaper, as a list in the table's own place: cost over
@@ -696,7 +704,7 @@ struct Solver {
                 for (int q = 0; q < 4; ++q)
                     if (x0 + 64 * q < W) row[x0 + 64 * q + lane] = (uint16_t)acc[q];
             }
-            wave_lds_fence();
+            rows_fence();
         }
         int x = -1;
         uint32_t ticks = 0;
@@ -884,8 +892,8 @@ struct Solver {
         return THEMIS_SOLVED;
     }
 
-    // Steps A, F and B (MARKED: B has been tried before).
-    template <bool SMALL, bool MARKED>
+    // Steps A, F and B.
+    template <bool SMALL>
     __device__ __forceinline__ int solve_valid(const Pair& first) const
     {
         least_costs<SMALL>(first);
@@ -903,32 +911,32 @@ struct Solver {
             return THEMIS_SOLVED;
         }
         if (ticks >= LT_NONE || fastest_ticks<SMALL>(first) > (uint32_t)T) return THEMIS_INFEASIBLE;
-        if (MARKED) return UNFINISHED;
         fill_all<SMALL, 16>(first);
         const int status = solve_sixteen(sum_models(key >> 15), key >> 15);
         wave_lds_fence();
         return status;
     }
 
-    // Steps C and, LAST, D.
-    template <bool LAST>
+    // Steps C and D.
     __device__ __forceinline__ int further(int inst, int budget, int32_t rate, int32_t objective)
     {
         i = inst, T = budget, lam = rate, slo = objective;
         lane_b = lane < a.n_batch ? (int32_t)a.bc[lane].b : 0;
-        int status = UNFINISHED;
-        if (a.tried == 0) {
-            fill_all<false, 64>(Pair());
-            status = solve_sixtyfour();
+        fill_all<false, 64>(Pair());
+        int status = solve_sixtyfour();
+        int W = 64;
+        while (status == UNFINISHED && W < a.window) {
             wave_lds_fence();
-        }
-        for (int W = a.tried > 64 ? a.tried : 64; status == UNFINISHED && W < a.window;) {
             W = 2 * W < a.window ? 2 * W : a.window;
-            status = solve_window(W);
-            wave_lds_fence();
+            status = solve_window<false>(W);
         }
-        if (LAST && status == UNFINISHED) status = solve_by_budget(a.window);
-        return status;
+        while (status == UNFINISHED && W < a.window_hbm) {
+            wave_lds_fence();
+            W = 2 * W < a.window_hbm ? 2 * W : a.window_hbm;
+            status = solve_window<true>(W);
+        }
+        wave_lds_fence();
+        return status == UNFINISHED ? solve_by_budget(a.window) : status;
     }
 
     // The inputs of instance `inst` at `rate`; valid: the input check's result.
@@ -954,9 +962,7 @@ struct Solver {
     }
 
     // Solves the instance that was begun, and is valid, at the rate `lam`; writes the
-    // results unless it is infeasible.  LAST: whatever it takes; else it may be left
-    // UNFINISHED.  MARKED: it was left so before.
-    template <bool LAST, bool MARKED>
+    // results unless it is infeasible.
     __device__ __forceinline__ int solve(const Pair& first) const
     {
         if (lane < a.S) {
@@ -967,19 +973,19 @@ struct Solver {
         int status;
         // row_is_small(), which is the same for all models of an instance
         if (__builtin_amdgcn_readfirstlane((int)((double)lam * (double)slo <= 0x1p42)))
-            status = solve_valid<true, MARKED>(first);
+            status = solve_valid<true>(first);
         else
-            status = solve_valid<false, MARKED>(first);
+            status = solve_valid<false>(first);
         status = __builtin_amdgcn_readfirstlane(status);
         if (status == UNFINISHED)
-            status = solve_further<QUEUE, DERIVE, ROLE, LAST>((uint64_t)(uintptr_t)&a, i, T, lam, slo);
+            status = solve_further<QUEUE, DERIVE, ROLE>((uint64_t)(uintptr_t)&a, i, T, lam, slo);
         return status;
     }
 };
 
 // Out of line, so that its registers do not weigh on the allocation of the steps
 // that nearly every instance ends with.
-template <int QUEUE, bool DERIVE, int ROLE, bool LAST>
+template <int QUEUE, bool DERIVE, int ROLE>
 __device__ __attribute__((noinline)) int solve_further(uint64_t args, int i, int T, int32_t lam,
                                                        int32_t slo)
 {
@@ -987,22 +993,19 @@ __device__ __attribute__((noinline)) int solve_further(uint64_t args, int i, int
     const uint64_t lo = (uint32_t)uniform((int)(uint32_t)args);
     const uint64_t hi = (uint32_t)uniform((int)(uint32_t)(args >> 32));
     Solver<QUEUE, DERIVE, false, ROLE> sv((ArgsPtr)(uintptr_t)(hi << 32 | lo));
-    return uniform(sv.template further<LAST>(uniform(i), uniform(T), uniform(lam), uniform(slo)));
+    return uniform(sv.further(uniform(i), uniform(T), uniform(lam), uniform(slo)));
 }
 
 // One whole solve of instance `inst` at `rate`.
-template <int QUEUE, bool DERIVE, bool ONE, int ROLE, bool LAST, bool MARKED>
+template <int QUEUE, bool DERIVE, bool ONE, int ROLE>
 __device__ __forceinline__ int solve_instance(ArgsPtr args, int inst, int32_t rate)
 {
     Solver<QUEUE, DERIVE, ONE, ROLE> sv(args);
     bool valid;
     const auto first = sv.begin(inst, rate, valid);
-    if (!valid) {
-        sv.put_none(THEMIS_INVALID);
-        return THEMIS_INVALID;
-    }
-    const int status = sv.template solve<LAST, MARKED>(first);
-    if (status == THEMIS_INFEASIBLE) sv.put_none(THEMIS_INFEASIBLE);
+    int status = THEMIS_INVALID;
+    if (valid) status = sv.solve(first);
+    if (status == THEMIS_INVALID || status == THEMIS_INFEASIBLE) sv.put_none(status);
     return status;
 }
 
@@ -1019,43 +1022,6 @@ __device__ __forceinline__ void mark_workspace(ArgsPtr args, int state)
             (args->keep + args->kept.coef)[x] = args->coef[x];
 }
 
-// A launch's share of the instances.  FIRST: instance by workgroup, `f` returns false
-// for those the first windows do not solve, which are marked in `hard`.  REST: the
-// marked instances.  ALL: instance by workgroup, to the end.  LISTED: the same for the
-// instances of a list.
-enum { FIRST, REST, ALL, LISTED };
-template <int PART, typename F>
-__device__ __forceinline__ void for_instances(ArgsPtr args, F f)
-{
-    const int me = (int)blockIdx.x, all = (int)gridDim.x;
-    if constexpr (PART == FIRST) {
-        const bool done = f(me);
-        if (threadIdx.x == 0) args->hard[me] = done ? 0 : 1;
-    } else if constexpr (PART == ALL) {
-        f(me);
-    } else if constexpr (PART == LISTED) {
-        const int n = args->ctrl[LIST_WORD];
-        for (int k = me; k < n; k += all) {
-            f(__builtin_amdgcn_readfirstlane(args->list[k]));
-            wave_lds_fence();
-        }
-    } else {
-        // lane l of a wavefront looks at every all-th instance: the marked ones spread
-        // over the wavefronts whatever their order
-        const int N = args->N;
-        for (long long i0 = me; i0 < N; i0 += 64ll * all) {
-            const long long mine = i0 + (long long)threadIdx.x * all;
-            unsigned long long m = __ballot(mine < N && args->hard[mine < N ? mine : 0] != 0);
-            while (m) {
-                const int l = __builtin_ctzll(m);
-                m &= m - 1ull;
-                f((int)(i0 + (long long)l * all));
-                wave_lds_fence();
-            }
-        }
-    }
-}
-
 // (Kernels read their arguments where they lie, see ArgsPtr.)
 __device__ __forceinline__ ArgsPtr kernel_args()
 {
@@ -1067,12 +1033,11 @@ __device__ __forceinline__ ArgsPtr kernel_args()
 // ---- launching ---------------------------------------------------------------------
 namespace {
 
+typedef void (*CostKernel)(CostArgs);
+
 constexpr size_t LDS_PER_CU = 160 * 1024;
 constexpr int MAX_WINDOW = 8192;
-
-// Batches of up to this many instances per compute unit take one launch whose
-// wavefronts finish whatever they take: a second launch costs some four microseconds.
-constexpr int SINGLE_LAUNCH_PER_CU = 32;
+constexpr int RESIDENT_PER_CU = 32;  // wavefronts
 
 // What does not depend on the entry point.
 inline CostArgs cost_args(const themis_problem_t& p, const Layout& L, const int32_t* d_coef,
@@ -1091,7 +1056,6 @@ inline CostArgs cost_args(const themis_problem_t& p, const Layout& L, const int3
     a.ticks = d_ticks;
     a.cfg = d_cfg;
     a.tmeta = (int32_t*)(ws + L.tmeta_off);
-    a.hard = (int32_t*)(ws + L.ans_off);
     a.ctrl = (int32_t*)(ws + L.ctrl_off);
     a.frow = (uint16_t*)(ws + L.frow_off);
     a.kept = make_keep_layout(p);
@@ -1116,52 +1080,42 @@ inline CostArgs cost_args(const themis_problem_t& p, const Layout& L, const int3
     return a;
 }
 
-// `kernel(part, one)` names the kernel for a part of the instances and for problems
-// whose (model, batch size) pairs fit a wavefront's lanes.
+// A workgroup per instance, or where `listed` as many as stay resident (the host does
+// not know how long the list is).  `one` in kernel(one): the (model, batch size) pairs
+// fit a wavefront's lanes.
+//
+// One launch, whatever the instances need: a second one with room for wider windows,
+// for the instances the first one could not solve, took 4.5 us to find that there are
+// none (of 24 at 16384 x 8, 55 at 86400 x 6); windows wider than the LDS of a full
+// compute unit allows have their rows in HBM instead.
 template <typename K>
-hipError_t launch_parts(const themis_problem_t& p, const Layout& L, CostArgs& a, hipStream_t st,
-                        K kernel)
+hipError_t launch_per_instance(const themis_problem_t& p, const Layout& L, CostArgs& a,
+                               hipStream_t st, bool listed, K kernel)
 {
-    auto lds_for = [&](int waves, int window) {
-        return (size_t)waves * cost_lds(L.S, window).words * sizeof(uint32_t);
-    };
-    // the largest window that leaves `per_cu` wavefronts on a compute unit, no larger
-    // than the costs of a pipeline can spread
-    auto widest = [&](int per_cu, int most) {
-        int w = 64;
-        while (w + 64 <= most && w < L.S * p.r_max * p.c_max &&
-               lds_for(1, w + 64) <= LDS_PER_CU / per_cu)
-            w += 64;
-        return w;
-    };
-    // (at most 40 KB, which a kernel may have without asking)
-    auto launch = [&](auto kernel, int grid, size_t lds) -> hipError_t {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64), lds, st, a);
-        return hipGetLastError();
-    };
     const int cus = compute_units();
-    const bool one = L.S * p.n_batch <= 64;
-    if (a.list) {
-        // the host does not know how many: as many workgroups as stay resident walk the list
-        const int grid = L.N < 32 * cus ? L.N : 32 * cus;
-        const int per_cu = (grid + cus - 1) / cus;
-        a.hard = nullptr;
-        a.window = widest(per_cu < 4 ? 4 : per_cu, MAX_WINDOW);
-        return launch(kernel(LISTED, one), grid, lds_for(1, a.window));
-    }
-    if (L.N <= SINGLE_LAUNCH_PER_CU * cus) {
-        // one launch, with whatever window they leave each other on a compute unit
-        const int per_cu = (L.N + cus - 1) / cus;
-        a.hard = nullptr;
-        a.window = widest(per_cu < 4 ? 4 : per_cu, MAX_WINDOW);
-        return launch(kernel(ALL, one), L.N, lds_for(1, a.window));
-    }
-    a.window = widest(32, FIRST_WINDOWS);
-    hipError_t e = launch(kernel(FIRST, one), L.N, lds_for(1, a.window));
-    if (e != hipSuccess) return e;
-    a.tried = a.window;
-    a.window = widest(4, MAX_WINDOW);
-    return launch(kernel(REST, false), 4 * cus, lds_for(1, a.window));
+    const int grid = listed && L.N > RESIDENT_PER_CU * cus ? RESIDENT_PER_CU * cus : L.N;
+    // the largest window that leaves the wavefronts that can be resident their LDS, no
+    // larger than the costs of a pipeline can spread
+    int per_cu = (int)(((long long)grid + cus - 1) / cus);
+    per_cu = per_cu < 4 ? 4 : per_cu > RESIDENT_PER_CU ? RESIDENT_PER_CU : per_cu;
+    auto lds_for = [&](int window) {
+        return (size_t)cost_lds(L.S, window).words * sizeof(uint32_t);
+    };
+    const int spread = L.S * p.r_max * p.c_max;
+    a.window = 64;
+    while (a.window + 64 <= MAX_WINDOW && a.window < spread &&
+           lds_for(a.window + 64) <= LDS_PER_CU / per_cu)
+        a.window += 64;
+    // rows in HBM: S + 1 of them in the S that an instance has of the row region, and the
+    // table of a model still in LDS
+    const CostLds lds = cost_lds(L.S, a.window);
+    const int fit = (int)((long long)L.S * L.row_stride / (L.S + 1)) - 2;
+    const int room = lds.words - lds.tab;
+    a.window_hbm = (fit < room ? fit : room) & ~63;
+    // (at most 40 KB of LDS, which a kernel may have without asking)
+    const CostKernel k = kernel(L.S * p.n_batch <= 64);
+    hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(64), lds_for(a.window), st, a);
+    return hipGetLastError();
 }
 
 }  // namespace
