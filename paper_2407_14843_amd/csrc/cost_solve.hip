@@ -41,8 +41,13 @@
 //      exactly when the fastest candidates of all models together exceed the budget.
 //   B  else the recurrence over the first 16 cells: one table of (lt, index) by model
 //      and cost over base in LDS, a row of the recurrence in every sixteen lanes.
-//   C  else over 64 cells, and wider (with the table of one model at a time) as far as
-//      LDS goes, with the rows in LDS and lane = cell; and past that
+//   C  else over 64 cells, rows in LDS, lane = cell;
+//   G  else lists of the candidates, those that Lagrangian bounds show to be in no
+//      answer dropped, and the recurrence over what is left of them, a few candidates
+//      per model and some tens of cells; or every combination of them, if those are few
+//      and far apart;
+//   W  else (a list too long) the recurrence over wider windows, with the table of one
+//      model at a time and the rows in LDS, then in HBM; and past that
 //   D  the recurrence over the budget with rows in HBM, which is bounded by T
 //      whatever the costs are (costs spread over thousands of cores in one model).
 //

@@ -285,7 +285,8 @@ struct Solver {
     }
 
     // per model: cost << 15 | lt of the best candidate met so far; the same with the
-    // index below it, complete after step A; lt of the fastest candidate
+    // index below it, complete after step A; lt << 15 | cost of the fastest candidate at
+    // the cap
     __device__ __forceinline__ uint32_t* keys() const { return lds + L.key; }
     __device__ __forceinline__ unsigned long long* bests() const
     {
@@ -442,15 +443,17 @@ struct Solver {
     template <bool SMALL>
     __device__ __forceinline__ uint32_t fastest_ticks(const Pair& first) const
     {
-        if (lane < a.S) fastest()[lane] = LT_NONE;
+        if (lane < a.S) fastest()[lane] = EMPTY;
         wave_lds_fence();
         for_pairs(first, [&](const Pair& p) {
             if (!p.there) return;
             const Eval ev = eval<SMALL>(p, recip_below((double)speed(p, p.last)));
-            if (ev.lt >= 0) atomicMin(&fastest()[p.s], (uint32_t)ev.lt);
+            if (ev.lt >= 0)
+                atomicMin(&fastest()[p.s],
+                          (uint32_t)ev.lt << 15 | __umul24((uint32_t)ev.n, p.last));
         });
         wave_lds_fence();
-        return sum_models(lane < a.S ? fastest()[lane] : 0u);
+        return sum_models(lane < a.S ? fastest()[lane] >> 15 : 0u);  // none: beyond any budget
     }
 
     // ---- step B ------------------------------------------------------------------
@@ -569,6 +572,353 @@ struct Solver {
         wave_lds_fence();
         return read_out<16>(total, ticks, x, my_base,
                             [&](int s, int y) { return rows[(s + 1) * 16 + y]; });
+    }
+
+    // ---- step G ------------------------------------------------------------------
+    // Entries of lists: lt | cost << 16, and the index beside it.
+    struct Lists {
+        uint32_t* bins;   // 64 words per model; later the survivors, KEPT of each kind
+        uint32_t* lists;  // 2 * len words per model; later the rows
+        uint32_t* kept;   // per model: entries listed, later survivors
+        uint32_t* floor;  // per model: the least cost among them
+        int len;          // entries a list has room for
+    };
+    static constexpr int KEPT = 32;
+
+    __device__ __forceinline__ Lists lists_of() const
+    {
+        Lists l;
+        l.bins = lds + L.tab;
+        l.lists = l.bins + 64 * a.S;
+        l.kept = lds + L.best;
+        l.floor = l.kept + a.S;
+        l.len = (L.words - L.tab - 64 * a.S) / (2 * a.S);
+        l.len = l.len < 64 ? l.len : 64;
+        return l;
+    }
+
+    // Lists, per model, the candidates that nothing in a cheaper bin of costs is as fast
+    // as (a bin is as many costs as it takes for 64 bins to reach the fastest candidate's).
+    // False when one does not fit its list.
+    __device__ __forceinline__ bool list_candidates(const Lists& l) const
+    {
+        for (int x = lane; x < 64 * a.S; x += 64) l.bins[x] = LT_NONE;
+        wave_lds_fence();
+        const Recips rc = recips();
+        auto each = [&](auto use) {
+            for_pairs(Pair(), [&](const Pair& p) {
+                const uint32_t base = keys()[p.s] >> 15;
+                const uint32_t top = fastest()[p.s] & 0x7FFFu;
+                const uint32_t range = top - base;  // its bits beyond six are cut
+                const int sh = range < 64u ? 0 : 26 - __builtin_clz(range);
+                auto one = [&](const Eval& ev, uint32_t c) {
+                    const uint32_t cost = __umul24((uint32_t)ev.n, c);
+                    if (ev.lt >= 0 && cost <= top)
+                        use(p, c, (uint32_t)ev.lt, cost, p.s * 64u + ((cost - base) >> sh));
+                };
+                uint32_t c = first_core(p);
+                for (;;) {
+                    const bool go = p.there && c <= p.last && may_cost(p, c, top);
+                    if (__ballot(go) == 0ull) break;
+                    const bool both = c < p.last;
+                    const double r0 = recip(rc, go ? speed(p, c) : 1u);
+                    const double r1 = recip(rc, go && both ? speed(p, c + 1u) : 1u);
+                    if (go) {
+                        const Eval e0 = eval<false>(p, r0), e1 = eval<false>(p, r1);
+                        one(e0, c);
+                        if (both) one(e1, c + 1u);
+                        c += 2u;
+                    }
+                }
+            });
+        };
+        each([&](const Pair&, uint32_t, uint32_t lt, uint32_t, uint32_t bin) {
+            atomicMin(&l.bins[bin], lt);
+        });
+        wave_lds_fence();
+        for (int s = 0; s < a.S; ++s) {
+            const uint32_t incl = wave_scan<true>(l.bins[64 * s + lane]);
+            l.bins[64 * s + lane] = from_lane_below(incl, LT_NONE);  // least of all cheaper bins
+        }
+        if (lane < a.S) l.kept[lane] = 0u;
+        wave_lds_fence();
+        each([&](const Pair& p, uint32_t c, uint32_t lt, uint32_t cost, uint32_t bin) {
+            if (lt >= l.bins[bin]) return;
+            const uint32_t at = atomicAdd(&l.kept[p.s], 1u);
+            if (at < (uint32_t)l.len) {
+                uint32_t* const e = l.lists + 2 * ((int)p.s * l.len + (int)at);
+                e[0] = lt | cost << 16;
+                e[1] = (c - 1u) * (uint32_t)a.n_batch + p.j;
+            }
+        });
+        wave_lds_fence();
+        const bool fits = lane >= a.S || l.kept[lane] <= (uint32_t)l.len;
+        return __ballot(!fits) == 0ull;
+    }
+
+    // Candidates that can be part of an answer at all, by Lagrangian bounds.  For any
+    // price mu >= 0 of a tick, sum over the models of min(cost + mu lt) less mu T is at
+    // most the optimum, and an assignment that uses a candidate whose cost + mu lt
+    // exceeds its model's least by r costs at least r more than that bound.  With the
+    // cost `ub` of some assignment within the budget, candidates with r > ub - bound are
+    // in no optimum.  mu is found by walking the lower hull of (ticks, cost) between the
+    // cheapest and the fastest assignment to where the budget lies.  Single precision;
+    // `slack` covers its error, so a candidate is kept rather than dropped.
+    // What is left is two or three candidates per model whose costs span some tens of
+    // cells, where the window would have to span hundreds.
+    __device__ __forceinline__ int solve_gap()
+    {
+        const Lists l = lists_of();
+        if (l.len < 16) return UNFINISHED;
+        // the cheapest assignment (too slow) and the fastest (within the budget)
+        uint32_t my_lt = 0, my_cost = 0, my_fast = 0;
+        if (lane < a.S) {
+            const uint32_t key = keys()[lane];
+            my_lt = key & 0x7FFFu, my_cost = key >> 15;
+            my_fast = fastest()[lane];
+        }
+        int64_t c0 = sum_models(my_cost), l0 = sum_models(my_lt);
+        int64_t c1 = sum_models(my_fast & 0x7FFFu), l1 = sum_models(my_fast >> 15);
+        if (!list_candidates(l)) return UNFINISHED;
+
+        // lanes: `width` of them per model, entries dealt in turn
+        int width = 1;
+        while (2 * width * a.S <= 64) width *= 2;
+        const int s = lane / width, sub = lane & (width - 1);
+        const bool there = s < a.S;
+        const int n = there ? (int)l.kept[s] : 0;
+        const uint32_t* const mine = l.lists + 2 * (there ? s : 0) * l.len;
+        auto lt_of = [](uint32_t w) { return w & 0xFFFFu; };
+        auto cost_of = [](uint32_t w) { return w >> 16; };
+        // the model's choice at a price, in all of its lanes, and its cost + mu lt
+        auto choose = [&](float mu, float& v) {
+            uint32_t w = 0u;
+            v = 3.0e38f;
+            for (int e = sub; e < n; e += width) {
+                const uint32_t x = mine[2 * e];
+                const float y = __builtin_fmaf(mu, (float)lt_of(x), (float)cost_of(x));
+                if (y < v) v = y, w = x;
+            }
+            for (int d = 1; d < width; d <<= 1) {
+                const float ov = __shfl_xor(v, d, 64);
+                const uint32_t ow = (uint32_t)__shfl_xor((int)w, d, 64);
+                if (ov < v || (ov == v && ow < w)) v = ov, w = ow;
+            }
+            return w;
+        };
+        auto total = [&](uint32_t x) { return (int64_t)wave_sum(there && sub == 0 ? x : 0u); };
+        float mu = 0.0f, v = 0.0f;
+        // the fastest assignment as choices: cost and lt of the caps' candidates
+        uint32_t chosen = there ? (fastest()[s] >> 15) | (fastest()[s] & 0x7FFFu) << 16 : 0u;
+        for (int turn = 0; turn < 16; ++turn) {
+            mu = (float)(c1 - c0) / (float)(l0 - l1);
+            const uint32_t w = choose(mu, v);
+            const int64_t c = total(cost_of(w)), t = total(lt_of(w));
+            // on the line between the two, or above it: the walk has ended
+            if (c * (l0 - l1) + (c1 - c0) * t >= c1 * (l0 - l1) + (c1 - c0) * l1) break;
+            if (t <= T)
+                c1 = c, l1 = t, chosen = w;
+            else
+                c0 = c, l0 = t;
+            if (c0 >= c1 || l0 <= l1) break;
+        }
+        // (the prices at which the walk stopped)
+        choose(mu, v);
+        // one change of a choice that the ticks left over allow, for a better `ub`
+        const int64_t left = T - l1;
+        uint32_t gain = 0u;
+        for (int e = sub; e < n; e += width) {
+            const uint32_t x = mine[2 * e];
+            if ((int64_t)lt_of(x) - (int64_t)lt_of(chosen) <= left && cost_of(x) < cost_of(chosen)) {
+                const uint32_t g = cost_of(chosen) - cost_of(x);
+                gain = g > gain ? g : gain;
+            }
+        }
+        for (int d = 32; d >= 1; d >>= 1) {
+            const uint32_t o = (uint32_t)__shfl_xor((int)gain, d, 64);
+            gain = o > gain ? o : gain;
+        }
+        const int ub = (int)c1 - (int)__builtin_amdgcn_readfirstlane((int)gain);
+        float bound = there && sub == 0 ? v : 0.0f;
+        for (int d = 32; d >= 1; d >>= 1) bound += __shfl_xor(bound, d, 64);
+        bound -= mu * (float)T;
+        const float slack = ((float)c1 + mu * (float)(T + l0)) * 0x1p-16f + 0x1p-10f;
+        const float gap = (float)ub - bound + slack;
+        wave_lds_fence();
+        if (lane < a.S) l.kept[lane] = 0u, l.floor[lane] = EMPTY;
+        wave_lds_fence();
+        for (int e = sub; e < n; e += width) {
+            const uint32_t x = mine[2 * e];
+            const float y = __builtin_fmaf(mu, (float)lt_of(x), (float)cost_of(x));
+            if (y - v <= gap) {
+                const uint32_t at = atomicAdd(&l.kept[s], 1u);
+                atomicMin(&l.floor[s], cost_of(x));
+                if (at < (uint32_t)KEPT) {
+                    l.bins[64 * s + (int)at] = x;
+                    l.bins[64 * s + KEPT + (int)at] = mine[2 * e + 1];
+                }
+            }
+        }
+        wave_lds_fence();
+        const uint32_t my_kept = lane < a.S ? l.kept[lane] : 1u;
+        if (__ballot(my_kept > (uint32_t)KEPT || my_kept == 0u) != 0ull) return UNFINISHED;
+        const int floor = (int)sum_models(lane < a.S ? l.floor[lane] : 0u);
+        const int span = ub - floor;  // cells above the first that can be needed
+        if (span < 0) return UNFINISHED;
+        const int W = (span + 64) & ~63;
+        // the rows in LDS where they fit; few combinations are tried one by one before rows
+        // in HBM are taken, many only where those do not fit either
+        const int cells = (a.S + 1) * (W + 2);
+        if (cells / 2 <= 2 * l.len * a.S) return solve_listed<false>(l, W, floor);
+        int status = solve_by_trial(l, my_kept, 1u << 10);
+        if (status == UNFINISHED && cells <= a.S * a.row_stride)
+            status = solve_listed<true>(l, W, floor);
+        return status == UNFINISHED ? solve_by_trial(l, my_kept, TRIALS) : status;
+    }
+
+    // The recurrence over the survivors: W cells over the sum of their least costs.
+    // HBM: the rows are in this instance's part of the row region.
+    template <bool HBM>
+    __device__ __forceinline__ int solve_listed(const Lists& l, int W, int floor) const
+    {
+        uint16_t* const rows = HBM ? a.frow + (size_t)i * a.S * a.row_stride
+                                   : reinterpret_cast<uint16_t*>(l.lists);
+        auto rows_fence = [] {  // a row's lanes read what others wrote
+            if (HBM)
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+            else
+                wave_lds_fence();
+        };
+        auto row_of = [&](int s) { return rows + s * (W + 2) + 2; };  // cell -1 is the guard
+        for (int x = lane; x <= a.S; x += 64) row_of(x)[-1] = (uint16_t)G_INF;
+        for (int x = lane; x < W; x += 64) row_of(a.S)[x] = 0;
+        rows_fence();
+        for (int s = a.S - 1; s >= 0; --s) {
+            const uint16_t* const next = row_of(s + 1);
+            uint16_t* const row = row_of(s);
+            const int n = __builtin_amdgcn_readfirstlane((int)l.kept[s]);
+            const uint32_t base = l.floor[s];
+            const uint32_t* const ent = l.bins + 64 * s;
+            for (int x0 = 0; x0 < W; x0 += 64) {
+                uint32_t acc = G_INF;
+                for (int e = 0; e < n; e += 2) {
+                    const uint32_t w0 = ent[e], w1 = ent[e + 1 < n ? e + 1 : e];
+                    const int y0 = x0 + lane - (int)((w0 >> 16) - base);
+                    const int y1 = x0 + lane - (int)((w1 >> 16) - base);
+                    const uint32_t v0 = next[y0 < -1 ? -1 : y0] + (w0 & 0xFFFFu);
+                    const uint32_t v1 = next[y1 < -1 ? -1 : y1] + (w1 & 0xFFFFu);
+                    acc = least(acc, least(v0, v1));
+                }
+                row[x0 + lane] = (uint16_t)acc;
+            }
+            rows_fence();
+        }
+        int x = -1;
+        uint32_t ticks = 0;
+        for (int x0 = 0; x0 < W && x < 0; x0 += 64) {
+            const uint32_t v = row_of(0)[x0 + lane];
+            const unsigned long long m = __ballot(v <= (uint32_t)T);
+            if (m) {
+                const int q = __builtin_ctzll(m);
+                x = x0 + q;
+                ticks = lane_value(v, q);
+            }
+        }
+        if (x < 0) return UNFINISHED;  // never expected: the assignment of cost ub is in reach
+        const uint32_t total = (uint32_t)(floor + x);
+        uint32_t t = ticks, my_k = 0, my_cost = 0;
+        for (int s = 0; s < a.S; ++s) {
+            const int n = (int)l.kept[s];
+            const uint32_t w = l.bins[64 * s + (lane & (KEPT - 1))];
+            const uint32_t k = l.bins[64 * s + KEPT + (lane & (KEPT - 1))];
+            const int d = (int)((w >> 16) - l.floor[s]);
+            const bool in = lane < n && d <= x;
+            const uint32_t rest = row_of(s + 1)[in ? x - d : 0];
+            unsigned long long m = __ballot(in && (w & 0xFFFFu) + rest == t);
+            uint32_t key = EMPTY, key_w = 0u;
+            int key_d = 0;
+            while (m) {
+                const int q = __builtin_ctzll(m);
+                m &= m - 1ull;
+                const uint32_t kq = lane_value(k, q);
+                if (kq < key) key = kq, key_w = lane_value(w, q), key_d = (int)lane_value((uint32_t)d, q);
+            }
+            if (key == EMPTY) {  // never expected
+                put_none(THEMIS_INTERNAL);
+                return THEMIS_INTERNAL;
+            }
+            if (lane == s) my_k = key, my_cost = key_w >> 16;
+            t -= key_w & 0xFFFFu;
+            x -= key_d;
+        }
+        put(THEMIS_SOLVED, (int32_t)total, (int32_t)ticks);
+        put_choice(my_k, my_cost);
+        return THEMIS_SOLVED;
+    }
+
+    // Every combination of the survivors, where there are few of them and their costs span
+    // more cells than the rows have room for.  The survivors of a model are put in index
+    // order first, so that of equal combinations the first one met is the smallest.
+    static constexpr uint32_t TRIALS = 1u << 14;
+    __device__ __forceinline__ int solve_by_trial(const Lists& l, uint32_t my_kept,
+                                                  uint32_t most) const
+    {
+        uint32_t count = 1u;
+        for (int s = 0; s < a.S; ++s) {
+            count *= lane_value(my_kept, s);
+            if (count > most) return UNFINISHED;
+        }
+        for (int s = 0; s < a.S; ++s) {
+            const int n = (int)l.kept[s];
+            const int e = lane & (KEPT - 1);
+            const uint32_t w = l.bins[64 * s + e], k = l.bins[64 * s + KEPT + e];
+            int rank = 0;
+            for (int o = 0; o < n; ++o) rank += l.bins[64 * s + KEPT + o] < k ? 1 : 0;
+            wave_lds_fence();
+            if (lane < n) {
+                l.bins[64 * s + rank] = w;
+                l.bins[64 * s + KEPT + rank] = k;
+            }
+            wave_lds_fence();
+        }
+        unsigned long long best = ~0ull;
+        for (uint32_t x0 = 0; x0 < count; x0 += 64u) {
+            const uint32_t x = x0 + (uint32_t)lane;
+            if (x < count) {
+                uint32_t rest = x, c = 0, t = 0;
+                for (int s = a.S - 1; s >= 0; --s) {  // model 0 is the most significant digit
+                    const uint32_t n = l.kept[s];
+                    const uint32_t q = rest / n;
+                    const uint32_t w = l.bins[64 * s + (int)(rest - q * n)];
+                    rest = q;
+                    c += w >> 16;
+                    t += w & 0xFFFFu;
+                }
+                if (t <= (uint32_t)T) {
+                    const unsigned long long key =
+                        ((unsigned long long)c << 32) | ((unsigned long long)t << 14) | x;
+                    best = key < best ? key : best;
+                }
+            }
+        }
+        for (int d = 32; d >= 1; d >>= 1) {
+            const unsigned long long o = __shfl_xor(best, d, 64);
+            best = o < best ? o : best;
+        }
+        if (best == ~0ull) return UNFINISHED;  // never expected
+        uint32_t rest = (uint32_t)best & (TRIALS - 1u), my_k = 0, my_cost = 0;
+        for (int s = a.S - 1; s >= 0; --s) {
+            const uint32_t n = l.kept[s];
+            const uint32_t q = rest / n;
+            if (lane == s) {
+                my_cost = l.bins[64 * s + (int)(rest - q * n)] >> 16;
+                my_k = l.bins[64 * s + KEPT + (int)(rest - q * n)];
+            }
+            rest = q;
+        }
+        put(THEMIS_SOLVED, (int32_t)(best >> 32), (int32_t)((best >> 14) & 0x3FFFFull));
+        put_choice(my_k, my_cost);
+        return THEMIS_SOLVED;
     }
 
     // ---- step C ------------------------------------------------------------------
@@ -917,13 +1267,15 @@ struct Solver {
         return status;
     }
 
-    // Steps C and D.
+    // Steps C, G and D.
     __device__ __forceinline__ int further(int inst, int budget, int32_t rate, int32_t objective)
     {
         i = inst, T = budget, lam = rate, slo = objective;
         lane_b = lane < a.n_batch ? (int32_t)a.bc[lane].b : 0;
         fill_all<false, 64>(Pair());
         int status = solve_sixtyfour();
+        wave_lds_fence();
+        if (status == UNFINISHED) status = solve_gap();
         int W = 64;
         while (status == UNFINISHED && W < a.window) {
             wave_lds_fence();
@@ -1037,7 +1389,11 @@ typedef void (*CostKernel)(CostArgs);
 
 constexpr size_t LDS_PER_CU = 160 * 1024;
 constexpr int MAX_WINDOW = 8192;
-constexpr int RESIDENT_PER_CU = 32;  // wavefronts
+// Wavefronts whose LDS a compute unit has room for.  Registers allow 32, but some twenty
+// are in flight on average, and the room of the others lets step G list more candidates:
+// at 16384 x 8 with a twelfth of the objectives 32 / 28 / 24 / 20 take 579 / 122 / 121 /
+// 129 us, at 86400 x 6 51 / 51 / 55 / 60.
+constexpr int RESIDENT_PER_CU = 28;
 
 // What does not depend on the entry point.
 inline CostArgs cost_args(const themis_problem_t& p, const Layout& L, const int32_t* d_coef,
