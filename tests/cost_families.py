@@ -32,6 +32,10 @@ def families(n):
                                              (10, 2000), r_fixed=8),
         # more core counts than the table of reciprocals holds
         "many cores": family(6, n, 2, 150, [1, 2, 5], 100, 500, 100_000, (10, 20_000)),
+        # lists of candidates longer than a compute unit full of wavefronts has room for,
+        # and costs spread over thousands
+        "long lists": family(11, n, 3, 64, list(range(1, 17)), 150, 50, 40_000,
+                             (20_000, 400_000)),
         "one model": family(7, n, 1, 6, [1, 2, 4], 50, 100, 60_000, (1, 3000)),
     }
 

@@ -27,13 +27,15 @@ def same(got, want):
         assert bad.size == 0, f"{n} differs at {bad[:8]}: got {g[bad[:2]]}, want {x[bad[:2]]}"
 
 
-# 300 instances are solved by one launch, 1500 by one with a window of 64 cells and a
-# second one for what that leaves over
-@pytest.mark.parametrize("n", [1, 300, 1500])
+# A wavefront has the more LDS the fewer instances there are: at 240 the widest windows
+# fit, at 7200 (the same 240 again and again) rows go to HBM and the last resort is met.
+@pytest.mark.parametrize("n", [1, 240, 7200])
 @pytest.mark.parametrize("name", list(families(1)))
 def test_windows(T, oracle, name, n):
-    w = families(n)[name]
-    want = oracle.solve(w, threads=8)
+    w = families(min(n, 240))[name]
+    again = np.arange(n) % w.n_inst
+    want = tuple(x[again] for x in oracle.solve(w, threads=8))
+    w = w.take(again)
     print(f"[case] {name} N={n}", flush=True)
     b = T.DeviceBatch(w)
     b.solve()
@@ -47,6 +49,31 @@ def test_windows_are_met(oracle):
                         for w in families(1500).values()])
     for lo, hi in ((0, 0), (1, 62), (63, 63), (64, 64), (65, 255), (256, 1023), (8192, 32767)):
         assert ((x >= lo) & (x <= hi)).any(), (lo, hi)
+
+
+def test_many_models_in_every_entry_point(T, oracle):
+    """More models than lanes: the passes of the three stages behind every entry point."""
+    rng = np.random.default_rng(66)
+    n, S = 33, 66
+    coef = wl._draw_coef(rng, (n, S), a=(1000, 9000), k=(100, 1000), q=(0, 10), p=(1, 3), o=(1, 500))
+    w = wl.Workload("models", wl.JOINT, n, S, 3, [1, 2, 4], 20, 1000, 900_000, False, coef,
+                    rng.integers(1, 900, n).astype(np.int32),
+                    rng.integers(0, 900_001, n).astype(np.int32))
+    w = w.take(np.arange(2 * n) % n)
+    b = T.DeviceBatch(w)
+    b.solve_distinct()
+    same(b.results(), oracle.solve(w, threads=8))
+    pred = np.where(np.arange(2 * n) % 3 == 0, w.lam + 1, w.lam).astype(np.int32)
+    stable = b.check_stability(pred)
+    want = oracle.stability(w, pred)
+    assert (stable.cpu().numpy() == want[0]).all()
+    same(b.results(), want[1:])
+    v = w.with_r_fixed(rng.integers(1, 4, (w.n_inst, S)))
+    b = T.DeviceBatch(v)
+    b.solve_vertical_fallback()
+    got, want = b.fallback_results(), oracle.vertical_fallback(v, threads=8)
+    for k in want:
+        assert (got[k] == want[k]).all(), k
 
 
 @pytest.mark.parametrize("n_stage", [1, 2, 63, 64, 65])
