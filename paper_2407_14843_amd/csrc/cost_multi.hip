@@ -17,8 +17,9 @@
 //
 // What bounds them is what bounds a single solve.  As passes over all instances with
 // the search by one thread per instance (170 us of it at 16384 x 8) and a compare
-// kernel, eight launches and three, they took 250 and 28 us at 16384 x 8 and 4099 x 5;
-// now two launches and one, 71 and 23.
+// kernel around one-wavefront solves, eight launches and three, they took 250 and 28 us
+// at 16384 x 8 and 4099 x 5; now one launch each, 62 and 23.  Pipelines of more than 64
+// models still go that way, over the three stages.
 #include "cost_solver.h"
 
 namespace themis {

@@ -56,8 +56,8 @@
 // with the candidate tables and the rate search, so that all agree bit for bit),
 // against 0.3 KB of inputs and outputs; nothing but those touches HBM.  Whole solves
 // by the three stages (dense / with dominated candidates pruned) against this one, in
-// microseconds: 65536 x 8 models 25900 / 3890 -> 94, 16384 x 8 with replicas given
-// 3360 -> 24, 86400 x 6 2790 -> 55, 4096 x 5 178 -> 12.6, 64 x 3 27.5 -> 9.7.
+// microseconds: 65536 x 8 models 25800 / 3880 -> 100, 16384 x 8 with replicas given
+// 3370 -> 29, 86400 x 6 2790 -> 54, 4096 x 5 177 -> 12.6, 64 x 3 27.2 -> 6.7.
 #include "cost_solver.h"
 
 namespace themis {

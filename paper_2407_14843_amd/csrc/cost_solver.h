@@ -31,7 +31,7 @@ struct CostArgs {
     int32_t* tmeta;     // budgets, for calls that inspect the workspace afterwards
     const int32_t* list;  // the instances to solve (LISTED)
     int32_t* ctrl;
-    uint16_t* frow;     // rows of steps C and D
+    uint16_t* frow;     // rows of steps W and D
     int32_t* keep;      // inputs and results for such calls, or null
     KeepLayout kept;
     BatchConst bc[THEMIS_MAX_BATCH];
@@ -921,7 +921,7 @@ struct Solver {
         return THEMIS_SOLVED;
     }
 
-    // ---- step C ------------------------------------------------------------------
+    // ---- steps C and W -------------------------------------------------------------
     // The recurrence over 64 cells, lane = cell, the table of all models in LDS.
     __device__ __forceinline__ int solve_sixtyfour() const
     {

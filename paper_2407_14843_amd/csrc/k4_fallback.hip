@@ -1,7 +1,8 @@
 // The fallback of Algorithm 1 (Section 4.4): when the replicas that are already
 // running cannot meet the SLO at the arrival rate lambda, a binary search finds
 // a rate they can absorb, the vertical configuration is taken at that rate, and
-// new instances with the same cores serve what is left.
+// new instances with the same cores serve what is left.  This form is for pipelines of
+// more models than a wavefront has lanes; cost_multi.hip serves the others.
 //
 // Reading of the printed search, which does not converge as listed: the
 // midpoint is (left + right) / 2 and a midpoint the replicas can absorb raises

@@ -2,7 +2,8 @@
 // current and at the predicted arrival rate, and the workload counts as stable
 // when both succeed with the same configuration for every model.  The two
 // solves are ordinary passes of the three stages; this kernel compares what
-// they left behind, one thread per instance.
+// they left behind, one thread per instance.  For pipelines of more models than a
+// wavefront has lanes; cost_multi.hip serves the others.
 #include "themis_internal.h"
 
 namespace themis {

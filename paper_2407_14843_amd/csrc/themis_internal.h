@@ -261,7 +261,7 @@ struct PassOpts {
                                     // their number in the control word LIST_WORD
 };
 
-// The one-wavefront solve: three stages' worth of results in one or two launches.
+// The one-wavefront solve: three stages' worth of results in one launch.
 constexpr int COST_MAX_STAGES = 64;  // a lane per model
 bool cost_solve_serves(const Layout& L);
 hipError_t launch_cost_solve(const themis_problem_t& p, const Layout& L, const int32_t* d_coef,
