@@ -39,8 +39,7 @@ struct CostArgs {
     int32_t N, S, cs, c_max, r_max, tick, slo_max, coef_shared, c_all, row_stride;
     int32_t window;     // cells of the largest window with rows in LDS, a multiple of 64
     int32_t window_hbm; // and in HBM (no larger than the other: none)
-    uint32_t nb_magic;  // ceil(2^16 / n_batch): x / n_batch = x * nb_magic >> 16 for x < 1024
-    uint32_t k_magic;   // ceil(2^20 / n_batch): the same with 20 for x < 8192
+    uint32_t magic;     // index_magic() of n_batch
     double rtick;
 };
 
@@ -203,7 +202,7 @@ struct Solver {
     __device__ __forceinline__ Pair pair_of_round(uint32_t r) const
     {
         const uint32_t x = r + (uint32_t)lane;
-        const uint32_t s = (x * a.nb_magic) >> 16;
+        const uint32_t s = index_quotient(x, a.magic);  // x < 64 * 16 + 64
         return pair_of(s, x - s * (uint32_t)a.n_batch, x < (uint32_t)(a.S * a.n_batch));
     }
 
@@ -348,7 +347,7 @@ struct Solver {
     // lane s < S: index and cost of model s's candidate
     __device__ __forceinline__ void put_choice(uint32_t k, uint32_t cost) const
     {
-        const uint32_t q = (k * a.k_magic) >> 20;
+        const uint32_t q = index_quotient(k, a.magic);
         const uint32_t c = q + 1u;
         const int32_t b = __shfl(lane_b, (int)(k - q * (uint32_t)a.n_batch), 64);
         if (lane >= a.S) return;
@@ -972,8 +971,8 @@ struct Solver {
         uint32_t* const tab = lds + L.tab;
         for (int x = lane; x < W; x += 64) tab[x] = EMPTY;
         const uint32_t nb = (uint32_t)a.n_batch;
-        const uint32_t parts = (64u * a.nb_magic) >> 16;
-        const uint32_t part = ((uint32_t)lane * a.nb_magic) >> 16;
+        const uint32_t parts = index_quotient(64u, a.magic);
+        const uint32_t part = index_quotient((uint32_t)lane, a.magic);
         const Pair p = pair_of((uint32_t)s, (uint32_t)lane - part * nb, part < parts);
         const uint32_t base = keys()[s] >> 15;
         const uint32_t top = base + (uint32_t)W - 1u;
@@ -1110,7 +1109,7 @@ struct Solver {
     __device__ __forceinline__ Eval candidate(int s, uint32_t x, uint32_t count, uint32_t& cost,
                                               uint32_t& k) const
     {
-        const uint32_t q = (x * a.k_magic) >> 20;
+        const uint32_t q = index_quotient(x, a.magic);  // x < MAX_CAND: a multiple of 64
         const Pair p = pair_of((uint32_t)s, x - q * (uint32_t)a.n_batch, true);
         const uint32_t c = p.lo + (x < count ? q : 0u);
         Eval ev = eval<false>(p, recip_below((double)speed(p, c)));
@@ -1430,8 +1429,7 @@ inline CostArgs cost_args(const themis_problem_t& p, const Layout& L, const int3
     a.c_all = opts.c_all;
     a.list = opts.list;
     a.row_stride = L.row_stride;
-    a.nb_magic = (65536u + (uint32_t)p.n_batch - 1u) / (uint32_t)p.n_batch;
-    a.k_magic = ((1u << 20) + (uint32_t)p.n_batch - 1u) / (uint32_t)p.n_batch;
+    a.magic = index_magic((uint32_t)p.n_batch);
     a.rtick = (1.0 / (double)p.tick_us) * (1.0 - 0x1p-45);
     return a;
 }

@@ -238,6 +238,20 @@ inline KeepLayout make_keep_layout(const themis_problem_t& p)
     return k;
 }
 
+// Candidate index / batch sizes = cores less one, as a product and a shift: x * magic
+// stays below 2^31 (magic <= 2^18, x < 2^13) and is above the quotient by at most
+// x * 15 / (n_batch 2^18) < 0.5 / n_batch, so its floor is the quotient's for every
+// x < MAX_CAND.
+constexpr uint32_t INDEX_DIV_SHIFT = 18;
+__host__ __device__ constexpr uint32_t index_magic(uint32_t n_batch)
+{
+    return ((1u << INDEX_DIV_SHIFT) + n_batch - 1u) / n_batch;
+}
+__host__ __device__ constexpr uint32_t index_quotient(uint32_t x, uint32_t magic)
+{
+    return (x * magic) >> INDEX_DIV_SHIFT;
+}
+
 struct BatchList {
     int32_t n;
     int32_t b[THEMIS_MAX_BATCH];

@@ -159,8 +159,23 @@ static void check_layout()
           "shortcut rule");
 }
 
+// Cores and batch size of a candidate from its index, for every number of batch sizes
+// and every index, those beyond the last candidate in a round of 64 included.
+static void check_index_division()
+{
+    static_assert(MAX_CAND % 64 == 0, "rounds of 64 candidates end at MAX_CAND");
+    for (uint32_t n = 1; n <= THEMIS_MAX_BATCH; ++n) {
+        const uint32_t magic = index_magic(n);
+        for (uint32_t x = 0; x < (uint32_t)MAX_CAND; ++x) {
+            const uint32_t q = index_quotient(x, magic);
+            CHECK(q == x / n && x - q * n < n, "%u batch sizes, index %u: quotient %u", n, x, q);
+        }
+    }
+}
+
 int main()
 {
+    check_index_division();
     check_layout();
     check_wide();
     check_narrow();
