@@ -382,9 +382,9 @@ int themis_stage_backtrack(const themis_problem_t *p, int32_t *d_status,
  * d_lt, d_cost int32 [N][S][K], K = c_max*n_batch; infeasible entries are -1
  * in both (under THEMIS_PRUNE_DOMINATED the dropped candidates too: what is
  * left is the cost/latency staircase of each row).  The replica count of a
- * feasible entry is cost / c.  After a whole solve that formed no tables they are
- * built first, in the workspace (`d_workspace` is const for the sake of the
- * interface only).
+ * feasible entry is cost / c.  After a whole solve that formed no tables the
+ * candidates are evaluated again, from the inputs it kept.  The workspace is only
+ * read: this call, the next one and themis_stage_backtrack may overlap.
  */
 int themis_export_candidates(const themis_problem_t *p, const void *d_workspace,
                              size_t workspace_bytes, int32_t *d_lt, int32_t *d_cost,
@@ -392,8 +392,9 @@ int themis_export_candidates(const themis_problem_t *p, const void *d_workspace,
 
 /*
  * Number of min-plus relaxations stage 2 executes for the tables currently
- * in the workspace (built first where a whole solve formed none), summed over all instances, written to d_count[0]
- * (d_count: uint64 [3], device): for every valid instance, model and feasible candidate,
+ * in the workspace (those it would form, where a whole solve formed none), summed
+ * over all instances, written to d_count[0] (d_count: uint64 [3], device): for
+ * every valid instance, model and feasible candidate,
  * T + 1 - lt, except for two models that take no relaxations when they
  * have candidates enough to make it pay: the one the recurrence starts with
  * (the last of the pipeline), whose row is then a running minimum over its

@@ -96,7 +96,7 @@ template <int QUEUE, bool ONE>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6, 8))) void kc_fallback(CostArgs)
 {
     const ArgsPtr args = kernel_args();
-    mark_workspace(args, STATE_KEPT_IN_TABLE | STATE_ONLY);
+    mark_workspace(args, STATE_KEPT | STATE_ONLY);
     fallback_instance<QUEUE, ONE>(args, (int)blockIdx.x);
 }
 
@@ -126,7 +126,7 @@ template <int QUEUE, bool ONE>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8, 8))) void kc_stability(CostArgs)
 {
     const ArgsPtr args = kernel_args();
-    mark_workspace(args, STATE_KEPT_IN_TABLE | (args->c_fixed ? STATE_ONLY : 0) |
+    mark_workspace(args, STATE_KEPT | (args->c_fixed ? STATE_ONLY : 0) |
                              args->c_all << STATE_C_ALL);
     stability_instance<QUEUE, ONE>(args, (int)blockIdx.x);
 }

@@ -68,7 +68,7 @@ template <int QUEUE, bool DERIVE, bool ONE, bool LISTED>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8, 8))) void kc_solve(CostArgs)
 {
     const ArgsPtr args = kernel_args();
-    mark_workspace(args, STATE_KEPT_IN_TABLE | (DERIVE ? 0 : STATE_GIVEN) |
+    mark_workspace(args, STATE_KEPT | (DERIVE ? 0 : STATE_GIVEN) |
                              (args->c_fixed ? STATE_ONLY : 0) | args->c_all << STATE_C_ALL);
     if (!LISTED) {
         const int i = (int)blockIdx.x;

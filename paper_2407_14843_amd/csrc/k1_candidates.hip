@@ -116,26 +116,6 @@ __global__ void k1_reset_ctrl(int32_t* ctrl)
     if (threadIdx.x <= STATE_WORD) ctrl[threadIdx.x] = 0;
 }
 
-// What a whole solve left in the table region moves to the row region, so that the
-// tables can be built from it (see STATE_WORD).
-__global__ __launch_bounds__(256) void k1_keep_move(const int32_t* __restrict__ ctrl,
-                                                    const int32_t* __restrict__ from,
-                                                    int32_t* __restrict__ to, size_t words)
-{
-    if (!(ctrl[STATE_WORD] & STATE_KEPT_IN_TABLE)) return;
-    for (size_t x = blockIdx.x * 256u + threadIdx.x; x < words; x += gridDim.x * 256u)
-        to[x] = from[x];
-}
-
-// ... after which the state says that, and whether the launches that follow build.
-__global__ void k1_keep_state(int32_t* ctrl)
-{
-    const int32_t s = ctrl[STATE_WORD];
-    ctrl[STATE_WORD] = (s & STATE_KEPT_IN_TABLE)
-                           ? (s & ~STATE_KEPT_IN_TABLE) | STATE_KEPT_IN_ROWS | STATE_REBUILD
-                           : s & ~STATE_REBUILD;
-}
-
 // The same check for a small batch, by one workgroup that owns the class lists:
 // slots come from LDS counters, and the workgroup writes the class sizes and
 // zeroes the queue cursors itself, so that no launch has to clear them first.
@@ -216,6 +196,10 @@ __global__ __launch_bounds__(VALIDATE_SINGLE_THREADS) void k1_validate_single(
 // candidate's exceed the table, 2^sh costs share a bin and only strictly cheaper
 // bins are compared, which drops fewer candidates but never a needed one.
 //
+// INSPECT: the same rows from what a whole solve kept (see STATE_WORD) and, instead of
+// into the tables, into the arrays or the sums that export and count hand out; the
+// workspace is only read.
+//
 // c_fixed (may be null; then c_all, 0 = free): cores given per row; the model is
 // evaluated for those cores only and no other candidate of the row competes.
 // sparse: rows of instances that failed the input check are left untouched.
@@ -255,11 +239,45 @@ struct K1RowIn {
     int32_t cf[6];
 };
 
+// What a row of n entries adds to the count of relaxations: whether its entries are
+// swept, and whether its T + 1 cells are formed.  Where the wide kernel serves the
+// instance and nothing is pruned, the model it handles first (s = S-1) and, in a pipeline
+// of two or more, the one it handles last (s = 0) are left out when they have entries
+// enough for their shortcuts (see worth_shortcut): the first row is then built by a
+// scatter and a scan, and of the last only the answer is computed.  (The step-row form
+// never forms that row.)
+struct RowCount {
+    bool swept, formed;
+};
+__device__ __forceinline__ RowCount row_count(uint32_t n, uint32_t s, uint32_t S, int T,
+                                              uint64_t class_map, int pruned, int steps)
+{
+    const int cls = effective_class(T, class_map);
+    const bool wide = cls != NARROW_CLS && !pruned;  // the kernels that have the shortcuts
+    const int npos = (T + BUCKET_CELLS) / BUCKET_CELLS;
+    const bool shortcut = wide && (s == S - 1 || (s == 0 && S > 1)) &&
+                          worth_shortcut((int)n, npos, cls_waves(cls));
+    const bool answer_only = s == 0 && ((shortcut && S > 1) || (steps && cls != NARROW_CLS));
+    return RowCount{!shortcut, !answer_only};
+}
+
+// The records of a whole solve, and where INSPECT puts what it finds in them: export's
+// arrays, or the three sums of the count.
+struct Inspection {
+    const int32_t* state;  // the state word; the kernel is for records with (`given`) or
+    int given;             // without given replicas and does nothing for anything else
+    uint32_t record;       // words per record
+    int32_t *lt, *cost;    // [rows][K], or null
+    uint32_t K;
+    unsigned long long* count;
+    int pruned, steps;
+};
+
 // ME > 0: a lane has at most ME singles and keeps them in registers from phase A to
 // phase C (the loops over them are unrolled), so the rows need no room for parked
 // singles and more wavefronts fit a compute unit; ME = 0: they are parked in LDS
 // (any number; the pruning pass needs them there).
-template <int QUEUE, bool PRUNE, bool DERIVE, int ME>
+template <int QUEUE, bool PRUNE, bool DERIVE, int ME, bool INSPECT>
 __global__ __launch_bounds__(64 * K1_WAVES) __attribute__((amdgpu_waves_per_eu(4, 8))) void k1_candidates(
     const int32_t* __restrict__ coef, const int32_t* __restrict__ lambda,
     const int32_t* __restrict__ slo_us, const int32_t* __restrict__ r_fixed,
@@ -268,18 +286,17 @@ __global__ __launch_bounds__(64 * K1_WAVES) __attribute__((amdgpu_waves_per_eu(4
     uint32_t S, uint32_t Kp, uint32_t c_max, uint32_t r_max, uint32_t tick, double rtick,
     int coef_shared, uint32_t lpr_log2, uint32_t split_log2, uint32_t nb, uint32_t nbs,
     uint64_t class_map, int sparse, uint32_t c_all, uint32_t cs, uint32_t s_magic,
-    uint32_t n_groups, const int32_t* __restrict__ gate, int32_t gate_want,
-    uint32_t record)
+    uint32_t n_groups, Inspection look)
 {
     extern __shared__ uint32_t smem[];
-    // (after a whole solve) only where there are tables to build, and in this form
-    if (gate) {
-        const int32_t state = *gate;
-        if ((state & (STATE_REBUILD | STATE_GIVEN)) != gate_want) return;
+    if (INSPECT) {
+        const int32_t state = *look.state;
+        if (!(state & STATE_KEPT) || ((state & STATE_GIVEN) != 0) != (look.given != 0)) return;
         if (!(state & STATE_ONLY)) c_fixed = nullptr, c_all = (uint32_t)state >> STATE_C_ALL;
     }
     const uint32_t nbat = (uint32_t)bl.n;
     static_assert(!(PRUNE && ME > 0) && ME % 2 == 0, "pruning works on parked singles");
+    static_assert(!(INSPECT && ME > 0), "one form is enough where nothing is timed");
     const K1Row R = k1_row(Kp, c_max, nbat, nb, ME > 0);
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -312,14 +329,14 @@ __global__ __launch_bounds__(64 * K1_WAVES) __attribute__((amdgpu_waves_per_eu(4
         const uint32_t s = row - i * S;
         K1RowIn in;
         in.T = tmeta[i];
-        // one array each, or `record` words per instance with everything in them
-        const size_t at = (size_t)i * (record ? record : 1u);
-        const size_t at_s = record ? at + s : row;
+        // one array each, or records with everything in them
+        const size_t at = INSPECT ? (size_t)i * look.record : i;
+        const size_t at_s = INSPECT ? at + s : row;
         in.lam = lambda[at];
         in.slo = slo_us[at];
         in.n_given = DERIVE ? 0 : r_fixed[at_s];
         in.only = c_fixed ? c_fixed[at_s] : (int32_t)c_all;
-        const int32_t* cf = coef + (coef_shared ? 0 : record ? at : (size_t)i * S * cs) + s * cs;
+        const int32_t* cf = coef + (coef_shared ? 0 : INSPECT ? at : (size_t)i * S * cs) + s * cs;
 #pragma unroll
         for (int x = 0; x < 5; ++x) in.cf[x] = cf[x];
         in.cf[5] = cs == 6 ? cf[5] : 0;
@@ -330,6 +347,7 @@ __global__ __launch_bounds__(64 * K1_WAVES) __attribute__((amdgpu_waves_per_eu(4
     const uint32_t g_step = gridDim.x * n_wv;
     uint32_t g = blockIdx.x * n_wv + wv;
     if (g >= n_groups) return;
+    unsigned long long swept = 0, entries = 0, formed = 0;  // INSPECT: the three sums
     K1RowIn next = load_rows(g);
     for (; g < n_groups; g += g_step) {
         const K1RowIn in = next;
@@ -589,6 +607,28 @@ __global__ __launch_bounds__(64 * K1_WAVES) __attribute__((amdgpu_waves_per_eu(4
         asm volatile("" ::"v"(next.T), "v"(next.lam), "v"(next.slo), "v"(next.n_given),
                      "v"(next.only), "v"(next.cf[0]), "v"(next.cf[1]), "v"(next.cf[2]),
                      "v"(next.cf[3]), "v"(next.cf[4]), "v"(next.cf[5]));
+        if constexpr (INSPECT) {
+            if (valid) {
+                const uint32_t n_ent = counts[nb];
+                const StepEntry* const img = reinterpret_cast<const StepEntry*>(image);
+                const RowCount rc = row_count(n_ent, row % S, S, T, class_map, look.pruned, look.steps);
+                for (uint32_t x = q; x < n_ent; x += lpr) {
+                    const uint32_t lt = lt_of_entry(img[x].shift, T, class_map);
+                    if (look.lt) {
+                        const size_t at = (size_t)row * look.K + (img[x].ck >> 16);
+                        look.lt[at] = (int32_t)lt;
+                        look.cost[at] = (int32_t)(img[x].ck & 0xFFFFu);
+                    }
+                    if (rc.swept) swept += (unsigned long long)(T + 1) - lt;
+                }
+                if (q == 0u) {
+                    entries += n_ent;
+                    if (rc.formed) formed += (unsigned long long)(T + 1);
+                }
+            }
+            wave_lds_fence();  // the next rows reuse this memory
+            continue;
+        }
         if (live) {
             // D: every bucket's cursor now stands at the start of the next bucket, which
             // is what bcum holds: bcum[0] = 0, bcum[x + 1] = cursor[x]; two per store
@@ -609,6 +649,19 @@ __global__ __launch_bounds__(64 * K1_WAVES) __attribute__((amdgpu_waves_per_eu(4
         }
         wave_lds_fence();  // the next rows reuse this memory
     }
+    if constexpr (INSPECT) {
+        if (!look.count) return;
+        for (int d = 32; d >= 1; d >>= 1) {
+            swept += __shfl_xor(swept, d, 64);
+            entries += __shfl_xor(entries, d, 64);
+            formed += __shfl_xor(formed, d, 64);
+        }
+        if (lane == 0u) {
+            atomicAdd(look.count, swept);
+            atomicAdd(look.count + 1, entries);
+            atomicAdd(look.count + 2, formed);
+        }
+    }
 }
 
 __global__ void k_zero64x3(unsigned long long* p) { p[0] = p[1] = p[2] = 0ull; }
@@ -620,10 +673,11 @@ __global__ __launch_bounds__(256) void k_export(const StepEntry* __restrict__ st
                                                 int32_t* __restrict__ lt,
                                                 int32_t* __restrict__ cost, uint32_t rows,
                                                 uint32_t S, uint32_t K, uint32_t Kp, uint32_t nb,
-                                                uint32_t nbs, uint64_t class_map)
+                                                uint32_t nbs, uint64_t class_map,
+                                                const int32_t* __restrict__ state)
 {
     uint32_t g = blockIdx.x * 256u + threadIdx.x;
-    if (g >= rows * Kp) return;
+    if (g >= rows * Kp || (*state & STATE_KEPT)) return;
     const uint32_t row = g / Kp, e = g - row * Kp;
     const int32_t T = tmeta[row / S];
     // the table holds the feasible candidates only; the arrays were filled with -1
@@ -645,42 +699,31 @@ __global__ __launch_bounds__(256) void k_fill_minus_one(int32_t* __restrict__ a,
 }
 
 // Sum over valid instances, models and feasible candidates of (T + 1 - lt): the
-// relaxations stage 2 executes.  Where the wide kernel serves the instance and
-// nothing is pruned, the model it handles first (s = S-1) and, in a pipeline of two or more, the one it
-// handles last (s = 0) are left out when they have entries enough for their
-// shortcuts (see worth_shortcut): the first row is then built by a scatter and
-// a scan, and of the last only the answer is computed.  out[1] takes the number
+// relaxations stage 2 executes, see row_count().  out[1] takes the number
 // of entries the table holds for those instances (the feasible candidates),
-// out[2] the cells (model, budget) whose value stage 2 forms: T + 1 per model,
-// less the model handled last where only the answer is computed.
+// out[2] the cells (model, budget) whose value stage 2 forms.
 __global__ __launch_bounds__(256) void k_count_relax(const StepEntry* __restrict__ step_tab,
                                                      const uint16_t* __restrict__ bcum,
                                                      const int32_t* __restrict__ tmeta,
                                                      unsigned long long* __restrict__ out,
                                                      uint32_t N, uint32_t S, uint32_t Kp,
                                                      uint32_t nb, uint32_t nbs,
-                                                     uint64_t class_map, int pruned, int steps)
+                                                     uint64_t class_map, int pruned, int steps,
+                                                     const int32_t* __restrict__ state)
 {
+    if (*state & STATE_KEPT) return;
     __shared__ unsigned long long part[256];
     unsigned long long acc = 0, entries = 0, formed = 0;
     for (uint32_t i = blockIdx.x; i < N; i += gridDim.x) {
         const int32_t T = tmeta[i];
         if (T < 0) continue;
-        const int cls = effective_class(T, class_map);
-        const bool wide = cls != NARROW_CLS && !pruned;  // the kernels that have the shortcuts
-        const int npos = (T + BUCKET_CELLS) / BUCKET_CELLS;
         for (uint32_t s = 0; s < S; ++s) {
             const size_t row = (size_t)i * S + s;
             const uint32_t n = bcum[row * nbs + nb];
             entries += n;
-            // the wide kernel's shortcuts for the model it handles first and for the
-            // one it handles last take no relaxations, and of the last one's row only
-            // the answer is formed (the step-row form never forms that row)
-            const bool shortcut = wide && (s == S - 1 || (s == 0 && S > 1)) &&
-                                  worth_shortcut((int)n, npos, cls_waves(cls));
-            const bool answer_only = s == 0 && ((shortcut && S > 1) || (steps && cls != NARROW_CLS));
-            if (!answer_only) formed += (unsigned long long)(T + 1);
-            if (shortcut) continue;
+            const RowCount rc = row_count(n, s, S, T, class_map, pruned, steps);
+            if (rc.formed) formed += (unsigned long long)(T + 1);
+            if (!rc.swept) continue;
             for (uint32_t e = threadIdx.x; e < n; e += 256)
                 acc += (unsigned long long)(T + 1) -
                        lt_of_entry(step_tab[row * Kp + e].shift, T, class_map);
@@ -701,13 +744,12 @@ __global__ __launch_bounds__(256) void k_count_relax(const StepEntry* __restrict
 
 }  // namespace
 
-// The table launch of launch_candidates().  `gate`: null, or a word in device memory
-// that says whether there is anything to do (see STATE_WORD).
+// The table launch of launch_candidates(), or (`look` not null) the same over what a whole
+// solve kept.
 static hipError_t launch_tables(const themis_problem_t& p, const Layout& L, const int32_t* d_coef,
                                 int coef_shared, const int32_t* d_lambda, const int32_t* d_slo_us,
                                 const int32_t* d_r_fixed, const int32_t* c_fixed, int c_all,
-                                int sparse, char* ws, hipStream_t st, const int32_t* gate,
-                                int32_t gate_want, uint32_t record)
+                                int sparse, char* ws, hipStream_t st, const Inspection* look)
 {
     BatchList bl{};
     bl.n = p.n_batch;
@@ -735,7 +777,7 @@ static hipError_t launch_tables(const themis_problem_t& p, const Layout& L, cons
     // Where a lane then has at most sixteen singles (and nothing is pruned) they
     // stay in registers and the rows need no room for them.
     const uint32_t lane_singles = ((uint32_t)p.c_max + (1u << split_log2) - 1u) >> split_log2;
-    const int me = prune || lane_singles > 16u ? 0 : lane_singles > 8u ? 16 : 8;
+    const int me = prune || look || lane_singles > 16u ? 0 : lane_singles > 8u ? 16 : 8;
     const K1Row R = k1_row((uint32_t)L.Kp, (uint32_t)p.c_max, (uint32_t)p.n_batch, (uint32_t)L.nb,
                            me > 0);
     const uint32_t row_bytes = R.words * (uint32_t)sizeof(uint32_t);
@@ -774,17 +816,21 @@ static hipError_t launch_tables(const themis_problem_t& p, const Layout& L, cons
                            (uint32_t)p.r_max, (uint32_t)p.tick_us,
                            (1.0 / (double)p.tick_us) * (1.0 - 0x1p-45), coef_shared, lpr_log2,
                            split_log2, (uint32_t)L.nb, (uint32_t)L.nbs, plan.class_map,
-                           sparse, (uint32_t)c_all, cs, s_magic, n_groups, gate, gate_want, record);
+                           sparse, (uint32_t)c_all, cs, s_magic, n_groups,
+                           look ? *look : Inspection{});
         return hipGetLastError();
     };
     const bool derive = d_r_fixed == nullptr;
     auto by_singles = [&](auto q_tag, auto d_tag) -> hipError_t {
         constexpr int Q = decltype(q_tag)::value;
         constexpr bool D = decltype(d_tag)::value;
-        if (prune) return launch(&k1_candidates<Q, true, D, 0>);
-        if (me == 8) return launch(&k1_candidates<Q, false, D, 8>);
-        if (me == 16) return launch(&k1_candidates<Q, false, D, 16>);
-        return launch(&k1_candidates<Q, false, D, 0>);
+        if (look)
+            return prune ? launch(&k1_candidates<Q, true, D, 0, true>)
+                         : launch(&k1_candidates<Q, false, D, 0, true>);
+        if (prune) return launch(&k1_candidates<Q, true, D, 0, false>);
+        if (me == 8) return launch(&k1_candidates<Q, false, D, 8, false>);
+        if (me == 16) return launch(&k1_candidates<Q, false, D, 16, false>);
+        return launch(&k1_candidates<Q, false, D, 0, false>);
     };
     auto by_replicas = [&](auto q_tag) -> hipError_t {
         return derive ? by_singles(q_tag, std::true_type{}) : by_singles(q_tag, std::false_type{});
@@ -826,34 +872,35 @@ hipError_t launch_candidates(const themis_problem_t& p, const Layout& L,
     if (e != hipSuccess) return e;
 
     return launch_tables(p, L, d_coef, p.coef_shared, d_lambda, d_slo_us, d_r_fixed, opts.c_fixed,
-                         opts.c_all, opts.sparse, ws, st, nullptr, 0, 0u);
+                         opts.c_all, opts.sparse, ws, st, nullptr);
 }
 
-hipError_t launch_tables_after_solve(const themis_problem_t& p, const Layout& L, char* ws,
-                                     hipStream_t st)
+// What a whole solve kept, into export's arrays or the count's sums; nothing after the
+// stage calls (decided on the device).
+static hipError_t launch_kept(const themis_problem_t& p, const Layout& L, const char* ws,
+                              Inspection look, hipStream_t st)
 {
     if (!cost_solve_serves(L)) return hipSuccess;  // the three stages did it: tables are there
-    int32_t* const ctrl = (int32_t*)(ws + L.ctrl_off);
-    int32_t* const rows = (int32_t*)(ws + L.frow_off);
+    const int32_t* const kept = (const int32_t*)(ws + L.step_off);
     const KeepLayout k = make_keep_layout(p);
-    const size_t words = (size_t)L.N * k.words, blocks = (words + 255u) / 256u;
-    hipLaunchKernelGGL(k1_keep_move, dim3((unsigned)(blocks < 4096u ? blocks : 4096u)), dim3(256), 0,
-                       st, (const int32_t*)ctrl, (const int32_t*)(ws + L.step_off), rows, words);
-    hipLaunchKernelGGL(k1_keep_state, dim3(1), dim3(1), 0, st, ctrl);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    // instances that failed the input check have a budget of -1 in tmeta
-    for (int given = 0; given < 2; ++given) {
-        e = launch_tables(p, L, rows + k.coef, p.coef_shared, rows + KEEP_LAM, rows + KEEP_SLO,
-                          given ? rows + k.given : nullptr, rows + k.only, 0, 0, ws, st,
-                          ctrl + STATE_WORD, STATE_REBUILD | (given ? STATE_GIVEN : 0), k.words);
+    look.state = (const int32_t*)(ws + L.ctrl_off) + STATE_WORD;
+    look.record = k.words;
+    look.K = (uint32_t)L.K;
+    look.pruned = p.prune != THEMIS_PRUNE_NONE;
+    look.steps = (p.prune & THEMIS_PRUNE_STEPS) != 0;
+    // instances that failed the input check have a budget of -1 in tmeta; the kernels of
+    // this form write nothing through the workspace's pointer
+    for (look.given = 0; look.given < 2; ++look.given) {
+        hipError_t e = launch_tables(p, L, kept + k.coef, p.coef_shared, kept + KEEP_LAM,
+                                     kept + KEEP_SLO, look.given ? kept + k.given : nullptr,
+                                     kept + k.only, 0, 0, const_cast<char*>(ws), st, &look);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
-hipError_t launch_export_candidates(const Layout& L, const char* ws, int32_t* d_lt,
-                                    int32_t* d_cost, hipStream_t st)
+hipError_t launch_export_candidates(const themis_problem_t& p, const Layout& L, const char* ws,
+                                    int32_t* d_lt, int32_t* d_cost, hipStream_t st)
 {
     const MinplusPlan plan = make_plan(L);
     uint32_t rows = (uint32_t)L.N * L.S;
@@ -867,8 +914,13 @@ hipError_t launch_export_candidates(const Layout& L, const char* ws, int32_t* d_
                        (const StepEntry*)(ws + L.step_off), (const uint16_t*)(ws + L.bcum_off),
                        (const int32_t*)(ws + L.tmeta_off), d_lt, d_cost, rows, (uint32_t)L.S,
                        (uint32_t)L.K, (uint32_t)L.Kp, (uint32_t)L.nb, (uint32_t)L.nbs,
-                       plan.class_map);
-    return hipGetLastError();
+                       plan.class_map, (const int32_t*)(ws + L.ctrl_off) + STATE_WORD);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    Inspection look{};
+    look.lt = d_lt;
+    look.cost = d_cost;
+    return launch_kept(p, L, ws, look, st);
 }
 
 hipError_t launch_count_relaxations(const themis_problem_t& p, const Layout& L, const char* ws,
@@ -883,8 +935,13 @@ hipError_t launch_count_relaxations(const themis_problem_t& p, const Layout& L, 
                        (const StepEntry*)(ws + L.step_off), (const uint16_t*)(ws + L.bcum_off),
                        (const int32_t*)(ws + L.tmeta_off), d_count, (uint32_t)L.N, (uint32_t)L.S,
                        (uint32_t)L.Kp, (uint32_t)L.nb, (uint32_t)L.nbs, plan.class_map,
-                       p.prune != THEMIS_PRUNE_NONE, (p.prune & THEMIS_PRUNE_STEPS) != 0);
-    return hipGetLastError();
+                       p.prune != THEMIS_PRUNE_NONE, (p.prune & THEMIS_PRUNE_STEPS) != 0,
+                       (const int32_t*)(ws + L.ctrl_off) + STATE_WORD);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    Inspection look{};
+    look.count = d_count;
+    return launch_kept(p, L, ws, look, st);
 }
 
 }  // namespace themis

@@ -37,14 +37,12 @@ __global__ __launch_bounds__(256) void k3_backtrack(
 
     int32_t* my_cfg = cfg + (size_t)i * S * 3;
     const int32_t kind = *state;
-    if (kind & (STATE_KEPT_IN_TABLE | STATE_KEPT_IN_ROWS)) {
+    if (kind & STATE_KEPT) {
         // no rows here: the workspace holds the results of a whole solve, of the
         // instances it was given and that passed its input check
         const bool solved_here = tmeta[i] >= 0;
-        const int32_t* const kp = ((kind & STATE_KEPT_IN_TABLE)
-                                       ? reinterpret_cast<const int32_t*>(step_tab)
-                                       : reinterpret_cast<const int32_t*>(frow)) +
-                                  (size_t)i * kept.words;
+        const int32_t* const kp =
+            reinterpret_cast<const int32_t*>(step_tab) + (size_t)i * kept.words;
         for (int x = lane; x < S * 3; x += LANES) my_cfg[x] = solved_here ? kp[kept.cfg + x] : 0;
         if (lane == 0) {
             status[i] = solved_here ? kp[KEEP_STATUS] : THEMIS_INVALID;

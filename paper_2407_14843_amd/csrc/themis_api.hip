@@ -372,12 +372,7 @@ int themis_export_candidates(const themis_problem_t* p, const void* d_workspace,
     Layout L;
     int rc = check_ws(p, d_workspace, workspace_bytes, &L);
     if (rc != THEMIS_OK) return rc;
-    // after a whole solve the tables are built first (the workspace is the caller's
-    // device memory, whatever the pointer's type says)
-    if (launch_tables_after_solve(*p, L, static_cast<char*>(const_cast<void*>(d_workspace)),
-                                  static_cast<hipStream_t>(stream)) != hipSuccess)
-        return THEMIS_ERR_LAUNCH;
-    return launch_export_candidates(L, static_cast<const char*>(d_workspace), d_lt, d_cost,
+    return launch_export_candidates(*p, L, static_cast<const char*>(d_workspace), d_lt, d_cost,
                                     static_cast<hipStream_t>(stream)) == hipSuccess
                ? THEMIS_OK
                : THEMIS_ERR_LAUNCH;
@@ -390,11 +385,6 @@ int themis_count_relaxations(const themis_problem_t* p, const void* d_workspace,
     Layout L;
     int rc = check_ws(p, d_workspace, workspace_bytes, &L);
     if (rc != THEMIS_OK) return rc;
-    // after a whole solve the tables are built first (the workspace is the caller's
-    // device memory, whatever the pointer's type says)
-    if (launch_tables_after_solve(*p, L, static_cast<char*>(const_cast<void*>(d_workspace)),
-                                  static_cast<hipStream_t>(stream)) != hipSuccess)
-        return THEMIS_ERR_LAUNCH;
     return launch_count_relaxations(*p, L, static_cast<const char*>(d_workspace), d_count,
                                     static_cast<hipStream_t>(stream)) == hipSuccess
                ? THEMIS_OK

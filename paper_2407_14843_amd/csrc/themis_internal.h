@@ -204,19 +204,18 @@ inline Layout make_layout(const themis_problem_t& p)
 // ---- what a whole solve leaves in the workspace ----------------------------------
 // The one-wavefront solve (cost_solve.hip) forms neither tables nor rows.  For the
 // calls that look at the workspace after a solve it leaves its inputs and results
-// instead, a record per instance (at most 5 + 11 words per model, of the sixteen per
-// model that the table region has at least), and says so in the state word:
-//   0                     tables (and rows) of the stage calls
-//   STATE_KEPT_IN_TABLE   records in the table region; no tables
-//   STATE_KEPT_IN_ROWS    records in the row region; tables built from them
-// Export and count first build the tables where there are none (launch_tables_after_solve);
-// the backtrack call then hands out the results.  Budgets are in tmeta in every state.
+// instead, a record per instance in the table region (at most 5 + 11 words per model, of
+// the sixteen per model that the region has at least), and says so in the state word:
+//   0            tables (and rows) of the stage calls
+//   STATE_KEPT   records; no tables
+// Export and count then evaluate the candidates again, from the records; the backtrack
+// call hands out the results.  None of the three writes to the workspace, in either
+// state, so they may overlap.  Budgets are in tmeta in both.
 constexpr int STATE_WORD = 2 * N_CLS;
 constexpr int LIST_WORD = STATE_WORD + 1;  // instances in the list of a listed solve
-constexpr int STATE_KEPT_IN_TABLE = 1, STATE_KEPT_IN_ROWS = 2;
-constexpr int STATE_GIVEN = 4;    // the replicas were given
-constexpr int STATE_REBUILD = 8;  // the candidate launches that follow have work to do
-constexpr int STATE_ONLY = 16;    // the cores were given, per model
+constexpr int STATE_KEPT = 1;
+constexpr int STATE_GIVEN = 2;    // the replicas were given
+constexpr int STATE_ONLY = 4;     // the cores were given, per model
 constexpr int STATE_C_ALL = 8;    // from this bit up: the same cores for every model, or 0
 
 // first words of a record
@@ -283,10 +282,6 @@ hipError_t launch_cost_solve(const themis_problem_t& p, const Layout& L, const i
                              const int32_t* d_r_fixed, int32_t* d_status, int32_t* d_cost,
                              int32_t* d_ticks, int32_t* d_cfg, char* ws, hipStream_t st,
                              const PassOpts& opts);
-// The candidate tables of the last whole solve on this workspace, where it left none;
-// nothing otherwise (decided on the device).
-hipError_t launch_tables_after_solve(const themis_problem_t& p, const Layout& L, char* ws,
-                                     hipStream_t st);
 int compute_units();  // of the current device
 
 // kernel launchers (one per stage), defined next to their kernels
@@ -419,8 +414,8 @@ hipError_t launch_same_config(const Layout& L, const int32_t* status_now, const 
                               const int32_t* status_pred, const int32_t* cfg_pred,
                               int32_t* stable, hipStream_t st);
 
-hipError_t launch_export_candidates(const Layout& L, const char* ws, int32_t* d_lt,
-                                    int32_t* d_cost, hipStream_t st);
+hipError_t launch_export_candidates(const themis_problem_t& p, const Layout& L, const char* ws,
+                                    int32_t* d_lt, int32_t* d_cost, hipStream_t st);
 hipError_t launch_count_relaxations(const themis_problem_t& p, const Layout& L, const char* ws,
                                     unsigned long long* d_count, hipStream_t st);
 
