@@ -36,7 +36,7 @@ struct CostArgs {
     KeepLayout kept;
     BatchConst bc[THEMIS_MAX_BATCH];
     int32_t n_batch;
-    int32_t N, S, cs, c_max, r_max, tick, slo_max, coef_shared, c_all, row_stride;
+    int32_t S, cs, c_max, r_max, tick, slo_max, coef_shared, c_all, row_stride;
     int32_t window;     // cells of the largest window with rows in LDS, a multiple of 64
     int32_t window_hbm; // and in HBM (no larger than the other: none)
     uint32_t magic;     // index_magic() of n_batch
@@ -1418,7 +1418,6 @@ inline CostArgs cost_args(const themis_problem_t& p, const Layout& L, const int3
     a.n_batch = p.n_batch;
     for (int j = 0; j < p.n_batch; ++j)
         a.bc[j] = {(double)p.batch_sizes[j], (1.0 / (1.0e6 * p.batch_sizes[j])) * (1.0 - 0x1p-45)};
-    a.N = L.N;
     a.S = L.S;
     a.cs = p.profile_form == THEMIS_PROFILE_EQ1 ? 6 : 5;
     a.c_max = p.c_max;
@@ -1434,11 +1433,33 @@ inline CostArgs cost_args(const themis_problem_t& p, const Layout& L, const int3
     return a;
 }
 
+// The arguments with the arrays of all instances but the first n, for the launches after
+// the first one of a large batch: offsets in the kernels would cost every solve (the
+// fallback at 16384 x 8 62.8 us instead of 61.8, 65536 x 8 99.5 instead of 98.8).  (Each
+// of these launches marks the workspace again, with the same words.)
+inline CostArgs past(CostArgs a, size_t n)
+{
+    auto skip = [](auto*& array, size_t elements) {
+        if (array) array += elements;
+    };
+    const size_t rows = n * (size_t)a.S;
+    if (!a.coef_shared) skip(a.coef, rows * a.cs);
+    for (const int32_t** in : {&a.lambda, &a.slo_us, &a.lambda2}) skip(*in, n);
+    for (const int32_t** in : {&a.r_fixed, &a.c_fixed}) skip(*in, rows);
+    for (int32_t** out : {&a.status, &a.cost, &a.ticks, &a.status2, &a.cost2, &a.ticks2, &a.lambda_v,
+                          &a.stable, &a.tmeta})
+        skip(*out, n);
+    for (int32_t** out : {&a.cfg, &a.cfg2}) skip(*out, 3 * rows);
+    skip(a.frow, rows * a.row_stride);
+    skip(a.keep, n * a.kept.words);
+    return a;
+}
+
 // A workgroup per instance, or where `listed` as many as stay resident (the host does
 // not know how long the list is).  `one` in kernel(one): the (model, batch size) pairs
 // fit a wavefront's lanes.
 //
-// One launch, whatever the instances need: a second one with room for wider windows,
+// One launch (of up to MAX_PER_LAUNCH instances), whatever the instances need: a second one with room for wider windows,
 // for the instances the first one could not solve, took 4.5 us to find that there are
 // none (of 24 at 16384 x 8, 55 at 86400 x 6); windows wider than the LDS of a full
 // compute unit allows have their rows in HBM instead.
@@ -1468,8 +1489,14 @@ hipError_t launch_per_instance(const themis_problem_t& p, const Layout& L, CostA
     a.window_hbm = (fit < room ? fit : room) & ~63;
     // (at most 40 KB of LDS, which a kernel may have without asking)
     const CostKernel k = kernel(L.S * p.n_batch <= 64);
-    hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(64), lds_for(a.window), st, a);
-    return hipGetLastError();
+    hipError_t e = hipSuccess;
+    in_launches(grid, [&](int first, int count) {
+        if (e != hipSuccess) return;
+        hipLaunchKernelGGL(k, dim3((unsigned)count), dim3(64), lds_for(a.window), st,
+                           past(a, (size_t)first));
+        e = hipGetLastError();
+    });
+    return e;
 }
 
 }  // namespace

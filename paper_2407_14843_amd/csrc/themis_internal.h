@@ -277,6 +277,15 @@ struct PassOpts {
 // The one-wavefront solve: three stages' worth of results in one launch.
 constexpr int COST_MAX_STAGES = 64;  // a lane per model
 bool cost_solve_serves(const Layout& L);
+// A launch has a wavefront per instance, and HIP takes fewer than 2^32 work-items, so
+// larger batches (of up to 2^28 instances) take several: launch(first, count) for each.
+constexpr int MAX_PER_LAUNCH = 1 << 25;
+template <typename F>
+void in_launches(int n, F launch)
+{
+    for (int first = 0; first < n; first += MAX_PER_LAUNCH)
+        launch(first, n - first < MAX_PER_LAUNCH ? n - first : MAX_PER_LAUNCH);
+}
 hipError_t launch_cost_solve(const themis_problem_t& p, const Layout& L, const int32_t* d_coef,
                              const int32_t* d_lambda, const int32_t* d_slo_us,
                              const int32_t* d_r_fixed, int32_t* d_status, int32_t* d_cost,

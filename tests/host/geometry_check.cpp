@@ -173,8 +173,24 @@ static void check_index_division()
     }
 }
 
+// Every instance is in exactly one launch of a wavefront each, none of which has as many
+// work-items as HIP refuses, up to the largest batch the problem check lets pass.
+static void check_launches()
+{
+    for (int n : {1, 2, (1 << 25) - 1, 1 << 25, (1 << 25) + 1, 1 << 26, (1 << 26) + 77, (1 << 28) - 1}) {
+        int next = 0;
+        in_launches(n, [&](int first, int count) {
+            CHECK(first == next && count > 0, "%d instances: launch at %d", n, first);
+            CHECK((unsigned long long)count * 64u < (1ull << 32), "%d instances: %d", n, count);
+            next = first + count;
+        });
+        CHECK(next == n, "%d instances: launches end at %d", n, next);
+    }
+}
+
 int main()
 {
+    check_launches();
     check_index_division();
     check_layout();
     check_wide();
