@@ -313,16 +313,18 @@ struct Solver {
         return (ROLE == SECOND || ROLE == PINNED ? a.cfg2 : a.cfg) + (size_t)i * a.S * 3;
     }
 
-    __device__ __forceinline__ void record_result(int32_t status, int32_t cost, int32_t ticks) const
+    __device__ __forceinline__ void record_result(int32_t status, int32_t cost, int32_t ticks,
+                                                  SolveStep step) const
     {
         if (!records() || lane != 0) return;
         int32_t* const kp = record();
-        kp[KEEP_STATUS] = status;
+        kp[KEEP_STATUS] = status | step << KEEP_STEP;
         kp[KEEP_COST] = cost;
         kp[KEEP_TICKS] = ticks;
     }
 
-    __device__ __forceinline__ void put(int32_t status, int32_t cost, int32_t ticks) const
+    __device__ __forceinline__ void put(int32_t status, int32_t cost, int32_t ticks,
+                                        SolveStep step = BY_A) const
     {
         constexpr bool TWO = ROLE == SECOND || ROLE == PINNED;
         if (lane == 0) {
@@ -330,7 +332,7 @@ struct Solver {
             (TWO ? a.cost2 : a.cost)[i] = cost;
             (TWO ? a.ticks2 : a.ticks)[i] = ticks;
         }
-        record_result(status, cost, ticks);
+        record_result(status, cost, ticks, step);
     }
 
     // `amount`: what the result says for cost and ticks
@@ -531,7 +533,7 @@ struct Solver {
             x -= l;
             e = e_next;
         }
-        put(THEMIS_SOLVED, (int32_t)total, (int32_t)ticks);
+        put(THEMIS_SOLVED, (int32_t)total, (int32_t)ticks, W == 16 ? BY_B : BY_C);
         put_choice(my_k, my_cost);
         return THEMIS_SOLVED;
     }
@@ -850,7 +852,7 @@ struct Solver {
             t -= key_w & 0xFFFFu;
             x -= key_d;
         }
-        put(THEMIS_SOLVED, (int32_t)total, (int32_t)ticks);
+        put(THEMIS_SOLVED, (int32_t)total, (int32_t)ticks, HBM ? BY_G_HBM : BY_G_LDS);
         put_choice(my_k, my_cost);
         return THEMIS_SOLVED;
     }
@@ -915,7 +917,7 @@ struct Solver {
             }
             rest = q;
         }
-        put(THEMIS_SOLVED, (int32_t)(best >> 32), (int32_t)((best >> 14) & 0x3FFFFull));
+        put(THEMIS_SOLVED, (int32_t)(best >> 32), (int32_t)((best >> 14) & 0x3FFFFull), BY_G_TRIAL);
         put_choice(my_k, my_cost);
         return THEMIS_SOLVED;
     }
@@ -1099,7 +1101,7 @@ struct Solver {
             x -= key_d;
             wave_lds_fence();
         }
-        put(THEMIS_SOLVED, (int32_t)total, (int32_t)ticks);
+        put(THEMIS_SOLVED, (int32_t)total, (int32_t)ticks, HBM ? BY_W_HBM : BY_W_LDS);
         put_choice(my_k, my_cost);
         return THEMIS_SOLVED;
     }
@@ -1236,7 +1238,7 @@ struct Solver {
                 return THEMIS_INTERNAL;
             }
         }
-        put(THEMIS_SOLVED, (int32_t)best, t_star);
+        put(THEMIS_SOLVED, (int32_t)best, t_star, BY_D);
         put_choice(my_k, my_cost);
         return THEMIS_SOLVED;
     }

@@ -45,7 +45,7 @@ __global__ __launch_bounds__(256) void k3_backtrack(
             reinterpret_cast<const int32_t*>(step_tab) + (size_t)i * kept.words;
         for (int x = lane; x < S * 3; x += LANES) my_cfg[x] = solved_here ? kp[kept.cfg + x] : 0;
         if (lane == 0) {
-            status[i] = solved_here ? kp[KEEP_STATUS] : THEMIS_INVALID;
+            status[i] = solved_here ? kp[KEEP_STATUS] & ((1 << KEEP_STEP) - 1) : THEMIS_INVALID;
             cost_out[i] = solved_here ? kp[KEEP_COST] : -1;
             ticks_out[i] = solved_here ? kp[KEEP_TICKS] : -1;
         }

@@ -218,8 +218,13 @@ constexpr int STATE_GIVEN = 2;    // the replicas were given
 constexpr int STATE_ONLY = 4;     // the cores were given, per model
 constexpr int STATE_C_ALL = 8;    // from this bit up: the same cores for every model, or 0
 
-// first words of a record
+// first words of a record; the status has the step that found the answer (see SolveStep)
+// from bit KEEP_STEP up, so that a test can tell which code its batch went through
 enum { KEEP_LAM = 0, KEEP_SLO, KEEP_STATUS, KEEP_COST, KEEP_TICKS, KEEP_HEAD };
+constexpr int KEEP_STEP = 8;
+// The steps of cost_solve.hip; LDS and HBM say where the rows were, TRIAL that the
+// combinations were tried.
+enum SolveStep { BY_A = 0, BY_B, BY_C, BY_G_LDS, BY_G_HBM, BY_G_TRIAL, BY_W_LDS, BY_W_HBM, BY_D };
 // offsets of the rest, and words per record; shared coefficients are in the first only
 struct KeepLayout {
     uint32_t coef, given, only, cfg, words;
