@@ -42,14 +42,15 @@
 //   B  else the recurrence over the first 16 cells: one table of (lt, index) by model
 //      and cost over base in LDS, a row of the recurrence in every sixteen lanes.
 //   C  else over 64 cells, rows in LDS, lane = cell;
-//   G  else lists of the candidates, those that Lagrangian bounds show to be in no
-//      answer dropped, and the recurrence over what is left of them, a few candidates
-//      per model and some tens of cells; or every combination of them, if those are few
-//      and far apart;
-//   W  else (a list too long) the recurrence over wider windows, with the table of one
-//      model at a time and the rows in LDS, then in HBM; and past that
+//   G  else lists of the candidates (of all, or where those do not fit of those that
+//      Lagrangian bounds leave), those that the bounds show to be in no answer dropped, and
+//      every combination of what is left, a few candidates per model; or the recurrence
+//      over them, if there are many combinations and their costs span few cells;
+//   W  else (a list too long even so, one instance in thousands of the densest) the
+//      recurrence over wider windows, with the table of one model at a time and the rows
+//      in LDS, then in HBM; and past that
 //   D  the recurrence over the budget with rows in HBM, which is bounded by T
-//      whatever the costs are (costs spread over thousands of cores in one model).
+//      whatever the costs are.
 //
 // What bounds it: vector issue.  An instance is some hundreds of instructions,
 // mostly the double-precision evaluation of candidates (candidate_eval.h, shared

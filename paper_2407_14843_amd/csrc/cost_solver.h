@@ -3,11 +3,8 @@
 #pragma once
 
 #include "candidate_eval.h"
-#include "instance_queue.h"
 #include "themis_internal.h"
 #include "wave_ops.h"
-
-#include <type_traits>
 
 namespace themis {
 namespace {
@@ -31,7 +28,9 @@ struct CostArgs {
     int32_t* tmeta;     // budgets, for calls that inspect the workspace afterwards
     const int32_t* list;  // the instances to solve (LISTED)
     int32_t* ctrl;
-    uint16_t* frow;     // rows of steps W and D
+    uint16_t* frow;     // rows of step D, by budget
+    uint16_t* hrow;     // rows of steps G and W, by cost, where LDS has no room
+    int32_t hrow_stride;  // cells of hrow per instance
     int32_t* keep;      // inputs and results for such calls, or null
     KeepLayout kept;
     BatchConst bc[THEMIS_MAX_BATCH];
@@ -40,6 +39,7 @@ struct CostArgs {
     int32_t window;     // cells of the largest window with rows in LDS, a multiple of 64
     int32_t window_hbm; // and in HBM (no larger than the other: none)
     uint32_t magic;     // index_magic() of n_batch
+    uint32_t parts, pair_magic;  // lanes per (model, batch size) pair of a sweep, see sweep()
     double rtick;
 };
 
@@ -105,12 +105,18 @@ __device__ __forceinline__ uint32_t least_of_rows(uint32_t x)
 // the record; QUIET, the same without the record; SECOND, the second set of results;
 // PINNED, the second set and the record, with the cores of every model taken from LDS.
 enum { PLAIN, QUIET, SECOND, PINNED };
-// Besides the status of an instance: the steps so far did not suffice.
-constexpr int UNFINISHED = -1;
+// Besides the status of an instance: the steps so far did not suffice; the lists are made;
+// the lists are to be made by narrowing.
+constexpr int UNFINISHED = -1, ARE_LISTED = -2, TOO_MANY = -3;
 
-template <int QUEUE, bool DERIVE, int ROLE>
-__device__ __attribute__((noinline)) int solve_further(uint64_t args, int i, int T, int32_t lam,
-                                                       int32_t slo);
+// What follows on step B is in functions of their own: FURTHER, step C and the lists of step
+// G where all candidates fit them, calls the others one after the other; NARROW, those lists
+// where they do not fit, by way of PRICE; GAP, step G up to its end, which is TRIAL, ROWS
+// or ROWS_HBM; WD, steps W and D.
+enum { PART_FURTHER, PART_PRICE, PART_NARROW, PART_GAP, PART_TRIAL, PART_ROWS, PART_ROWS_HBM, PART_WD };
+template <int QUEUE, bool DERIVE, int ROLE, int PART>
+__device__ __attribute__((noinline)) int solve_part(uint64_t args, int i, int T, int32_t lam,
+                                                    int32_t slo, int x);
 
 // One wavefront's view of the instance it works on.  ONE: its (model, batch size)
 // pairs fit the lanes, so every lane keeps its own from step A on.
@@ -575,86 +581,608 @@ struct Solver {
                             [&](int s, int y) { return rows[(s + 1) * 16 + y]; });
     }
 
-    // ---- step G ------------------------------------------------------------------
-    // Entries of lists: lt | cost << 16, and the index beside it.
-    struct Lists {
-        uint32_t* bins;   // 64 words per model; later the survivors, KEPT of each kind
-        uint32_t* lists;  // 2 * len words per model; later the rows
-        uint32_t* kept;   // per model: entries listed, later survivors
-        uint32_t* floor;  // per model: the least cost among them
-        int len;          // entries a list has room for
+    // ---- sweeps over the candidates, for steps C and G -----------------------------
+    struct Cores {
+        uint32_t lo, hi;  // lo > hi: none
     };
-    static constexpr int KEPT = 32;
+
+    // The cores with which candidates of the pair can cost as little as `limit`: the cost is
+    // at least c (given replicas: n c) and at least lambda (num + fixed c) / (b 1e6).  Here
+    // and below in single precision, with every term moved to the safe side by far more than
+    // its error (2^-22 or so).
+    __device__ __forceinline__ Cores cores_up_to(const Pair& p, uint32_t limit) const
+    {
+        const float most = (float)limit * 1.0001f;
+        float hi;
+        if (DERIVE) {
+            hi = ((float)limit * __builtin_amdgcn_rcpf((float)p.lam_per_M) * 1.0001f -
+                  (float)p.num * 0.9999f) *
+                     __builtin_amdgcn_rcpf((float)p.fixed) * 1.0001f + 1.0f;
+            hi = most < hi ? most : hi;
+        } else {
+            hi = most * __builtin_amdgcn_rcpf((float)p.h.n_given) + 1.0f;
+        }
+        hi = hi < (float)p.last ? hi : (float)p.last;
+        return Cores{first_core(p), hi > 0.0f ? (uint32_t)hi : 0u};
+    }
+
+    // The cores with which candidates of the pair can have cost + mu lt <= limit.  The cost
+    // is as above, the latency at least (num / c + fixed + wait) / tick and, where the replica
+    // count is derived and each one queues by itself, n >= lambda proc / (b 1e6) makes it
+    // (2 - 1 / b) (num / c + fixed) / tick: with either of both, k0 + k1 c + latency + M / c
+    // <= limit, so c lies between the roots of a quadratic.
+    __device__ __forceinline__ Cores cores_within(const Pair& p, float mu, float limit) const
+    {
+        const float per_us = mu * (float)a.rtick;
+        const float num = (float)p.num, fixed = (float)p.fixed;
+        float wait = (float)p.bh.w * __builtin_amdgcn_rcpf((float)lam);
+        if (QUEUE == THEMIS_QUEUE_PER_REPLICA && !DERIVE) wait *= (float)p.h.n_given;
+        float lo = (float)first_core(p), hi = (float)p.last;
+        auto cut = [&](float k0, float k1, float M, float latency) {
+            const float R =
+                limit - k0 - latency + 1.0e-4f * (limit + k0 + latency) + 1.0e-3f;
+            const float D = R * R - 4.0f * k1 * (M * 0.9999f);
+            if (!(R > 0.0f) || !(D >= 0.0f)) {
+                hi = 0.0f;
+                return;
+            }
+            const float q = R + __builtin_amdgcn_sqrtf(D);
+            const float top = q * __builtin_amdgcn_rcpf(2.0f * k1) * 1.0001f + 1.0f;
+            const float bottom = 2.0f * M * __builtin_amdgcn_rcpf(q) * 0.9998f - 1.0f;
+            hi = top < hi ? top : hi;
+            lo = bottom > lo ? bottom : lo;
+        };
+        const float M = per_us * num, latency = per_us * (fixed + wait);
+        if (DERIVE) {
+            const float rate = (float)p.lam_per_M;
+            const bool each_queues = QUEUE == THEMIS_QUEUE_PER_REPLICA;
+            const float both = 2.0f - __builtin_amdgcn_rcpf((float)p.bh.b) * 1.0001f;
+            auto cuts = [&](float k0, float k1) {
+                cut(k0, k1, M, latency);
+                if (each_queues) cut(k0, k1, both * M, both * per_us * fixed);
+            };
+            cuts(0.0f, 1.0f);
+            cuts(rate * num, rate * fixed);
+            // no fewer replicas than with the most cores left, in turn
+            for (int turn = 0; turn < 2; ++turn) {
+                const float n = rate * (num * __builtin_amdgcn_rcpf(hi) + fixed) * 0.9999f;
+                if (hi >= lo) cuts(0.0f, __builtin_ceilf(n));
+            }
+        } else {
+            cut(0.0f, (float)p.h.n_given, M, latency);
+        }
+        return Cores{(uint32_t)lo, (uint32_t)hi};
+    }
+
+    // The cores of the pair with about the least cost + mu lt at the least replica count (or
+    // `more` above it): as few as that count allows, or where another one saves less in
+    // latency than it costs.
+    __device__ __forceinline__ uint32_t likely_core(const Pair& p, float mu, uint32_t more) const
+    {
+        const float num = (float)p.num, fixed = (float)p.fixed, rate = (float)p.lam_per_M;
+        const float last = (float)p.last;
+        float n = (float)p.h.n_given, least_c = 0.0f;
+        if (DERIVE) {
+            n = __builtin_ceilf(rate * (num * __builtin_amdgcn_rcpf(last) + fixed)) + (float)more;
+            least_c = rate * num * __builtin_amdgcn_rcpf(n - rate * fixed);
+        }
+        float c = __builtin_amdgcn_sqrtf(mu * (float)a.rtick * num * __builtin_amdgcn_rcpf(n));
+        c = c > least_c ? c : least_c;
+        c = __builtin_ceilf(c);
+        c = c < last ? c : last;
+        return c > (float)p.lo ? (uint32_t)c : p.lo;
+    }
+
+    // Calls use(pair)(cores, lt, cost) for the feasible candidates among range(pair).  Lanes
+    // are pairs, 64 at a time; where all pairs fit half of the lanes, several lanes share a
+    // pair's cores.  DEALT: where one lane would have far more of them than the others, all
+    // are dealt out, 64 at a time (1400 cycles, against 650 for two of every lane's own; with
+    // the replicas given the lanes' shares differ too little to look for that).
+    // SAMPLE: the more cores, the fewer of them (every eighth of their number).
+    // One or two core counts are evaluated whatever range() would say, which takes longer.
+    enum How { DEALT, SAMPLE };
+    template <How HOW, typename R, typename F>
+    __device__ __forceinline__ void sweep(R range, F use) const
+    {
+        const Recips rc = recips();
+        const bool few = ROLE == PINNED || a.c_fixed || a.c_all || a.c_max <= 2;
+        const uint32_t pairs = (uint32_t)(a.S * a.n_batch), parts = a.parts;
+        const uint32_t part = parts > 1u ? index_quotient((uint32_t)lane, a.pair_magic) : 0u;
+        auto after = [&](uint32_t c) {
+            return c + (HOW == SAMPLE && (c >> 3) > parts ? c >> 3 : parts);
+        };
+        for (uint32_t r = 0; r < pairs; r += 64u) {
+            const uint32_t x = r + (uint32_t)lane - part * pairs;
+            const uint32_t s = index_quotient(x, a.magic);
+            const Pair p = pair_of(s, x - s * (uint32_t)a.n_batch, x < pairs && part < parts);
+            Cores c = few ? Cores{p.lo, p.last} : range(p);
+            if (!p.there) c.hi = 0u;
+            if (HOW == DEALT && DERIVE && !few && (uint32_t)a.c_max > 8u * parts) {
+                const uint32_t mine = part == 0u && c.lo <= c.hi ? c.hi - c.lo + 1u : 0u;
+                const uint32_t end = wave_scan<false>(mine), all = lane_value(end, 63);
+                const uint32_t most = ~lane_value(wave_scan<true>(~mine), 63);
+                if (most > 5u * parts * ((all + 63u) / 64u)) {
+                    deal_out(p, rc, c.lo, end - mine, all, use);
+                    continue;
+                }
+            }
+            const auto meet = use(p);
+            c.lo += part;
+            for (;;) {
+                // two at a time: their chains of dependent operations fill each other's waits
+                const bool go = c.lo <= c.hi;
+                if (__ballot(go) == 0ull) break;
+                const uint32_t c1 = after(c.lo);
+                const bool both = go && c1 <= c.hi;
+                const double r0 = recip(rc, go ? speed(p, c.lo) : 1u);
+                const double r1 = recip(rc, both ? speed(p, c1) : 1u);
+                if (go) {
+                    const Eval e0 = eval<false>(p, r0), e1 = eval<false>(p, r1);
+                    if (e0.lt >= 0) meet(c.lo, (uint32_t)e0.lt, __umul24((uint32_t)e0.n, c.lo));
+                    if (both && e1.lt >= 0) meet(c1, (uint32_t)e1.lt, __umul24((uint32_t)e1.n, c1));
+                    c.lo = after(c1);
+                }
+            }
+        }
+        wave_lds_fence();
+    }
+
+    // The candidates of all lanes' pairs p, `all` of them: a lane's first one is number
+    // `start` of all and has `lo` cores.
+    template <typename F>
+    __device__ __forceinline__ void deal_out(const Pair& p, const Recips& rc, uint32_t lo,
+                                             uint32_t start, uint32_t all, F use) const
+    {
+        auto fetch = [](uint32_t v, int from) { return (uint32_t)__shfl((int)v, from, 64); };
+        const uint32_t what = p.s << 4 | p.j;
+        for (uint32_t x0 = 0; x0 < all; x0 += 64u) {
+            const uint32_t x = x0 + (uint32_t)lane;
+            // whose it is: the last lane that starts at or before it
+            int of = 0;
+            for (int d = 32; d >= 1; d >>= 1)
+                if (fetch(start, of + d) <= x) of += d;
+            Pair q = p;
+            const uint32_t sj = fetch(what, of);
+            q.s = sj >> 4, q.j = sj & 15u;
+            q.num = __shfl(p.num, of, 64);
+            q.fixed = __shfl(p.fixed, of, 64);
+            q.pcap = fetch(p.pcap, of);
+            q.bh.M = __shfl(p.bh.M, of, 64);
+            q.bh.rM = __shfl(p.bh.rM, of, 64);
+            q.bh.w = q.bh.M - 1.0e6;
+            const uint32_t c = fetch(lo, of) + (x - fetch(start, of));
+            const bool go = x < all;
+            const double rd = recip(rc, go ? speed(q, c) : 1u);
+            if (go) {
+                const Eval ev = eval<false>(q, rd);
+                if (ev.lt >= 0) use(q)(c, (uint32_t)ev.lt, __umul24((uint32_t)ev.n, c));
+            }
+        }
+    }
+
+    // The table of 64 cells per model.  (With the replicas given the ranges are even and the
+    // plain loop is the faster one, by half a microsecond at 16384 x 8.)
+    __device__ __forceinline__ void fill_sixtyfour() const
+    {
+        if (!DERIVE) return fill_all<false, 64>(Pair());
+        uint32_t* const tab = lds + L.tab;
+        for (int x = lane; x < a.S * 64; x += 64) tab[x] = EMPTY;
+        wave_lds_fence();
+        sweep<DEALT>(
+            [&](const Pair& p) { return cores_up_to(p, (keys()[p.s] >> 15) + 63u); },
+            [&](const Pair& p) {
+                return [=, base = keys()[p.s] >> 15, mine = tab + 64u * p.s, j = p.j](
+                           uint32_t c, uint32_t lt, uint32_t cost) {
+                    if (cost - base < 64u)
+                        atomicMin(&mine[cost - base],
+                                  (lt << INDEX_BITS) | ((c - 1u) * (uint32_t)a.n_batch + j));
+                };
+            });
+    }
+
+    // ---- step G ------------------------------------------------------------------
+    // A candidate as lt << 15 | cost; in lists the index is in the next word.
+    static __device__ __forceinline__ uint32_t lt_of(uint32_t w) { return w >> 15; }
+    static __device__ __forceinline__ uint32_t cost_of(uint32_t w) { return w & 0x7FFFu; }
+    static __device__ __forceinline__ float priced(float mu, uint32_t w)
+    {
+        return __builtin_fmaf(mu, (float)lt_of(w), (float)cost_of(w));
+    }
+
+    // Two words per candidate in lists: the above, and its index.
+    struct Lists {
+        uint32_t* bins;   // 64 words per model
+        uint32_t* kept;   // per model: entries listed, later survivors
+        uint32_t* floor;  // per model: entries its list has room for, later the least cost of
+                          // its survivors
+        uint32_t* first;  // per model: where its list starts, later its survivors, in words
+                          // from `bins` on
+        uint32_t* plan;   // cells of the survivors' rows, combinations worth trying
+        uint32_t* lists;
+        int room;         // words from `lists` on
+    };
 
     __device__ __forceinline__ Lists lists_of() const
     {
         Lists l;
         l.bins = lds + L.tab;
-        l.lists = l.bins + 64 * a.S;
-        l.kept = lds + L.best;
+        l.kept = l.bins + 64 * a.S;
         l.floor = l.kept + a.S;
-        l.len = (L.words - L.tab - 64 * a.S) / (2 * a.S);
-        l.len = l.len < 64 ? l.len : 64;
+        l.first = l.floor + a.S;
+        l.plan = l.first + a.S;
+        l.lists = l.plan + 2;
+        l.room = L.words - L.tab - 67 * a.S - 2;
+        return l;
+    }
+    // The room for lists divided evenly (at least fourteen entries each, see cost_lds()).
+    __device__ __forceinline__ void divide_evenly(const Lists& l) const
+    {
+        const uint32_t len = (uint32_t)(l.room / (2 * a.S));
+        if (lane < a.S) {
+            l.first[lane] = (uint32_t)(l.lists - l.bins) + 2u * (uint32_t)lane * len;
+            l.floor[lane] = len;
+        }
+        wave_lds_fence();
+    }
+    // ... or as the numbers in `kept` need it; false where there is not enough.
+    __device__ __forceinline__ bool divide_by_need(const Lists& l) const
+    {
+        const uint32_t need = lane < a.S ? l.kept[lane] : 0u;
+        const uint32_t end = wave_scan<false>(need);
+        if (2u * lane_value(end, 63) > (uint32_t)l.room) return false;
+        if (lane < a.S) {
+            l.first[lane] = (uint32_t)(l.lists - l.bins) + 2u * (end - need);
+            l.floor[lane] = need;
+        }
+        wave_lds_fence();
+        return true;
+    }
+
+    // The survivors are packed in the place of the bins, in the order of their indices, or
+    // still in the lists.  `free`: the other of the two places.
+    struct Survivors : Lists {
+        bool packed;
+        uint32_t* free;
+        int free_words;
+    };
+    __device__ __forceinline__ Survivors survivors() const
+    {
+        Survivors l{lists_of()};
+        l.packed = __builtin_amdgcn_readfirstlane((int)l.first[0]) == 0;
+        l.free = l.packed ? l.lists : l.bins;
+        l.free_words = l.packed ? l.room : 64 * a.S;
         return l;
     }
 
-    // Lists, per model, the candidates that nothing in a cheaper bin of costs is as fast
-    // as (a bin is as many costs as it takes for 64 bins to reach the fastest candidate's).
-    // False when one does not fit its list.
-    __device__ __forceinline__ bool list_candidates(const Lists& l) const
+    // A model's bins: as many costs in each as it takes for 64 of them to reach the fastest
+    // candidate's.
+    struct Bins {
+        uint32_t* words;
+        uint32_t base, top;  // least cost, fastest candidate's
+        int shift;
+        __device__ __forceinline__ bool reach(uint32_t cost) const { return cost <= top; }
+        __device__ __forceinline__ uint32_t at(uint32_t cost) const { return (cost - base) >> shift; }
+    };
+    __device__ __forceinline__ Bins bins_of(const Lists& l, uint32_t s) const
     {
-        for (int x = lane; x < 64 * a.S; x += 64) l.bins[x] = LT_NONE;
+        Bins b;
+        b.words = l.bins + 64u * s;
+        b.base = keys()[s] >> 15;
+        b.top = cost_of(fastest()[s]);
+        const uint32_t range = b.top - b.base;  // its bits beyond six are cut
+        b.shift = range < 64u ? 0 : 26 - __builtin_clz(range);
+        return b;
+    }
+    // The fastest candidate of every bin, of all or of a sample of the candidates.
+    template <How HOW>
+    __device__ __forceinline__ void fill_bins(const Lists& l) const
+    {
+        for (int x = lane; x < 64 * a.S; x += 64) l.bins[x] = EMPTY;
         wave_lds_fence();
-        const Recips rc = recips();
-        auto each = [&](auto use) {
-            for_pairs(Pair(), [&](const Pair& p) {
-                const uint32_t base = keys()[p.s] >> 15;
-                const uint32_t top = fastest()[p.s] & 0x7FFFu;
-                const uint32_t range = top - base;  // its bits beyond six are cut
-                const int sh = range < 64u ? 0 : 26 - __builtin_clz(range);
-                auto one = [&](const Eval& ev, uint32_t c) {
-                    const uint32_t cost = __umul24((uint32_t)ev.n, c);
-                    if (ev.lt >= 0 && cost <= top)
-                        use(p, c, (uint32_t)ev.lt, cost, p.s * 64u + ((cost - base) >> sh));
+        if (lane < a.S) {
+            const uint32_t cheapest = keys()[lane], fast = fastest()[lane];
+            l.bins[64 * lane] = (cheapest & 0x7FFFu) << 15 | cheapest >> 15;
+            const Bins b = bins_of(l, (uint32_t)lane);
+            uint32_t* const last = &b.words[b.at(b.top)];
+            *last = least(*last, fast);
+        }
+        wave_lds_fence();
+        sweep<HOW>(
+            [&](const Pair& p) { return cores_up_to(p, cost_of(fastest()[p.s])); },
+            [&](const Pair& p) {
+                return [b = bins_of(l, p.s)](uint32_t, uint32_t lt, uint32_t cost) {
+                    if (b.reach(cost)) atomicMin(&b.words[b.at(cost)], lt << 15 | cost);
                 };
-                uint32_t c = first_core(p);
-                for (;;) {
-                    const bool go = p.there && c <= p.last && may_cost(p, c, top);
-                    if (__ballot(go) == 0ull) break;
-                    const bool both = c < p.last;
-                    const double r0 = recip(rc, go ? speed(p, c) : 1u);
-                    const double r1 = recip(rc, go && both ? speed(p, c + 1u) : 1u);
-                    if (go) {
-                        const Eval e0 = eval<false>(p, r0), e1 = eval<false>(p, r1);
-                        one(e0, c);
-                        if (both) one(e1, c + 1u);
-                        c += 2u;
-                    }
-                }
             });
-        };
-        each([&](const Pair&, uint32_t, uint32_t lt, uint32_t, uint32_t bin) {
-            atomicMin(&l.bins[bin], lt);
-        });
-        wave_lds_fence();
-        for (int s = 0; s < a.S; ++s) {
-            const uint32_t incl = wave_scan<true>(l.bins[64 * s + lane]);
-            l.bins[64 * s + lane] = from_lane_below(incl, LT_NONE);  // least of all cheaper bins
+    }
+    // Lists the candidates among range(pair) that pass(pair)(candidate) and that the fastest
+    // candidate of their own and all cheaper bins, which the bins are turned into, does not
+    // beat, nor that of the cheaper ones alone.  False when there are more of a model than its
+    // list has room for.
+    template <typename R, typename F>
+    __device__ __forceinline__ bool list_candidates(const Lists& l, R range, F pass) const
+    {
+        for (int m = 0; m < a.S; m += 4) {
+            uint32_t fast[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                fast[q] = m + q < a.S ? l.bins[64 * (m + q) + lane] : 0u;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                fast[q] = wave_scan<true>(fast[q]);
+                if (m + q < a.S) l.bins[64 * (m + q) + lane] = fast[q];
+            }
         }
         if (lane < a.S) l.kept[lane] = 0u;
         wave_lds_fence();
-        each([&](const Pair& p, uint32_t c, uint32_t lt, uint32_t cost, uint32_t bin) {
-            if (lt >= l.bins[bin]) return;
-            const uint32_t at = atomicAdd(&l.kept[p.s], 1u);
-            if (at < (uint32_t)l.len) {
-                uint32_t* const e = l.lists + 2 * ((int)p.s * l.len + (int)at);
-                e[0] = lt | cost << 16;
-                e[1] = (c - 1u) * (uint32_t)a.n_batch + p.j;
-            }
+        sweep<DEALT>(range, [&](const Pair& p) {
+            return [=, passes = pass(p), b = bins_of(l, p.s), list = l.bins + l.first[p.s],
+                    room = l.floor[p.s], s = p.s, j = p.j](uint32_t c, uint32_t lt, uint32_t cost) {
+                const uint32_t x = lt << 15 | cost;
+                if (!b.reach(cost) || !passes(x)) return;
+                const uint32_t bin = b.at(cost);
+                const uint32_t y = b.words[bin], z = bin > 0u ? b.words[bin - 1u] : EMPTY;
+                if ((x != y && cost_of(y) <= cost && lt_of(y) <= lt) || lt_of(z) <= lt) return;
+                const uint32_t at = atomicAdd(&l.kept[s], 1u);
+                if (at < room) {
+                    list[2u * at] = x;
+                    list[2u * at + 1u] = (c - 1u) * (uint32_t)a.n_batch + j;
+                }
+            };
         });
+        return __ballot(lane < a.S && l.kept[lane] > l.floor[lane]) == 0ull;
+    }
+
+    // The walk along the lower hull of (ticks, cost) between the cheapest assignment (too
+    // slow) and the fastest (within the budget) to where the budget lies.
+    struct Source {
+        const uint32_t* words;  // this lane's model's candidates
+        int n, step;
+    };
+    struct Hull {
+        const Solver& sv;
+        int width, s, sub;  // lanes per model; this lane's model, and which of its lanes it is
+        bool there;
+        int64_t c0, l0, c1, l1;  // cost and ticks of the assignments at both ends
+        uint32_t cheap, fast;    // their choices of this lane's model
+        float mu, v;             // the price of a tick; the model's least cost + mu lt
+        uint32_t held[4];        // this lane's first entries of what the walk goes over
+
+        __device__ __forceinline__ explicit Hull(const Solver& solver) : sv(solver), mu(0.0f), v(0.0f)
+        {
+            const int S = sv.a.S;
+            width = 1;
+            while (2 * width * S <= 64) width *= 2;
+            s = sv.lane / width, sub = sv.lane & (width - 1);
+            there = s < S;
+            if (!there) s = 0;
+            const uint32_t key = sv.keys()[s];
+            cheap = (key & 0x7FFFu) << 15 | key >> 15, fast = sv.fastest()[s];
+            c0 = total(cost_of(cheap)), l0 = total(lt_of(cheap));
+            c1 = total(cost_of(fast)), l1 = total(lt_of(fast));
+        }
+
+        __device__ __forceinline__ int total(uint32_t x) const
+        {
+            return (int)wave_sum(there && sub == 0 ? x : 0u);
+        }
+        // (any price gives a bound, so its last bits do not matter)
+        __device__ __forceinline__ float price() const
+        {
+            return (float)(int)(c1 - c0) * __builtin_amdgcn_rcpf((float)(int)(l0 - l1));
+        }
+        // Has choose() and changed() go over these candidates.
+        __device__ __forceinline__ void hold(const Source& from)
+        {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int e = sub + q * width;
+                held[q] = e < from.n ? from.words[from.step * e] : EMPTY;
+            }
+        }
+        // calls f(candidate) for this lane's entries (EMPTY reads as a candidate slower and
+        // dearer than any)
+        template <typename F>
+        __device__ __forceinline__ void each(const Source& from, F f) const
+        {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) f(held[q]);
+            for (int e = sub + 4 * width; e < from.n; e += width) f(from.words[from.step * e]);
+        }
+        // The model's choice at the price, in all of its lanes, and its cost + mu lt.
+        __device__ __forceinline__ uint32_t choose(const Source& from)
+        {
+            uint32_t w = EMPTY;
+            v = 3.0e38f;
+            each(from, [&](uint32_t x) {
+                const float y = priced(mu, x);
+                if (y < v) v = y, w = x;
+            });
+            with_partners(width, [&](auto of) {
+                const float ov = __uint_as_float(of(__float_as_uint(v)));
+                const uint32_t ow = of(w);
+                if (ov < v || (ov == v && ow < w)) v = ov, w = ow;
+            });
+            return w;
+        }
+        // The assignment of the choices w becomes an end; true where the walk is over: on the
+        // line between the ends, or above it.
+        __device__ __forceinline__ bool ends(uint32_t w)
+        {
+            const int64_t c = total(cost_of(w)), t = total(lt_of(w));
+            if (c * (l0 - l1) + (c1 - c0) * t >= c1 * (l0 - l1) + (c1 - c0) * l1) return true;
+            if (t <= sv.T)
+                c1 = c, l1 = t, fast = w;
+            else
+                c0 = c, l0 = t, cheap = w;
+            return c0 >= c1 || l0 <= l1;
+        }
+        __device__ __forceinline__ void walk(const Source& from)
+        {
+            // (c0 >= c1: the price at hand is the last that means anything)
+            for (int turn = 0; turn < 16 && c0 < c1; ++turn) {
+                mu = price();
+                if (ends(choose(from))) break;
+            }
+        }
+
+        // The least cost after a change of one choice that leaves an assignment (cost c, t
+        // ticks) within the budget; 2^30: there is none.
+        __device__ __forceinline__ int changed(const Source& from, uint32_t choice) const
+        {
+            const int c = total(cost_of(choice)), t = total(lt_of(choice));
+            uint32_t best = 0u;  // 2^16 less the change of the cost
+            each(from, [&](uint32_t x) {
+                const uint32_t gain = 0x10000u + cost_of(choice) - cost_of(x);
+                if (t + (int)lt_of(x) - (int)lt_of(choice) <= sv.T && gain > best) best = gain;
+            });
+            const int b = (int)~lane_value(wave_scan<true>(~best), 63);  // the most of all lanes
+            return b ? c + 0x10000 - b : 1 << 30;
+        }
+        // The cost of some assignment within the budget: from the choices of the faster end,
+        // as many models as the ticks left over allow go over to those of the cheaper end,
+        // then one choice changes; or one model more goes over, or all, and then one choice
+        // changes that takes it back into the budget.
+        __device__ __forceinline__ int upper(const Source& from) const
+        {
+            const int left = sv.T - (int)l1;
+            const int d = there ? (int)lt_of(cheap) - (int)lt_of(fast) : 0;
+            // (the first lane of a model counts, so its lanes have the same sum)
+            const int sum = (int)wave_scan<false>(sub == 0 && d > 0 ? (uint32_t)d : 0u);
+            uint32_t choice[3];
+            choice[0] = d > 0 && sum <= left ? cheap : fast;
+            choice[1] = d > 0 && sum - d <= left ? cheap : fast;
+            choice[2] = cheap;
+            int ub = (int)c1;
+#pragma unroll 1
+            for (int x = 0; x < 3; ++x) {
+                const int u = changed(from, x == 0 ? choice[0] : x == 1 ? choice[1] : choice[2]);
+                ub = u < ub ? u : ub;
+            }
+            return ub;
+        }
+        // How much more than its model's least a candidate of an answer can have at the price,
+        // in the light of an assignment of cost `ub`.
+        __device__ __forceinline__ float gap_to(int ub) const
+        {
+            float bound = there && sub == 0 ? v : 0.0f;
+            with_partners(64, [&](auto of) { bound += __uint_as_float(of(__float_as_uint(bound))); });
+            bound -= mu * (float)sv.T;
+            const float slack =
+                ((float)(int)c1 + mu * (float)(sv.T + (int)l0)) * 0x1p-16f + 0x1p-10f;
+            return (float)ub - bound + slack;
+        }
+    };
+
+    // The price, and the gap at it, where there are too many candidates for a list of all: the
+    // walk goes over a sample of them first and then over all, of which only those are
+    // evaluated that can beat the sample's best at that price (cores_within()).
+    __device__ __forceinline__ int find_price() const
+    {
+        const Lists l = lists_of();
+        fill_bins<SAMPLE>(l);
+        Hull h(*this);
+        const Source bins{l.bins + 64 * h.s, h.there ? 64 : 0, 1};
+        h.hold(bins);
+        h.walk(bins);
+        // over all candidates: per model the least cost + mu lt, and whose it is, from the
+        // sample's on
+        uint32_t w = 0u;
+        for (int turn = 0;; ++turn) {
+            h.hold(bins);
+            const uint32_t sampled = h.choose(bins);
+            if (turn > 0 && priced(h.mu, w) < h.v)
+                h.v = priced(h.mu, w);
+            else
+                w = sampled;
+            if (h.there && h.sub == 0)
+                bests()[h.s] = (unsigned long long)__float_as_uint(h.v) << 32 | w;
+            wave_lds_fence();
+            auto offer = [&](const Pair& p) {
+                return [mine = bests() + p.s, mu = h.mu](uint32_t, uint32_t lt, uint32_t cost) {
+                    const uint32_t x = lt << 15 | cost;
+                    atomicMin(mine, (unsigned long long)__float_as_uint(priced(mu, x)) << 32 | x);
+                };
+            };
+            sweep<DEALT>(
+                [&](const Pair& p) {
+                    // the likeliest first: what they offer leaves the others less room
+#pragma unroll 1
+                    for (uint32_t more = 0u; more < 2u; ++more) {
+                        const uint32_t c = likely_core(p, h.mu, more);
+                        const Eval ev = eval<false>(p, recip_below((double)speed(p, c)));
+                        if (p.there && ev.lt >= 0)
+                            offer(p)(c, (uint32_t)ev.lt, __umul24((uint32_t)ev.n, c));
+                    }
+                    wave_lds_fence();
+                    return cores_within(p, h.mu, __uint_as_float((uint32_t)(bests()[p.s] >> 32)));
+                },
+                offer);
+            const unsigned long long best = bests()[h.s];
+            h.v = __uint_as_float((uint32_t)(best >> 32));
+            w = (uint32_t)best;
+            if (h.ends(w) || turn == 7) break;
+            h.mu = h.price();
+        }
+        h.hold(bins);
+        const float gap = h.gap_to(h.upper(bins));
+        if (lane == 0) l.plan[0] = __float_as_uint(h.mu), l.plan[1] = __float_as_uint(gap);
         wave_lds_fence();
-        const bool fits = lane >= a.S || l.kept[lane] <= (uint32_t)l.len;
-        return __ballot(!fits) == 0ull;
+        return TOO_MANY;
+    }
+
+    // Lists those within the gap at the price; false when they do not fit either.
+    __device__ __forceinline__ bool list_narrowed() const
+    {
+        const Lists l = lists_of();
+        const float mu = __uint_as_float(__builtin_amdgcn_readfirstlane(l.plan[0]));
+        const float gap = __uint_as_float(__builtin_amdgcn_readfirstlane(l.plan[1]));
+        auto least_priced = [&](const Pair& p) {
+            return __uint_as_float((uint32_t)(bests()[p.s] >> 32));
+        };
+        auto range = [&](const Pair& p) { return cores_within(p, mu, least_priced(p) + gap); };
+        auto near = [&](const Pair& p) {
+            return [mu, gap, v = least_priced(p)](uint32_t x) { return priced(mu, x) - v <= gap; };
+        };
+        uint32_t key = 0, fast = 0;
+        if (lane < a.S) key = keys()[lane], fast = fastest()[lane];
+        bool fits = false;
+        for (int turn = 0; turn < 4 && !fits; ++turn) {
+            if (turn == 2) {
+                // bins of the costs that those within the gap have
+                if (lane < a.S) l.floor[lane] = EMPTY, l.first[lane] = 0u;
+                wave_lds_fence();
+                sweep<DEALT>(range, [&](const Pair& p) {
+                    return [is_near = near(p), lo = l.floor + p.s, hi = l.first + p.s](
+                               uint32_t, uint32_t lt, uint32_t cost) {
+                        if (!is_near(lt << 15 | cost)) return;
+                        atomicMin(lo, cost);
+                        atomicMax(hi, cost);
+                    };
+                });
+                for (int x = lane; x < 64 * a.S; x += 64) l.bins[x] = EMPTY;
+                wave_lds_fence();
+                // (in the place of what bins_of() goes by)
+                if (lane < a.S) keys()[lane] = l.floor[lane] << 15, fastest()[lane] = l.first[lane];
+                wave_lds_fence();
+                sweep<DEALT>(range, [&](const Pair& p) {
+                    return [is_near = near(p), b = bins_of(l, p.s)](uint32_t, uint32_t lt, uint32_t cost) {
+                        const uint32_t x = lt << 15 | cost;
+                        if (is_near(x)) atomicMin(&b.words[b.at(cost)], x);
+                    };
+                });
+            }
+            if (turn & 1) {
+                if (!divide_by_need(l)) continue;
+            } else {
+                divide_evenly(l);
+            }
+            fits = list_candidates(l, range, near);
+        }
+        wave_lds_fence();
+        if (lane < a.S) keys()[lane] = key, fastest()[lane] = fast;
+        wave_lds_fence();
+        return fits;
     }
 
     // Candidates that can be part of an answer at all, by Lagrangian bounds.  For any
@@ -662,128 +1190,143 @@ struct Solver {
     // most the optimum, and an assignment that uses a candidate whose cost + mu lt
     // exceeds its model's least by r costs at least r more than that bound.  With the
     // cost `ub` of some assignment within the budget, candidates with r > ub - bound are
-    // in no optimum.  mu is found by walking the lower hull of (ticks, cost) between the
-    // cheapest and the fastest assignment to where the budget lies.  Single precision;
-    // `slack` covers its error, so a candidate is kept rather than dropped.
+    // in no optimum.  mu is found by walking the lower hull to where the budget lies.  Single
+    // precision; `slack` covers its error, so a candidate is kept rather than dropped.
     // What is left is two or three candidates per model whose costs span some tens of
     // cells, where the window would have to span hundreds.
-    __device__ __forceinline__ int solve_gap()
+    //
+    // What bounds it: latency, a chain of one wavefront's sweeps (300 cycles an evaluation),
+    // walks (1200 a turn) and instruction fetches.  One instance of 8 models with 256
+    // candidates takes 43 us (steps A to C 23 of them), of 3 models with 8192 75 to 96.
+    // Before the narrowing and the trial by halves, where lists overflowed and the wide
+    // windows and step D took over, batches of 4096 took, in microseconds, then and now (in
+    // brackets by the three stages, dense / pruned): 64 models 8320 -> 407 (1240 / 647), 32
+    // models 1980 -> 137 (626 / 334), 3 models of 8192 candidates with tight objectives
+    // 5100 -> 1980 (3850 / 2280); 240 of 8 models with 2000 replicas 104 -> 41 (51 / 47).
+    __device__ __forceinline__ int list_all() const
+    {
+        if (a.c_max * a.n_batch > FEW) return TOO_MANY;
+        const Lists l = lists_of();
+        fill_bins<DEALT>(l);
+        divide_evenly(l);
+        for (int turn = 0; turn < 2; ++turn) {
+            if (turn > 0 && !divide_by_need(l)) break;
+            if (list_candidates(
+                    l, [&](const Pair& p) { return cores_up_to(p, cost_of(fastest()[p.s])); },
+                    [](const Pair&) { return [](uint32_t) { return true; }; }))
+                return ARE_LISTED;
+        }
+        return TOO_MANY;
+    }
+
+    // The survivors of the listed candidates, and what to do with them.
+    __device__ __forceinline__ int find_survivors() const
     {
         const Lists l = lists_of();
-        if (l.len < 16) return UNFINISHED;
-        // the cheapest assignment (too slow) and the fastest (within the budget)
-        uint32_t my_lt = 0, my_cost = 0, my_fast = 0;
-        if (lane < a.S) {
-            const uint32_t key = keys()[lane];
-            my_lt = key & 0x7FFFu, my_cost = key >> 15;
-            my_fast = fastest()[lane];
-        }
-        int64_t c0 = sum_models(my_cost), l0 = sum_models(my_lt);
-        int64_t c1 = sum_models(my_fast & 0x7FFFu), l1 = sum_models(my_fast >> 15);
-        if (!list_candidates(l)) return UNFINISHED;
-
-        // lanes: `width` of them per model, entries dealt in turn
-        int width = 1;
-        while (2 * width * a.S <= 64) width *= 2;
-        const int s = lane / width, sub = lane & (width - 1);
-        const bool there = s < a.S;
-        const int n = there ? (int)l.kept[s] : 0;
-        const uint32_t* const mine = l.lists + 2 * (there ? s : 0) * l.len;
-        auto lt_of = [](uint32_t w) { return w & 0xFFFFu; };
-        auto cost_of = [](uint32_t w) { return w >> 16; };
-        // the model's choice at a price, in all of its lanes, and its cost + mu lt
-        auto choose = [&](float mu, float& v) {
-            uint32_t w = 0u;
-            v = 3.0e38f;
-            for (int e = sub; e < n; e += width) {
-                const uint32_t x = mine[2 * e];
-                const float y = __builtin_fmaf(mu, (float)lt_of(x), (float)cost_of(x));
-                if (y < v) v = y, w = x;
-            }
-            for (int d = 1; d < width; d <<= 1) {
-                const float ov = __shfl_xor(v, d, 64);
-                const uint32_t ow = (uint32_t)__shfl_xor((int)w, d, 64);
-                if (ov < v || (ov == v && ow < w)) v = ov, w = ow;
-            }
-            return w;
-        };
-        auto total = [&](uint32_t x) { return (int64_t)wave_sum(there && sub == 0 ? x : 0u); };
-        float mu = 0.0f, v = 0.0f;
-        // the fastest assignment as choices: cost and lt of the caps' candidates
-        uint32_t chosen = there ? (fastest()[s] >> 15) | (fastest()[s] & 0x7FFFu) << 16 : 0u;
-        for (int turn = 0; turn < 16; ++turn) {
-            mu = (float)(c1 - c0) / (float)(l0 - l1);
-            const uint32_t w = choose(mu, v);
-            const int64_t c = total(cost_of(w)), t = total(lt_of(w));
-            // on the line between the two, or above it: the walk has ended
-            if (c * (l0 - l1) + (c1 - c0) * t >= c1 * (l0 - l1) + (c1 - c0) * l1) break;
-            if (t <= T)
-                c1 = c, l1 = t, chosen = w;
-            else
-                c0 = c, l0 = t;
-            if (c0 >= c1 || l0 <= l1) break;
-        }
-        // (the prices at which the walk stopped)
-        choose(mu, v);
-        // one change of a choice that the ticks left over allow, for a better `ub`
-        const int64_t left = T - l1;
-        uint32_t gain = 0u;
-        for (int e = sub; e < n; e += width) {
-            const uint32_t x = mine[2 * e];
-            if ((int64_t)lt_of(x) - (int64_t)lt_of(chosen) <= left && cost_of(x) < cost_of(chosen)) {
-                const uint32_t g = cost_of(chosen) - cost_of(x);
-                gain = g > gain ? g : gain;
-            }
-        }
-        for (int d = 32; d >= 1; d >>= 1) {
-            const uint32_t o = (uint32_t)__shfl_xor((int)gain, d, 64);
-            gain = o > gain ? o : gain;
-        }
-        const int ub = (int)c1 - (int)__builtin_amdgcn_readfirstlane((int)gain);
-        float bound = there && sub == 0 ? v : 0.0f;
-        for (int d = 32; d >= 1; d >>= 1) bound += __shfl_xor(bound, d, 64);
-        bound -= mu * (float)T;
-        const float slack = ((float)c1 + mu * (float)(T + l0)) * 0x1p-16f + 0x1p-10f;
-        const float gap = (float)ub - bound + slack;
-        wave_lds_fence();
-        if (lane < a.S) l.kept[lane] = 0u, l.floor[lane] = EMPTY;
-        wave_lds_fence();
-        for (int e = sub; e < n; e += width) {
-            const uint32_t x = mine[2 * e];
-            const float y = __builtin_fmaf(mu, (float)lt_of(x), (float)cost_of(x));
-            if (y - v <= gap) {
-                const uint32_t at = atomicAdd(&l.kept[s], 1u);
-                atomicMin(&l.floor[s], cost_of(x));
-                if (at < (uint32_t)KEPT) {
-                    l.bins[64 * s + (int)at] = x;
-                    l.bins[64 * s + KEPT + (int)at] = mine[2 * e + 1];
+        Hull h(*this);
+        uint32_t* const mine = l.bins + l.first[h.s];
+        const Source listed{mine, h.there ? (int)l.kept[h.s] : 0, 2};
+        h.hold(listed);
+        h.walk(listed);
+        h.choose(listed);  // (the prices at which the walk stopped)
+        const int ub = h.upper(listed);
+        const float gap = h.gap_to(ub);
+        // Those of this model's n entries that stay(entry, index), to the front of its list.
+        auto keep = [&](int n, auto stay) {
+            wave_lds_fence();
+            if (lane < a.S) l.kept[lane] = 0u;
+            wave_lds_fence();
+            // (`width` entries at a time; their places are not behind those read so far)
+            for (int e0 = 0; __ballot(e0 < n) != 0ull; e0 += h.width) {
+                const int e = e0 + h.sub;
+                const uint32_t x = e < n ? mine[2 * e] : 0u, k = e < n ? mine[2 * e + 1] : 0u;
+                const bool stays = e < n && stay(x, k);
+                wave_lds_fence();
+                if (stays) {
+                    const uint32_t at = atomicAdd(&l.kept[h.s], 1u);
+                    mine[2 * at] = x, mine[2 * at + 1] = k;
                 }
+                wave_lds_fence();
+            }
+            return h.there ? (int)l.kept[h.s] : 0;
+        };
+        const int near =
+            keep(listed.n, [&](uint32_t x, uint32_t) { return priced(h.mu, x) - h.v <= gap; });
+        // no other one beats or ties it on cost and ticks (ties: smaller index)
+        const int n = keep(near, [&](uint32_t x, uint32_t k) {
+            bool beaten = false;
+            for (int o0 = 0; o0 < near; o0 += 4) {
+                uint32_t y[4], ky[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int o = o0 + q < near ? o0 + q : o0;
+                    y[q] = mine[2 * o], ky[q] = mine[2 * o + 1];
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    beaten |= cost_of(y[q]) <= cost_of(x) && lt_of(y[q]) <= lt_of(x) &&
+                              (y[q] != x || ky[q] < k);
+            }
+            return !beaten;
+        });
+        const uint32_t my_kept = lane < a.S ? l.kept[lane] : 1u;
+        if (__ballot(my_kept == 0u) != 0ull) return UNFINISHED;
+        // the survivors of all models one after the other in the place of the bins, where that
+        // has room for them
+        const int entries = (int)sum_models(lane < a.S ? my_kept : 0u);
+        const bool packed = entries <= 32 * a.S;
+        const uint32_t before = wave_scan<false>(lane < a.S ? my_kept : 0u) - my_kept;
+        if (lane < a.S) {
+            l.floor[lane] = EMPTY;
+            if (packed) l.first[lane] = 2u * before;
+        }
+        wave_lds_fence();
+        for (int e = h.sub; e < n; e += h.width) {
+            const uint32_t x = mine[2 * e], k = mine[2 * e + 1];
+            atomicMin(&l.floor[h.s], cost_of(x));
+            if (packed) {
+                uint32_t rank = 0u;
+                for (int o = 0; o < n; ++o) rank += mine[2 * o + 1] < k ? 1u : 0u;
+                uint32_t* const to = l.bins + l.first[h.s] + 2u * rank;
+                to[0] = x, to[1] = k;
             }
         }
         wave_lds_fence();
-        const uint32_t my_kept = lane < a.S ? l.kept[lane] : 1u;
-        if (__ballot(my_kept > (uint32_t)KEPT || my_kept == 0u) != 0ull) return UNFINISHED;
-        const int floor = (int)sum_models(lane < a.S ? l.floor[lane] : 0u);
-        const int span = ub - floor;  // cells above the first that can be needed
+        const int span = ub - (int)sum_models(lane < a.S ? l.floor[lane] : 0u);
         if (span < 0) return UNFINISHED;
-        const int W = (span + 64) & ~63;
-        // the rows in LDS where they fit; few combinations are tried one by one before rows
-        // in HBM are taken, many only where those do not fit either
-        const int cells = (a.S + 1) * (W + 2);
-        if (cells / 2 <= 2 * l.len * a.S) return solve_listed<false>(l, W, floor);
-        int status = solve_by_trial(l, my_kept, 1u << 10);
-        if (status == UNFINISHED && cells <= a.S * a.row_stride)
-            status = solve_listed<true>(l, W, floor);
-        return status == UNFINISHED ? solve_by_trial(l, my_kept, TRIALS) : status;
+        const int W = (span + 64) & ~63;  // cells above the first that can be needed
+        // Rows over W cells, or every combination.  By instructions: some 60 for every 256
+        // cells and pair of entries (three times that with rows in HBM), 8 for every 64
+        // combinations.
+        const bool in_lds = (a.S + 1) * (W + 2) / 2 <= (packed ? l.room : 64 * a.S);
+        const int rows = (W + 255) / 256 * entries * (in_lds ? 240 : 720);
+        const int most = rows < TRIALS ? rows : TRIALS;
+        // (the number of combinations by its logarithm, rounded down)
+        auto log_of = [](uint32_t n) { return __builtin_amdgcn_logf((float)n) * 256.0f; };
+        const bool few = (float)sum_models(lane < a.S ? (uint32_t)log_of(my_kept) : 0u) <= log_of((uint32_t)most);
+        if (lane == 0) l.plan[0] = (uint32_t)W, l.plan[1] = few ? (uint32_t)most : 0u;
+        wave_lds_fence();
+        return ARE_LISTED;
     }
+    // Candidates per model up to which all of them are listed if they fit: two evaluations of
+    // each, against one of a sample and four or five of a few per pair otherwise (one
+    // instance of 8 models with 256: 43 us this way, 52 the other).
+    static constexpr int FEW = 512;
+    // Combinations that are tried at all, and where nothing but step D is left.
+    static constexpr int TRIALS = 1 << 18, MOST_TRIALS = 1 << 22;
 
     // The recurrence over the survivors: W cells over the sum of their least costs.
     // HBM: the rows are in this instance's part of the row region.
     template <bool HBM>
-    __device__ __forceinline__ int solve_listed(const Lists& l, int W, int floor) const
+    __device__ __forceinline__ int solve_listed(int W) const
     {
-        uint16_t* const rows = HBM ? a.frow + (size_t)i * a.S * a.row_stride
-                                   : reinterpret_cast<uint16_t*>(l.lists);
+        const Survivors l = survivors();
+        const bool there = lane < a.S;
+        const uint32_t my_floor = there ? l.floor[lane] : 0u, my_kept = there ? l.kept[lane] : 1u;
+        const uint32_t my_first = there ? l.first[lane] : 0u;
+        const int floor = (int)sum_models(my_floor);
+        uint16_t* const rows = HBM ? a.hrow + (size_t)i * a.hrow_stride
+                                   : reinterpret_cast<uint16_t*>(l.free);
         auto rows_fence = [] {  // a row's lanes read what others wrote
             if (HBM)
                 __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
@@ -794,24 +1337,47 @@ struct Solver {
         for (int x = lane; x <= a.S; x += 64) row_of(x)[-1] = (uint16_t)G_INF;
         for (int x = lane; x < W; x += 64) row_of(a.S)[x] = 0;
         rows_fence();
+        // entry e of model s, one of the lane's in advance
+        auto entry_of = [&](int s, int e) {
+            const int n = (int)lane_value(my_kept, s);
+            return (l.bins + lane_value(my_first, s))[2 * (e < n ? e : 0)];
+        };
+        uint32_t w = entry_of(a.S - 1, lane);
         for (int s = a.S - 1; s >= 0; --s) {
             const uint16_t* const next = row_of(s + 1);
             uint16_t* const row = row_of(s);
-            const int n = __builtin_amdgcn_readfirstlane((int)l.kept[s]);
-            const uint32_t base = l.floor[s];
-            const uint32_t* const ent = l.bins + 64 * s;
-            for (int x0 = 0; x0 < W; x0 += 64) {
-                uint32_t acc = G_INF;
-                for (int e = 0; e < n; e += 2) {
-                    const uint32_t w0 = ent[e], w1 = ent[e + 1 < n ? e + 1 : e];
-                    const int y0 = x0 + lane - (int)((w0 >> 16) - base);
-                    const int y1 = x0 + lane - (int)((w1 >> 16) - base);
-                    const uint32_t v0 = next[y0 < -1 ? -1 : y0] + (w0 & 0xFFFFu);
-                    const uint32_t v1 = next[y1 < -1 ? -1 : y1] + (w1 & 0xFFFFu);
-                    acc = least(acc, least(v0, v1));
+            const int n = (int)lane_value(my_kept, s);
+            const uint32_t base = lane_value(my_floor, s);
+            // (four stretches of 64 and four entries at a time: reads that do not wait for
+            // one another)
+            for (int x0 = 0; x0 < W; x0 += 256) {
+                uint32_t acc[4] = {G_INF, G_INF, G_INF, G_INF};
+                for (int e = 0; e < n; e += 4) {
+                    if (n > 64 && (e & 63) == 0) w = entry_of(s, e + lane);
+                    uint32_t lt[4];
+                    int d[4];
+#pragma unroll
+                    for (int z = 0; z < 4; ++z) {
+                        const uint32_t wz = lane_value(w, (e + z < n ? e + z : e) & 63);
+                        lt[z] = lt_of(wz), d[z] = (int)(cost_of(wz) - base);
+                    }
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        if (x0 + 64 * q >= W) break;
+                        uint32_t v[4];
+#pragma unroll
+                        for (int z = 0; z < 4; ++z) {
+                            const int y = x0 + 64 * q + lane - d[z];
+                            v[z] = next[y < -1 ? -1 : y] + lt[z];
+                        }
+                        acc[q] = least(least(acc[q], v[0]), least(v[1], least(v[2], v[3])));
+                    }
                 }
-                row[x0 + lane] = (uint16_t)acc;
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (x0 + 64 * q < W) row[x0 + 64 * q + lane] = (uint16_t)acc[q];
             }
+            if (s > 0) w = entry_of(s - 1, lane);
             rows_fence();
         }
         int x = -1;
@@ -829,95 +1395,146 @@ struct Solver {
         const uint32_t total = (uint32_t)(floor + x);
         uint32_t t = ticks, my_k = 0, my_cost = 0;
         for (int s = 0; s < a.S; ++s) {
-            const int n = (int)l.kept[s];
-            const uint32_t w = l.bins[64 * s + (lane & (KEPT - 1))];
-            const uint32_t k = l.bins[64 * s + KEPT + (lane & (KEPT - 1))];
-            const int d = (int)((w >> 16) - l.floor[s]);
-            const bool in = lane < n && d <= x;
-            const uint32_t rest = row_of(s + 1)[in ? x - d : 0];
-            unsigned long long m = __ballot(in && (w & 0xFFFFu) + rest == t);
+            const int n = (int)lane_value(my_kept, s), base = (int)lane_value(my_floor, s);
+            const uint32_t* const ent = l.bins + lane_value(my_first, s);
             uint32_t key = EMPTY, key_w = 0u;
-            int key_d = 0;
-            while (m) {
-                const int q = __builtin_ctzll(m);
-                m &= m - 1ull;
-                const uint32_t kq = lane_value(k, q);
-                if (kq < key) key = kq, key_w = lane_value(w, q), key_d = (int)lane_value((uint32_t)d, q);
+            for (int e0 = 0; e0 < n; e0 += 64) {
+                const int e = e0 + lane;
+                const uint32_t w = e < n ? ent[2 * e] : 0u, k = e < n ? ent[2 * e + 1] : 0u;
+                const int d = (int)cost_of(w) - base;
+                const bool in = e < n && d <= x;
+                const uint32_t rest = row_of(s + 1)[in ? x - d : 0];
+                unsigned long long m = __ballot(in && lt_of(w) + rest == t);
+                while (m) {
+                    const int q = __builtin_ctzll(m);
+                    m &= m - 1ull;
+                    const uint32_t kq = lane_value(k, q);
+                    if (kq < key) key = kq, key_w = lane_value(w, q);
+                }
             }
             if (key == EMPTY) {  // never expected
                 put_none(THEMIS_INTERNAL);
                 return THEMIS_INTERNAL;
             }
-            if (lane == s) my_k = key, my_cost = key_w >> 16;
-            t -= key_w & 0xFFFFu;
-            x -= key_d;
+            if (lane == s) my_k = key, my_cost = cost_of(key_w);
+            t -= lt_of(key_w);
+            x -= (int)cost_of(key_w) - base;
         }
         put(THEMIS_SOLVED, (int32_t)total, (int32_t)ticks, HBM ? BY_G_HBM : BY_G_LDS);
         put_choice(my_k, my_cost);
         return THEMIS_SOLVED;
     }
 
-    // Every combination of the survivors, where there are few of them and their costs span
-    // more cells than the rows have room for.  The survivors of a model are put in index
-    // order first, so that of equal combinations the first one met is the smallest.
-    static constexpr uint32_t TRIALS = 1u << 14;
-    __device__ __forceinline__ int solve_by_trial(const Lists& l, uint32_t my_kept,
-                                                  uint32_t most) const
+    // Every combination of the survivors, if there are no more than `most`: every pair of a
+    // combination of the first models, a lane each, and one of the others, in a list.  Both
+    // are ticks << 15 | cost, beyond any budget where the ticks are.  (Costs add up to 32767
+    // at most, so they do not carry into the ticks.)
+    __device__ __forceinline__ int solve_by_trial(uint32_t most) const
     {
+        const Survivors l = survivors();
+        const uint32_t my_kept = lane < a.S ? l.kept[lane] : 1u;
+        constexpr uint32_t LATE = 0xFFFFu << 15;
         uint32_t count = 1u;
         for (int s = 0; s < a.S; ++s) {
             count *= lane_value(my_kept, s);
             if (count > most) return UNFINISHED;
         }
-        for (int s = 0; s < a.S; ++s) {
-            const int n = (int)l.kept[s];
-            const int e = lane & (KEPT - 1);
-            const uint32_t w = l.bins[64 * s + e], k = l.bins[64 * s + KEPT + e];
-            int rank = 0;
-            for (int o = 0; o < n; ++o) rank += l.bins[64 * s + KEPT + o] < k ? 1 : 0;
-            wave_lds_fence();
-            if (lane < n) {
-                l.bins[64 * s + rank] = w;
-                l.bins[64 * s + KEPT + rank] = k;
+        // the first models: as many as it takes to have work for all lanes and at least half of
+        // the combinations' digits
+        int half = 0;
+        uint32_t n0 = 1u;
+        while (half < a.S && (n0 < 64u || n0 * n0 < count)) n0 *= lane_value(my_kept, half++);
+        const uint32_t n1 = count / n0;
+        if (n1 + 3u > (uint32_t)l.free_words || n0 > 0xFFFFu) return UNFINISHED;
+        uint32_t* const list = l.free;
+        // Model s's digit of combination x as that survivor's words; x is left to the models
+        // before it.  x / n: half of 1 / n from where the truncation would go wrong.
+        const float my_recip = __builtin_amdgcn_rcpf((float)my_kept);
+        const uint32_t my_first = lane < a.S ? l.first[lane] : 0u;
+        auto digit = [&](uint32_t& x, int s) {
+            const uint32_t n = lane_value(my_kept, s);
+            const float r = __uint_as_float(lane_value(__float_as_uint(my_recip), s));
+            const uint32_t q = (uint32_t)(((float)x + 0.5f) * r);
+            const uint32_t* const e = l.bins + lane_value(my_first, s) + 2u * (x - q * n);
+            x = q;
+            return e;
+        };
+        // the models of either part, and its part of a pair x << 16 | y
+        auto from = [&](int part) { return part ? half : 0; };
+        auto to = [&](int part) { return part ? a.S : half; };
+        auto of_pair = [](uint32_t pair, int part) { return part ? pair & 0xFFFFu : pair >> 16; };
+        // an entry: combination x of one part's models
+        auto entry_of = [&](int part, uint32_t x) {
+            uint32_t c = 0, t = 0;
+            // (four models at a time: reads that do not wait for one another)
+            for (int s = to(part) - 1; s >= from(part); s -= 4) {
+                uint32_t e[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) e[q] = s - q >= from(part) ? *digit(x, s - q) : 0u;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) c += cost_of(e[q]), t += lt_of(e[q]);
             }
-            wave_lds_fence();
-        }
-        unsigned long long best = ~0ull;
-        for (uint32_t x0 = 0; x0 < count; x0 += 64u) {
+            return t <= (uint32_t)T ? t << 15 | c : LATE;
+        };
+        wave_lds_fence();
+        for (uint32_t x = (uint32_t)lane; x < n1 + 3u; x += 64u)  // read in fours
+            list[x] = x < n1 ? entry_of(1, x) : LATE;
+        wave_lds_fence();
+        // whether one pair comes before another, by the indices of model 0, 1, ..
+        auto precedes = [&](uint32_t p, uint32_t o) {
+            if (l.packed) return p < o;
+            bool is = false;  // the more significant a digit, the later it has its say
+            for (int part = 1; part >= 0; --part) {
+                uint32_t x = of_pair(p, part), y = of_pair(o, part);
+                for (int s = to(part) - 1; s >= from(part); --s) {
+                    const uint32_t kx = digit(x, s)[1], ky = digit(y, s)[1];
+                    is = kx == ky ? is : kx < ky;
+                }
+            }
+            return is;
+        };
+        const uint32_t late = ((uint32_t)T + 1u) << 15;
+        uint32_t best = EMPTY, at = 0u;  // cost << 17 | ticks; which pair
+        for (uint32_t x0 = 0; x0 < n0; x0 += 64u) {
             const uint32_t x = x0 + (uint32_t)lane;
-            if (x < count) {
-                uint32_t rest = x, c = 0, t = 0;
-                for (int s = a.S - 1; s >= 0; --s) {  // model 0 is the most significant digit
-                    const uint32_t n = l.kept[s];
-                    const uint32_t q = rest / n;
-                    const uint32_t w = l.bins[64 * s + (int)(rest - q * n)];
-                    rest = q;
-                    c += w >> 16;
-                    t += w & 0xFFFFu;
-                }
-                if (t <= (uint32_t)T) {
-                    const unsigned long long key =
-                        ((unsigned long long)c << 32) | ((unsigned long long)t << 14) | x;
-                    best = key < best ? key : best;
+            const uint32_t mine = x < n0 ? entry_of(0, x) : LATE;
+            for (uint32_t y = 0; y < n1; y += 4u) {
+                uint32_t v[4];
+#pragma unroll
+                for (uint32_t q = 0; q < 4u; ++q) v[q] = list[y + q];
+#pragma unroll
+                for (uint32_t q = 0; q < 4u; ++q) {
+                    const uint32_t sum = mine + v[q];
+                    const uint32_t key = sum < late ? sum << 17 | sum >> 15 : EMPTY;
+                    if (key < best || (key == best && key != EMPTY && !l.packed)) {
+                        const uint32_t now = x << 16 | (y + q);  // (ascending)
+                        if (key < best || precedes(now, at)) at = now;
+                        best = key;
+                    }
                 }
             }
         }
-        for (int d = 32; d >= 1; d >>= 1) {
-            const unsigned long long o = __shfl_xor(best, d, 64);
-            best = o < best ? o : best;
+        const uint32_t key = lane_value(wave_scan<true>(best), 63);
+        if (key == EMPTY) return UNFINISHED;  // never expected
+        unsigned long long m = __ballot(best == key);
+        uint32_t found = lane_value(at, __builtin_ctzll(m));
+        for (m &= m - 1ull; m; m &= m - 1ull) {
+            const uint32_t other = lane_value(at, __builtin_ctzll(m));
+            if (__builtin_amdgcn_readfirstlane((int)precedes(other, found))) found = other;
         }
-        if (best == ~0ull) return UNFINISHED;  // never expected
-        uint32_t rest = (uint32_t)best & (TRIALS - 1u), my_k = 0, my_cost = 0;
-        for (int s = a.S - 1; s >= 0; --s) {
-            const uint32_t n = l.kept[s];
-            const uint32_t q = rest / n;
-            if (lane == s) {
-                my_cost = l.bins[64 * s + (int)(rest - q * n)] >> 16;
-                my_k = l.bins[64 * s + KEPT + (int)(rest - q * n)];
-            }
-            rest = q;
+        // lane s: model s's digit of its part
+        uint32_t below = 1u;  // combinations of the models after this one in its list
+        for (int s = 1; s < a.S; ++s) {
+            const uint32_t n = lane_value(my_kept, s);
+            if (lane < s && s < to(lane >= half)) below *= n;
         }
-        put(THEMIS_SOLVED, (int32_t)(best >> 32), (int32_t)((best >> 14) & 0x3FFFFull), BY_G_TRIAL);
+        uint32_t my_k = 0, my_cost = 0;
+        if (lane < a.S) {
+            const uint32_t x = of_pair(found, lane >= half) / below;
+            const uint32_t* const e = l.bins + my_first + 2u * (x % my_kept);
+            my_cost = cost_of(e[0]), my_k = e[1];
+        }
+        put(THEMIS_SOLVED, (int32_t)(key >> 17), (int32_t)(key & 0x1FFFFu), BY_G_TRIAL);
         put_choice(my_k, my_cost);
         return THEMIS_SOLVED;
     }
@@ -996,7 +1613,7 @@ struct Solver {
     __device__ __forceinline__ int solve_window(int W) const
     {
         uint32_t* const tab = lds + L.tab;
-        uint16_t* const rows = HBM ? a.frow + (size_t)i * a.S * a.row_stride
+        uint16_t* const rows = HBM ? a.hrow + (size_t)i * a.hrow_stride
                                    : reinterpret_cast<uint16_t*>(lds + L.rows);
         // a row's lanes read what others wrote
         auto rows_fence = [] {
@@ -1268,15 +1885,49 @@ struct Solver {
         return status;
     }
 
-    // Steps C, G and D.
-    __device__ __forceinline__ int further(int inst, int budget, int32_t rate, int32_t objective)
+    template <int PART>
+    __device__ __forceinline__ int out_of_line(int x = 0) const
     {
-        i = inst, T = budget, lam = rate, slo = objective;
-        lane_b = lane < a.n_batch ? (int32_t)a.bc[lane].b : 0;
-        fill_all<false, 64>(Pair());
-        int status = solve_sixtyfour();
+        return __builtin_amdgcn_readfirstlane(
+            solve_part<QUEUE, DERIVE, ROLE, PART>((uint64_t)(uintptr_t)&a, i, T, lam, slo, x));
+    }
+
+    // Step C, and if it does not suffice the lists of step G.
+    __device__ __forceinline__ int solve_c() const
+    {
+        fill_sixtyfour();
+        const int status = solve_sixtyfour();
         wave_lds_fence();
-        if (status == UNFINISHED) status = solve_gap();
+        return status == UNFINISHED ? list_all() : status;
+    }
+
+    // Steps C, G, W and D.
+    __device__ __forceinline__ int solve_further() const
+    {
+        int status = solve_c();
+        if (status == TOO_MANY) {
+            out_of_line<PART_PRICE>();
+            status = out_of_line<PART_NARROW>();
+        }
+        if (status == ARE_LISTED) status = out_of_line<PART_GAP>();
+        if (status == ARE_LISTED) {
+            const Survivors l = survivors();
+            const int W = __builtin_amdgcn_readfirstlane((int)l.plan[0]);
+            const int most = __builtin_amdgcn_readfirstlane((int)l.plan[1]);
+            const int cells = (a.S + 1) * (W + 2);
+            const bool in_lds = cells / 2 <= l.free_words;
+            status = most ? out_of_line<PART_TRIAL>(most) : UNFINISHED;
+            if (status == UNFINISHED && in_lds) status = out_of_line<PART_ROWS>(W);
+            else if (status == UNFINISHED && cells <= a.hrow_stride) status = out_of_line<PART_ROWS_HBM>(W);
+            if (status == UNFINISHED) status = out_of_line<PART_TRIAL>(MOST_TRIALS);
+        }
+        return status == UNFINISHED ? out_of_line<PART_WD>() : status;
+    }
+
+    // Steps W and D.
+    __device__ __forceinline__ int solve_wide() const
+    {
+        int status = UNFINISHED;
         int W = 64;
         while (status == UNFINISHED && W < a.window) {
             wave_lds_fence();
@@ -1290,6 +1941,22 @@ struct Solver {
         }
         wave_lds_fence();
         return status == UNFINISHED ? solve_by_budget(a.window) : status;
+    }
+
+    // A part of the solve of the instance, in a function of its own.
+    template <int PART>
+    __device__ __forceinline__ int part(int inst, int budget, int32_t rate, int32_t objective, int x)
+    {
+        i = inst, T = budget, lam = rate, slo = objective;
+        lane_b = lane < a.n_batch ? (int32_t)a.bc[lane].b : 0;
+        if constexpr (PART == PART_FURTHER) return solve_further();
+        if constexpr (PART == PART_PRICE) return find_price();
+        if constexpr (PART == PART_NARROW) return list_narrowed() ? ARE_LISTED : UNFINISHED;
+        if constexpr (PART == PART_GAP) return find_survivors();
+        if constexpr (PART == PART_TRIAL) return solve_by_trial((uint32_t)x);
+        if constexpr (PART == PART_ROWS) return solve_listed<false>(x);
+        if constexpr (PART == PART_ROWS_HBM) return solve_listed<true>(x);
+        if constexpr (PART == PART_WD) return solve_wide();
     }
 
     // The inputs of instance `inst` at `rate`; valid: the input check's result.
@@ -1330,23 +1997,23 @@ struct Solver {
         else
             status = solve_valid<false>(first);
         status = __builtin_amdgcn_readfirstlane(status);
-        if (status == UNFINISHED)
-            status = solve_further<QUEUE, DERIVE, ROLE>((uint64_t)(uintptr_t)&a, i, T, lam, slo);
+        if (status == UNFINISHED) status = out_of_line<PART_FURTHER>();
         return status;
     }
 };
 
-// Out of line, so that its registers do not weigh on the allocation of the steps
-// that nearly every instance ends with.
-template <int QUEUE, bool DERIVE, int ROLE>
-__device__ __attribute__((noinline)) int solve_further(uint64_t args, int i, int T, int32_t lam,
-                                                       int32_t slo)
+// Out of line, so that their registers do not weigh on the allocation of the steps that
+// nearly every instance ends with, nor on one another's.
+template <int QUEUE, bool DERIVE, int ROLE, int PART>
+__device__ __attribute__((noinline)) int solve_part(uint64_t args, int i, int T, int32_t lam,
+                                                    int32_t slo, int x)
 {
     auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
     const uint64_t lo = (uint32_t)uniform((int)(uint32_t)args);
     const uint64_t hi = (uint32_t)uniform((int)(uint32_t)(args >> 32));
     Solver<QUEUE, DERIVE, false, ROLE> sv((ArgsPtr)(uintptr_t)(hi << 32 | lo));
-    return uniform(sv.further(uniform(i), uniform(T), uniform(lam), uniform(slo)));
+    return uniform(
+        sv.template part<PART>(uniform(i), uniform(T), uniform(lam), uniform(slo), uniform(x)));
 }
 
 // One whole solve of instance `inst` at `rate`.
@@ -1391,9 +2058,9 @@ typedef void (*CostKernel)(CostArgs);
 constexpr size_t LDS_PER_CU = 160 * 1024;
 constexpr int MAX_WINDOW = 8192;
 // Wavefronts whose LDS a compute unit has room for.  Registers allow 32, but some twenty
-// are in flight on average, and the room of the others lets step G list more candidates:
-// at 16384 x 8 with a twelfth of the objectives 32 / 28 / 24 / 20 take 579 / 122 / 121 /
-// 129 us, at 86400 x 6 51 / 51 / 55 / 60.
+// are in flight on average, and the room of the others lets step G list more candidates
+// (measured while it could only list all of them: at 16384 x 8 with a twelfth of the
+// objectives 32 / 28 / 24 / 20 took 579 / 122 / 121 / 129 us, at 86400 x 6 51 / 51 / 55 / 60).
 constexpr int RESIDENT_PER_CU = 28;
 
 // What does not depend on the entry point.
@@ -1416,6 +2083,15 @@ inline CostArgs cost_args(const themis_problem_t& p, const Layout& L, const int3
     a.ctrl = (int32_t*)(ws + L.ctrl_off);
     a.frow = (uint16_t*)(ws + L.frow_off);
     a.kept = make_keep_layout(p);
+    // Rows by cost go where an instance has more of: of the row region, or of what the
+    // records (at most sixteen words per model) leave of the table region.
+    a.hrow = a.frow;
+    a.hrow_stride = L.S * L.row_stride;
+    const int left = L.S * (L.Kp - 8) * (int)(sizeof(StepEntry) / sizeof(uint16_t));
+    if (left > a.hrow_stride) {
+        a.hrow = (uint16_t*)(ws + L.step_off + (size_t)L.N * L.S * 8 * sizeof(StepEntry));
+        a.hrow_stride = left;
+    }
     a.keep = opts.inspectable ? (int32_t*)(ws + L.step_off) : nullptr;
     a.n_batch = p.n_batch;
     for (int j = 0; j < p.n_batch; ++j)
@@ -1431,6 +2107,9 @@ inline CostArgs cost_args(const themis_problem_t& p, const Layout& L, const int3
     a.list = opts.list;
     a.row_stride = L.row_stride;
     a.magic = index_magic((uint32_t)p.n_batch);
+    const uint32_t pairs = (uint32_t)(L.S * p.n_batch);
+    a.parts = pairs < 64u ? 64u / pairs : 1u;
+    a.pair_magic = index_magic(pairs < 64u ? pairs : 64u);
     a.rtick = (1.0 / (double)p.tick_us) * (1.0 - 0x1p-45);
     return a;
 }
@@ -1453,6 +2132,7 @@ inline CostArgs past(CostArgs a, size_t n)
         skip(*out, n);
     for (int32_t** out : {&a.cfg, &a.cfg2}) skip(*out, 3 * rows);
     skip(a.frow, rows * a.row_stride);
+    skip(a.hrow, n * a.hrow_stride);
     skip(a.keep, n * a.kept.words);
     return a;
 }
@@ -1483,10 +2163,9 @@ hipError_t launch_per_instance(const themis_problem_t& p, const Layout& L, CostA
     while (a.window + 64 <= MAX_WINDOW && a.window < spread &&
            lds_for(a.window + 64) <= LDS_PER_CU / per_cu)
         a.window += 64;
-    // rows in HBM: S + 1 of them in the S that an instance has of the row region, and the
-    // table of a model still in LDS
+    // rows in HBM: S + 1 of them, and the table of a model still in LDS
     const CostLds lds = cost_lds(L.S, a.window);
-    const int fit = (int)((long long)L.S * L.row_stride / (L.S + 1)) - 2;
+    const int fit = a.hrow_stride / (L.S + 1) - 2;
     const int room = lds.words - lds.tab;
     a.window_hbm = (fit < room ? fit : room) & ~63;
     // (at most 40 KB of LDS, which a kernel may have without asking)

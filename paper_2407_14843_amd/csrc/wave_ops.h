@@ -63,6 +63,34 @@ __device__ __forceinline__ uint32_t lane_value(uint32_t x, int lane)
     return (uint32_t)__builtin_amdgcn_readlane((int)x, lane);
 }
 
+// A butterfly over groups of `width` lanes (a power of two): calls f(of) for partners at
+// distance 1, 2, 4, ..; of(x) is the partner's x.  What f makes of a lane's values and its
+// partner's has to be the same for both.  Within 16 lanes by data-parallel primitives:
+// after the steps before it, a mirrored half row is as good as a distance of 4, a
+// mirrored row as one of 8.
+template <int CTRL>
+__device__ __forceinline__ uint32_t mirrored(uint32_t x)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, false);
+}
+template <typename F>
+__device__ __forceinline__ void with_partners(int width, F f)
+{
+    if (width > 1) f([](uint32_t x) { return mirrored<0xB1 /* quad_perm:[1,0,3,2] */>(x); });
+    if (width > 2) f([](uint32_t x) { return mirrored<0x4E /* quad_perm:[2,3,0,1] */>(x); });
+    if (width > 4) f([](uint32_t x) { return mirrored<0x141 /* row_half_mirror */>(x); });
+    if (width > 8) f([](uint32_t x) { return mirrored<0x140 /* row_mirror */>(x); });
+    // (swapped with itself, a value comes back as the lane's and its partner's)
+    if (width > 16) f([](uint32_t x) {
+        const auto both = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        return both[0] ^ both[1] ^ x;
+    });
+    if (width > 32) f([](uint32_t x) {
+        const auto both = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        return both[0] ^ both[1] ^ x;
+    });
+}
+
 // Sum over all lanes, the same in every lane (and known to be).
 __device__ __forceinline__ uint32_t wave_sum(uint32_t x) { return lane_value(wave_scan<false>(x), 63); }
 
