@@ -41,22 +41,32 @@ VALU_PEAK_GOPS = N_CU * 64 * CLOCK_GHZ                          # 39322 G lane-o
 # the counters were taken on, fingerprint of the kernel sources at that time).
 # `roofline.traffic` is null unless both still match this run.
 K2_HBM_TRAFFIC = {
-    "w1-joint-4096x5": (116087588, 5247396664, "a8ac712c3ea0c256"),
-    "w3-joint-65536x8": (11098611448, 1422380424686, "a8ac712c3ea0c256"),
+    "w1-joint-4096x5": (116367746, 5247396664, "24f8a557aa636b2c"),
+    "w3-joint-65536x8": (11106687523, 1422380424686, "24f8a557aa636b2c"),
 }
 # the same for stage 1 (input check + candidate kernel): workload -> (bytes, fingerprint)
 K1_HBM_TRAFFIC = {
-    "w1-joint-4096x5": (20110660, "a8ac712c3ea0c256"),
-    "w3-joint-65536x8": (1056616749, "a8ac712c3ea0c256"),
+    "w1-joint-4096x5": (20099780, "24f8a557aa636b2c"),
+    "w3-joint-65536x8": (1064619748, "24f8a557aa636b2c"),
 }
-KERNEL_SOURCES = ("k1_candidates.hip", "candidate_eval.h", "k2_minplus.hip", "instance_queue.h",
-                  "themis_internal.h")
+KERNEL_SOURCES = ("k1_candidates.hip", "candidate_eval.h", "wave_ops.h", "k2_minplus.hip",
+                  "instance_queue.h", "themis_internal.h")
 
 
-def kernel_fingerprint():
-    """sha256 (first 16 hex digits) over the sources of stages 1 and 2."""
+# vector instructions of the timed whole solve per instance (the pipe counters in
+# profiles/*_kernel_trace.txt): workload -> (instructions, fingerprint of its sources)
+SOLVE_VALU = {
+    "w1-joint-4096x5": (450.0, "0587b805d377e532"),
+    "w3-joint-65536x8": (576.0, "0587b805d377e532"),
+}
+SOLVE_SOURCES = ("cost_solve.hip", "cost_solver.h", "candidate_eval.h", "wave_ops.h",
+                 "themis_internal.h")
+
+
+def kernel_fingerprint(sources=KERNEL_SOURCES):
+    """sha256 (first 16 hex digits) over sources, by default those of stages 1 and 2."""
     h = hashlib.sha256()
-    for name in KERNEL_SOURCES:
+    for name in sources:
         with open(os.path.join(ROOT, "paper_2407_14843_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]
@@ -67,6 +77,15 @@ def hbm_traffic(workload, bytes_per_launch):
     if rec is None or rec[1] != bytes_per_launch or rec[2] != kernel_fingerprint():
         return None
     return rec[0]
+
+
+def solve_roofline(workload, solves_per_s):
+    rec = SOLVE_VALU.get(workload)
+    if rec is None or rec[1] != kernel_fingerprint(SOLVE_SOURCES):
+        return None
+    gops = rec[0] * 64 * solves_per_s / 1e9
+    return {"kernel": "kc_solve", "bound": "valu", "achieved": gops, "peak": VALU_PEAK_GOPS,
+            "unit": "G lane-ops/s", "frac": gops / VALU_PEAK_GOPS}
 
 
 def _events(n):
@@ -321,7 +340,7 @@ def next_rows(themis, wl, steps, warmup):
         out["vertical_fallback" + ("_pruned" if prune else "")] = {
             "workload": w2.name + ", rates x U{1..5}", "ms_per_call": ms,
             "instances_per_s": w2.n_inst / (ms * 1e-3),
-            "passes_of_the_three_stages": 3,
+            "launches": 1,  # an instance's solves, up to three, and the search in one wavefront
             "absorbed_outright": float((lv == w2.lam).mean()),
             "split_between_old_and_new_instances": float(((lv > 0) & (lv < w2.lam)).mean()),
             "remainder_served": float((r["status_h"][(lv > 0) & (lv < w2.lam)] == 0).mean())}
@@ -547,6 +566,9 @@ def main():
         "relaxations_per_s": m["relaxations_per_s"],
         "feasible_fraction": m["feasible_fraction"],
         "kernel_ms": m["kernel_ms"],
+        # the timed call itself: vector issue, 64 lane operations per instruction
+        "roofline_solve": solve_roofline(m["workload"], m["solves_per_s"]),
+        # the stage calls' kernels
         "roofline": {
             "kernel": ("k2_minplus_pruned" if a.prune else "k2_minplus_wide") +
                       " (the stage calls' recurrence, all class launches of a step)",
