@@ -259,10 +259,11 @@ size_t themis_fallback_workspace_bytes(const themis_problem_t *p);
  *
  * The search itself does not run the dynamic program: the replicas can absorb
  * a rate exactly when the fastest feasible candidate of every model (with the
- * replicas given, the one at the core cap) fits the budget together, which one
- * thread per instance tests with the candidate stage's arithmetic.  The three
- * stages run three times: at lambda for all instances, then at lambda_v and
- * for the remainder over the instances the first pass left open.
+ * replicas given, the one at the core cap) fits the budget together, which is
+ * tested with the candidate stage's arithmetic.  Pipelines of up to 64 models
+ * take one launch, with an instance's solves (at lambda, and where that fails at
+ * lambda_v and for the remainder) and its search in one wavefront; longer ones
+ * go through the three stages three times.
  *
  *   d_r_fixed   int32 [N][S]  running replicas, 1..r_max
  * Outputs, all int32 on the device:
@@ -327,7 +328,7 @@ size_t themis_memo_workspace_bytes(const themis_problem_t *p);
  * inputs recur, as in a sweep over an arrival-rate trace (Section 6 drives the
  * system with the per-second rates of one): instances are grouped by their
  * input words (lambda, slo_us, the replica counts if given, the coefficients
- * unless shared), one instance per group goes through the three stages, and
+ * unless shared), one instance per group is solved, and
  * the others receive its results.  Outputs are those of themis_solve_joint /
  * themis_solve_vertical on the same arguments, word for word, invalid
  * instances included; only the work differs.  The measured hot path does not

@@ -3,7 +3,7 @@
 // A sweep over an arrival-rate trace (Section 6 drives the system with the
 // per-second rates of one) hands the solver the same (rate, objective, replicas,
 // profile) tuple again and again.  Equal inputs have equal answers, so only one
-// instance per distinct tuple needs the three stages:
+// instance per distinct tuple is solved:
 //   k6_fill     empties the hash table;
 //   k6_dedupe   one thread per instance: hash the instance's input words, find the
 //               first of its workgroup with equal words in a table in LDS, and insert
@@ -21,7 +21,8 @@
 // per slot: of 86400 instances with 261 distinct tuples every one did one (36 us; now
 // a tenth of them do, 8.6 us).  The scatter took a thread per instance, with rows of
 // 72 bytes in strides (12 us, now 5.4), and the solve a wavefront per instance to find
-// that it was not to be solved (25 us, now 7).  The whole call: 80 -> 21 us.
+// that it was not to be solved (25 us, now 7).  The whole call: 80 -> 21 us by the traces of
+// its kernels, 24 from call to call.
 //
 // Pipelines of more than 64 models go through the three stages, which take no list:
 // there the pass gets an arrival rate of zero for the instances it is not to solve,
