@@ -1,0 +1,730 @@
+// The start of one wavefront's solve of one instance: inputs, steps A, F and B of
+// cost_solve.hip, and the table of step C; what they do not settle goes on in the functions
+// of cost_solver.h.
+//
+// What bounds it: for large batches vector issue (86400 x 6: the vector ALUs are busy 93 %
+// of the time), for small ones the chain of dependent instructions of the slowest wavefront, at
+// eight cycles each where four would issue and 40 to 60 for a branch, an LDS read or a value
+// that goes through a scalar register.  So: minima per model in registers, bounds in
+// single precision ahead of evaluations, no loop over the models in step B, one call at the
+// very end.  Against evaluating every core count that the real-valued bound allows, with
+// LDS atomics per model and sixteen cells one model after the other, in microseconds:
+// 512 x 5 9.5 -> 7.7, 4096 x 5 13.3 -> 11.3, 3001 x 7 17.3 -> 12.9, stability 4099 x 5
+// 23.3 -> 19.2, 16384 x 8 with replicas given 26.2 -> 25.0, 86400 x 6 51.7 -> 39.7,
+// 65536 x 8 98.2 -> 77.8, fallback 16384 x 8 65 -> 30.4.
+#pragma once
+
+#include "cost_solver.h"
+
+namespace themis {
+namespace {
+
+// A model's (model, batch size) pairs are neighbouring lanes, `width` of them, a power of
+// two, so what is sought per model is found between neighbours in registers, by
+// data-parallel primitives: a minimum over eight lanes is three instructions, where LDS
+// atomics took an initial value, a wait for each atomic and a read (some 200 cycles).
+// WIDTH: that width, where all models fit the wavefront that way (every lane keeps its pair
+// from step A on); PACKED: where they fit it only without gaps between the models, and
+// minima go through LDS; 0: the models in rounds of a.per_round, in 1 << width_log lanes each
+// or, where that takes fewer rounds (width_log < 0), without gaps, and what is found
+// about them in LDS.
+constexpr int PACKED = WIDTH_PACKED;
+template <int QUEUE, bool DERIVE, int ROLE>
+__device__ __attribute__((noinline)) int solve_rest(uint64_t args, int i, int T, int32_t lam,
+                                                    int32_t slo, bool none);
+
+template <int QUEUE, bool DERIVE, int WIDTH, int ROLE = PLAIN>
+struct Front : Solver<QUEUE, DERIVE, ROLE> {
+    using Base = Solver<QUEUE, DERIVE, ROLE>;
+    using typename Base::Pair;
+    using Base::a, Base::args, Base::i, Base::L, Base::lam, Base::lane, Base::lds, Base::slo, Base::T;
+    static constexpr bool ONE = WIDTH != 0;
+
+    __device__ __forceinline__ explicit Front(ArgsPtr p) : Base(p) {}
+
+    __device__ __forceinline__ int width_log() const
+    {
+        return WIDTH == 16 ? 4 : WIDTH == 8 ? 3 : WIDTH == 4 ? 2 : a.width_log;
+    }
+    // this lane's pair of the round that starts with model s0
+    __device__ __forceinline__ Pair pair_of_round(int s0) const
+    {
+        uint32_t s, j;
+        if (packed()) {
+            s = index_quotient((uint32_t)lane, a.magic);
+            j = (uint32_t)lane - s * (uint32_t)a.n_batch;
+        } else {
+            s = (uint32_t)lane >> width_log();
+            j = (uint32_t)lane & ((1u << width_log()) - 1u);
+        }
+        const bool mine = ONE || s < (uint32_t)a.per_round;
+        s = mine ? s + (uint32_t)s0 : (uint32_t)a.S;
+        return this->pair_of(s, j, (int)(s < (uint32_t)a.S) & (int)(j < (uint32_t)a.n_batch));
+    }
+    // Calls f(pair) for this lane's pair of every round; lanes without one get a pair with
+    // `there` unset.  `mine`: the pair, where there is one round only.
+    template <typename F>
+    __device__ __forceinline__ void for_pairs(const Pair& mine, F f) const
+    {
+        if constexpr (ONE) {
+            f(mine);
+        } else {
+            for (int s0 = 0; s0 < a.S; s0 += a.per_round) f(pair_of_round(s0));
+        }
+    }
+    __device__ __forceinline__ bool packed() const
+    {
+        return WIDTH == PACKED || (WIDTH == 0 && a.width_log < 0);
+    }
+    // whether this lane is the first of its model's
+    static __device__ __forceinline__ bool leads(const Pair& p) { return (int)p.in & (int)p.first; }
+
+    static __device__ __forceinline__ bool any(bool x) { return __builtin_amdgcn_ballot_w64(x) != 0ull; }
+
+    // The least of a model's lanes, in all of them.
+    template <int CTRL>
+    static __device__ __forceinline__ uint32_t least_step(uint32_t x)
+    {
+        return least(x, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)x, CTRL, 0xF, 0xF, false));
+    }
+    __device__ __forceinline__ uint32_t model_least(const Pair& p, uint32_t x) const
+    {
+        if (packed()) {
+            // (a wavefront's LDS operations complete in order)
+            uint32_t* const slot = this->fastest() + p.s;
+            if (leads(p)) *slot = EMPTY;
+            wave_lds_fence();
+            if (p.there) atomicMin(slot, x);
+            wave_lds_fence();
+            const uint32_t least_x = *slot;
+            wave_lds_fence();
+            return p.there ? least_x : EMPTY;
+        }
+        const int w = width_log();
+        if (w > 0) x = least_step<0xB1 /* quad_perm:[1,0,3,2] */>(x);
+        if (w > 1) x = least_step<0x4E /* quad_perm:[2,3,0,1] */>(x);
+        if (w > 2) x = least_step<0x141 /* row_half_mirror */>(x);
+        if (w > 3) x = least_step<0x140 /* row_mirror */>(x);
+        return x;
+    }
+    // The sum over all models of a value that their lanes share.
+    template <int CTRL>
+    static __device__ __forceinline__ uint32_t add_step(uint32_t x)
+    {
+        return x + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, false);
+    }
+    __device__ __forceinline__ uint32_t sum_of_models(const Pair& p, uint32_t x) const
+    {
+        if constexpr (ONE && WIDTH != PACKED) {
+            x = p.in ? x : 0u;
+            if (WIDTH <= 4) x = add_step<0x124 /* row_ror:4 */>(x);
+            if (WIDTH <= 8) x = add_step<0x128 /* row_ror:8 */>(x);
+            return lane_value(x, 0) + lane_value(x, 16) + lane_value(x, 32) + lane_value(x, 48);
+        } else {
+            return wave_sum(leads(p) ? x : 0u);
+        }
+    }
+
+    // What step A finds about a model, the same in all its lanes: cost << 15 | lt of the best
+    // candidate (EMPTY: none is feasible) and its index.  c0: the lane's first_core().
+    // mine: this lane's own best is the one, with that many cores.
+    struct Best {
+        uint32_t key, k, c0, c;
+        bool mine;
+    };
+
+    // Cost << 15 | lt of the pair's candidate with c cores, EMPTY where it is infeasible.
+    // rd: recip_below() of what they do to its speed.
+    template <bool SMALL>
+    __device__ __forceinline__ uint32_t meet(const Pair& p, uint32_t c, double rd) const
+    {
+        if (!SMALL || QUEUE == THEMIS_QUEUE_WORST_CASE) {
+            const Eval ev = this->template eval<SMALL>(p, rd);
+            return ev.lt >= 0 ? __umul24((uint32_t)ev.n, c) << 15 | (uint32_t)ev.lt : EMPTY;
+        }
+        // eval_parts() with the division by b 1e6 of lambda as a factor that all candidates of
+        // the pair share.  p.ratio is lambda / (b 1e6) less at most 2^-44 of it, so
+        // ceil_div_small()'s argument holds for proc * ratio as it does for
+        // (lambda proc) * rM.  (A candidate for which lambda proc exceeds 2^42 is slower than
+        // the objective and fails the last test whatever its replica count comes out as.)
+        const double proc = ceil_div_small(p.num, rd) + p.fixed;
+        const double need = proc * p.ratio;
+        const double n = DERIVE ? __builtin_ceil(need) : p.h.n_given;
+        // the given replicas carry lambda exactly when the least number that does is no larger
+        bool ok = DERIVE ? n <= a.r_max_d : need <= n;
+        const double top =
+            __builtin_fma(proc, p.h.lam, QUEUE == THEMIS_QUEUE_PER_REPLICA ? p.bh.w * n : p.bh.w);
+        const double lt = ceil_div_small(top, p.h.rlt_den);
+        ok = ok && lt <= p.h.T;
+        const double key = __builtin_fma(n * (double)c, 32768.0, lt);
+        return ok ? (uint32_t)key : EMPTY;
+    }
+    template <bool SMALL>
+    __device__ __forceinline__ uint32_t meet(const Pair& p, uint32_t c) const
+    {
+        return meet<SMALL>(p, c, recip_below((double)this->speed(p, c)));
+    }
+
+    // ---- step A ------------------------------------------------------------------
+    // What the cost and the latency of a pair's candidates are at least, in single precision
+    // with every term moved to the safe side by more than its error (2^-22 or so): with c
+    // cores n = ceil(rn / c + rf) replicas, and td / c + tf + n tw ticks.
+    struct Bounds {
+        float rn, rf, td, tf, tw, per_n;
+    };
+    __device__ __forceinline__ Bounds bounds_of(const Pair& p) const
+    {
+        constexpr float DOWN = 0.999998f;
+        Bounds b;
+        const float num = (float)p.num, fixed = (float)p.fixed, rate = (float)p.ratio;
+        b.per_n = (float)p.h.n_given;
+        b.rn = rate * num * DOWN, b.rf = rate * fixed * DOWN;
+        const float per_us = (float)a.rtick * DOWN;
+        b.td = num * per_us, b.tf = fixed * per_us;
+        b.tw = p.w * __builtin_amdgcn_rcpf((float)lam) * per_us * DOWN;
+        // (the queue does not depend on n, or n does not on the cores)
+        if (QUEUE != THEMIS_QUEUE_PER_REPLICA || !DERIVE) {
+            b.tf += QUEUE == THEMIS_QUEUE_PER_REPLICA ? b.tw * b.per_n : b.tw;
+            b.tw = 0.0f;
+        }
+        return b;
+    }
+    // The most cores with which candidates of the pair can cost as little as `limit`.
+    __device__ __forceinline__ float most_cores(const Pair& p, const Bounds& b, float limit) const
+    {
+        float most;
+        if (DERIVE)
+            most = __builtin_fminf((limit - b.rn) * __builtin_amdgcn_rcpf(b.rf) * 1.00001f, limit);
+        else
+            most = limit * __builtin_amdgcn_rcpf(b.per_n) * 1.00001f;
+        return __builtin_fminf(most, (float)p.last);
+    }
+    // Which of the 32 core counts from c0 on, and up to `most`, can cost as little as `limit`
+    // and (LATE) take fewer than `before` ticks: bit 31 is c0's.  Nine instructions a
+    // count, four counts at a time, against thirty for an evaluation.
+    template <bool LATE>
+    __device__ __forceinline__ uint32_t promising(const Bounds& b, uint32_t c0, float most,
+                                                  float limit, float before) const
+    {
+        uint32_t mask = 0u;
+        const float over = most - (float)c0;
+        float c = (float)c0;
+        int n = 0;
+#pragma unroll 1
+        for (; n < 32 && any((float)n <= over); n += 4) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float r = __builtin_amdgcn_rcpf(c);
+                // negative where the count is promising
+                uint32_t sign = 0x80000000u;
+                float y = b.tf;
+                if (DERIVE) {
+                    const float reps = __builtin_ceilf(__builtin_fmaf(b.rn, r, b.rf));
+                    sign &= __float_as_uint(__builtin_fmaf(reps, c, -0.5f - limit));
+                    if (QUEUE == THEMIS_QUEUE_PER_REPLICA) y = __builtin_fmaf(reps, b.tw, y);
+                }
+                if (LATE) sign &= __float_as_uint(__builtin_fmaf(b.td, r, y) + (0.9f - before));
+                mask = __builtin_amdgcn_alignbit(mask, sign, 31);
+                c += 1.0f;
+            }
+        }
+        if (n == 0 || over < 0.0f) return 0u;
+        const uint32_t counts = (uint32_t)(over < 31.0f ? over : 31.0f);
+        return mask << (32 - n) & ~(0x7FFFFFFFu >> counts);
+    }
+
+    // The best candidate of the lanes' models.
+    //
+    // A lane evaluates the first core count that can be feasible, and then those that can
+    // cost as little as the model's best: of 31 per instance at 65536 x 8 that lambda (num /
+    // c + fixed) / (b 1e6) allows some two are left where that is rounded up.
+    template <bool SMALL>
+    __device__ __forceinline__ Best best_of(const Pair& p) const
+    {
+        const uint32_t c0 = this->first_core(p);
+        bool go = p.there && c0 <= p.last;
+        uint32_t c = go ? c0 : p.lo;
+        uint32_t best = meet<SMALL>(p, c), best_c = c;
+        best = go ? best : EMPTY;
+        uint32_t model = model_least(p, best);
+        if (DERIVE) {
+            go = go && c < p.last;
+            if (any(go)) {
+                const Bounds b = bounds_of(p);
+                for (;;) {
+                    const float limit = (float)(model >> 15);
+                    const float most = go ? most_cores(p, b, limit) : -1.0f;
+                    go = go && (float)(c + 1u) <= most;
+                    if (!any(go)) break;
+                    uint32_t mask = promising<false>(b, c + 1u, most, limit, 0.0f);
+                    const uint32_t from = c + 1u;
+                    while (any(mask != 0u)) {
+                        const bool is = mask != 0u;
+                        const uint32_t z = (uint32_t)__builtin_clz(mask | 1u);
+                        mask &= ~(0x80000000u >> z);
+                        c = is ? from + z : p.lo;
+                        const uint32_t key = meet<SMALL>(p, c);
+                        // (cores ascend: of equal keys the first one met has the smaller index)
+                        if (is && key < best) best = key, best_c = c;
+                    }
+                    model = model_least(p, best);
+                    c = from + 31u;
+                }
+            }
+        } else {
+            // the cost grows with every core: a lane is done with its first feasible count
+            go = go && best == EMPTY;
+            while (any(go)) {
+                go = go && ++c <= p.last && (double)c * p.h.n_given <= (double)(model >> 15);
+                const uint32_t key = meet<SMALL>(p, c);
+                if (go && key != EMPTY) best = key, best_c = c, go = false;
+                model = model_least(p, best);
+            }
+        }
+        Best b;
+        b.key = model;
+        b.c0 = c0;
+        const uint32_t mine = __umul24(best_c - 1u, (uint32_t)a.n_batch) + p.j;
+        b.k = model_least(p, best == model ? mine : EMPTY);
+        b.c = best_c;
+        b.mine = p.there && best == model && mine == b.k;
+        return b;
+    }
+
+    // ---- step F ------------------------------------------------------------------
+    // lt << 15 | cost of the fastest candidate of the lanes' models, EMPTY where there is none.
+    template <bool SMALL>
+    __device__ __forceinline__ uint32_t fastest_of(const Pair& p) const
+    {
+        const uint32_t key = meet<SMALL>(p, p.last);
+        // (of equal latencies any cost will do)
+        const uint32_t turned = key == EMPTY || !p.there ? EMPTY : (key & 0x7FFFu) << 15 | key >> 15;
+        return model_least(p, turned);
+    }
+    // Sum of the models' least latencies, beyond any budget where one has no candidate.
+    template <bool SMALL>
+    __device__ __forceinline__ uint32_t fastest_ticks(const Pair& first) const
+    {
+        if constexpr (ONE) {
+            return sum_of_models(first, fastest_of<SMALL>(first) >> 15);
+        } else {
+            uint32_t sum = 0u;
+            for_pairs(first, [&](const Pair& p) {
+                const uint32_t f = fastest_of<SMALL>(p);
+                sum += sum_of_models(p, f >> 15);
+            });
+            return sum;
+        }
+    }
+
+    // ---- the tables of steps B and C ----------------------------------------------
+    // (lt, index) by cost over base, `cells` cells per model, of the candidates that are
+    // dearer (by less than `span`) and faster than the model's best (`best`: its cost << 15 | lt).
+    template <bool SMALL>
+    __device__ __forceinline__ void enter(const Pair& p, uint32_t c0, uint32_t best, uint32_t cells,
+                                          uint32_t span) const
+    {
+        uint32_t* const tab = lds + L.tab;
+        const Bounds b = bounds_of(p);
+        const uint32_t base = best >> 15, before = best & 0x7FFFu;
+        const float limit = (float)(base + span - 1u);
+        const float most = p.there ? most_cores(p, b, limit) : -1.0f;
+        uint32_t from = c0;
+        if (!DERIVE) {
+            const float least_c = (float)base * __builtin_amdgcn_rcpf(b.per_n) * 0.9999f;
+            from = least_c > (float)from ? (uint32_t)least_c : from;
+        }
+        for (; any((float)from <= most); from += 32u) {
+            uint32_t mask = promising<true>(b, from, most, limit, (float)before);
+            while (any(mask != 0u)) {
+                // two at a time: their chains of dependent operations fill each other's waits
+                uint32_t c[2], at[2], what[2];
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const bool is = mask != 0u;
+                    const uint32_t z = (uint32_t)__builtin_clz(mask | 1u);
+                    mask &= ~(0x80000000u >> z);
+                    c[q] = is ? from + z : p.lo;
+                    const uint32_t key = meet<SMALL>(p, c[q]);
+                    const uint32_t d = (key >> 15) - base, lt = key & 0x7FFFu;
+                    // (EMPTY is beyond any cell)
+                    const bool use = (int)is & (int)(d - 1u < span - 1u) & (int)(lt < before);
+                    at[q] = use ? p.s * cells + d : 0u;
+                    what[q] = use ? lt << INDEX_BITS | (__umul24(c[q] - 1u, (uint32_t)a.n_batch) + p.j) : EMPTY;
+                }
+                // (EMPTY changes nothing)
+                atomicMin(&tab[at[0]], what[0]);
+                atomicMin(&tab[at[1]], what[1]);
+            }
+        }
+    }
+
+    // ---- step B ------------------------------------------------------------------
+    // The recurrence over eight cells for eight models at a time (or sixteen for four), lane =
+    // (model, cell): rows of neighbouring models are combined, then of two and two, of four
+    // and four (and with the row of the models behind those), so that three or four
+    // dependent steps take the place of one per model.  The choices of all models at all
+    // cells are read out together, and what is left per model is one lane index.  (With the
+    // results' way out: 2.0 us for five models and 3.3 for eight as sixteen cells a model
+    // after the other, 1.6 and 1.9 as eight this way.)
+    // `span`: the cells over base up to which the table is complete.
+    template <int CELLS>
+    __device__ __forceinline__ int solve_cells(uint32_t base_sum, int span) const
+    {
+        typedef uint32_t four __attribute__((ext_vector_type(4), aligned(16)));
+        constexpr uint32_t INDEX = (1u << INDEX_BITS) - 1u;
+        constexpr int MODELS = 64 / CELLS, STRIDE = 2 * CELLS, BITS = CELLS == 8 ? 3 : 4;
+        const uint32_t* const tab = lds + L.tab;
+        // rows of CELLS cells, as many guard cells in front of each
+        uint32_t* const rows = lds + L.tab + 64 * a.S + CELLS;
+        const int S = a.S, x = lane & (CELLS - 1), g = lane / CELLS;
+        for (int y = g; y <= S; y += MODELS) rows[STRIDE * y + x - CELLS] = LT_NONE;
+        if (lane < CELLS) rows[STRIDE * S + lane] = 0u;  // nothing left to run
+        // eight at a time: cells x - q0, x - q0 - 1, .. of a row, and cells q0, q0 + 1, .. of one
+        auto backwards = [&](const uint32_t* row, int q0, uint32_t (&v)[8]) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = (row + x - q0 - 7)[7 - q];
+        };
+        auto forwards = [](const uint32_t* row, int q0, uint32_t (&v)[8]) {
+            const four a = *reinterpret_cast<const four*>(row + q0);
+            const four b = *reinterpret_cast<const four*>(row + q0 + 4);
+            v[0] = a.x, v[1] = a.y, v[2] = a.z, v[3] = a.w, v[4] = b.x, v[5] = b.y, v[6] = b.z, v[7] = b.w;
+        };
+        uint32_t h = 0u;
+        for (int s0 = (S - 1) & ~(MODELS - 1); s0 >= 0; s0 -= MODELS) {
+            const int end = s0 + MODELS < S ? s0 + MODELS : S;
+            const bool is = s0 + g < end;
+            const int s = is ? s0 + g : end - 1;
+            uint32_t* const mine = rows + STRIDE * s;
+            // (of at most x cells: with nothing behind them the models are done)
+            h = segmented_scan<true>(tab[CELLS * s + x] >> INDEX_BITS, (uint32_t)x, CELLS);
+            if (is) mine[x] = h;
+            wave_lds_fence();
+            const int to = end < S ? end + 1 : end;
+            for (int l = 1; l < to - s0; l *= 2) {
+                const bool on = is && s + l < to;
+                uint32_t all = LT_NONE;
+#pragma unroll 1
+                for (int q0 = 0; q0 < CELLS; q0 += 8) {
+                    uint32_t f[8], o[8];
+                    forwards(mine, q0, f);
+                    backwards(rows + STRIDE * (on ? s + l : end), q0, o);
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) all = least(all, f[q] + o[q]);
+                }
+                wave_lds_fence();
+                if (on) mine[x] = h = all;
+                wave_lds_fence();
+            }
+        }
+        const uint32_t m = (uint32_t)__builtin_amdgcn_ballot_w64(h <= (uint32_t)T) & ((1u << span) - 1u);
+        if (m == 0u) return UNFINISHED;
+        int left = __builtin_ctz(m);
+        this->put(THEMIS_SOLVED, (int32_t)(base_sum + (uint32_t)left), (int32_t)lane_value(h, left), BY_B);
+        for (int s0 = 0; s0 < S; s0 += MODELS) {
+            const int s = s0 + g < S ? s0 + g : S - 1;
+            const uint32_t ticks = rows[STRIDE * s + x];
+            // the smallest index among the candidates that continue an optimum, and its cell
+            uint32_t pick = EMPTY;
+#pragma unroll 1
+            for (int q0 = 0; q0 < CELLS; q0 += 8) {
+                uint32_t w[8], o[8];
+                forwards(tab + CELLS * s, q0, w);
+                backwards(rows + STRIDE * (s + 1), q0, o);
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    const bool hit = (w[q] >> INDEX_BITS) + o[q] == ticks;
+                    pick = least(pick, hit ? (w[q] & INDEX) << BITS | (uint32_t)(q0 + q) : EMPTY);
+                }
+            }
+            const int n = S - s0 < MODELS ? S - s0 : MODELS;
+            unsigned long long chosen = 0ull;
+            uint32_t none = 0u;
+            for (int q = 0; q < n; ++q) {
+                const int at = CELLS * q + left;
+                const uint32_t p = lane_value(pick, at);
+                none |= p;
+                chosen |= 1ull << at;
+                left -= (int)(p & (uint32_t)(CELLS - 1));
+            }
+            if (none == EMPTY) {  // never expected
+                this->put_none(THEMIS_INTERNAL);
+                return THEMIS_INTERNAL;
+            }
+            this->put_row((int)((chosen >> lane) & 1ull), (uint32_t)s, pick >> BITS,
+                          (this->keys()[s] >> 15) + (pick & (uint32_t)(CELLS - 1)));
+        }
+        return THEMIS_SOLVED;
+    }
+
+    // The largest rate for which the given replicas are known to do, by halves between 1 and
+    // lambda, at which they do not.  A midpoint needs no recurrence: a configuration within
+    // the budget exists exactly when the fastest candidates of all models fit it together, and
+    // with the replicas given those are the ones at the core cap, whatever the rate.
+    template <bool SMALL>
+    __device__ __forceinline__ int32_t search_rate(const Pair& first)
+    {
+        constexpr bool KEPT = ONE && SMALL && QUEUE != THEMIS_QUEUE_WORST_CASE;
+        const int32_t lambda = lam;
+        int32_t lo = 1, hi = lambda;
+        const double proc =
+            KEPT ? ceil_div_small(first.num, recip_below((double)this->speed(first, first.last))) +
+                       first.fixed
+                 : 0.0;
+        const double wait =
+            QUEUE == THEMIS_QUEUE_PER_REPLICA ? first.bh.w * first.h.n_given : first.bh.w;
+        while (hi - lo > 1) {
+            lam = lo + ((hi - lo) >> 1);
+            uint32_t ticks;
+            if constexpr (KEPT) {
+                // what meet() makes of it
+                const double rate = (double)lam;
+                const double lt = ceil_div_small(__builtin_fma(proc, rate, wait),
+                                                 recip_below(rate * a.tick_d));
+                const bool ok = (int)first.there & (int)(proc * (rate * first.bh.rM) <= first.h.n_given) &
+                                (int)(lt <= first.h.T);
+                const uint32_t fast = model_least(first, ok ? (uint32_t)lt : LT_NONE);
+                ticks = sum_of_models(first, fast);
+            } else {
+                ticks = fastest_ticks<SMALL>(at_rate(first));
+            }
+            if (ticks <= (uint32_t)T)
+                lo = lam;
+            else
+                hi = lam;
+        }
+        lam = lambda;
+        return lo;
+    }
+
+    // Steps A and F and the first eight cells of step B of a valid instance.
+    template <bool SMALL>
+    __device__ __forceinline__ int solve_valid(const Pair& first) const
+    {
+        Best mine{EMPTY, 0u, 0u, 0u, false};
+        uint32_t ticks = 0u;
+        for_pairs(first, [&](const Pair& p) {
+            const Best b = best_of<SMALL>(p);
+            if (ONE) mine = b;
+            ticks += sum_of_models(p, b.key == EMPTY ? LT_NONE : b.key & 0x7FFFu);
+            if (!ONE && leads(p)) {
+                this->keys()[p.s] = b.key;
+                this->bests()[p.s] = (unsigned long long)b.key << INDEX_BITS | b.k;
+            }
+        });
+        if (ticks >= LT_NONE) return THEMIS_INFEASIBLE;
+        uint32_t base_sum;
+        unsigned long long best = 0ull;  // not ONE: lane s: that of model s
+        if constexpr (ONE) {
+            base_sum = sum_of_models(first, mine.key >> 15);
+        } else {
+            wave_lds_fence();
+            if (lane < a.S) best = this->bests()[lane];
+            base_sum = this->sum_models((uint32_t)(best >> (INDEX_BITS + 15)));
+        }
+        if (ticks <= (uint32_t)T) {
+            this->put(THEMIS_SOLVED, (int32_t)base_sum, (int32_t)ticks);
+            if constexpr (ONE) {
+                this->put_row(mine.mine, first.s, mine.c, first.size, mine.k, mine.key >> 15);
+            } else {
+                this->put_choice((uint32_t)best & ((1u << INDEX_BITS) - 1u),
+                                 (uint32_t)(best >> (INDEX_BITS + 15)));
+            }
+            return THEMIS_SOLVED;
+        }
+        uint32_t least_ticks = 0u;
+        for_pairs(first, [&](const Pair& p) {
+            const uint32_t f = fastest_of<SMALL>(p);
+            least_ticks += sum_of_models(p, f >> 15);
+            if (leads(p)) {
+                this->fastest()[p.s] = f;
+                if (ONE) this->keys()[p.s] = mine.key;
+            }
+        });
+        if (least_ticks > (uint32_t)T) return THEMIS_INFEASIBLE;
+        const int reach = reach_of(ticks, least_ticks);
+        if (reach <= 8) {
+            fill<SMALL>(first, mine, best, 8, reach);
+            //STAMP5
+            const int status = solve_cells<8>(base_sum, reach);
+            if (status != UNFINISHED) return status;
+            wave_lds_fence();
+        }
+        if (reach <= 16) {
+            fill<SMALL>(first, mine, best, 16, 16);
+            const int status = solve_cells<16>(base_sum, 16);
+            if (status != UNFINISHED) return status;
+            wave_lds_fence();
+        }
+        fill<SMALL>(first, mine, best, 64, 64);
+        return UNFINISHED;
+    }
+    // How many cells it takes, by how much the cheapest assignment is late, as a part of
+    // what the fastest gains on it.  By the checker's answers for 1500 instances of each of
+    // the timed shapes, and of drawn ones: where the replicas are derived, up to three tenths
+    // of it is made up for within four cells, with next to no exception; beyond five eighths
+    // it mostly takes more than eight, beyond three quarters more than sixteen.  With the
+    // replicas given the gains are spread more evenly.  (Where an answer lies beyond these
+    // cells, or they are more than it takes, it is found all the same.)
+    __device__ __forceinline__ int reach_of(uint32_t ticks, uint32_t least_ticks) const
+    {
+        const uint32_t late = (ticks - (uint32_t)T) * 40u, gain = ticks - least_ticks;
+        if (DERIVE && late <= gain * 12u) return 4;
+        return late <= gain * (DERIVE ? 25u : 17u) ? 8 : late <= gain * (DERIVE ? 30u : 26u) ? 16 : 64;
+    }
+    // The table of `cells` cells per model.  mine, best: what step A found, see solve_valid().
+    template <bool SMALL>
+    __device__ __forceinline__ void fill(const Pair& first, const Best& mine, unsigned long long best,
+                                         int cells, int span) const
+    {
+        uint32_t* const tab = lds + L.tab;
+        for (int y = lane; y < cells * a.S; y += 64) tab[y] = EMPTY;
+        wave_lds_fence();
+        if constexpr (ONE) {
+            if (leads(first)) tab[first.s * cells] = (mine.key & 0x7FFFu) << INDEX_BITS | mine.k;
+        } else {
+            if (lane < a.S) tab[lane * cells] = (uint32_t)best & ((1u << (INDEX_BITS + 15)) - 1u);
+        }
+        wave_lds_fence();
+        for_pairs(first, [&](const Pair& p) {
+            if constexpr (ONE)
+                enter<SMALL>(p, mine.c0, mine.key, (uint32_t)cells, (uint32_t)span);
+            else
+                enter<SMALL>(p, this->first_core(p), this->keys()[p.s], (uint32_t)cells, (uint32_t)span);
+        });
+        wave_lds_fence();
+    }
+    // The inputs of instance `inst` at the rate rates[inst], or at `rate`; valid: the input
+    // check's result.
+    //
+    // The arguments this takes are held in scalar registers from the start: where the
+    // compiler is free to load each where it is used, there are a dozen waits of 50 to 200
+    // cycles, and the coefficients are asked for only after the rate has come.
+    __device__ __forceinline__ Pair begin(int inst, const int32_t* rates, bool& valid)
+    {
+        asm volatile("" ::"s"(rates));
+        return begin(inst, constant(rates)[inst], valid);
+    }
+    __device__ __forceinline__ Pair begin(int inst, int32_t rate, bool& valid)
+    {
+        i = inst;
+        // (asked for, and not changed, here)
+        asm volatile("" ::"s"(a.coef), "s"(a.slo_us), "s"(a.S), "s"(a.cs), "s"(a.n_batch), "s"(a.c_max),
+                     "s"(a.r_max), "s"(a.tick), "s"(a.slo_max), "s"(a.coef_stride), "s"(a.c_all),
+                     "s"(a.keep), "s"(a.c_fixed), "s"(a.r_fixed), "s"(a.kept.coef),
+                     "s"(a.kept.cfg), "s"(a.kept.words), "s"(a.tmeta), "s"(a.tick_magic));
+        lam = rate;
+        slo = constant(a.slo_us)[inst];
+        // floor(slo / tick), from below by at most one
+        T = (int)__umulhi((uint32_t)slo, a.tick_magic);
+        T += (uint32_t)(slo - T * a.tick) >= (uint32_t)a.tick ? 1 : 0;
+        int32_t word = 0;
+        const bool keeps = (ROLE == PLAIN || ROLE == PINNED) && a.keep && a.coef_stride;
+        if (keeps && lane < a.S * a.cs) word = (a.coef + (size_t)i * (uint32_t)a.coef_stride)[lane];
+        Pair first = pair_of_round(0);
+        this->lane_b = first.size;  // (the first lanes have the first model's pairs)
+        int fine = (int)in_range(lam, 1, THEMIS_VALUE_MAX) & (int)in_range(slo, 0, a.slo_max);
+        for_pairs(first, [&](const Pair& p) { fine &= (int)!p.there | (int)p.valid; });
+        valid = !any(!fine);
+        this->keep_inputs(valid, word);
+        if (this->records() && lane == 0) a.tmeta[i] = valid ? T : -1;
+        return first;
+    }
+    // The pair kept from another rate at the rate `lam` (where pairs are not kept they are
+    // formed at that rate anyway).
+    __device__ __forceinline__ Pair at_rate(Pair p) const
+    {
+        if (ONE) {
+            this->set_rate(p);
+        }
+        return p;
+    }
+
+    // row_is_small(), which is the same for all models of an instance
+    __device__ __forceinline__ bool is_small() const
+    {
+        return __umulhi((uint32_t)lam, (uint32_t)slo) < 1u << 10;
+    }
+    // Steps A, F and B of the instance that was begun, at the rate `lam`, with the results
+    // where these suffice.
+    __device__ __forceinline__ int solve(const Pair& first, bool valid) const
+    {
+        int status = valid ? LARGE : THEMIS_INVALID;
+        if (valid && is_small())
+            status = solve_valid<true>(first);
+        return __builtin_amdgcn_readfirstlane(status);
+    }
+    // What is left to do after that; `none`: also to write the results of an instance
+    // without an answer.
+    __device__ __forceinline__ int finish(int status, bool none) const
+    {
+        if (status == THEMIS_SOLVED) return status;
+        if (status != UNFINISHED && status != LARGE) {
+            if (none) this->put_none(status);
+            return status;
+        }
+        return __builtin_amdgcn_readfirstlane(solve_rest<QUEUE, DERIVE, ROLE>(
+            (uint64_t)(uintptr_t)afresh(args), i, T, lam, slo, none));
+    }
+    // The same pointer, to arguments that the compiler hasn't loaded yet.
+    static __device__ __forceinline__ ArgsPtr afresh(ArgsPtr p)
+    {
+        asm volatile("" : "+s"(p));
+        return p;
+    }
+};
+
+// The rate the given replicas of an instance are solved at (see Front::search_rate()), where
+// products exceed 2^42.
+template <int QUEUE>
+__device__ __attribute__((noinline)) int32_t rate_of_large(uint64_t args, int i, int T, int32_t lam,
+                                                           int32_t slo)
+{
+    auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+    const uint64_t lo = (uint32_t)uniform((int)(uint32_t)args);
+    const uint64_t hi = (uint32_t)uniform((int)(uint32_t)(args >> 32));
+    Front<QUEUE, false, 0, QUIET> sv((ArgsPtr)(uintptr_t)(hi << 32 | lo));
+    sv.instance(uniform(i), uniform(T), uniform(lam), uniform(slo));
+    const auto first = sv.pair_of_round(0);
+    return uniform(sv.template fastest_ticks<false>(first) <= (uint32_t)sv.T
+                       ? sv.lam
+                       : sv.template search_rate<false>(first));
+}
+
+// What an instance needs that most of them do not, out of their way: with calls between the
+// steps instead of one behind them all, what the steps keep in registers went to scratch
+// memory around them (86400 x 6: 99 us instead of 45 at the time).  That includes steps A, F
+// and B where products exceed 2^42, with rates times objectives beyond those of any of the
+// numbered workloads by a factor of 200.  (Step B's sixteen cells stay with the others:
+// from here 4096 x 5 took 12.4 us instead of 11.2.)
+template <int QUEUE, bool DERIVE, int ROLE>
+__device__ __attribute__((noinline)) int solve_rest(uint64_t args, int i, int T, int32_t lam,
+                                                    int32_t slo, bool none)
+{
+    auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+    const uint64_t lo = (uint32_t)uniform((int)(uint32_t)args);
+    const uint64_t hi = (uint32_t)uniform((int)(uint32_t)(args >> 32));
+    Front<QUEUE, DERIVE, 0, ROLE> sv((ArgsPtr)(uintptr_t)(hi << 32 | lo));
+    sv.instance(uniform(i), uniform(T), uniform(lam), uniform(slo));
+    int status;
+    if (sv.is_small())
+        status = sv.solve_further();
+    else if ((status = uniform(sv.template solve_valid<false>(sv.pair_of_round(0)))) == UNFINISHED)
+        status = sv.solve_further();
+    status = uniform(status);
+    if (uniform((int)none) && (status == THEMIS_INVALID || status == THEMIS_INFEASIBLE)) sv.put_none(status);
+    return status;
+}
+
+// One whole solve of instance `inst` at the rate rates[inst].
+template <int QUEUE, bool DERIVE, int WIDTH, int ROLE>
+__device__ __forceinline__ int solve_instance(ArgsPtr args, int inst, const int32_t* rates)
+{
+    Front<QUEUE, DERIVE, WIDTH, ROLE> sv(args);
+    bool valid;
+    const auto first = sv.begin(inst, rates, valid);
+    return sv.finish(sv.solve(first, valid), true);
+}
+
+}  // namespace
+}  // namespace themis

@@ -1,10 +1,10 @@
 // The entry points that solve an instance more than once, each with all of an
 // instance's solves in one wavefront (cost_solver.h), one after the other:
 //
-//   kc_fallback   Algorithm 1 with its fallback (Section 4.4): the vertical solve at
-//                 lambda; where the replicas given cannot meet the SLO, the binary
-//                 search on the rate, the vertical solve at the rate it settles on, and
-//                 the horizontal solve of the rest with the cores just chosen.
+//   kc_fallback   Algorithm 1 with its fallback (Section 4.4): whether the replicas given
+//                 can meet the SLO at lambda; where they cannot, the binary search on the
+//                 rate; the vertical solve at lambda or the rate found, and the horizontal
+//                 solve of the rest with the cores just chosen.
 //   kc_stability  the stability test of Section 5.1.3: the horizontal solve at the
 //                 current and, where that succeeds and the rate differs, at the
 //                 predicted rate, and whether the configurations agree.
@@ -18,129 +18,128 @@
 // What bounds them is what bounds a single solve.  As passes over all instances with
 // the search by one thread per instance (170 us of it at 16384 x 8) and a compare
 // kernel around one-wavefront solves, eight launches and three, they took 250 and 28 us
-// at 16384 x 8 and 4099 x 5; now one launch each, 62 and 23.  Pipelines of more than 64
-// models still go that way, over the three stages.
-#include "cost_solver.h"
+// at 16384 x 8 and 4099 x 5; as one launch each 65 and 23, with a solve at lambda ahead of
+// the search, an evaluation from the start for each of its midpoints and some sixty registers
+// spilled; now 30 and 19.  Pipelines of more than 64 models still go the other way, over the
+// three stages.
+#include "cost_front.h"
 
 namespace themis {
 namespace {
 
-// The largest rate the search finds; `first`: the pair at lambda, which is infeasible.
-template <int QUEUE, bool ONE, bool SMALL>
-__device__ __forceinline__ int32_t search_rate(Solver<QUEUE, false, ONE, QUIET>& sv,
-                                               const typename Solver<QUEUE, false, ONE, QUIET>::Pair& first)
-{
-    int32_t lo = 1, hi = sv.lam;
-    while (hi - lo > 1) {
-        const int32_t mid = lo + ((hi - lo) >> 1);
-        sv.lam = mid;
-        const bool fits = sv.template fastest_ticks<SMALL>(sv.at_rate(first)) <= (uint32_t)sv.T;
-        if (fits)
-            lo = mid;
-        else
-            hi = mid;
-    }
-    return lo;
-}
-
-template <int QUEUE, bool ONE>
+// (Every solve starts from the arguments again: what could be kept of them from one to the
+// next, and over the calls behind it, would cost registers that the steps need.)
+template <int QUEUE, int WIDTH>
 __device__ __forceinline__ void fallback_instance(ArgsPtr args, int i)
 {
-    Solver<QUEUE, false, ONE, QUIET> sv(args);
-    const int32_t lambda = args->lambda[i];
+    const int32_t lambda = constant(args->lambda)[i];
     int32_t rate = lambda;  // what the running replicas are solved at
     int status;
     {
+        Front<QUEUE, false, WIDTH, QUIET> sv(args);
         bool valid;
         auto first = sv.begin(i, lambda, valid);
-        status = valid ? THEMIS_INFEASIBLE : THEMIS_INVALID;
-        for (bool searched = false; valid; searched = true) {
-            status = sv.solve(first);
-            if (searched || status != THEMIS_INFEASIBLE) break;
-            // (lambda is the largest rate met, so the short divisions stay allowed)
-            if (__builtin_amdgcn_readfirstlane((int)((double)lambda * (double)sv.slo <= 0x1p42)))
-                rate = search_rate<QUEUE, ONE, true>(sv, first);
-            else
-                rate = search_rate<QUEUE, ONE, false>(sv, first);
-            sv.lam = rate;
+        // Whether they can carry lambda is asked before anything is solved for it: it takes a
+        // third of what step A does, which then is taken at one rate only.
+        if (valid && sv.is_small()) {
+            if (sv.template fastest_ticks<true>(first) > (uint32_t)sv.T) {
+                sv.lam = rate = sv.template search_rate<true>(first);
+                first = sv.at_rate(first);
+            }
+        } else if (valid) {
+            rate = rate_of_large<QUEUE>((uint64_t)(uintptr_t)args, i, sv.T, lambda, sv.slo);
+            sv.lam = rate = __builtin_amdgcn_readfirstlane(rate);
             first = sv.at_rate(first);
         }
+        status = sv.finish(sv.solve(first, valid), true);
     }
     const bool solved = status == THEMIS_SOLVED;
-    if (!solved) sv.put_none(status);
-    if (sv.lane == 0) args->lambda_v[i] = solved ? rate : 0;
+    args = Front<QUEUE, false, WIDTH, QUIET>::afresh(args);
+    if (threadIdx.x == 0) args->lambda_v[i] = solved ? rate : 0;
 
     // new instances for what is left, with the cores of the configuration
-    Solver<QUEUE, true, ONE, PINNED> nw(args);
+    Front<QUEUE, true, WIDTH, PINNED> nw(args);
     const int32_t rest = solved ? lambda - rate : 0;
     nw.i = i;
     if (nw.lane < nw.a.S) {
-        // (this lane wrote the configuration's row)
-        const int32_t c = solved ? (sv.config() + 3 * nw.lane)[0] : 1;
-        nw.lds[nw.L.pin + nw.lane] = (uint32_t)c;
+        // what put_row() left there
+        const uint32_t k = nw.lds[nw.L.pin + nw.lane] & ((1u << INDEX_BITS) - 1u);
+        nw.lds[nw.L.pin + nw.lane] = solved ? index_quotient(k, nw.a.magic) + 1u : 1u;
     }
     wave_lds_fence();
     if (rest == 0) {
         // nothing to solve; for calls that look at the workspace afterwards the instance
         // is one that the last solve was not given
         nw.put_none(solved ? THEMIS_SOLVED : THEMIS_INVALID, solved ? 0 : -1);
-        if (nw.lane == 0) args->tmeta[i] = -1;
+        if (nw.lane == 0) nw.a.tmeta[i] = -1;
         return;
     }
     bool valid;
     const auto first = nw.begin(i, rest, valid);
-    if (nw.solve(first) == THEMIS_INFEASIBLE) nw.put_none(THEMIS_INFEASIBLE);
+    nw.finish(nw.solve(first, valid), true);
 }
 
-template <int QUEUE, bool ONE>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6, 8))) void kc_fallback(CostArgs)
+template <int QUEUE, int WIDTH>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6, 6))) void kc_fallback(CostArgs)
 {
     const ArgsPtr args = kernel_args();
-    mark_workspace(args, STATE_KEPT | STATE_ONLY);
-    fallback_instance<QUEUE, ONE>(args, (int)blockIdx.x);
+    fallback_instance<QUEUE, WIDTH>(args, (int)blockIdx.x);
+    mark_workspace(Front<QUEUE, false, WIDTH>::afresh(args), STATE_KEPT | STATE_ONLY);
 }
 
-template <int QUEUE, bool ONE>
+template <int QUEUE, int WIDTH>
 __device__ __forceinline__ void stability_instance(ArgsPtr args, int i)
 {
-    const int32_t now = args->lambda[i], pred = args->lambda2[i];
-    bool stable = solve_instance<QUEUE, true, ONE, PLAIN>(args, i, now) == THEMIS_SOLVED;
+    const int32_t now = constant(args->lambda)[i], pred = constant(args->lambda2)[i];
+    bool stable = solve_instance<QUEUE, true, WIDTH, PLAIN>(args, i, args->lambda) == THEMIS_SOLVED;
     wave_lds_fence();
+    args = Front<QUEUE, true, WIDTH>::afresh(args);
     if (stable && pred != now) {
-        stable = solve_instance<QUEUE, true, ONE, SECOND>(args, i, pred) == THEMIS_SOLVED;
+        stable = solve_instance<QUEUE, true, WIDTH, SECOND>(args, i, args->lambda2) == THEMIS_SOLVED;
+        args = Front<QUEUE, true, WIDTH>::afresh(args);
         if (stable) {
-            bool same = true;
-            if ((int)threadIdx.x < args->S) {
-                // (this lane wrote both rows)
-                const size_t at = ((size_t)i * args->S + threadIdx.x) * 3;
-                const int32_t *const x = args->cfg + at, *const y = args->cfg2 + at;
-                same = x[0] == y[0] && x[1] == y[1] && x[2] == y[2];
-            }
+            wave_lds_fence();
+            const CostLds L = cost_lds(args->S, args->window);
+            // what put_row() made of the choices of both
+            const bool same =
+                (int)threadIdx.x >= args->S || cost_smem[L.pin + threadIdx.x] == SAME;
             stable = __ballot(!same) == 0ull;
         }
     }
     if (threadIdx.x == 0) args->stable[i] = stable ? 1 : 0;
 }
 
-template <int QUEUE, bool ONE>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8, 8))) void kc_stability(CostArgs)
+template <int QUEUE, int WIDTH>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6, 6))) void kc_stability(CostArgs)
 {
     const ArgsPtr args = kernel_args();
+    stability_instance<QUEUE, WIDTH>(args, (int)blockIdx.x);
     mark_workspace(args, STATE_KEPT | (args->c_fixed ? STATE_ONLY : 0) |
                              args->c_all << STATE_C_ALL);
-    stability_instance<QUEUE, ONE>(args, (int)blockIdx.x);
 }
 
 template <int QUEUE>
-CostKernel fallback_kernel(bool one)
+CostKernel fallback_kernel(int width)
 {
-    return one ? &kc_fallback<QUEUE, true> : &kc_fallback<QUEUE, false>;
+    switch (width) {
+    case WIDTH_PACKED: return &kc_fallback<QUEUE, PACKED>;
+    case 4: return &kc_fallback<QUEUE, 4>;
+    case 8: return &kc_fallback<QUEUE, 8>;
+    case 16: return &kc_fallback<QUEUE, 16>;
+    default: return &kc_fallback<QUEUE, 0>;
+    }
 }
 
 template <int QUEUE>
-CostKernel stability_kernel(bool one)
+CostKernel stability_kernel(int width)
 {
-    return one ? &kc_stability<QUEUE, true> : &kc_stability<QUEUE, false>;
+    switch (width) {
+    case WIDTH_PACKED: return &kc_stability<QUEUE, PACKED>;
+    case 4: return &kc_stability<QUEUE, 4>;
+    case 8: return &kc_stability<QUEUE, 8>;
+    case 16: return &kc_stability<QUEUE, 16>;
+    default: return &kc_stability<QUEUE, 0>;
+    }
 }
 
 }  // namespace
@@ -157,11 +156,11 @@ hipError_t launch_cost_fallback(const themis_problem_t& p, const Layout& L, cons
     a.ticks2 = out.ticks_h;
     a.cfg2 = out.cfg_h;
     a.lambda_v = out.lambda_v;
-    return launch_per_instance(p, L, a, st, false, [&](bool one) {
+    return launch_per_instance(p, L, a, st, false, [&](int width) {
         switch (p.queue_model) {
-        case THEMIS_QUEUE_SHARED: return fallback_kernel<THEMIS_QUEUE_SHARED>(one);
-        case THEMIS_QUEUE_WORST_CASE: return fallback_kernel<THEMIS_QUEUE_WORST_CASE>(one);
-        default: return fallback_kernel<THEMIS_QUEUE_PER_REPLICA>(one);
+        case THEMIS_QUEUE_SHARED: return fallback_kernel<THEMIS_QUEUE_SHARED>(width);
+        case THEMIS_QUEUE_WORST_CASE: return fallback_kernel<THEMIS_QUEUE_WORST_CASE>(width);
+        default: return fallback_kernel<THEMIS_QUEUE_PER_REPLICA>(width);
         }
     });
 }
@@ -181,11 +180,11 @@ hipError_t launch_cost_stability(const themis_problem_t& p, const Layout& L,
     a.cost2 = (int32_t*)(ws + B.cost_off);
     a.ticks2 = (int32_t*)(ws + B.ticks_off);
     a.cfg2 = (int32_t*)(ws + B.cfg_off);
-    return launch_per_instance(p, L, a, st, false, [&](bool one) {
+    return launch_per_instance(p, L, a, st, false, [&](int width) {
         switch (p.queue_model) {
-        case THEMIS_QUEUE_SHARED: return stability_kernel<THEMIS_QUEUE_SHARED>(one);
-        case THEMIS_QUEUE_WORST_CASE: return stability_kernel<THEMIS_QUEUE_WORST_CASE>(one);
-        default: return stability_kernel<THEMIS_QUEUE_PER_REPLICA>(one);
+        case THEMIS_QUEUE_SHARED: return stability_kernel<THEMIS_QUEUE_SHARED>(width);
+        case THEMIS_QUEUE_WORST_CASE: return stability_kernel<THEMIS_QUEUE_WORST_CASE>(width);
+        default: return stability_kernel<THEMIS_QUEUE_PER_REPLICA>(width);
         }
     });
 }

@@ -32,15 +32,15 @@
 //
 // Steps per instance, all of them within one wavefront:
 //   A  input check, budget; base[s], with the least (lt, index) at that cost.
-//      Lane = (model, batch size); a lane walks the cores upward from the first that
-//      can be feasible and stops where a lower bound of everything beyond exceeds
-//      the model's best.  When these candidates fit the budget together, x* = 0 and
-//      they are the answer.
+//      Lane = (model, batch size); a lane evaluates the first core count that can be
+//      feasible, and of the others those that can cost as little as the model's best.
+//      When these candidates fit the budget together, x* = 0 and they are the answer.
 //   F  else the fastest candidate of every (model, batch size), which is the one at
 //      the core cap (latency never grows with the cores): the instance is infeasible
 //      exactly when the fastest candidates of all models together exceed the budget.
-//   B  else the recurrence over the first 16 cells: one table of (lt, index) by model
-//      and cost over base in LDS, a row of the recurrence in every sixteen lanes.
+//   B  else the recurrence over the first 8 or 16 cells: one table of (lt, index) by
+//      model and cost over base in LDS, lane = (model, cell), rows of neighbouring models
+//      combined in turns.  How late the candidates of step A are says which it takes.
 //   C  else over 64 cells, rows in LDS, lane = cell;
 //   G  else lists of the candidates (of all, or where those do not fit of those that
 //      Lagrangian bounds leave), those that the bounds show to be in no answer dropped, and
@@ -57,23 +57,29 @@
 // with the candidate tables and the rate search, so that all agree bit for bit),
 // against 0.3 KB of inputs and outputs; nothing but those touches HBM.  Whole solves
 // by the three stages (dense / with dominated candidates pruned) against this one, in
-// microseconds: 65536 x 8 models 25800 / 3880 -> 100, 16384 x 8 with replicas given
-// 3370 -> 29, 86400 x 6 2790 -> 54, 4096 x 5 177 -> 12.6, 64 x 3 27.2 -> 6.7.
-#include "cost_solver.h"
+// microseconds: 65536 x 8 models 25800 / 3880 -> 78, 16384 x 8 with replicas given
+// 3370 -> 25, 86400 x 6 2790 -> 40, 4096 x 5 177 -> 11.3, 64 x 3 27.2 -> 6.1.
+#include "cost_front.h"
 
 namespace themis {
 namespace {
 
 // LISTED: the instances of a list, each workgroup some of them; else one per workgroup.
-template <int QUEUE, bool DERIVE, bool ONE, bool LISTED>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8, 8))) void kc_solve(CostArgs)
+// Seven wavefronts per SIMD, as LDS has room for: eight, with 64 registers, have to spill in the
+// steps that every instance takes (86400 x 6: 52 us instead of 42; six: 43.5).
+template <int QUEUE, bool DERIVE, int WIDTH, bool LISTED>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(7, 7))) void kc_solve(CostArgs)
 {
     const ArgsPtr args = kernel_args();
-    mark_workspace(args, STATE_KEPT | (DERIVE ? 0 : STATE_GIVEN) |
-                             (args->c_fixed ? STATE_ONLY : 0) | args->c_all << STATE_C_ALL);
+    auto mark = [](ArgsPtr p) {
+        p = Front<QUEUE, DERIVE, WIDTH>::afresh(p);
+        mark_workspace(p, STATE_KEPT | (DERIVE ? 0 : STATE_GIVEN) | (p->c_fixed ? STATE_ONLY : 0) |
+                              p->c_all << STATE_C_ALL);
+    };
     if (!LISTED) {
         const int i = (int)blockIdx.x;
-        solve_instance<QUEUE, DERIVE, ONE, PLAIN>(args, i, args->lambda[i]);
+        solve_instance<QUEUE, DERIVE, WIDTH, PLAIN>(args, i, args->lambda);
+        mark(args);
         return;
     }
     const int n = args->ctrl[LIST_WORD];
@@ -83,17 +89,28 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8, 8))) void
         ArgsPtr again = args;
         asm volatile("" : "+s"(again));
         const int i = __builtin_amdgcn_readfirstlane(again->list[k]);
-        solve_instance<QUEUE, DERIVE, ONE, PLAIN>(again, i, again->lambda[i]);
+        solve_instance<QUEUE, DERIVE, WIDTH, PLAIN>(again, i, again->lambda);
         wave_lds_fence();
+    }
+    mark(args);
+}
+
+template <int QUEUE, bool DERIVE, bool LISTED>
+CostKernel solve_kernel(int width)
+{
+    switch (width) {
+    case WIDTH_PACKED: return &kc_solve<QUEUE, DERIVE, PACKED, LISTED>;
+    case 4: return &kc_solve<QUEUE, DERIVE, 4, LISTED>;
+    case 8: return &kc_solve<QUEUE, DERIVE, 8, LISTED>;
+    case 16: return &kc_solve<QUEUE, DERIVE, 16, LISTED>;
+    default: return &kc_solve<QUEUE, DERIVE, 0, LISTED>;
     }
 }
 
 template <int QUEUE, bool DERIVE>
-CostKernel solve_kernel(bool listed, bool one)
+CostKernel solve_kernel(bool listed, int width)
 {
-    if (listed)
-        return one ? &kc_solve<QUEUE, DERIVE, true, true> : &kc_solve<QUEUE, DERIVE, false, true>;
-    return one ? &kc_solve<QUEUE, DERIVE, true, false> : &kc_solve<QUEUE, DERIVE, false, false>;
+    return listed ? solve_kernel<QUEUE, DERIVE, true>(width) : solve_kernel<QUEUE, DERIVE, false>(width);
 }
 
 }  // namespace
@@ -109,17 +126,17 @@ hipError_t launch_cost_solve(const themis_problem_t& p, const Layout& L, const i
     CostArgs a = cost_args(p, L, d_coef, d_lambda, d_slo_us, d_r_fixed, d_status, d_cost, d_ticks,
                            d_cfg, ws, opts);
     const bool listed = opts.list != nullptr;
-    return launch_per_instance(p, L, a, st, listed, [&](bool one) {
+    return launch_per_instance(p, L, a, st, listed, [&](int width) {
         switch (p.queue_model) {
         case THEMIS_QUEUE_SHARED:
-            return d_r_fixed ? solve_kernel<THEMIS_QUEUE_SHARED, false>(listed, one)
-                             : solve_kernel<THEMIS_QUEUE_SHARED, true>(listed, one);
+            return d_r_fixed ? solve_kernel<THEMIS_QUEUE_SHARED, false>(listed, width)
+                             : solve_kernel<THEMIS_QUEUE_SHARED, true>(listed, width);
         case THEMIS_QUEUE_WORST_CASE:
-            return d_r_fixed ? solve_kernel<THEMIS_QUEUE_WORST_CASE, false>(listed, one)
-                             : solve_kernel<THEMIS_QUEUE_WORST_CASE, true>(listed, one);
+            return d_r_fixed ? solve_kernel<THEMIS_QUEUE_WORST_CASE, false>(listed, width)
+                             : solve_kernel<THEMIS_QUEUE_WORST_CASE, true>(listed, width);
         default:
-            return d_r_fixed ? solve_kernel<THEMIS_QUEUE_PER_REPLICA, false>(listed, one)
-                             : solve_kernel<THEMIS_QUEUE_PER_REPLICA, true>(listed, one);
+            return d_r_fixed ? solve_kernel<THEMIS_QUEUE_PER_REPLICA, false>(listed, width)
+                             : solve_kernel<THEMIS_QUEUE_PER_REPLICA, true>(listed, width);
         }
     });
 }

@@ -13,40 +13,53 @@ constexpr uint32_t LT_NONE = 1u << 22;       // "no candidate": above any sum of
 constexpr uint32_t EMPTY = 0xFFFFFFFFu;      // empty cell of the (lt, index) table
 constexpr int INDEX_BITS = 13;               // candidate indices are below 8192
 constexpr uint32_t G_INF = 0x8000u;          // row cell beyond any budget
+constexpr uint32_t SAME = 0xFFFFFFFFu;       // for a choice: the one of the solve before
 
-// a batch size b, and recip_below(b * 1e6)
+// A batch size b: recip_below(b 1e6), (b - 1) 1e6, and in single precision b 1e6 and
+// b / (2 b - 1).  (What takes one instruction to form from these is not here: a launch
+// takes the longer the larger its arguments are.)
 struct __attribute__((aligned(16))) BatchConst {
-    double b, rM;
+    double rM, w;
+    float M, both;
+    int32_t size, unused;
 };
 
-struct CostArgs {
+// What every instance needs.
+struct HotArgs {
     const int32_t *coef, *lambda, *slo_us, *r_fixed, *c_fixed;
-    const int32_t* lambda2;  // stability test: the predicted rates
+    int32_t S, cs, n_batch, width_log, per_round;  // see Front
+    int32_t c_max, r_max, tick, slo_max;
+    int32_t coef_stride;  // words of an instance's coefficients (shared: 0)
+    int32_t c_all;
+    uint32_t magic;       // index_magic() of n_batch
+    int32_t window;       // cells of the largest window with rows in LDS, a multiple of 64
+    double rtick, tick_d, r_max_d;
+    uint32_t tick_magic;  // floor(2^32 / tick)
+    float r_max_f;
+    int32_t* keep;        // inputs and results for calls that inspect the workspace, or null
+    KeepLayout kept;
+    int32_t* tmeta;       // budgets, for such calls
     int32_t *status, *cost, *ticks, *cfg;
+};
+struct CostArgs : HotArgs {
+    const int32_t* lambda2;  // stability test: the predicted rates
     int32_t *status2, *cost2, *ticks2, *cfg2;  // results of the second kind, see ROLE
     int32_t *lambda_v, *stable;
-    int32_t* tmeta;     // budgets, for calls that inspect the workspace afterwards
     const int32_t* list;  // the instances to solve (LISTED)
     int32_t* ctrl;
-    uint16_t* frow;     // rows of step D, by budget
-    uint16_t* hrow;     // rows of steps G and W, by cost, where LDS has no room
+    uint16_t* frow;       // rows of step D, by budget
+    uint16_t* hrow;       // rows of steps G and W, by cost, where LDS has no room
     int32_t hrow_stride;  // cells of hrow per instance
-    int32_t* keep;      // inputs and results for such calls, or null
-    KeepLayout kept;
-    BatchConst bc[THEMIS_MAX_BATCH];
-    int32_t n_batch;
-    int32_t S, cs, c_max, r_max, tick, slo_max, coef_shared, c_all, row_stride;
-    int32_t window;     // cells of the largest window with rows in LDS, a multiple of 64
-    int32_t window_hbm; // and in HBM (no larger than the other: none)
-    uint32_t magic;     // index_magic() of n_batch
+    int32_t row_stride;
+    int32_t window_hbm;   // like `window`, in HBM (no larger than the other: none)
     uint32_t parts, pair_magic;  // lanes per (model, batch size) pair of a sweep, see sweep()
-    double rtick;
+    BatchConst bc[THEMIS_MAX_BATCH];
 };
 
-// LDS words of one wavefront.  From `tab` on, step B takes 32 words per model, a table
-// and rows of sixteen words; the window of 64 cells a table of 64 words per model and
-// S + 1 rows of 16-bit cells, each with a guard cell (and one of padding) in front; wider
-// windows a table of one model and such rows.
+// LDS words of one wavefront.  From `tab` on, steps B and C take a table of up to 64 words
+// per model and S + 1 rows: of 32-bit cells behind as many guard cells, or of 16-bit cells,
+// each with a guard cell (and one of padding) in front; wider windows a table of one model
+// and such rows.
 struct CostLds {
     int best, key, fast, pin, tab, rows, words;
 };
@@ -77,52 +90,38 @@ typedef int32_t words4 __attribute__((ext_vector_type(4), aligned(4)));
 // constant address space, so that uniform reads stay scalar loads.
 typedef const __attribute__((address_space(4))) CostArgs* ArgsPtr;
 
+// Inputs that no kernel of the solve writes: uniform reads as scalar loads.
+template <typename T>
+__device__ __forceinline__ const __attribute__((address_space(4))) T* constant(const T* p)
+{
+    return (const __attribute__((address_space(4))) T*)(uintptr_t)p;
+}
+
 extern __shared__ uint32_t cost_smem[];
 
-// The value D lanes down within the rows of sixteen that `ROWS` names; `fill` where
-// there is none, x itself in the other rows.
-template <int D, int ROWS = 0xF>
-__device__ __forceinline__ uint32_t row_shifted(uint32_t x, uint32_t fill)
-{
-    const uint32_t old = ROWS == 0xF ? fill : x;
-    return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)x, 0x110 | D, ROWS, 0xF, false);
-}
-
 __device__ __forceinline__ uint32_t least(uint32_t a, uint32_t b) { return a < b ? a : b; }
-
-// The least of the four lanes that have the same place in the rows of sixteen, in all
-// of them.
-__device__ __forceinline__ uint32_t least_of_rows(uint32_t x)
-{
-    typedef uint32_t two __attribute__((ext_vector_type(2)));
-    const two h = __builtin_amdgcn_permlane32_swap(x, x, false, false);
-    x = least(h.x, h.y);
-    const two q = __builtin_amdgcn_permlane16_swap(x, x, false, false);
-    return least(q.x, q.y);
-}
 
 // What a solve is for, which says where its results go: PLAIN, the caller's results and
 // the record; QUIET, the same without the record; SECOND, the second set of results;
 // PINNED, the second set and the record, with the cores of every model taken from LDS.
 enum { PLAIN, QUIET, SECOND, PINNED };
 // Besides the status of an instance: the steps so far did not suffice; the lists are made;
-// the lists are to be made by narrowing.
-constexpr int UNFINISHED = -1, ARE_LISTED = -2, TOO_MANY = -3;
+// the lists are to be made by narrowing; products exceed 2^42.
+constexpr int UNFINISHED = -1, ARE_LISTED = -2, TOO_MANY = -3, LARGE = -4;
 
-// What follows on step B is in functions of their own: FURTHER, step C and the lists of step
-// G where all candidates fit them, calls the others one after the other; NARROW, those lists
-// where they do not fit, by way of PRICE; GAP, step G up to its end, which is TRIAL, ROWS
-// or ROWS_HBM; WD, steps W and D.
-enum { PART_FURTHER, PART_PRICE, PART_NARROW, PART_GAP, PART_TRIAL, PART_ROWS, PART_ROWS_HBM, PART_WD };
+// What follows on the lists of step G, where all candidates fit them, is in functions of their
+// own, called one after the other: NARROW, those lists where they do not fit, by way of
+// PRICE; GAP, step G up to its end, which is TRIAL, ROWS or ROWS_HBM; WD, steps W and D.
+enum { PART_PRICE, PART_NARROW, PART_GAP, PART_TRIAL, PART_ROWS, PART_ROWS_HBM, PART_WD };
 template <int QUEUE, bool DERIVE, int ROLE, int PART>
 __device__ __attribute__((noinline)) int solve_part(uint64_t args, int i, int T, int32_t lam,
                                                     int32_t slo, int x);
 
-// One wavefront's view of the instance it works on.  ONE: its (model, batch size)
-// pairs fit the lanes, so every lane keeps its own from step A on.
-template <int QUEUE, bool DERIVE, bool ONE, int ROLE = PLAIN>
+// One wavefront's view of the instance it works on.
+template <int QUEUE, bool DERIVE, int ROLE>
 struct Solver {
-    const __attribute__((address_space(4))) CostArgs& a;
+    const ArgsPtr args;
+    HotArgs a;
     uint32_t* const lds;  // the wavefront's words: a workgroup is one wavefront
     const CostLds L;
     const int lane;
@@ -132,10 +131,26 @@ struct Solver {
     int32_t lam, slo;
     int32_t lane_b;  // lane j: batch size j
 
-    __device__ __forceinline__ explicit Solver(ArgsPtr args)
-        : a(*args), lds(cost_smem), L(cost_lds(args->S, args->window)),
-          lane(threadIdx.x)
+    __device__ __forceinline__ explicit Solver(ArgsPtr p)
+        : args(p), a(hot_args(p)), lds(cost_smem), L(cost_lds(p->S, p->window)), lane(threadIdx.x)
     {
+    }
+    static __device__ __forceinline__ HotArgs hot_args(ArgsPtr p)
+    {
+        HotArgs h;
+        h.coef = p->coef, h.lambda = p->lambda, h.slo_us = p->slo_us;
+        h.r_fixed = p->r_fixed, h.c_fixed = p->c_fixed;
+        h.S = p->S, h.cs = p->cs, h.n_batch = p->n_batch, h.width_log = p->width_log, h.per_round = p->per_round;
+        h.c_max = p->c_max, h.r_max = p->r_max, h.tick = p->tick, h.slo_max = p->slo_max;
+        h.coef_stride = p->coef_stride, h.c_all = p->c_all, h.magic = p->magic;
+        h.window = p->window, h.rtick = p->rtick, h.tick_d = p->tick_d, h.r_max_d = p->r_max_d;
+        h.tick_magic = p->tick_magic, h.r_max_f = p->r_max_f;
+        h.keep = p->keep;
+        h.kept.coef = p->kept.coef, h.kept.given = p->kept.given, h.kept.only = p->kept.only;
+        h.kept.cfg = p->kept.cfg, h.kept.words = p->kept.words;
+        h.tmeta = p->tmeta;
+        h.status = p->status, h.cost = p->cost, h.ticks = p->ticks, h.cfg = p->cfg;
+        return h;
     }
 
     // What a lane works on: one model and one batch size, cores lo .. last.
@@ -143,9 +158,12 @@ struct Solver {
         RowHdr h;
         BatchHdr bh;
         double num, fixed;  // numerator of the division by the cores; what they do not shrink
-        double lam_per_M;   // at most lambda / (b 1e6)
+        double ratio;       // at most lambda / (b 1e6), by 2^-44 of it or less
+        float M, w, both;   // b 1e6, (b - 1) 1e6, see BatchConst
+        int32_t size;
         uint32_t s, j, lo, last, pcap;
-        bool there, valid;
+        bool there, valid;  // there: the lane has a pair
+        bool in, first;     // its model exists; it is the model's first
     };
 
     __device__ __forceinline__ Pair pair_of(uint32_t s, uint32_t j, bool there) const
@@ -154,74 +172,64 @@ struct Solver {
         p.there = there;
         p.s = there ? s : 0u;
         p.j = there ? j : 0u;
-        const double b = a.bc[p.j].b;
-        const double rM = a.bc[p.j].rM;
+        p.in = s < (uint32_t)a.S;
+        p.first = j == 0u;
+        const auto& bc = args->bc[p.j];
+        p.bh.rM = bc.rM, p.bh.w = bc.w;
+        p.M = bc.M, p.both = bc.both, p.size = bc.size;
+        p.bh.b = (double)p.size;
+        p.bh.b2 = p.bh.b * p.bh.b;
+        p.bh.M = p.bh.b * 1.0e6;
+        p.w = (float)p.bh.w;
         const size_t row0 = (size_t)i * a.S;
-        const int32_t* const cf = a.coef + (a.coef_shared ? 0 : row0 * a.cs) + p.s * (uint32_t)a.cs;
+        const int32_t* const cf = a.coef + (size_t)i * (uint32_t)a.coef_stride + p.s * (uint32_t)a.cs;
         const words4 c4 = *reinterpret_cast<const words4*>(cf);
-        int32_t v[6] = {c4.x, c4.y, c4.z, c4.w, cf[4], 0};
-        if (a.cs == 6) v[5] = cf[5];
+        const int32_t v4 = cf[4];
+        int32_t v5 = 0;
+        const bool eq1 = a.cs == 6;
+        if (eq1) v5 = cf[5];
         const int32_t given = DERIVE ? 0 : (a.r_fixed + row0)[p.s];
-        const int32_t only = ROLE == PINNED ? (int32_t)lds[L.pin + p.s]
-                             : a.c_fixed    ? (a.c_fixed + row0)[p.s]
-                                            : a.c_all;
         // a, k, q, d in 0 .. max, p >= 1, o in 1 .. max
-        uint32_t top = (uint32_t)v[0] > (uint32_t)v[1] ? (uint32_t)v[0] : (uint32_t)v[1];
-        top = (uint32_t)v[2] > top ? (uint32_t)v[2] : top;
-        top = (uint32_t)v[5] > top ? (uint32_t)v[5] : top;
-        p.valid = top <= (uint32_t)THEMIS_VALUE_MAX && v[3] >= 1 && in_range(v[4], 1, THEMIS_VALUE_MAX);
-        if (!DERIVE) p.valid = p.valid && in_range(given, 1, a.r_max);
-        if (ROLE != PINNED && a.c_fixed) p.valid = p.valid && in_range(only, 1, a.c_max);
-        p.h = make_row_hdr(v, 6u, lam, slo, T, (uint32_t)a.tick, given);
-        p.bh.b = b;
-        p.bh.b2 = b * b;
-        p.bh.M = b * 1.0e6;
-        p.bh.rM = rM;
-        p.bh.w = p.bh.M - 1.0e6;
-        p.pcap = (uint32_t)v[3];
-        p.lo = only > 0 ? (uint32_t)only : 1u;
-        const uint32_t hi = only > 0 ? (uint32_t)only : (uint32_t)a.c_max;
+        uint32_t top = (uint32_t)c4.x > (uint32_t)c4.y ? (uint32_t)c4.x : (uint32_t)c4.y;
+        top = (uint32_t)c4.z > top ? (uint32_t)c4.z : top;
+        top = (uint32_t)v5 > top ? (uint32_t)v5 : top;
+        p.valid = (int)(top <= (uint32_t)THEMIS_VALUE_MAX) & (int)(c4.w >= 1) &
+                  (int)in_range(v4, 1, THEMIS_VALUE_MAX);
+        if (!DERIVE) p.valid &= (int)in_range(given, 1, a.r_max);
+        // the cores: all, or one count for all models, or one for each
+        p.lo = a.c_all > 0 ? (uint32_t)a.c_all : 1u;
+        uint32_t hi = a.c_all > 0 ? (uint32_t)a.c_all : (uint32_t)a.c_max;
+        if (ROLE == PINNED) {
+            p.lo = hi = lds[L.pin + p.s];
+        } else if (a.c_fixed) {
+            const int32_t only = (a.c_fixed + row0)[p.s];
+            p.valid &= (int)in_range(only, 1, a.c_max);
+            p.lo = hi = only > 0 ? (uint32_t)only : 1u;
+        }
+        p.pcap = (uint32_t)c4.w;
         // beyond the cap a candidate has the cap's latency and costs more
         const uint32_t reach = p.pcap > p.lo ? p.pcap : p.lo;
         p.last = hi < reach ? hi : reach;
+        p.h.a = (double)c4.x, p.h.k = (double)c4.y, p.h.q = (double)c4.z, p.h.o = (double)v4;
+        p.h.d = (double)v5;
+        p.h.p = (double)c4.w;
+        p.h.slo = (double)slo, p.h.T = (double)T;
+        p.h.n_given = (double)given;
         p.num = __builtin_fma(p.h.q, p.bh.b2, __builtin_fma(p.h.k, p.bh.b, p.h.a));
-        p.fixed = __builtin_fma(p.h.d, p.bh.b, p.h.o);
-        p.lam_per_M = p.h.lam * p.bh.rM * (1.0 - 0x1p-40);
+        p.fixed = p.h.o;
+        if (eq1) p.fixed = __builtin_fma(p.h.d, p.bh.b, p.fixed);
+        set_rate(p);
         return p;
     }
 
-    // The pair kept from another rate at the rate `lam` (where pairs are not kept they are
-    // formed at that rate anyway).
-    __device__ __forceinline__ Pair at_rate(Pair p) const
+    // What depends on the rate.
+    __device__ __forceinline__ void set_rate(Pair& p) const
     {
-        if (ONE) {
-            p.h.lam = (double)lam;
-            p.h.rlam = recip_below(p.h.lam);
-            p.h.lt_den = p.h.lam * (double)a.tick;
-            p.h.rlt_den = recip_below(p.h.lt_den);
-            p.lam_per_M = p.h.lam * p.bh.rM * (1.0 - 0x1p-40);
-        }
-        return p;
-    }
-
-    // this lane's pair of the round that starts with pair r
-    __device__ __forceinline__ Pair pair_of_round(uint32_t r) const
-    {
-        const uint32_t x = r + (uint32_t)lane;
-        const uint32_t s = index_quotient(x, a.magic);  // x < 64 * 16 + 64
-        return pair_of(s, x - s * (uint32_t)a.n_batch, x < (uint32_t)(a.S * a.n_batch));
-    }
-
-    // Calls f(pair) for this lane's pair of every round of 64; lanes without one get a
-    // pair with `there` unset.  `mine`: the pair, where there is one round only.
-    template <typename F>
-    __device__ __forceinline__ void for_pairs(const Pair& mine, F f) const
-    {
-        if constexpr (ONE) {
-            f(mine);
-        } else {
-            for (uint32_t r = 0; r < (uint32_t)(a.S * a.n_batch); r += 64u) f(pair_of_round(r));
-        }
+        p.h.lam = (double)lam;
+        p.h.rlam = recip_below(p.h.lam);
+        p.h.lt_den = p.h.lam * a.tick_d;
+        p.h.rlt_den = recip_below(p.h.lt_den);
+        p.ratio = p.h.lam * p.bh.rM;
     }
 
     // Reciprocals of the core counts, for loops over them: lane l holds that of l + 1, a
@@ -244,7 +252,7 @@ struct Solver {
     __device__ __forceinline__ Eval eval(const Pair& p, double rd) const
     {
         return eval_parts<QUEUE, SMALL, DERIVE ? N_DERIVED : N_GIVEN>(
-            p.h, p.bh, p.num, p.fixed, rd, (double)a.r_max, (double)a.tick, a.rtick);
+            p.h, p.bh, p.num, p.fixed, rd, a.r_max_d, a.tick_d, a.rtick);
     }
 
     static __device__ __forceinline__ uint32_t speed(const Pair& p, uint32_t c)
@@ -260,24 +268,20 @@ struct Solver {
     __device__ __forceinline__ uint32_t first_core(const Pair& p) const
     {
         constexpr float UP = 1.00001f, DOWN = 0.99999f;
-        const float room = (float)((double)T * (double)a.tick) * UP;
+        const float room = (float)(T * a.tick) * UP;
         const float rl = __builtin_amdgcn_rcpf((float)lam);
-        const float b = (float)p.bh.b;
-        const float n_max = DERIVE ? (float)a.r_max : (float)p.h.n_given;
-        float most = n_max * (float)p.bh.M * rl * UP;
-        float wait = (float)p.bh.w * rl * DOWN;
+        const float n_max = DERIVE ? a.r_max_f : (float)p.h.n_given;
+        float wait = rl * DOWN * p.w;
         if (QUEUE == THEMIS_QUEUE_PER_REPLICA && !DERIVE) wait *= n_max;
-        most = room - wait < most ? room - wait : most;
-        if (QUEUE == THEMIS_QUEUE_PER_REPLICA && DERIVE) {
-            // n >= lambda proc / (b 1e6), so the queue is at least (b - 1) / b proc
-            const float both = room * b * __builtin_amdgcn_rcpf(2.0f * b - 1.0f) * UP;
-            most = both < most ? both : most;
-        }
+        float most = __builtin_fminf(n_max * rl * UP * p.M, room - wait);
+        // n >= lambda proc / (b 1e6), so the queue is at least (b - 1) / b proc
+        if (QUEUE == THEMIS_QUEUE_PER_REPLICA && DERIVE)
+            most = __builtin_fminf(most, room * UP * p.both);
         const float left = most - (float)p.fixed * DOWN;
         const float c = (float)p.num * __builtin_amdgcn_rcpf(left) * DOWN;
-        if (!(left > 0.0f) || c > (float)p.last) return p.last + 1u;
-        const uint32_t c0 = (uint32_t)__builtin_ceilf(c);
-        return c0 > p.lo ? c0 : p.lo;
+        const uint32_t c0 = (uint32_t)__builtin_ceilf(__builtin_fminf(c, 1.0e6f));
+        // (c >= 0: num is)
+        return !(left > 0.0f) || c0 > p.last ? p.last + 1u : c0 > p.lo ? c0 : p.lo;
     }
 
     // Whether a candidate of the pair with c cores or more can cost as little as
@@ -286,7 +290,7 @@ struct Solver {
     {
         if (!DERIVE) return (double)c * p.h.n_given <= (double)limit;
         return c <= limit &&
-               __builtin_fma((double)c, p.fixed, p.num) * p.lam_per_M <= (double)limit;
+               __builtin_fma((double)c, p.fixed, p.num) * p.ratio <= (double)limit * (1.0 + 0x1p-40);
     }
 
     // per model: cost << 15 | lt of the best candidate met so far; the same with the
@@ -316,7 +320,7 @@ struct Solver {
     // where configurations go
     __device__ __forceinline__ int32_t* config() const
     {
-        return (ROLE == SECOND || ROLE == PINNED ? a.cfg2 : a.cfg) + (size_t)i * a.S * 3;
+        return (ROLE == SECOND || ROLE == PINNED ? args->cfg2 : a.cfg) + (size_t)i * a.S * 3;
     }
 
     __device__ __forceinline__ void record_result(int32_t status, int32_t cost, int32_t ticks,
@@ -334,9 +338,9 @@ struct Solver {
     {
         constexpr bool TWO = ROLE == SECOND || ROLE == PINNED;
         if (lane == 0) {
-            (TWO ? a.status2 : a.status)[i] = status;
-            (TWO ? a.cost2 : a.cost)[i] = cost;
-            (TWO ? a.ticks2 : a.ticks)[i] = ticks;
+            (TWO ? args->status2 : a.status)[i] = status;
+            (TWO ? args->cost2 : a.cost)[i] = cost;
+            (TWO ? args->ticks2 : a.ticks)[i] = ticks;
         }
         record_result(status, cost, ticks, step);
     }
@@ -352,17 +356,16 @@ struct Solver {
         }
     }
 
-    // lane s < S: index and cost of model s's candidate
-    __device__ __forceinline__ void put_choice(uint32_t k, uint32_t cost) const
+    // Model s's candidate into the configuration, of the lanes with `who`: its cores, batch
+    // size, index and cost.
+    __device__ __forceinline__ void put_row(bool who, uint32_t s, uint32_t c, int32_t b, uint32_t k,
+                                            uint32_t cost) const
     {
-        const uint32_t q = index_quotient(k, a.magic);
-        const uint32_t c = q + 1u;
-        const int32_t b = __shfl(lane_b, (int)(k - q * (uint32_t)a.n_batch), 64);
-        if (lane >= a.S) return;
+        if (!who) return;
         // cost / c: the exact quotient is a whole number up to 32767, half of 1 / c away
         // from where the truncation would go wrong
         const uint32_t n = (uint32_t)(((float)cost + 0.5f) * __builtin_amdgcn_rcpf((float)c));
-        const uint32_t off = 3u * (uint32_t)lane;
+        const uint32_t off = 3u * s;
         int32_t* const out = config();
         out[off] = (int32_t)c;
         out[off + 1u] = b;
@@ -373,13 +376,32 @@ struct Solver {
             kp[off + 1u] = b;
             kp[off + 2u] = (int32_t)n;
         }
+        // for what the entry point does with it next
+        if (ROLE != PINNED) {
+            uint32_t* const at = lds + L.pin + s;
+            const uint32_t choice = n << INDEX_BITS | k;
+            *at = ROLE == SECOND && *at == choice ? SAME : choice;
+        }
+    }
+    // ... by its index and cost (of all lanes together)
+    __device__ __forceinline__ void put_row(bool who, uint32_t s, uint32_t k, uint32_t cost) const
+    {
+        const uint32_t q = index_quotient(k, a.magic);
+        const int32_t b = __shfl(lane_b, (int)(k - q * (uint32_t)a.n_batch), 64);
+        put_row(who, s, q + 1u, b, k, cost);
+    }
+
+    // lane s < S: index and cost of model s's candidate
+    __device__ __forceinline__ void put_choice(uint32_t k, uint32_t cost) const
+    {
+        put_row(lane < a.S, (uint32_t)lane, k, cost);
     }
 
     // The instance's inputs into its record, see STATE_WORD.  `word`: word `lane` of the
     // coefficients, loaded with the rest of the inputs.
     __device__ __forceinline__ bool keeps_coef() const
     {
-        return records() && !a.coef_shared;  // shared: see mark_workspace()
+        return records() && a.coef_stride;  // shared: see mark_workspace()
     }
     __device__ __forceinline__ void keep_inputs(bool valid, int32_t word) const
     {
@@ -402,127 +424,29 @@ struct Solver {
         }
     }
 
-    // ---- step A ------------------------------------------------------------------
-    template <bool SMALL>
-    __device__ __forceinline__ void least_costs(const Pair& first) const
-    {
-        for_pairs(first, [&](const Pair& p) {
-            uint32_t best = EMPTY, best_c = 0;
-            auto meet = [&](uint32_t c, double rd) {
-                const Eval ev = eval<SMALL>(p, rd);
-                if (ev.lt >= 0) {
-                    const uint32_t key = (__umul24((uint32_t)ev.n, c) << 15) | (uint32_t)ev.lt;
-                    // (cores ascend: of equal keys the first one met has the smaller index)
-                    if (key < best) best = key, best_c = c;
-                    atomicMin(&keys()[p.s], key);
-                }
-            };
-            auto goes_on = [&](uint32_t c) {
-                return c <= p.last && may_cost(p, c, keys()[p.s] >> 15);
-            };
-            // most pipelines at low rates are done with the first core count
-            uint32_t c = p.lo;
-            if (p.there) meet(c, recip_below((double)speed(p, c)));
-            wave_lds_fence();
-            ++c;
-            bool go = p.there && goes_on(c);
-            if (__ballot(go) != 0ull) {
-                const uint32_t c0 = first_core(p);
-                c = c0 > c ? c0 : c;
-                const Recips rc = recips();
-                for (;;) {
-                    go = go && goes_on(c);
-                    if (__ballot(go) == 0ull) break;
-                    const double rd = recip(rc, go ? speed(p, c) : 1u);
-                    if (go) meet(c++, rd);
-                    wave_lds_fence();
-                }
-            }
-            if (best != EMPTY)
-                atomicMin(&bests()[p.s],
-                          ((unsigned long long)best << INDEX_BITS) |
-                              ((best_c - 1u) * (uint32_t)a.n_batch + p.j));
-        });
-        wave_lds_fence();
-    }
-
-    // ---- step F ------------------------------------------------------------------
-    template <bool SMALL>
-    __device__ __forceinline__ uint32_t fastest_ticks(const Pair& first) const
-    {
-        if (lane < a.S) fastest()[lane] = EMPTY;
-        wave_lds_fence();
-        for_pairs(first, [&](const Pair& p) {
-            if (!p.there) return;
-            const Eval ev = eval<SMALL>(p, recip_below((double)speed(p, p.last)));
-            if (ev.lt >= 0)
-                atomicMin(&fastest()[p.s],
-                          (uint32_t)ev.lt << 15 | __umul24((uint32_t)ev.n, p.last));
-        });
-        wave_lds_fence();
-        return sum_models(lane < a.S ? fastest()[lane] >> 15 : 0u);  // none: beyond any budget
-    }
-
     // ---- step B ------------------------------------------------------------------
     static __device__ __forceinline__ uint32_t entry(const Eval& ev, uint32_t k)
     {
         return ((uint32_t)ev.lt << INDEX_BITS) | k;
     }
 
-    // The table of (lt, index) by cost over base, W cells per model.
-    template <bool SMALL, int W>
-    __device__ __forceinline__ void fill_all(const Pair& first) const
-    {
-        uint32_t* const tab = lds + L.tab;
-        for (int x = lane; x < a.S * W; x += 64) tab[x] = EMPTY;
-        const Recips rc = recips();
-        wave_lds_fence();
-        for_pairs(first, [&](const Pair& p) {
-            const uint32_t base = keys()[p.s] >> 15;
-            const uint32_t top = base + (uint32_t)W - 1u;
-            uint32_t* const mine = tab + p.s * (uint32_t)W;
-            auto enter = [&](const Eval& ev, uint32_t c) {
-                const uint32_t cost = __umul24((uint32_t)ev.n, c);
-                if (ev.lt >= 0 && cost <= top)
-                    atomicMin(&mine[cost - base], entry(ev, (c - 1u) * (uint32_t)a.n_batch + p.j));
-            };
-            // two at a time: their chains of dependent operations fill each other's waits
-            uint32_t c = first_core(p);
-            for (;;) {
-                const bool go = p.there && c <= p.last && may_cost(p, c, top);
-                if (__ballot(go) == 0ull) break;
-                const uint32_t c1 = c < p.last ? c + 1u : c;
-                const double r0 = recip(rc, go ? speed(p, c) : 1u);
-                const double r1 = recip(rc, go ? speed(p, c1) : 1u);
-                if (go) {
-                    const Eval e0 = eval<SMALL>(p, r0), e1 = eval<SMALL>(p, r1);
-                    enter(e0, c);
-                    enter(e1, c1);
-                    c += 2u;
-                }
-            }
-        });
-        wave_lds_fence();
-    }
-
-    // Forward over the models, with the table of W <= 64 cells per model: the smallest
+    // Forward over the models, with the table of 64 cells per model: the smallest
     // index among the candidates that continue an optimum of x cells over base and
     // `ticks`.  rest(s, y): cell y of row s + 1; lane s: base of model s.
-    template <int W, typename F>
+    template <typename F>
     __device__ __forceinline__ int read_out(uint32_t total, uint32_t ticks, int x,
                                             uint32_t my_base, F rest) const
     {
         constexpr uint32_t INDEX = (1u << INDEX_BITS) - 1u;
         const uint32_t* const tab = lds + L.tab;
         uint32_t t = ticks, my_k = 0, my_cost = my_base;
-        const int d = lane & (W - 1);
+        const int d = lane, over = x;
         uint32_t e = tab[d];
         for (int s = 0; s < a.S; ++s) {
             const bool more_models = s + 1 < a.S;
             const uint32_t r = more_models ? rest(s, x >= d ? x - d : 0) : 0u;
-            const uint32_t e_next = more_models ? tab[(s + 1) * W + d] : 0u;
+            const uint32_t e_next = more_models ? tab[(s + 1) * 64 + d] : 0u;
             unsigned long long who = __ballot(d <= x && (e >> INDEX_BITS) + r == t);
-            if (W < 64) who &= (1ull << (W & 63)) - 1ull;
             if (who == 0ull) {  // never expected
                 put_none(THEMIS_INTERNAL);
                 return THEMIS_INTERNAL;
@@ -539,46 +463,9 @@ struct Solver {
             x -= l;
             e = e_next;
         }
-        put(THEMIS_SOLVED, (int32_t)total, (int32_t)ticks, W == 16 ? BY_B : BY_C);
+        put(THEMIS_SOLVED, (int32_t)total, (int32_t)ticks, over < 16 ? BY_B : BY_C);
         put_choice(my_k, my_cost);
         return THEMIS_SOLVED;
-    }
-
-    // The recurrence over 16 cells.  Every row of sixteen lanes holds g[s+1][0..15]; row r
-    // takes the table's costs 4 q + r, so its copy is first shifted by r and then by 4 q,
-    // both operand modifiers, and the four rows' minima are combined.  (What does not beat
-    // everything cheaper does no harm.)  `base_sum`: the sum of the models' least costs.
-    __device__ __forceinline__ int solve_sixteen(uint32_t base_sum, uint32_t my_base) const
-    {
-        const uint32_t* const tab = lds + L.tab;
-        uint32_t* const rows = lds + L.tab + 16 * a.S;
-        uint32_t g = 0u;  // g[S]: nothing left to run
-        const int at = lane >> 4;
-        for (int s = a.S - 1; s >= 0; --s) {
-            const uint32_t* const mine = tab + s * 16 + at;
-            uint32_t v[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = mine[4 * q] >> INDEX_BITS;  // EMPTY: 2^19 - 1
-            uint32_t h = row_shifted<1, 0x2>(g, LT_NONE);
-            // the lanes a shift leaves without a source keep their own value: mark them
-            h = row_shifted<2, 0x4>(h, LT_NONE);
-            h = row_shifted<3, 0x8>(h, LT_NONE);
-            h = (lane & 15) < at ? LT_NONE : h;
-            uint32_t acc = h + v[0];
-            acc = least(acc, row_shifted<4>(h, LT_NONE) + v[1]);
-            acc = least(acc, row_shifted<8>(h, LT_NONE) + v[2]);
-            acc = least(acc, row_shifted<12>(h, LT_NONE) + v[3]);
-            g = least_of_rows(acc);
-            if (lane < 16) rows[s * 16 + lane] = g;
-        }
-        const uint32_t m = (uint32_t)__ballot(g <= (uint32_t)T) & 0xFFFFu;
-        if (m == 0u) return UNFINISHED;
-        const int x = __builtin_ctz(m);
-        const uint32_t ticks = lane_value(g, x);
-        const uint32_t total = base_sum + (uint32_t)x;
-        wave_lds_fence();
-        return read_out<16>(total, ticks, x, my_base,
-                            [&](int s, int y) { return rows[(s + 1) * 16 + y]; });
     }
 
     // ---- sweeps over the candidates, for steps C and G -----------------------------
@@ -595,7 +482,7 @@ struct Solver {
         const float most = (float)limit * 1.0001f;
         float hi;
         if (DERIVE) {
-            hi = ((float)limit * __builtin_amdgcn_rcpf((float)p.lam_per_M) * 1.0001f -
+            hi = ((float)limit * __builtin_amdgcn_rcpf((float)p.ratio) * 1.0001f -
                   (float)p.num * 0.9999f) *
                      __builtin_amdgcn_rcpf((float)p.fixed) * 1.0001f + 1.0f;
             hi = most < hi ? most : hi;
@@ -634,7 +521,7 @@ struct Solver {
         };
         const float M = per_us * num, latency = per_us * (fixed + wait);
         if (DERIVE) {
-            const float rate = (float)p.lam_per_M;
+            const float rate = (float)p.ratio;
             const bool each_queues = QUEUE == THEMIS_QUEUE_PER_REPLICA;
             const float both = 2.0f - __builtin_amdgcn_rcpf((float)p.bh.b) * 1.0001f;
             auto cuts = [&](float k0, float k1) {
@@ -659,7 +546,7 @@ struct Solver {
     // latency than it costs.
     __device__ __forceinline__ uint32_t likely_core(const Pair& p, float mu, uint32_t more) const
     {
-        const float num = (float)p.num, fixed = (float)p.fixed, rate = (float)p.lam_per_M;
+        const float num = (float)p.num, fixed = (float)p.fixed, rate = (float)p.ratio;
         const float last = (float)p.last;
         float n = (float)p.h.n_given, least_c = 0.0f;
         if (DERIVE) {
@@ -686,8 +573,8 @@ struct Solver {
     {
         const Recips rc = recips();
         const bool few = ROLE == PINNED || a.c_fixed || a.c_all || a.c_max <= 2;
-        const uint32_t pairs = (uint32_t)(a.S * a.n_batch), parts = a.parts;
-        const uint32_t part = parts > 1u ? index_quotient((uint32_t)lane, a.pair_magic) : 0u;
+        const uint32_t pairs = (uint32_t)(a.S * a.n_batch), parts = args->parts;
+        const uint32_t part = parts > 1u ? index_quotient((uint32_t)lane, args->pair_magic) : 0u;
         auto after = [&](uint32_t c) {
             return c + (HOW == SAMPLE && (c >> 3) > parts ? c >> 3 : parts);
         };
@@ -758,26 +645,6 @@ struct Solver {
                 if (ev.lt >= 0) use(q)(c, (uint32_t)ev.lt, __umul24((uint32_t)ev.n, c));
             }
         }
-    }
-
-    // The table of 64 cells per model.  (With the replicas given the ranges are even and the
-    // plain loop is the faster one, by half a microsecond at 16384 x 8.)
-    __device__ __forceinline__ void fill_sixtyfour() const
-    {
-        if (!DERIVE) return fill_all<false, 64>(Pair());
-        uint32_t* const tab = lds + L.tab;
-        for (int x = lane; x < a.S * 64; x += 64) tab[x] = EMPTY;
-        wave_lds_fence();
-        sweep<DEALT>(
-            [&](const Pair& p) { return cores_up_to(p, (keys()[p.s] >> 15) + 63u); },
-            [&](const Pair& p) {
-                return [=, base = keys()[p.s] >> 15, mine = tab + 64u * p.s, j = p.j](
-                           uint32_t c, uint32_t lt, uint32_t cost) {
-                    if (cost - base < 64u)
-                        atomicMin(&mine[cost - base],
-                                  (lt << INDEX_BITS) | ((c - 1u) * (uint32_t)a.n_batch + j));
-                };
-            });
     }
 
     // ---- step G ------------------------------------------------------------------
@@ -1325,7 +1192,7 @@ struct Solver {
         const uint32_t my_floor = there ? l.floor[lane] : 0u, my_kept = there ? l.kept[lane] : 1u;
         const uint32_t my_first = there ? l.first[lane] : 0u;
         const int floor = (int)sum_models(my_floor);
-        uint16_t* const rows = HBM ? a.hrow + (size_t)i * a.hrow_stride
+        uint16_t* const rows = HBM ? args->hrow + (size_t)i * args->hrow_stride
                                    : reinterpret_cast<uint16_t*>(l.free);
         auto rows_fence = [] {  // a row's lanes read what others wrote
             if (HBM)
@@ -1579,7 +1446,7 @@ struct Solver {
         if (m == 0ull) return UNFINISHED;
         const int x = __builtin_ctzll(m);
         const uint32_t my_base = lane < a.S ? keys()[lane] >> 15 : 0u;
-        return read_out<64>(sum_models(my_base) + (uint32_t)x, lane_value(acc, x), x, my_base,
+        return read_out(sum_models(my_base) + (uint32_t)x, lane_value(acc, x), x, my_base,
                             [&](int s, int y) { return (uint32_t)row_of(s + 1)[y]; });
     }
 
@@ -1613,7 +1480,7 @@ struct Solver {
     __device__ __forceinline__ int solve_window(int W) const
     {
         uint32_t* const tab = lds + L.tab;
-        uint16_t* const rows = HBM ? a.hrow + (size_t)i * a.hrow_stride
+        uint16_t* const rows = HBM ? args->hrow + (size_t)i * args->hrow_stride
                                    : reinterpret_cast<uint16_t*>(lds + L.rows);
         // a row's lanes read what others wrote
         auto rows_fence = [] {
@@ -1747,11 +1614,11 @@ struct Solver {
         uint32_t* const tab = lds + L.tab;
         uint32_t* const list = lds + L.rows;  // lt | cost << 16
         const int cap = a.S * W / 2;          // entries of the list (the rows have room)
-        uint16_t* const rows = a.frow + (size_t)i * a.S * a.row_stride;
+        uint16_t* const rows = args->frow + (size_t)i * a.S * args->row_stride;
         const uint32_t nbat = (uint32_t)a.n_batch;
         for (int s = a.S - 1; s >= 0; --s) {
-            uint16_t* const out = rows + (size_t)s * a.row_stride;
-            const uint16_t* const next = out + a.row_stride;
+            uint16_t* const out = rows + (size_t)s * args->row_stride;
+            const uint16_t* const next = out + args->row_stride;
             const bool first_model = s == a.S - 1;
             const Pair p0 = pair_of((uint32_t)s, 0u, true);
             const uint32_t count = (p0.last - p0.lo + 1u) * nbat;
@@ -1830,7 +1697,7 @@ struct Solver {
         const int t_star = t;
         uint32_t my_k = 0, my_cost = 0, target = best;
         for (int s = 0; s < a.S; ++s) {
-            const uint16_t* const next = rows + (size_t)(s + 1) * a.row_stride;
+            const uint16_t* const next = rows + (size_t)(s + 1) * args->row_stride;
             const Pair p0 = pair_of((uint32_t)s, 0u, true);
             const uint32_t count = (p0.last - p0.lo + 1u) * nbat;
             bool found = false;
@@ -1860,42 +1727,16 @@ struct Solver {
         return THEMIS_SOLVED;
     }
 
-    // Steps A, F and B.
-    template <bool SMALL>
-    __device__ __forceinline__ int solve_valid(const Pair& first) const
-    {
-        least_costs<SMALL>(first);
-        uint32_t key = 0, k = 0, lt = 0;
-        if (lane < a.S) {
-            const unsigned long long best = bests()[lane];
-            key = (uint32_t)(best >> INDEX_BITS);
-            k = (uint32_t)best & ((1u << INDEX_BITS) - 1u);
-            lt = key == EMPTY ? LT_NONE : key & 0x7FFFu;
-        }
-        const uint32_t ticks = sum_models(lt);
-        if (ticks <= (uint32_t)T) {
-            put(THEMIS_SOLVED, (int32_t)sum_models(key >> 15), (int32_t)ticks);
-            put_choice(k, key >> 15);
-            return THEMIS_SOLVED;
-        }
-        if (ticks >= LT_NONE || fastest_ticks<SMALL>(first) > (uint32_t)T) return THEMIS_INFEASIBLE;
-        fill_all<SMALL, 16>(first);
-        const int status = solve_sixteen(sum_models(key >> 15), key >> 15);
-        wave_lds_fence();
-        return status;
-    }
-
     template <int PART>
     __device__ __forceinline__ int out_of_line(int x = 0) const
     {
         return __builtin_amdgcn_readfirstlane(
-            solve_part<QUEUE, DERIVE, ROLE, PART>((uint64_t)(uintptr_t)&a, i, T, lam, slo, x));
+            solve_part<QUEUE, DERIVE, ROLE, PART>((uint64_t)(uintptr_t)args, i, T, lam, slo, x));
     }
 
     // Step C, and if it does not suffice the lists of step G.
     __device__ __forceinline__ int solve_c() const
     {
-        fill_sixtyfour();
         const int status = solve_sixtyfour();
         wave_lds_fence();
         return status == UNFINISHED ? list_all() : status;
@@ -1918,7 +1759,7 @@ struct Solver {
             const bool in_lds = cells / 2 <= l.free_words;
             status = most ? out_of_line<PART_TRIAL>(most) : UNFINISHED;
             if (status == UNFINISHED && in_lds) status = out_of_line<PART_ROWS>(W);
-            else if (status == UNFINISHED && cells <= a.hrow_stride) status = out_of_line<PART_ROWS_HBM>(W);
+            else if (status == UNFINISHED && cells <= args->hrow_stride) status = out_of_line<PART_ROWS_HBM>(W);
             if (status == UNFINISHED) status = out_of_line<PART_TRIAL>(MOST_TRIALS);
         }
         return status == UNFINISHED ? out_of_line<PART_WD>() : status;
@@ -1934,22 +1775,27 @@ struct Solver {
             W = 2 * W < a.window ? 2 * W : a.window;
             status = solve_window<false>(W);
         }
-        while (status == UNFINISHED && W < a.window_hbm) {
+        while (status == UNFINISHED && W < args->window_hbm) {
             wave_lds_fence();
-            W = 2 * W < a.window_hbm ? 2 * W : a.window_hbm;
+            W = 2 * W < args->window_hbm ? 2 * W : args->window_hbm;
             status = solve_window<true>(W);
         }
         wave_lds_fence();
         return status == UNFINISHED ? solve_by_budget(a.window) : status;
     }
 
+    // An instance that was begun elsewhere.
+    __device__ __forceinline__ void instance(int inst, int budget, int32_t rate, int32_t objective)
+    {
+        i = inst, T = budget, lam = rate, slo = objective;
+        lane_b = lane < a.n_batch ? args->bc[lane].size : 0;
+    }
+
     // A part of the solve of the instance, in a function of its own.
     template <int PART>
     __device__ __forceinline__ int part(int inst, int budget, int32_t rate, int32_t objective, int x)
     {
-        i = inst, T = budget, lam = rate, slo = objective;
-        lane_b = lane < a.n_batch ? (int32_t)a.bc[lane].b : 0;
-        if constexpr (PART == PART_FURTHER) return solve_further();
+        instance(inst, budget, rate, objective);
         if constexpr (PART == PART_PRICE) return find_price();
         if constexpr (PART == PART_NARROW) return list_narrowed() ? ARE_LISTED : UNFINISHED;
         if constexpr (PART == PART_GAP) return find_survivors();
@@ -1959,47 +1805,6 @@ struct Solver {
         if constexpr (PART == PART_WD) return solve_wide();
     }
 
-    // The inputs of instance `inst` at `rate`; valid: the input check's result.
-    __device__ __forceinline__ Pair begin(int inst, int32_t rate, bool& valid)
-    {
-        i = inst;
-        lam = rate;
-        slo = a.slo_us[i];
-        const bool rates = in_range(lam, 1, THEMIS_VALUE_MAX) && in_range(slo, 0, a.slo_max);
-        // floor(slo / tick): the quotient lies at least half of 1 / tick above any whole
-        // number below it, which the reciprocal's error (2^-44 relative) does not reach
-        T = __builtin_amdgcn_readfirstlane((int)(((double)slo + 0.5) * a.rtick));
-        int32_t word = 0;
-        if (keeps_coef() && lane < a.S * a.cs) word = (a.coef + (size_t)i * (a.S * a.cs))[lane];
-        const Pair first = pair_of_round(0u);
-        lane_b = (int32_t)first.bh.b;  // the first n_batch lanes have the first model's pairs
-        bool fine = rates;
-        for_pairs(first, [&](const Pair& p) { fine = fine && (!p.there || p.valid); });
-        valid = __ballot(!fine) == 0ull;
-        keep_inputs(valid, word);
-        if (records() && lane == 0) a.tmeta[i] = valid ? T : -1;
-        return first;
-    }
-
-    // Solves the instance that was begun, and is valid, at the rate `lam`; writes the
-    // results unless it is infeasible.
-    __device__ __forceinline__ int solve(const Pair& first) const
-    {
-        if (lane < a.S) {
-            keys()[lane] = EMPTY;
-            bests()[lane] = ~0ull;
-        }
-        wave_lds_fence();
-        int status;
-        // row_is_small(), which is the same for all models of an instance
-        if (__builtin_amdgcn_readfirstlane((int)((double)lam * (double)slo <= 0x1p42)))
-            status = solve_valid<true>(first);
-        else
-            status = solve_valid<false>(first);
-        status = __builtin_amdgcn_readfirstlane(status);
-        if (status == UNFINISHED) status = out_of_line<PART_FURTHER>();
-        return status;
-    }
 };
 
 // Out of line, so that their registers do not weigh on the allocation of the steps that
@@ -2011,22 +1816,9 @@ __device__ __attribute__((noinline)) int solve_part(uint64_t args, int i, int T,
     auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
     const uint64_t lo = (uint32_t)uniform((int)(uint32_t)args);
     const uint64_t hi = (uint32_t)uniform((int)(uint32_t)(args >> 32));
-    Solver<QUEUE, DERIVE, false, ROLE> sv((ArgsPtr)(uintptr_t)(hi << 32 | lo));
+    Solver<QUEUE, DERIVE, ROLE> sv((ArgsPtr)(uintptr_t)(hi << 32 | lo));
     return uniform(
         sv.template part<PART>(uniform(i), uniform(T), uniform(lam), uniform(slo), uniform(x)));
-}
-
-// One whole solve of instance `inst` at `rate`.
-template <int QUEUE, bool DERIVE, bool ONE, int ROLE>
-__device__ __forceinline__ int solve_instance(ArgsPtr args, int inst, int32_t rate)
-{
-    Solver<QUEUE, DERIVE, ONE, ROLE> sv(args);
-    bool valid;
-    const auto first = sv.begin(inst, rate, valid);
-    int status = THEMIS_INVALID;
-    if (valid) status = sv.solve(first);
-    if (status == THEMIS_INVALID || status == THEMIS_INFEASIBLE) sv.put_none(status);
-    return status;
 }
 
 // What the class lists and the state word say about the workspace after a solve: no
@@ -2037,7 +1829,7 @@ __device__ __forceinline__ void mark_workspace(ArgsPtr args, int state)
     if (blockIdx.x != 0) return;
     if ((int)threadIdx.x <= STATE_WORD)
         args->ctrl[threadIdx.x] = (int)threadIdx.x < STATE_WORD || !args->keep ? 0 : state;
-    if (args->keep && args->coef_shared)
+    if (args->keep && !args->coef_stride)
         for (int x = (int)threadIdx.x; x < args->S * args->cs; x += 64)
             (args->keep + args->kept.coef)[x] = args->coef[x];
 }
@@ -2054,6 +1846,7 @@ __device__ __forceinline__ ArgsPtr kernel_args()
 namespace {
 
 typedef void (*CostKernel)(CostArgs);
+constexpr int WIDTH_PACKED = 1;  // see Front
 
 constexpr size_t LDS_PER_CU = 160 * 1024;
 constexpr int MAX_WINDOW = 8192;
@@ -2095,14 +1888,24 @@ inline CostArgs cost_args(const themis_problem_t& p, const Layout& L, const int3
     a.keep = opts.inspectable ? (int32_t*)(ws + L.step_off) : nullptr;
     a.n_batch = p.n_batch;
     for (int j = 0; j < p.n_batch; ++j)
-        a.bc[j] = {(double)p.batch_sizes[j], (1.0 / (1.0e6 * p.batch_sizes[j])) * (1.0 - 0x1p-45)};
+{
+        const double b = (double)p.batch_sizes[j];
+        a.bc[j] = {(1.0 / (1.0e6 * b)) * (1.0 - 0x1p-45), 1.0e6 * (b - 1.0), (float)(1.0e6 * b),
+                   (float)(b / (2.0 * b - 1.0)), p.batch_sizes[j], 0};
+    }
+    while (1 << a.width_log < p.n_batch) ++a.width_log;
+    if (a.width_log < 2 && L.S <= 16) a.width_log = 2;
+    a.per_round = 64 >> a.width_log;
+    auto rounds = [&](int models) { return (L.S + models - 1) / models; };
+    if (L.S > a.per_round && rounds(64 / p.n_batch) < rounds(a.per_round))
+        a.per_round = 64 / p.n_batch, a.width_log = -1;
     a.S = L.S;
     a.cs = p.profile_form == THEMIS_PROFILE_EQ1 ? 6 : 5;
     a.c_max = p.c_max;
     a.r_max = p.r_max;
     a.tick = p.tick_us;
     a.slo_max = p.slo_max_us;
-    a.coef_shared = p.coef_shared;
+    a.coef_stride = p.coef_shared ? 0 : L.S * a.cs;
     a.c_all = opts.c_all;
     a.list = opts.list;
     a.row_stride = L.row_stride;
@@ -2111,6 +1914,10 @@ inline CostArgs cost_args(const themis_problem_t& p, const Layout& L, const int3
     a.parts = pairs < 64u ? 64u / pairs : 1u;
     a.pair_magic = index_magic(pairs < 64u ? pairs : 64u);
     a.rtick = (1.0 / (double)p.tick_us) * (1.0 - 0x1p-45);
+    a.tick_d = (double)p.tick_us;
+    a.r_max_d = (double)p.r_max;
+    a.r_max_f = (float)p.r_max;
+    a.tick_magic = p.tick_us > 1 ? (uint32_t)((1ull << 32) / (uint32_t)p.tick_us) : 0xFFFFFFFFu;
     return a;
 }
 
@@ -2124,7 +1931,7 @@ inline CostArgs past(CostArgs a, size_t n)
         if (array) array += elements;
     };
     const size_t rows = n * (size_t)a.S;
-    if (!a.coef_shared) skip(a.coef, rows * a.cs);
+    if (a.coef_stride) skip(a.coef, rows * a.cs);
     for (const int32_t** in : {&a.lambda, &a.slo_us, &a.lambda2}) skip(*in, n);
     for (const int32_t** in : {&a.r_fixed, &a.c_fixed}) skip(*in, rows);
     for (int32_t** out : {&a.status, &a.cost, &a.ticks, &a.status2, &a.cost2, &a.ticks2, &a.lambda_v,
@@ -2138,8 +1945,7 @@ inline CostArgs past(CostArgs a, size_t n)
 }
 
 // A workgroup per instance, or where `listed` as many as stay resident (the host does
-// not know how long the list is).  `one` in kernel(one): the (model, batch size) pairs
-// fit a wavefront's lanes.
+// not know how long the list is).  `width` in kernel(width): see Front.
 //
 // One launch (of up to MAX_PER_LAUNCH instances), whatever the instances need: a second one with room for wider windows,
 // for the instances the first one could not solve, took 4.5 us to find that there are
@@ -2169,12 +1975,16 @@ hipError_t launch_per_instance(const themis_problem_t& p, const Layout& L, CostA
     const int room = lds.words - lds.tab;
     a.window_hbm = (fit < room ? fit : room) & ~63;
     // (at most 40 KB of LDS, which a kernel may have without asking)
-    const CostKernel k = kernel(L.S * p.n_batch <= 64);
+    const bool one = L.S <= a.per_round;
+    const CostKernel k = kernel(!one ? 0 : a.width_log < 2 ? WIDTH_PACKED : 1 << a.width_log);
     hipError_t e = hipSuccess;
     in_launches(grid, [&](int first, int count) {
         if (e != hipSuccess) return;
-        hipLaunchKernelGGL(k, dim3((unsigned)count), dim3(64), lds_for(a.window), st,
-                           past(a, (size_t)first));
+        const dim3 groups((unsigned)count);
+        if (first == 0)
+            hipLaunchKernelGGL(k, groups, dim3(64), lds_for(a.window), st, a);
+        else
+            hipLaunchKernelGGL(k, groups, dim3(64), lds_for(a.window), st, past(a, (size_t)first));
         e = hipGetLastError();
     });
     return e;
