@@ -40,7 +40,7 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
     using Base::a, Base::args, Base::i, Base::L, Base::lam, Base::lane, Base::lds, Base::slo, Base::T;
     static constexpr bool ONE = WIDTH != 0;
 
-    __device__ __forceinline__ explicit Front(ArgsPtr p) : Base(p) {}
+    __device__ __forceinline__ explicit Front(ArgsPtr p, int l = (int)threadIdx.x) : Base(p, l) {}
 
     __device__ __forceinline__ int width_log() const
     {
@@ -360,12 +360,12 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
     }
 
     // ---- step B ------------------------------------------------------------------
-    // The recurrence over eight cells for eight models at a time (or sixteen for four), lane =
-    // (model, cell): rows of neighbouring models are combined, then of two and two, of four
-    // and four (and with the row of the models behind those), so that three or four
-    // dependent steps take the place of one per model.  The choices of all models at all
-    // cells are read out together, and what is left per model is one lane index.  (With the
-    // results' way out: 2.0 us for five models and 3.3 for eight as sixteen cells a model
+    // The recurrence over eight or sixteen cells for eight models at a time, lane = (model,
+    // cell, and the one eight above it): rows of neighbouring models are combined, then of two
+    // and two, of four and four (and with the row of the models behind those), so that three
+    // or four dependent steps take the place of one per model.  The choices of all models
+    // at all cells are read out together, and what is left per model is one lane index.  (With
+    // the results' way out: 2.0 us for five models and 3.3 for eight as sixteen cells a model
     // after the other, 1.6 and 1.9 as eight this way.)
     // `span`: the cells over base up to which the table is complete.
     template <int CELLS>
@@ -373,86 +373,124 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
     {
         typedef uint32_t four __attribute__((ext_vector_type(4), aligned(16)));
         constexpr uint32_t INDEX = (1u << INDEX_BITS) - 1u;
-        constexpr int MODELS = 64 / CELLS, STRIDE = 2 * CELLS, BITS = CELLS == 8 ? 3 : 4;
+        constexpr int STRIDE = 8 + CELLS, BITS = CELLS == 8 ? 3 : 4;
+        constexpr bool TWO = CELLS == 16;
         const uint32_t* const tab = lds + L.tab;
-        // rows of CELLS cells, as many guard cells in front of each
-        uint32_t* const rows = lds + L.tab + 64 * a.S + CELLS;
-        const int S = a.S, x = lane & (CELLS - 1), g = lane / CELLS;
-        for (int y = g; y <= S; y += MODELS) rows[STRIDE * y + x - CELLS] = LT_NONE;
+        // rows of CELLS cells, eight guard cells in front of each
+        uint32_t* const rows = lds + L.tab + 64 * a.S + 8;
+        const int S = a.S, x = lane & 7, g = lane >> 3;
+        for (int y = g; y <= S; y += 8) rows[STRIDE * y + x - 8] = LT_NONE;
         if (lane < CELLS) rows[STRIDE * S + lane] = 0u;  // nothing left to run
-        // eight at a time: cells x - q0, x - q0 - 1, .. of a row, and cells q0, q0 + 1, .. of one
-        auto backwards = [&](const uint32_t* row, int q0, uint32_t (&v)[8]) {
+        // cells x, x - 1, .. x - 7 of a row that starts at `row`, and cells 0 .. 7
+        auto backwards = [&](const uint32_t* row, uint32_t (&v)[8]) {
 #pragma unroll
-            for (int q = 0; q < 8; ++q) v[q] = (row + x - q0 - 7)[7 - q];
+            for (int q = 0; q < 8; ++q) v[q] = (row + x - 7)[7 - q];
         };
-        auto forwards = [](const uint32_t* row, int q0, uint32_t (&v)[8]) {
-            const four a = *reinterpret_cast<const four*>(row + q0);
-            const four b = *reinterpret_cast<const four*>(row + q0 + 4);
+        auto forwards = [](const uint32_t* row, uint32_t (&v)[8]) {
+            const four a = *reinterpret_cast<const four*>(row);
+            const four b = *reinterpret_cast<const four*>(row + 4);
             v[0] = a.x, v[1] = a.y, v[2] = a.z, v[3] = a.w, v[4] = b.x, v[5] = b.y, v[6] = b.z, v[7] = b.w;
         };
-        uint32_t h = 0u;
-        for (int s0 = (S - 1) & ~(MODELS - 1); s0 >= 0; s0 -= MODELS) {
-            const int end = s0 + MODELS < S ? s0 + MODELS : S;
+        uint32_t h = 0u, h8 = 0u;  // cells x and x + 8
+        for (int s0 = (S - 1) & ~7; s0 >= 0; s0 -= 8) {
+            const int end = s0 + 8 < S ? s0 + 8 : S;
             const bool is = s0 + g < end;
             const int s = is ? s0 + g : end - 1;
             uint32_t* const mine = rows + STRIDE * s;
             // (of at most x cells: with nothing behind them the models are done)
-            h = segmented_scan<true>(tab[CELLS * s + x] >> INDEX_BITS, (uint32_t)x, CELLS);
-            if (is) mine[x] = h;
+            const uint32_t first = tab[CELLS * s + x] >> INDEX_BITS;
+            h = segmented_scan<true>(first, (uint32_t)x, 8u);
+            uint32_t last = h;
+            if (TWO) {
+                uint32_t below = least_step<0xB1 /* quad_perm:[1,0,3,2] */>(first);
+                below = least_step<0x4E /* quad_perm:[2,3,0,1] */>(below);
+                below = least_step<0x141 /* row_half_mirror */>(below);
+                h8 = segmented_scan<true>(tab[CELLS * s + x + 8] >> INDEX_BITS, (uint32_t)x, 8u);
+                last = h8 = least(h8, below);
+            }
+            // (no assignment takes fewer ticks than all models with the most cells)
+            if (S <= 8 && wave_sum(is && x == 7 ? last : 0u) > (uint32_t)T) return UNFINISHED;
+            if (is) {
+                mine[x] = h;
+                if (TWO) mine[x + 8] = h8;
+            }
             wave_lds_fence();
             const int to = end < S ? end + 1 : end;
             for (int l = 1; l < to - s0; l *= 2) {
                 const bool on = is && s + l < to;
-                uint32_t all = LT_NONE;
-#pragma unroll 1
-                for (int q0 = 0; q0 < CELLS; q0 += 8) {
-                    uint32_t f[8], o[8];
-                    forwards(mine, q0, f);
-                    backwards(rows + STRIDE * (on ? s + l : end), q0, o);
+                const uint32_t* const other = rows + STRIDE * (on ? s + l : end);
+                uint32_t f[8], o[8], all = LT_NONE, all8 = LT_NONE;
+                forwards(mine, f);
+                backwards(other, o);
 #pragma unroll
-                    for (int q = 0; q < 8; ++q) all = least(all, f[q] + o[q]);
+                for (int q = 0; q < 8; ++q) all = least(all, f[q] + o[q]);
+                if (TWO) {
+                    uint32_t f8[8], o8[8];
+                    backwards(other + 8, o8);
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) all8 = least(all8, f[q] + o8[q]);
+                    forwards(mine + 8, f8);
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) all8 = least(all8, f8[q] + o[q]);
                 }
                 wave_lds_fence();
-                if (on) mine[x] = h = all;
+                if (on) {
+                    mine[x] = h = all;
+                    if (TWO) mine[x + 8] = h8 = all8;
+                }
                 wave_lds_fence();
             }
         }
-        const uint32_t m = (uint32_t)__builtin_amdgcn_ballot_w64(h <= (uint32_t)T) & ((1u << span) - 1u);
+        uint32_t m = (uint32_t)__builtin_amdgcn_ballot_w64(h <= (uint32_t)T) & 0xFFu;
+        if (TWO) m |= ((uint32_t)__builtin_amdgcn_ballot_w64(h8 <= (uint32_t)T) & 0xFFu) << 8;
+        m &= (1u << span) - 1u;
         if (m == 0u) return UNFINISHED;
         int left = __builtin_ctz(m);
-        this->put(THEMIS_SOLVED, (int32_t)(base_sum + (uint32_t)left), (int32_t)lane_value(h, left), BY_B);
-        for (int s0 = 0; s0 < S; s0 += MODELS) {
+        const uint32_t ticks = TWO && left >= 8 ? lane_value(h8, left & 7) : lane_value(h, left & 7);
+        this->put(THEMIS_SOLVED, (int32_t)(base_sum + (uint32_t)left), (int32_t)ticks, BY_B);
+        for (int s0 = 0; s0 < S; s0 += 8) {
             const int s = s0 + g < S ? s0 + g : S - 1;
-            const uint32_t ticks = rows[STRIDE * s + x];
+            const uint32_t *const mine = rows + STRIDE * s, *const other = mine + STRIDE;
             // the smallest index among the candidates that continue an optimum, and its cell
-            uint32_t pick = EMPTY;
-#pragma unroll 1
-            for (int q0 = 0; q0 < CELLS; q0 += 8) {
-                uint32_t w[8], o[8];
-                forwards(tab + CELLS * s, q0, w);
-                backwards(rows + STRIDE * (s + 1), q0, o);
+            uint32_t pick = EMPTY, pick8 = EMPTY;
+            auto offer = [](uint32_t& p, uint32_t w, uint32_t rest, uint32_t t, int cell) {
+                const bool hit = (w >> INDEX_BITS) + rest == t;
+                p = least(p, hit ? (w & INDEX) << BITS | (uint32_t)cell : EMPTY);
+            };
+            uint32_t w[8], o[8];
+            const uint32_t t = mine[x], t8 = TWO ? mine[x + 8] : 0u;
+            forwards(tab + CELLS * s, w);
+            backwards(other, o);
 #pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    const bool hit = (w[q] >> INDEX_BITS) + o[q] == ticks;
-                    pick = least(pick, hit ? (w[q] & INDEX) << BITS | (uint32_t)(q0 + q) : EMPTY);
-                }
+            for (int q = 0; q < 8; ++q) offer(pick, w[q], o[q], t, q);
+            if (TWO) {
+                uint32_t v[8];
+                backwards(other + 8, v);
+#pragma unroll
+                for (int q = 0; q < 8; ++q) offer(pick8, w[q], v[q], t8, q);
+                forwards(tab + CELLS * s + 8, v);
+#pragma unroll
+                for (int q = 0; q < 8; ++q) offer(pick8, v[q], o[q], t8, q + 8);
             }
-            const int n = S - s0 < MODELS ? S - s0 : MODELS;
-            unsigned long long chosen = 0ull;
+            const int n = S - s0 < 8 ? S - s0 : 8;
+            unsigned long long chosen = 0ull, chosen8 = 0ull;
             uint32_t none = 0u;
             for (int q = 0; q < n; ++q) {
-                const int at = CELLS * q + left;
-                const uint32_t p = lane_value(pick, at);
+                const int at = 8 * q + (left & 7);
+                const bool upper = TWO && left >= 8;
+                const uint32_t p = upper ? lane_value(pick8, at) : lane_value(pick, at);
                 none |= p;
-                chosen |= 1ull << at;
+                (upper ? chosen8 : chosen) |= 1ull << at;
                 left -= (int)(p & (uint32_t)(CELLS - 1));
             }
             if (none == EMPTY) {  // never expected
                 this->put_none(THEMIS_INTERNAL);
                 return THEMIS_INTERNAL;
             }
-            this->put_row((int)((chosen >> lane) & 1ull), (uint32_t)s, pick >> BITS,
-                          (this->keys()[s] >> 15) + (pick & (uint32_t)(CELLS - 1)));
+            const bool upper = TWO && ((chosen8 >> lane) & 1ull);
+            const uint32_t p = upper ? pick8 : pick;
+            this->put_row((int)(((chosen | chosen8) >> lane) & 1ull), (uint32_t)s, p >> BITS,
+                          (this->keys()[s] >> 15) + (p & (uint32_t)(CELLS - 1)));
         }
         return THEMIS_SOLVED;
     }
@@ -570,7 +608,7 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
     {
         const uint32_t late = (ticks - (uint32_t)T) * 40u, gain = ticks - least_ticks;
         if (DERIVE && late <= gain * 12u) return 4;
-        return late <= gain * (DERIVE ? 25u : 17u) ? 8 : late <= gain * (DERIVE ? 30u : 26u) ? 16 : 64;
+        return late <= gain * (DERIVE ? 26u : 14u) ? 8 : late <= gain * (DERIVE ? 30u : 26u) ? 16 : 64;
     }
     // The table of `cells` cells per model.  mine, best: what step A found, see solve_valid().
     template <bool SMALL>
@@ -718,9 +756,10 @@ __device__ __attribute__((noinline)) int solve_rest(uint64_t args, int i, int T,
 
 // One whole solve of instance `inst` at the rate rates[inst].
 template <int QUEUE, bool DERIVE, int WIDTH, int ROLE>
-__device__ __forceinline__ int solve_instance(ArgsPtr args, int inst, const int32_t* rates)
+__device__ __forceinline__ int solve_instance(ArgsPtr args, int inst, const int32_t* rates,
+                                              int lane = (int)threadIdx.x)
 {
-    Front<QUEUE, DERIVE, WIDTH, ROLE> sv(args);
+    Front<QUEUE, DERIVE, WIDTH, ROLE> sv(args, lane);
     bool valid;
     const auto first = sv.begin(inst, rates, valid);
     return sv.finish(sv.solve(first, valid), true);

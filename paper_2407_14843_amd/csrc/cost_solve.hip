@@ -84,12 +84,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(7, 7))) void
     }
     const int n = args->ctrl[LIST_WORD];
     for (int k = (int)blockIdx.x; k < n; k += (int)gridDim.x) {
-        // every instance starts from the arguments again: what could be kept of them from
-        // one to the next would cost registers that the steps need
+        // every instance starts from the arguments and the lane's number again: what could
+        // be kept of them from one to the next would cost registers that the steps need
         ArgsPtr again = args;
-        asm volatile("" : "+s"(again));
+        int lane = (int)threadIdx.x;
+        asm volatile("" : "+s"(again), "+v"(lane));
         const int i = __builtin_amdgcn_readfirstlane(again->list[k]);
-        solve_instance<QUEUE, DERIVE, WIDTH, PLAIN>(again, i, again->lambda);
+        solve_instance<QUEUE, DERIVE, WIDTH, PLAIN>(again, i, again->lambda, lane);
         wave_lds_fence();
     }
     mark(args);

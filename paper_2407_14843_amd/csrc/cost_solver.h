@@ -131,8 +131,8 @@ struct Solver {
     int32_t lam, slo;
     int32_t lane_b;  // lane j: batch size j
 
-    __device__ __forceinline__ explicit Solver(ArgsPtr p)
-        : args(p), a(hot_args(p)), lds(cost_smem), L(cost_lds(p->S, p->window)), lane(threadIdx.x)
+    __device__ __forceinline__ explicit Solver(ArgsPtr p, int l = (int)threadIdx.x)
+        : args(p), a(hot_args(p)), lds(cost_smem), L(cost_lds(p->S, p->window)), lane(l)
     {
     }
     static __device__ __forceinline__ HotArgs hot_args(ArgsPtr p)
