@@ -1426,15 +1426,17 @@ struct Solver {
             const uint32_t lt_next = s > 0 ? tab[(s - 1) * 64 + lane] >> INDEX_BITS : 0u;
             acc = G_INF;
             unsigned long long m = __ballot(on);
-            while (m) {  // four entries at a time: independent reads
+            // four entries at a time: independent reads
+            const unsigned long long none = 1ull << 63;
+            while (m) {
                 uint32_t v[4];
 #pragma unroll
                 for (int z = 0; z < 4; ++z) {
-                    const int d = m ? __builtin_ctzll(m) : 64;
-                    const uint32_t l = m ? lane_value(lt, d & 63) : 0u;
-                    m &= m - 1ull;
+                    // (where there is none left, the same as the one before)
+                    const int d = __builtin_ctzll(z == 0 ? m : m | none);
                     const int y = lane - d;
-                    v[z] = (uint32_t)next[y < -1 ? -1 : y] + l;
+                    v[z] = (uint32_t)next[y < -1 ? -1 : y] + lane_value(lt, d);
+                    m &= m - 1ull;
                 }
                 acc = least(least(acc, v[0]), least(v[1], least(v[2], v[3])));
             }

@@ -1,0 +1,84 @@
+"""The start of the one-wavefront solve (csrc/cost_front.h) at the sizes where its branches
+meet: every way the (model, batch size) pairs lie in a wavefront, answers at the edges of the
+windows of four, eight and sixteen cells, and products beyond 2^42.  Whole numbers, so the
+checker's answers word for word: no tolerance."""
+
+import numpy as np
+import pytest
+
+from cost_families import families, family, over_base
+from test_gpu_cost_solve import T, same  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def every_call(T, oracle, w, r_most):
+    """Each entry point on w, against the checker."""
+    rng = np.random.default_rng(w.n_stage)
+    b = T.DeviceBatch(w)
+    b.solve()
+    want = oracle.solve(w, threads=8)
+    same(b.results(), want)
+    b.solve_distinct()
+    same(b.results(), want)
+    cores = rng.integers(1, w.c_max + 1, (w.n_inst, w.n_stage)).astype(np.int32)
+    b.solve_horizontal(cores)
+    same(b.results(), oracle.solve(w, threads=8, c_fixed=cores))
+    pred = np.minimum(w.lam + rng.integers(0, 3, w.n_inst), 1 << 20).astype(np.int32)
+    stable = b.check_stability(pred)
+    flags = oracle.stability(w, pred)
+    assert (stable.cpu().numpy() == flags[0]).all()
+    same(b.results(), flags[1:])
+    v = w.with_r_fixed(rng.integers(1, r_most + 1, (w.n_inst, w.n_stage)))
+    b = T.DeviceBatch(v)
+    b.solve()
+    same(b.results(), oracle.solve(v, threads=8))
+    b.solve_vertical_fallback()
+    got, fell = b.fallback_results(), oracle.vertical_fallback(v, threads=8)
+    for k in fell:
+        assert (got[k] == fell[k]).all(), k
+    return want
+
+
+# lanes per model 4, 8 and 16, the fewest and the most models and batch sizes that fit; pairs
+# that fit only without gaps; rounds of models with gaps, and without where that takes fewer
+@pytest.mark.parametrize("S,n_batch", [
+    (1, 1), (16, 4), (3, 3), (8, 8), (8, 5), (1, 16), (4, 16), (4, 9),
+    (10, 6), (12, 5), (7, 9), (9, 7), (5, 12), (32, 2),
+    (17, 4), (9, 8), (7, 12), (5, 16), (33, 2), (9, 9), (10, 10)])
+@pytest.mark.parametrize("queue", [0, 1])
+def test_layouts(T, oracle, S, n_batch, queue):
+    r_max = min(40, 32767 // (S * 7))
+    w = family([S, n_batch], 96, S, 7, list(range(1, n_batch + 1)), r_max, 250, S * 60_000, (10, 900))
+    w = w.with_model(queue, None)
+    print(f"[case] {S} models, {n_batch} batch sizes, queue {queue}", flush=True)
+    want = every_call(T, oracle, w, min(r_max, 6))
+    assert (want[0] == 0).any()
+
+
+@pytest.mark.parametrize("given", [False, True])
+def test_window_edges(T, oracle, given):
+    """Answers 0 to 17 over the least cost, all in one batch and each in one of its own."""
+    w = (family(21, 4000, 6, 16, [1, 2, 4, 8, 16], 5, 250, 700_000, (10, 400), r_fixed=5) if given
+         else families(4000)["three models"])
+    want = oracle.solve(w, threads=8)
+    at = np.nonzero(want[0] == 0)[0]
+    over = over_base(w, oracle, want)
+    picks = [at[over == x][:40] for x in (0, 1, 3, 4, 5, 7, 8, 9, 15, 16, 17)]
+    assert sum(p.size > 0 for p in picks) >= 9, [p.size for p in picks]
+    for pick in picks + [np.concatenate(picks)]:
+        if pick.size:
+            b = T.DeviceBatch(w.take(pick))
+            b.solve()
+            same(b.results(), tuple(x[pick] for x in want))
+
+
+@pytest.mark.parametrize("n_batch", [7, 13])
+def test_products_beyond_42_bits(T, oracle, n_batch):
+    """Rates times objectives on both sides of 2^42."""
+    w = family(9, 300, 3, 1, [2 ** j if n_batch == 7 else j + 1 for j in range(n_batch)], 10_000,
+               1000, 30_000_000, (50_000, 1_000_000))
+    large = w.lam.astype(np.int64) * w.slo_us >= 1 << 42
+    assert large.any() and not large.all()
+    want = every_call(T, oracle, w, 10_000)
+    assert (want[0][large] == 0).any()
