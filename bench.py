@@ -59,8 +59,8 @@ SOLVE_VALU = {
     "w1-joint-4096x5": (450.0, "0587b805d377e532"),
     "w3-joint-65536x8": (576.0, "0587b805d377e532"),
 }
-SOLVE_SOURCES = ("cost_solve.hip", "cost_solver.h", "candidate_eval.h", "wave_ops.h",
-                 "themis_internal.h")
+SOLVE_SOURCES = ("cost_solve.hip", "cost_front.h", "cost_solver.h", "candidate_eval.h",
+                 "wave_ops.h", "themis_internal.h")
 
 
 def kernel_fingerprint(sources=KERNEL_SOURCES):
