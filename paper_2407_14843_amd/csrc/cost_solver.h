@@ -1426,13 +1426,13 @@ struct Solver {
             const uint32_t lt_next = s > 0 ? tab[(s - 1) * 64 + lane] >> INDEX_BITS : 0u;
             acc = G_INF;
             unsigned long long m = __ballot(on);
-            // four entries at a time: independent reads
+            // Four entries at a time: independent reads.  (Where there are none left, that of
+            // cell 63, which is a candidate or beyond any budget and does no harm.)
             const unsigned long long none = 1ull << 63;
             while (m) {
                 uint32_t v[4];
 #pragma unroll
                 for (int z = 0; z < 4; ++z) {
-                    // (where there is none left, the same as the one before)
                     const int d = __builtin_ctzll(z == 0 ? m : m | none);
                     const int y = lane - d;
                     v[z] = (uint32_t)next[y < -1 ? -1 : y] + lane_value(lt, d);
