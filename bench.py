@@ -56,8 +56,8 @@ KERNEL_SOURCES = ("k1_candidates.hip", "candidate_eval.h", "wave_ops.h", "k2_min
 # vector instructions of the timed whole solve per instance (the pipe counters in
 # profiles/*_kernel_trace.txt): workload -> (instructions, fingerprint of its sources)
 SOLVE_VALU = {
-    "w1-joint-4096x5": (383.3, "bc9f861b06ce25ea"),
-    "w3-joint-65536x8": (465.3, "bc9f861b06ce25ea"),
+    "w1-joint-4096x5": (383.3, "512d5256f5297d7b"),
+    "w3-joint-65536x8": (465.3, "512d5256f5297d7b"),
 }
 SOLVE_SOURCES = ("cost_solve.hip", "cost_front.h", "cost_solver.h", "candidate_eval.h",
                  "wave_ops.h", "themis_internal.h")

@@ -9,9 +9,9 @@
 // single precision ahead of evaluations, no loop over the models in step B, one call at the
 // very end.  Against evaluating every core count that the real-valued bound allows, with
 // LDS atomics per model and sixteen cells one model after the other, in microseconds:
-// 512 x 5 9.5 -> 7.7, 4096 x 5 13.3 -> 11.3, 3001 x 7 17.3 -> 12.9, stability 4099 x 5
-// 23.3 -> 19.2, 16384 x 8 with replicas given 26.2 -> 25.0, 86400 x 6 51.7 -> 39.7,
-// 65536 x 8 98.2 -> 77.8, fallback 16384 x 8 65 -> 30.4.
+// 512 x 5 9.5 -> 7.1, 4096 x 5 13.3 -> 11.1, 3001 x 7 17.3 -> 13.0, stability 4099 x 5
+// 23.3 -> 19.5, 16384 x 8 with replicas given 26.2 -> 24.2, 86400 x 6 51.7 -> 39.7,
+// 65536 x 8 98.1 -> 76.3, fallback 16384 x 8 65 -> 29.3.
 #pragma once
 
 #include "cost_solver.h"
@@ -598,7 +598,7 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
         return UNFINISHED;
     }
     // How many cells it takes, by how much the cheapest assignment is late, as a part of
-    // what the fastest gains on it.  By the checker's answers for 1500 instances of each of
+    // what the fastest gains on it.  By the oracle's answers for 1500 instances of each of
     // the timed shapes, and of drawn ones: where the replicas are derived, up to three tenths
     // of it is made up for within four cells, with next to no exception; beyond five eighths
     // it mostly takes more than eight, beyond three quarters more than sixteen.  With the

@@ -1,7 +1,7 @@
 """The start of the one-wavefront solve (csrc/cost_front.h) at the sizes where its branches
 meet: every way the (model, batch size) pairs lie in a wavefront, answers at the edges of the
 windows of four, eight and sixteen cells, and products beyond 2^42.  Whole numbers, so the
-checker's answers word for word: no tolerance."""
+oracle's answers word for word: no tolerance."""
 
 import numpy as np
 import pytest
@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 
 def every_call(T, oracle, w, r_most):
-    """Each entry point on w, against the checker."""
+    """Each entry point on w, against the oracle."""
     rng = np.random.default_rng(w.n_stage)
     b = T.DeviceBatch(w)
     b.solve()
