@@ -447,7 +447,8 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
         if (m == 0u) return UNFINISHED;
         int left = __builtin_ctz(m);
         const uint32_t ticks = TWO && left >= 8 ? lane_value(h8, left & 7) : lane_value(h, left & 7);
-        this->put(THEMIS_SOLVED, (int32_t)(base_sum + (uint32_t)left), (int32_t)ticks, BY_B);
+        this->put(THEMIS_SOLVED, (int32_t)(base_sum + (uint32_t)left), (int32_t)ticks,
+                  TWO ? BY_B16 : BY_B8);
         for (int s0 = 0; s0 < S; s0 += 8) {
             const int s = s0 + g < S ? s0 + g : S - 1;
             const uint32_t *const mine = rows + STRIDE * s, *const other = mine + STRIDE;

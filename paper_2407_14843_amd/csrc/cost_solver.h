@@ -440,7 +440,7 @@ struct Solver {
         constexpr uint32_t INDEX = (1u << INDEX_BITS) - 1u;
         const uint32_t* const tab = lds + L.tab;
         uint32_t t = ticks, my_k = 0, my_cost = my_base;
-        const int d = lane, over = x;
+        const int d = lane;
         uint32_t e = tab[d];
         for (int s = 0; s < a.S; ++s) {
             const bool more_models = s + 1 < a.S;
@@ -463,7 +463,7 @@ struct Solver {
             x -= l;
             e = e_next;
         }
-        put(THEMIS_SOLVED, (int32_t)total, (int32_t)ticks, over < 16 ? BY_B : BY_C);
+        put(THEMIS_SOLVED, (int32_t)total, (int32_t)ticks, BY_C);
         put_choice(my_k, my_cost);
         return THEMIS_SOLVED;
     }

@@ -222,9 +222,10 @@ constexpr int STATE_C_ALL = 8;    // from this bit up: the same cores for every 
 // from bit KEEP_STEP up, so that a test can tell which code its batch went through
 enum { KEEP_LAM = 0, KEEP_SLO, KEEP_STATUS, KEEP_COST, KEEP_TICKS, KEEP_HEAD };
 constexpr int KEEP_STEP = 8;
-// The steps of cost_solve.hip; LDS and HBM say where the rows were, TRIAL that the
+// The steps of cost_solve.hip, by the code that found the answer, wherever another one might
+// have; 8 and 16 are step B's cells, LDS and HBM say where the rows were, TRIAL that the
 // combinations were tried.
-enum SolveStep { BY_A = 0, BY_B, BY_C, BY_G_LDS, BY_G_HBM, BY_G_TRIAL, BY_W_LDS, BY_W_HBM, BY_D };
+enum SolveStep { BY_A = 0, BY_B8, BY_B16, BY_C, BY_G_LDS, BY_G_HBM, BY_G_TRIAL, BY_W_LDS, BY_W_HBM, BY_D };
 // offsets of the rest, and words per record; shared coefficients are in the first only
 struct KeepLayout {
     uint32_t coef, given, only, cfg, words;

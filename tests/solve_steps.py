@@ -4,7 +4,7 @@ region, KEEP_STATUS, KEEP_STEP)."""
 
 import numpy as np
 
-STEPS = ("A", "B", "C", "G LDS", "G HBM", "G trial", "W LDS", "W HBM", "D")
+STEPS = ("A", "B8", "B16", "C", "G LDS", "G HBM", "G trial", "W LDS", "W HBM", "D")
 
 
 def steps_of(p, workspace):
@@ -15,3 +15,26 @@ def steps_of(p, workspace):
     kept = workspace[: 4 * words * p.n_inst].view(torch.int32).reshape(p.n_inst, words)
     status = kept[:, 2].cpu().numpy()
     return np.where(status & 0xFF, -1, status >> 8)
+
+
+def steps_by_rule(w, oracle, want):
+    """The step that csrc/cost_front.h's rule (Front::reach_of) and the answers `want` make it,
+    per instance; "" where there is no answer, or it lies beyond the 64 cells of step C."""
+    lt, cost, _ = oracle.candidates(w)
+    cost = np.where(lt >= 0, cost, 1 << 20)
+    base = cost.min(axis=2)
+    ticks = np.where((lt >= 0) & (cost == base[..., None]), lt, 1 << 20).min(axis=2).sum(axis=1)
+    least = np.where(lt >= 0, lt, 1 << 20).min(axis=2).sum(axis=1)
+    T = w.slo_us // w.tick_us
+    x = want[1] - base.sum(axis=1)
+    late, gain = (ticks - T) * 40, ticks - least
+    given = w.r_fixed is not None
+    steps = []
+    for i in range(w.n_inst):
+        cells = (4 if not given and late[i] <= 12 * gain[i] else
+                 8 if late[i] <= (14 if given else 26) * gain[i] else
+                 16 if late[i] <= (26 if given else 31) * gain[i] else 64)
+        steps.append("" if want[0][i] != 0 else "A" if late[i] <= 0 else
+                     "B8" if x[i] < cells <= 8 else "B16" if x[i] < 16 and cells <= 16 else
+                     "C" if x[i] < 64 else "")
+    return np.array(steps)

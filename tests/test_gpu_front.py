@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 
 from cost_families import families, family, over_base
+from solve_steps import STEPS, steps_by_rule, steps_of
 from test_gpu_cost_solve import T, same  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -58,7 +59,8 @@ def test_layouts(T, oracle, S, n_batch, queue):
 
 @pytest.mark.parametrize("given", [False, True])
 def test_window_edges(T, oracle, given):
-    """Answers 0 to 17 over the least cost, all in one batch and each in one of its own."""
+    """Answers 0 to 17 over the least cost, all in one batch and each in one of its own, and the
+    step that finds each of them."""
     w = (family(21, 4000, 6, 16, [1, 2, 4, 8, 16], 5, 250, 700_000, (10, 400), r_fixed=5) if given
          else families(4000)["three models"])
     want = oracle.solve(w, threads=8)
@@ -66,11 +68,19 @@ def test_window_edges(T, oracle, given):
     over = over_base(w, oracle, want)
     picks = [at[over == x][:40] for x in (0, 1, 3, 4, 5, 7, 8, 9, 15, 16, 17)]
     assert sum(p.size > 0 for p in picks) >= 9, [p.size for p in picks]
+    met = set()
     for pick in picks + [np.concatenate(picks)]:
         if pick.size:
-            b = T.DeviceBatch(w.take(pick))
+            v, x = w.take(pick), tuple(x[pick] for x in want)
+            b = T.DeviceBatch(v)
             b.solve()
-            same(b.results(), tuple(x[pick] for x in want))
+            same(b.results(), x)
+            steps = np.array(STEPS)[steps_of(b.p, b.workspace)]
+            rule = steps_by_rule(v, oracle, x)
+            assert (steps == rule).all(), list(zip(steps, rule))
+            met |= {(s, n) for s, n in zip(steps, over_base(v, oracle, x).tolist())}
+    # each window up to its last cells, and step C where it found what step B was not asked for
+    assert {("B8", 7), ("B16", 15), ("B16", 8), ("C", 15), ("C", 16)} <= met, sorted(met)
 
 
 @pytest.mark.parametrize("n_batch", [7, 13])

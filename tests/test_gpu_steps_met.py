@@ -8,7 +8,7 @@ import pytest
 
 from cost_families import families, family, over_base
 from paper_2407_14843_amd import workloads as wl
-from solve_steps import STEPS, steps_of
+from solve_steps import STEPS, steps_by_rule, steps_of
 from test_gpu_cost_solve import T, same  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -46,8 +46,9 @@ def dense(n, tick, slo, lam=(10, 20_000)):
     ("many cores", "A,B,C,G trial"), ("long lists", "B,C,G trial"), ("one model", "A")])
 def test_families(T, oracle, name, steps, n):
     step, _ = solved(T, oracle, families(240)[name], n)
+    met = {STEPS[k] for k in np.unique(step[step >= 0])}
     for s in steps.split(","):
-        assert (step == STEPS.index(s)).any(), s
+        assert any(m.startswith(s) for m in met), s
 
 
 @pytest.mark.parametrize("w,n,steps", [
@@ -60,8 +61,9 @@ def test_families(T, oracle, name, steps, n):
     (lambda: dense(64, 100, 200_000), 64, "A,B,G trial")])
 def test_little_room_and_many_candidates(T, oracle, w, n, steps):
     step, _ = solved(T, oracle, w(), n)
+    met = {STEPS[k] for k in np.unique(step[step >= 0])}
     for s in steps.split(","):
-        assert (step == STEPS.index(s)).any(), s
+        assert any(m.startswith(s) for m in met), s
 
 
 # Lists that no wavefront of a full compute unit has room for, however they are cut (of some
@@ -75,8 +77,9 @@ def test_little_room_and_many_candidates(T, oracle, w, n, steps):
      [2714, 3546], "D")])
 def test_last_resorts(T, oracle, w, which, steps):
     step, _ = solved(T, oracle, w().take(which), 7200)
+    met = {STEPS[k] for k in np.unique(step[step >= 0])}
     for s in steps.split(","):
-        assert (step == STEPS.index(s)).any(), s
+        assert any(m.startswith(s) for m in met), s
 
 
 @pytest.mark.parametrize("x", [14, 15, 16, 17, 62, 63, 64, 65])
@@ -88,9 +91,11 @@ def test_window_edges(T, oracle, x):
     over = over_base(w, oracle, (status, cost))
     pick = at[over == x]
     assert pick.size, "no such instance"
-    step, _ = solved(T, oracle, w.take(pick))
-    want = "B" if x < 16 else "C" if x < 64 else "G"
-    assert all(STEPS[k].startswith(want) for k in step), [STEPS[k] for k in step]
+    step, want = solved(T, oracle, w.take(pick))
+    rule = steps_by_rule(w.take(pick), oracle, want)
+    assert all(r in ("B8", "B16", "C") if x < 64 else r == "" for r in rule), rule
+    for k, r in zip(step, rule):
+        assert STEPS[k] == r if r else STEPS[k].startswith("G"), (STEPS[k], r)
 
 
 # The forms in which the steps after B are compiled or fed: queue models, Eq. 1's delta, cores
