@@ -59,6 +59,7 @@ __device__ __forceinline__ void fallback_instance(ArgsPtr args, int i)
 
     // new instances for what is left, with the cores of the configuration
     Front<QUEUE, true, WIDTH, PINNED> nw(args);
+    wave_lds_fence();  // (other lanes wrote what a lane reads here)
     const int32_t rest = solved ? lambda - rate : 0;
     nw.i = i;
     if (nw.lane < nw.a.S) {

@@ -92,3 +92,25 @@ def test_products_beyond_42_bits(T, oracle, n_batch):
     assert large.any() and not large.all()
     want = every_call(T, oracle, w, 10_000)
     assert (want[0][large] == 0).any()
+
+
+@pytest.mark.parametrize("S,n_batch", [(8, 8), (16, 4), (4, 16), (7, 9), (9, 9)])
+def test_cores_handed_on(T, oracle, S, n_batch):
+    """The cores of the vertical part, found by any step and so left behind by any lane, are
+    those of the new instances."""
+    w = family([S, n_batch, 3], 400, S, 7, list(range(1, n_batch + 1)), min(40, 32767 // (S * 7)),
+               250, S * 60_000, (10, 2500), r_fixed=6)
+    want = oracle.vertical_fallback(w, threads=8)
+    at = (want["lambda_v"] > 0) & (want["lambda_v"] < w.lam) & (want["status_h"] == 0)
+    kept = w.take(np.arange(w.n_inst))
+    kept.lam = np.maximum(want["lambda_v"], 1).astype(np.int32)
+    met = set(steps_by_rule(kept, oracle, (want["status"], want["cost"]))[at])
+    assert {"A", "B8", "B16", "C"} <= met, met
+    cores = want["cfg"][at][:, :, 0]
+    assert (cores.min(axis=1) < cores.max(axis=1)).mean() > 0.5
+    print(f"[case] fallback {S} models, {n_batch} batch sizes", flush=True)
+    b = T.DeviceBatch(w)
+    b.solve_vertical_fallback()
+    got = b.fallback_results()
+    for k in want:
+        assert (got[k] == want[k]).all(), k
