@@ -360,23 +360,23 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
     }
 
     // ---- step B ------------------------------------------------------------------
-    // The recurrence over eight or sixteen cells for eight models at a time, lane = (model,
-    // cell, and the one eight above it): rows of neighbouring models are combined, then of two
-    // and two, of four and four (and with the row of the models behind those), so that three
-    // or four dependent steps take the place of one per model.  The choices of all models
-    // at all cells are read out together, and what is left per model is one lane index.  (With
-    // the results' way out: 2.0 us for five models and 3.3 for eight as sixteen cells a model
-    // after the other, 1.6 and 1.9 as eight this way.)
+    // The recurrence over eight cells for eight models at a time, lane = (model, cell): rows of
+    // neighbouring models are combined, then of two and two, of four and four (and with the
+    // row of the models behind those), so that three or four dependent steps take the place of
+    // one per model.  The choices of all models at all cells are read out together, and what
+    // is left per model is one lane index.  (With the results' way out: 2.0 us for five models
+    // and 3.3 for eight as sixteen cells a model after the other, 1.6 and 1.9 this way.  Sixteen
+    // cells this way, two per lane, hold 32 values at once, with twenty registers spilled in
+    // every kernel: 512 x 5 7.5 us instead of 7.2, stability 4099 x 5 19.4 instead of 18.8,
+    // 22473 x 9 with replicas given 58.9 instead of 55.2.)
     // `span`: the cells over base up to which the table is complete.
-    template <int CELLS>
-    __device__ __forceinline__ int solve_cells(uint32_t base_sum, int span) const
+    __device__ __forceinline__ int solve_eight(uint32_t base_sum, int span) const
     {
         typedef uint32_t four __attribute__((ext_vector_type(4), aligned(16)));
         constexpr uint32_t INDEX = (1u << INDEX_BITS) - 1u;
-        constexpr int STRIDE = 8 + CELLS, BITS = CELLS == 8 ? 3 : 4;
-        constexpr bool TWO = CELLS == 16;
+        constexpr int CELLS = 8, STRIDE = 16, BITS = 3;
         const uint32_t* const tab = lds + L.tab;
-        // rows of CELLS cells, eight guard cells in front of each
+        // rows of eight cells, as many guard cells in front of each
         uint32_t* const rows = lds + L.tab + 64 * a.S + 8;
         const int S = a.S, x = lane & 7, g = lane >> 3;
         for (int y = g; y <= S; y += 8) rows[STRIDE * y + x - 8] = LT_NONE;
@@ -391,107 +391,62 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
             const four b = *reinterpret_cast<const four*>(row + 4);
             v[0] = a.x, v[1] = a.y, v[2] = a.z, v[3] = a.w, v[4] = b.x, v[5] = b.y, v[6] = b.z, v[7] = b.w;
         };
-        uint32_t h = 0u, h8 = 0u;  // cells x and x + 8
+        uint32_t h = 0u;
         for (int s0 = (S - 1) & ~7; s0 >= 0; s0 -= 8) {
             const int end = s0 + 8 < S ? s0 + 8 : S;
             const bool is = s0 + g < end;
             const int s = is ? s0 + g : end - 1;
             uint32_t* const mine = rows + STRIDE * s;
             // (of at most x cells: with nothing behind them the models are done)
-            const uint32_t first = tab[CELLS * s + x] >> INDEX_BITS;
-            h = segmented_scan<true>(first, (uint32_t)x, 8u);
-            uint32_t last = h;
-            if (TWO) {
-                uint32_t below = least_step<0xB1 /* quad_perm:[1,0,3,2] */>(first);
-                below = least_step<0x4E /* quad_perm:[2,3,0,1] */>(below);
-                below = least_step<0x141 /* row_half_mirror */>(below);
-                h8 = segmented_scan<true>(tab[CELLS * s + x + 8] >> INDEX_BITS, (uint32_t)x, 8u);
-                last = h8 = least(h8, below);
-            }
-            // (no assignment takes fewer ticks than all models with the most cells)
-            if (S <= 8 && wave_sum(is && x == 7 ? last : 0u) > (uint32_t)T) return UNFINISHED;
-            if (is) {
-                mine[x] = h;
-                if (TWO) mine[x + 8] = h8;
-            }
+            h = segmented_scan<true>(tab[CELLS * s + x] >> INDEX_BITS, (uint32_t)x, 8u);
+            if (is) mine[x] = h;
             wave_lds_fence();
             const int to = end < S ? end + 1 : end;
             for (int l = 1; l < to - s0; l *= 2) {
                 const bool on = is && s + l < to;
-                const uint32_t* const other = rows + STRIDE * (on ? s + l : end);
-                uint32_t f[8], o[8], all = LT_NONE, all8 = LT_NONE;
+                uint32_t f[8], o[8], all = LT_NONE;
                 forwards(mine, f);
-                backwards(other, o);
+                backwards(rows + STRIDE * (on ? s + l : end), o);
 #pragma unroll
                 for (int q = 0; q < 8; ++q) all = least(all, f[q] + o[q]);
-                if (TWO) {
-                    uint32_t f8[8], o8[8];
-                    backwards(other + 8, o8);
-#pragma unroll
-                    for (int q = 0; q < 8; ++q) all8 = least(all8, f[q] + o8[q]);
-                    forwards(mine + 8, f8);
-#pragma unroll
-                    for (int q = 0; q < 8; ++q) all8 = least(all8, f8[q] + o[q]);
-                }
                 wave_lds_fence();
-                if (on) {
-                    mine[x] = h = all;
-                    if (TWO) mine[x + 8] = h8 = all8;
-                }
+                if (on) mine[x] = h = all;
                 wave_lds_fence();
             }
         }
-        uint32_t m = (uint32_t)__builtin_amdgcn_ballot_w64(h <= (uint32_t)T) & 0xFFu;
-        if (TWO) m |= ((uint32_t)__builtin_amdgcn_ballot_w64(h8 <= (uint32_t)T) & 0xFFu) << 8;
-        m &= (1u << span) - 1u;
+        uint32_t m = (uint32_t)__builtin_amdgcn_ballot_w64(h <= (uint32_t)T) & ((1u << span) - 1u);
         if (m == 0u) return UNFINISHED;
         int left = __builtin_ctz(m);
-        const uint32_t ticks = TWO && left >= 8 ? lane_value(h8, left & 7) : lane_value(h, left & 7);
-        this->put(THEMIS_SOLVED, (int32_t)(base_sum + (uint32_t)left), (int32_t)ticks,
-                  TWO ? BY_B16 : BY_B8);
+        this->put(THEMIS_SOLVED, (int32_t)(base_sum + (uint32_t)left), (int32_t)lane_value(h, left), BY_B8);
         for (int s0 = 0; s0 < S; s0 += 8) {
             const int s = s0 + g < S ? s0 + g : S - 1;
-            const uint32_t *const mine = rows + STRIDE * s, *const other = mine + STRIDE;
+            const uint32_t* const mine = rows + STRIDE * s;
             // the smallest index among the candidates that continue an optimum, and its cell
-            uint32_t pick = EMPTY, pick8 = EMPTY;
-            auto offer = [](uint32_t& p, uint32_t w, uint32_t rest, uint32_t t, int cell) {
-                const bool hit = (w >> INDEX_BITS) + rest == t;
-                p = least(p, hit ? (w & INDEX) << BITS | (uint32_t)cell : EMPTY);
-            };
-            uint32_t w[8], o[8];
-            const uint32_t t = mine[x], t8 = TWO ? mine[x + 8] : 0u;
+            uint32_t pick = EMPTY, w[8], o[8];
+            const uint32_t t = mine[x];
             forwards(tab + CELLS * s, w);
-            backwards(other, o);
+            backwards(mine + STRIDE, o);
 #pragma unroll
-            for (int q = 0; q < 8; ++q) offer(pick, w[q], o[q], t, q);
-            if (TWO) {
-                uint32_t v[8];
-                backwards(other + 8, v);
-#pragma unroll
-                for (int q = 0; q < 8; ++q) offer(pick8, w[q], v[q], t8, q);
-                forwards(tab + CELLS * s + 8, v);
-#pragma unroll
-                for (int q = 0; q < 8; ++q) offer(pick8, v[q], o[q], t8, q + 8);
+            for (int q = 0; q < 8; ++q) {
+                const bool hit = (w[q] >> INDEX_BITS) + o[q] == t;
+                pick = least(pick, hit ? (w[q] & INDEX) << BITS | (uint32_t)q : EMPTY);
             }
             const int n = S - s0 < 8 ? S - s0 : 8;
-            unsigned long long chosen = 0ull, chosen8 = 0ull;
+            unsigned long long chosen = 0ull;
             uint32_t none = 0u;
             for (int q = 0; q < n; ++q) {
                 const int at = 8 * q + (left & 7);
-                const bool upper = TWO && left >= 8;
-                const uint32_t p = upper ? lane_value(pick8, at) : lane_value(pick, at);
+                const uint32_t p = lane_value(pick, at);
                 none |= p;
-                (upper ? chosen8 : chosen) |= 1ull << at;
+                chosen |= 1ull << at;
                 left -= (int)(p & (uint32_t)(CELLS - 1));
             }
             if (none == EMPTY) {  // never expected
                 this->put_none(THEMIS_INTERNAL);
                 return THEMIS_INTERNAL;
             }
-            const bool upper = TWO && ((chosen8 >> lane) & 1ull);
-            const uint32_t p = upper ? pick8 : pick;
-            this->put_row((int)(((chosen | chosen8) >> lane) & 1ull), (uint32_t)s, p >> BITS,
-                          (this->keys()[s] >> 15) + (p & (uint32_t)(CELLS - 1)));
+            this->put_row((int)((chosen >> lane) & 1ull), (uint32_t)s, pick >> BITS,
+                          (this->keys()[s] >> 15) + (pick & (uint32_t)(CELLS - 1)));
         }
         return THEMIS_SOLVED;
     }
@@ -536,7 +491,7 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
         return lo;
     }
 
-    // Steps A and F and the first eight cells of step B of a valid instance.
+    // Steps A, F and B of a valid instance.
     template <bool SMALL>
     __device__ __forceinline__ int solve_valid(const Pair& first) const
     {
@@ -584,14 +539,13 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
         const int reach = reach_of(ticks, least_ticks);
         if (reach <= 8) {
             fill<SMALL>(first, mine, best, 8, reach);
-            //STAMP5
-            const int status = solve_cells<8>(base_sum, reach);
+            const int status = solve_eight(base_sum, reach);
             if (status != UNFINISHED) return status;
             wave_lds_fence();
         }
         if (reach <= 16) {
             fill<SMALL>(first, mine, best, 16, 16);
-            const int status = solve_cells<16>(base_sum, 16);
+            const int status = this->solve_sixteen(base_sum);
             if (status != UNFINISHED) return status;
             wave_lds_fence();
         }

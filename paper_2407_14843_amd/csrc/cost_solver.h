@@ -99,7 +99,27 @@ __device__ __forceinline__ const __attribute__((address_space(4))) T* constant(c
 
 extern __shared__ uint32_t cost_smem[];
 
+// The value D lanes down within the rows of sixteen that `ROWS` names; `fill` where
+// there is none, x itself in the other rows.
+template <int D, int ROWS = 0xF>
+__device__ __forceinline__ uint32_t row_shifted(uint32_t x, uint32_t fill)
+{
+    const uint32_t old = ROWS == 0xF ? fill : x;
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)x, 0x110 | D, ROWS, 0xF, false);
+}
+
 __device__ __forceinline__ uint32_t least(uint32_t a, uint32_t b) { return a < b ? a : b; }
+
+// The least of the four lanes that have the same place in the rows of sixteen, in all
+// of them.
+__device__ __forceinline__ uint32_t least_of_rows(uint32_t x)
+{
+    typedef uint32_t two __attribute__((ext_vector_type(2)));
+    const two h = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    x = least(h.x, h.y);
+    const two q = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    return least(q.x, q.y);
+}
 
 // What a solve is for, which says where its results go: PLAIN, the caller's results and
 // the record; QUIET, the same without the record; SECOND, the second set of results;
@@ -430,23 +450,23 @@ struct Solver {
         return ((uint32_t)ev.lt << INDEX_BITS) | k;
     }
 
-    // Forward over the models, with the table of 64 cells per model: the smallest
+    // Forward over the models, with the table of W <= 64 cells per model: the smallest
     // index among the candidates that continue an optimum of x cells over base and
-    // `ticks`.  rest(s, y): cell y of row s + 1; lane s: base of model s.
-    template <typename F>
-    __device__ __forceinline__ int read_out(uint32_t total, uint32_t ticks, int x,
-                                            uint32_t my_base, F rest) const
+    // `ticks`.  rest(s, y): cell y of row s + 1.
+    template <int W, typename F>
+    __device__ __forceinline__ int read_out(uint32_t total, uint32_t ticks, int x, F rest) const
     {
         constexpr uint32_t INDEX = (1u << INDEX_BITS) - 1u;
         const uint32_t* const tab = lds + L.tab;
-        uint32_t t = ticks, my_k = 0, my_cost = my_base;
-        const int d = lane;
+        uint32_t t = ticks, my_k = 0, my_cost = lane < a.S ? keys()[lane] >> 15 : 0u;
+        const int d = lane & (W - 1);
         uint32_t e = tab[d];
         for (int s = 0; s < a.S; ++s) {
             const bool more_models = s + 1 < a.S;
             const uint32_t r = more_models ? rest(s, x >= d ? x - d : 0) : 0u;
-            const uint32_t e_next = more_models ? tab[(s + 1) * 64 + d] : 0u;
+            const uint32_t e_next = more_models ? tab[(s + 1) * W + d] : 0u;
             unsigned long long who = __ballot(d <= x && (e >> INDEX_BITS) + r == t);
+            if (W < 64) who &= (1ull << (W & 63)) - 1ull;
             if (who == 0ull) {  // never expected
                 put_none(THEMIS_INTERNAL);
                 return THEMIS_INTERNAL;
@@ -463,9 +483,45 @@ struct Solver {
             x -= l;
             e = e_next;
         }
-        put(THEMIS_SOLVED, (int32_t)total, (int32_t)ticks, BY_C);
+        put(THEMIS_SOLVED, (int32_t)total, (int32_t)ticks, W == 16 ? BY_B16 : BY_C);
         put_choice(my_k, my_cost);
         return THEMIS_SOLVED;
+    }
+
+    // The recurrence over 16 cells.  Every row of sixteen lanes holds g[s+1][0..15]; row r
+    // takes the table's costs 4 q + r, so its copy is first shifted by r and then by 4 q,
+    // both operand modifiers, and the four rows' minima are combined.  (What does not beat
+    // everything cheaper does no harm.)  `base_sum`: the sum of the models' least costs.
+    __device__ __forceinline__ int solve_sixteen(uint32_t base_sum) const
+    {
+        const uint32_t* const tab = lds + L.tab;
+        uint32_t* const rows = lds + L.tab + 64 * a.S;
+        uint32_t g = 0u;  // g[S]: nothing left to run
+        const int at = lane >> 4;
+        for (int s = a.S - 1; s >= 0; --s) {
+            const uint32_t* const mine = tab + s * 16 + at;
+            uint32_t v[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] = mine[4 * q] >> INDEX_BITS;  // EMPTY: 2^19 - 1
+            uint32_t h = row_shifted<1, 0x2>(g, LT_NONE);
+            // the lanes a shift leaves without a source keep their own value: mark them
+            h = row_shifted<2, 0x4>(h, LT_NONE);
+            h = row_shifted<3, 0x8>(h, LT_NONE);
+            h = (lane & 15) < at ? LT_NONE : h;
+            uint32_t acc = h + v[0];
+            acc = least(acc, row_shifted<4>(h, LT_NONE) + v[1]);
+            acc = least(acc, row_shifted<8>(h, LT_NONE) + v[2]);
+            acc = least(acc, row_shifted<12>(h, LT_NONE) + v[3]);
+            g = least_of_rows(acc);
+            if (lane < 16) rows[s * 16 + lane] = g;
+        }
+        const uint32_t m = (uint32_t)__ballot(g <= (uint32_t)T) & 0xFFFFu;
+        if (m == 0u) return UNFINISHED;
+        const int x = __builtin_ctz(m);
+        const uint32_t ticks = lane_value(g, x);
+        wave_lds_fence();
+        return read_out<16>(base_sum + (uint32_t)x, ticks, x,
+                            [&](int s, int y) { return rows[(s + 1) * 16 + y]; });
     }
 
     // ---- sweeps over the candidates, for steps C and G -----------------------------
@@ -1448,7 +1504,7 @@ struct Solver {
         if (m == 0ull) return UNFINISHED;
         const int x = __builtin_ctzll(m);
         const uint32_t my_base = lane < a.S ? keys()[lane] >> 15 : 0u;
-        return read_out(sum_models(my_base) + (uint32_t)x, lane_value(acc, x), x, my_base,
+        return read_out<64>(sum_models(my_base) + (uint32_t)x, lane_value(acc, x), x,
                             [&](int s, int y) { return (uint32_t)row_of(s + 1)[y]; });
     }
 
