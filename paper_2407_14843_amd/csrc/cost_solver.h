@@ -129,10 +129,10 @@ enum { PLAIN, QUIET, SECOND, PINNED };
 // the lists are to be made by narrowing; products exceed 2^42.
 constexpr int UNFINISHED = -1, ARE_LISTED = -2, TOO_MANY = -3, LARGE = -4;
 
-// What follows on the lists of step G, where all candidates fit them, is in functions of their
-// own, called one after the other: NARROW, those lists where they do not fit, by way of
+// What follows on step C is in functions of their own, called one after the other: LIST, the lists
+// of step G where all candidates fit them; NARROW, those lists where they do not, by way of
 // PRICE; GAP, step G up to its end, which is TRIAL, ROWS or ROWS_HBM; WD, steps W and D.
-enum { PART_PRICE, PART_NARROW, PART_GAP, PART_TRIAL, PART_ROWS, PART_ROWS_HBM, PART_WD };
+enum { PART_LIST, PART_PRICE, PART_NARROW, PART_GAP, PART_TRIAL, PART_ROWS, PART_ROWS_HBM, PART_WD };
 template <int QUEUE, bool DERIVE, int ROLE, int PART>
 __device__ __attribute__((noinline)) int solve_part(uint64_t args, int i, int T, int32_t lam,
                                                     int32_t slo, int x);
@@ -1797,7 +1797,7 @@ struct Solver {
     {
         const int status = solve_sixtyfour();
         wave_lds_fence();
-        return status == UNFINISHED ? list_all() : status;
+        return status == UNFINISHED ? out_of_line<PART_LIST>() : status;
     }
 
     // Steps C, G, W and D.
@@ -1854,6 +1854,7 @@ struct Solver {
     __device__ __forceinline__ int part(int inst, int budget, int32_t rate, int32_t objective, int x)
     {
         instance(inst, budget, rate, objective);
+        if constexpr (PART == PART_LIST) return list_all();
         if constexpr (PART == PART_PRICE) return find_price();
         if constexpr (PART == PART_NARROW) return list_narrowed() ? ARE_LISTED : UNFINISHED;
         if constexpr (PART == PART_GAP) return find_survivors();
