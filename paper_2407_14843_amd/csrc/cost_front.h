@@ -549,7 +549,7 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
             if (status != UNFINISHED) return status;
             wave_lds_fence();
         }
-        fill<SMALL>(first, mine, best, 64, 64);
+        if (!this->shares_pairs()) fill<SMALL>(first, mine, best, 64, 64);
         return UNFINISHED;
     }
     // How many cells it takes, by how much the cheapest assignment is late, as a part of
@@ -703,10 +703,11 @@ __device__ __attribute__((noinline)) int solve_rest(uint64_t args, int i, int T,
     Front<QUEUE, DERIVE, 0, ROLE> sv((ArgsPtr)(uintptr_t)(hi << 32 | lo));
     sv.instance(uniform(i), uniform(T), uniform(lam), uniform(slo));
     int status;
-    if (sv.is_small())
+    if (sv.is_small() ||
+        (status = uniform(sv.template solve_valid<false>(sv.pair_of_round(0)))) == UNFINISHED) {
+        if (sv.shares_pairs()) sv.fill_sixtyfour();
         status = sv.solve_further();
-    else if ((status = uniform(sv.template solve_valid<false>(sv.pair_of_round(0)))) == UNFINISHED)
-        status = sv.solve_further();
+    }
     status = uniform(status);
     if (uniform((int)none) && (status == THEMIS_INVALID || status == THEMIS_INFEASIBLE)) sv.put_none(status);
     return status;

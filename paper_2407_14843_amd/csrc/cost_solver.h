@@ -1508,6 +1508,39 @@ struct Solver {
                             [&](int s, int y) { return (uint32_t)row_of(s + 1)[y]; });
     }
 
+    // Whether several lanes share a pair's cores in sweeps.
+    __device__ __forceinline__ bool shares_pairs() const { return args->parts > 1u; }
+    // The table of 64 cells per model, where they do: with a lane per pair half of the lanes
+    // or more would have no part in it (16193 x 7 with three batch sizes 118 us instead of
+    // 84, 25925 x 6 with four, replicas given, 73 instead of 60).  With more pairs than half
+    // the lanes, those of step A, kept in registers, are the faster way (16384 x 8 with
+    // replicas given 23.9 us instead of 25.2, 65536 x 8 76.0 instead of 77.4).
+    __device__ __forceinline__ void fill_sixtyfour() const
+    {
+        uint32_t* const tab = lds + L.tab;
+        for (int x = lane; x < a.S * 64; x += 64) tab[x] = EMPTY;
+        wave_lds_fence();
+        sweep<DEALT>(
+            [&](const Pair& p) {
+                const uint32_t base = keys()[p.s] >> 15;
+                Cores c = cores_up_to(p, base + 63u);
+                if (!DERIVE) {
+                    const float least_c =
+                        (float)base * __builtin_amdgcn_rcpf((float)p.h.n_given) * 0.9999f;
+                    c.lo = least_c > (float)c.lo ? (uint32_t)least_c : c.lo;
+                }
+                return c;
+            },
+            [&](const Pair& p) {
+                return [=, base = keys()[p.s] >> 15, mine = tab + 64u * p.s, j = p.j](
+                           uint32_t c, uint32_t lt, uint32_t cost) {
+                    if (cost - base < 64u)
+                        atomicMin(&mine[cost - base],
+                                  (lt << INDEX_BITS) | ((c - 1u) * (uint32_t)a.n_batch + j));
+                };
+            });
+    }
+
     // The table of one model, W cells.  All lanes work on it: lane = (part, batch size),
     // the parts take the cores in turn.
     __device__ __forceinline__ void fill_model(int s, int W) const
