@@ -349,10 +349,14 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
                     const uint32_t d = (key >> 15) - base, lt = key & 0x7FFFu;
                     // (EMPTY is beyond any cell)
                     const bool use = (int)is & (int)(d - 1u < span - 1u) & (int)(lt < before);
-                    at[q] = use ? p.s * cells + d : 0u;
+                    at[q] = use ? p.s * cells + d : (uint32_t)lane;
                     what[q] = use ? lt << INDEX_BITS | (__umul24(c[q] - 1u, (uint32_t)a.n_batch) + p.j) : EMPTY;
                 }
-                // (EMPTY changes nothing)
+                // EMPTY changes nothing, in a word of the lane's own: where all lanes without an
+                // entry had the first word, one after the other, the atomics of a compute unit's
+                // wavefronts took most of the time of a table (24000 x 6 with answers of 8 to 15
+                // cells and replicas given 80 us instead of 48; under a branch 49.4, and
+                // small batches up to half a microsecond longer)
                 atomicMin(&tab[at[0]], what[0]);
                 atomicMin(&tab[at[1]], what[1]);
             }
