@@ -168,35 +168,28 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
     // ---- step A ------------------------------------------------------------------
     // What the cost and the latency of a pair's candidates are at least, in single precision
     // with every term moved to the safe side by more than its error (2^-22 or so): with c
-    // cores n = ceil(rn / c + rf) replicas, and td / c + tf + n tw ticks.
+    // cores n = ceil(rn / c + rf) replicas, and td / c + tf + n tw ticks.  (With the replicas
+    // given a cost says which core count it is, and every one is worth its evaluation.)
     struct Bounds {
-        float rn, rf, td, tf, tw, per_n;
+        float rn, rf, td, tf, tw;
     };
     __device__ __forceinline__ Bounds bounds_of(const Pair& p) const
     {
         constexpr float DOWN = 0.999998f;
         Bounds b;
         const float num = (float)p.num, fixed = (float)p.fixed, rate = (float)p.ratio;
-        b.per_n = (float)p.h.n_given;
         b.rn = rate * num * DOWN, b.rf = rate * fixed * DOWN;
         const float per_us = (float)a.rtick * DOWN;
         b.td = num * per_us, b.tf = fixed * per_us;
         b.tw = p.w * __builtin_amdgcn_rcpf((float)lam) * per_us * DOWN;
-        // (the queue does not depend on n, or n does not on the cores)
-        if (QUEUE != THEMIS_QUEUE_PER_REPLICA || !DERIVE) {
-            b.tf += QUEUE == THEMIS_QUEUE_PER_REPLICA ? b.tw * b.per_n : b.tw;
-            b.tw = 0.0f;
-        }
+        if (QUEUE != THEMIS_QUEUE_PER_REPLICA) b.tf += b.tw, b.tw = 0.0f;
         return b;
     }
     // The most cores with which candidates of the pair can cost as little as `limit`.
     __device__ __forceinline__ float most_cores(const Pair& p, const Bounds& b, float limit) const
     {
-        float most;
-        if (DERIVE)
-            most = __builtin_fminf((limit - b.rn) * __builtin_amdgcn_rcpf(b.rf) * 1.00001f, limit);
-        else
-            most = limit * __builtin_amdgcn_rcpf(b.per_n) * 1.00001f;
+        const float most =
+            __builtin_fminf((limit - b.rn) * __builtin_amdgcn_rcpf(b.rf) * 1.00001f, limit);
         return __builtin_fminf(most, (float)p.last);
     }
     // Which of the 32 core counts from c0 on, and up to `most`, can cost as little as `limit`
@@ -216,13 +209,10 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
             for (int q = 0; q < 4; ++q) {
                 const float r = __builtin_amdgcn_rcpf(c);
                 // negative where the count is promising
-                uint32_t sign = 0x80000000u;
+                const float reps = __builtin_ceilf(__builtin_fmaf(b.rn, r, b.rf));
+                uint32_t sign = __float_as_uint(__builtin_fmaf(reps, c, -0.5f - limit));
                 float y = b.tf;
-                if (DERIVE) {
-                    const float reps = __builtin_ceilf(__builtin_fmaf(b.rn, r, b.rf));
-                    sign &= __float_as_uint(__builtin_fmaf(reps, c, -0.5f - limit));
-                    if (QUEUE == THEMIS_QUEUE_PER_REPLICA) y = __builtin_fmaf(reps, b.tw, y);
-                }
+                if (QUEUE == THEMIS_QUEUE_PER_REPLICA) y = __builtin_fmaf(reps, b.tw, y);
                 if (LATE) sign &= __float_as_uint(__builtin_fmaf(b.td, r, y) + (0.9f - before));
                 mask = __builtin_amdgcn_alignbit(mask, sign, 31);
                 c += 1.0f;
@@ -325,40 +315,55 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
                                           uint32_t span) const
     {
         uint32_t* const tab = lds + L.tab;
-        const Bounds b = bounds_of(p);
         const uint32_t base = best >> 15, before = best & 0x7FFFu;
         const float limit = (float)(base + span - 1u);
-        const float most = p.there ? most_cores(p, b, limit) : -1.0f;
-        uint32_t from = c0;
-        if (!DERIVE) {
-            const float least_c = (float)base * __builtin_amdgcn_rcpf(b.per_n) * 0.9999f;
-            from = least_c > (float)from ? (uint32_t)least_c : from;
-        }
-        for (; any((float)from <= most); from += 32u) {
-            uint32_t mask = promising<true>(b, from, most, limit, (float)before);
-            while (any(mask != 0u)) {
-                // two at a time: their chains of dependent operations fill each other's waits
-                uint32_t c[2], at[2], what[2];
+        // two at a time: their chains of dependent operations fill each other's waits
+        auto enter_two = [&](const bool (&is)[2], const uint32_t (&c)[2]) {
+            uint32_t at[2], what[2];
 #pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    const bool is = mask != 0u;
-                    const uint32_t z = (uint32_t)__builtin_clz(mask | 1u);
-                    mask &= ~(0x80000000u >> z);
-                    c[q] = is ? from + z : p.lo;
-                    const uint32_t key = meet<SMALL>(p, c[q]);
-                    const uint32_t d = (key >> 15) - base, lt = key & 0x7FFFu;
-                    // (EMPTY is beyond any cell)
-                    const bool use = (int)is & (int)(d - 1u < span - 1u) & (int)(lt < before);
-                    at[q] = use ? p.s * cells + d : (uint32_t)lane;
-                    what[q] = use ? lt << INDEX_BITS | (__umul24(c[q] - 1u, (uint32_t)a.n_batch) + p.j) : EMPTY;
+            for (int q = 0; q < 2; ++q) {
+                const uint32_t key = meet<SMALL>(p, c[q]);
+                const uint32_t d = (key >> 15) - base, lt = key & 0x7FFFu;
+                // (EMPTY is beyond any cell)
+                const bool use = (int)is[q] & (int)(d - 1u < span - 1u) & (int)(lt < before);
+                at[q] = use ? p.s * cells + d : (uint32_t)lane;
+                what[q] = use ? lt << INDEX_BITS | (__umul24(c[q] - 1u, (uint32_t)a.n_batch) + p.j) : EMPTY;
+            }
+            // EMPTY changes nothing, in a word of the lane's own: where all lanes without an
+            // entry had the first word, one after the other, the atomics of a compute unit's
+            // wavefronts took most of the time of a table (24000 x 6 with answers of 8 to 15
+            // cells and replicas given 80 us instead of 48; under a branch 49.4, and small
+            // batches up to half a microsecond longer)
+            atomicMin(&tab[at[0]], what[0]);
+            atomicMin(&tab[at[1]], what[1]);
+        };
+        if constexpr (DERIVE) {
+            const Bounds b = bounds_of(p);
+            const float most = p.there ? most_cores(p, b, limit) : -1.0f;
+            for (uint32_t from = c0; any((float)from <= most); from += 32u) {
+                uint32_t mask = promising<true>(b, from, most, limit, (float)before);
+                while (any(mask != 0u)) {
+                    bool is[2];
+                    uint32_t c[2];
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) {
+                        is[q] = mask != 0u;
+                        const uint32_t z = (uint32_t)__builtin_clz(mask | 1u);
+                        mask &= ~(0x80000000u >> z);
+                        c[q] = is[q] ? from + z : p.lo;
+                    }
+                    enter_two(is, c);
                 }
-                // EMPTY changes nothing, in a word of the lane's own: where all lanes without an
-                // entry had the first word, one after the other, the atomics of a compute unit's
-                // wavefronts took most of the time of a table (24000 x 6 with answers of 8 to 15
-                // cells and replicas given 80 us instead of 48; under a branch 49.4, and
-                // small batches up to half a microsecond longer)
-                atomicMin(&tab[at[0]], what[0]);
-                atomicMin(&tab[at[1]], what[1]);
+            }
+        } else {
+            const float r = __builtin_amdgcn_rcpf((float)p.h.n_given);
+            const float most =
+                p.there ? __builtin_fminf(limit * r * 1.00001f, (float)p.last) : -1.0f;
+            const uint32_t least_c = (uint32_t)((float)base * r * 0.9999f);
+            for (uint32_t from = least_c > c0 ? least_c : c0; any((float)from <= most); from += 2u) {
+                const bool is[2] = {(float)from <= most, (float)(from + 1u) <= most};
+                const uint32_t c[2] = {is[0] ? from : p.lo, is[1] ? from + 1u : p.lo};
+                enter_two(is, c);
             }
         }
     }
