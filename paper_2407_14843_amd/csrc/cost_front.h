@@ -128,8 +128,9 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
     // What step A finds about a model, the same in all its lanes: cost << 15 | lt of the best
     // candidate (EMPTY: none is feasible) and its index.  c0: the lane's first_core().
     // mine: this lane's own best is the one, with that many cores.
+    // own: the lane's own best's.
     struct Best {
-        uint32_t key, k, c0, c;
+        uint32_t key, k, c0, c, own;
         bool mine;
     };
 
@@ -276,17 +277,21 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
         b.c0 = c0;
         const uint32_t mine = __umul24(best_c - 1u, (uint32_t)a.n_batch) + p.j;
         b.k = model_least(p, best == model ? mine : EMPTY);
-        b.c = best_c;
+        b.c = best_c, b.own = best;
         b.mine = p.there && best == model && mine == b.k;
         return b;
     }
 
     // ---- step F ------------------------------------------------------------------
     // lt << 15 | cost of the fastest candidate of the lanes' models, EMPTY where there is none.
+    // fastest: the lane's own, where it is known.
     template <bool SMALL>
     __device__ __forceinline__ uint32_t fastest_of(const Pair& p) const
     {
-        const uint32_t key = meet<SMALL>(p, p.last);
+        return fastest_of(p, meet<SMALL>(p, p.last));
+    }
+    __device__ __forceinline__ uint32_t fastest_of(const Pair& p, uint32_t key) const
+    {
         // (of equal latencies any cost will do)
         const uint32_t turned = key == EMPTY || !p.there ? EMPTY : (key & 0x7FFFu) << 15 | key >> 15;
         return model_least(p, turned);
@@ -378,8 +383,9 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
     // cells this way, two per lane, hold 32 values at once, with twenty registers spilled in
     // every kernel: 512 x 5 7.5 us instead of 7.2, stability 4099 x 5 19.4 instead of 18.8,
     // 22473 x 9 with replicas given 58.9 instead of 55.2.)
-    // `span`: the cells over base up to which the table is complete.
-    __device__ __forceinline__ int solve_eight(uint32_t base_sum, int span) const
+    // `span`: the cells over base up to which the table is complete; shift: its words per model,
+    // as a power of two.
+    __device__ __forceinline__ int solve_eight(uint32_t base_sum, int span, uint32_t shift) const
     {
         typedef uint32_t four __attribute__((ext_vector_type(4), aligned(16)));
         constexpr uint32_t INDEX = (1u << INDEX_BITS) - 1u;
@@ -407,7 +413,7 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
             const int s = is ? s0 + g : end - 1;
             uint32_t* const mine = rows + STRIDE * s;
             // (of at most x cells: with nothing behind them the models are done)
-            h = segmented_scan<true>(tab[CELLS * s + x] >> INDEX_BITS, (uint32_t)x, 8u);
+            h = segmented_scan<true>(tab[(s << shift) + x] >> INDEX_BITS, (uint32_t)x, 8u);
             if (is) mine[x] = h;
             wave_lds_fence();
             const int to = end < S ? end + 1 : end;
@@ -433,7 +439,7 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
             // the smallest index among the candidates that continue an optimum, and its cell
             uint32_t pick = EMPTY, w[8], o[8];
             const uint32_t t = mine[x];
-            forwards(tab + CELLS * s, w);
+            forwards(tab + (s << shift), w);
             backwards(mine + STRIDE, o);
 #pragma unroll
             for (int q = 0; q < 8; ++q) {
@@ -504,7 +510,7 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
     template <bool SMALL>
     __device__ __forceinline__ int solve_valid(const Pair& first) const
     {
-        Best mine{EMPTY, 0u, 0u, 0u, false};
+        Best mine{EMPTY, 0u, 0u, 0u, EMPTY, false};
         uint32_t ticks = 0u;
         for_pairs(first, [&](const Pair& p) {
             const Best b = best_of<SMALL>(p);
@@ -535,9 +541,11 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
             }
             return THEMIS_SOLVED;
         }
+        const bool one = this->one_each();
         uint32_t least_ticks = 0u;
         for_pairs(first, [&](const Pair& p) {
-            const uint32_t f = fastest_of<SMALL>(p);
+            // (where it is the lane's only candidate step A has met it)
+            const uint32_t f = ONE && one ? fastest_of(p, mine.own) : fastest_of<SMALL>(p);
             least_ticks += sum_of_models(p, f >> 15);
             if (leads(p)) {
                 this->fastest()[p.s] = f;
@@ -546,17 +554,19 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
         });
         if (least_ticks > (uint32_t)T) return THEMIS_INFEASIBLE;
         const int reach = reach_of(ticks, least_ticks);
+        // (one candidate each: what there is to enter is at hand, for all windows at once)
+        if (one) fill_one_each<SMALL>(first, mine);
         if (reach <= 8) {
-            fill<SMALL>(first, mine, best, 8, reach);
-            const int status = solve_eight(base_sum, reach);
+            if (!one) fill<SMALL>(first, mine, best, 8, reach);
+            const int status = solve_eight(base_sum, one ? 8 : reach, one ? 6u : 3u);
             if (status != UNFINISHED) return status;
             wave_lds_fence();
         }
-        if (reach <= 16) {
-            fill<SMALL>(first, mine, best, 16, 16);
-            const int status = this->solve_sixteen(base_sum);
-            if (status != UNFINISHED) return status;
+        if (one || reach <= 16) {
+            if (!one) fill<SMALL>(first, mine, best, 16, 16);
+            const int status = this->solve_sixteen(base_sum, one ? 64 : 16);
             wave_lds_fence();
+            if (one || status != UNFINISHED) return status;
         }
         if (!this->shares_pairs()) fill<SMALL>(first, mine, best, 64, 64);
         return UNFINISHED;
@@ -596,6 +606,24 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
                 enter<SMALL>(p, mine.c0, mine.key, (uint32_t)cells, (uint32_t)span);
             else
                 enter<SMALL>(p, this->first_core(p), this->keys()[p.s], (uint32_t)cells, (uint32_t)span);
+        });
+        wave_lds_fence();
+    }
+    // The table of 64 cells per model where every pair has one candidate.
+    template <bool SMALL>
+    __device__ __forceinline__ void fill_one_each(const Pair& first, const Best& mine) const
+    {
+        uint32_t* const tab = lds + L.tab;
+        for (int y = lane; y < 64 * a.S; y += 64) tab[y] = EMPTY;
+        wave_lds_fence();
+        for_pairs(first, [&](const Pair& p) {
+            const uint32_t key = ONE ? mine.own : meet<SMALL>(p, p.last);
+            const uint32_t base = (ONE ? mine.key : this->keys()[p.s]) >> 15, d = (key >> 15) - base;
+            // (EMPTY is beyond any cell)
+            const bool use = (int)p.there & (int)(d < 64u);
+            atomicMin(&tab[use ? 64u * p.s + d : (uint32_t)lane],
+                      use ? (key & 0x7FFFu) << INDEX_BITS | (__umul24(p.last - 1u, (uint32_t)a.n_batch) + p.j)
+                          : EMPTY);
         });
         wave_lds_fence();
     }
@@ -714,7 +742,7 @@ __device__ __attribute__((noinline)) int solve_rest(uint64_t args, int i, int T,
     int status;
     if (sv.is_small() ||
         (status = uniform(sv.template solve_valid<false>(sv.pair_of_round(0)))) == UNFINISHED) {
-        if (sv.shares_pairs()) sv.fill_sixtyfour();
+        if (sv.shares_pairs() && !sv.one_each()) sv.fill_sixtyfour();
         status = sv.solve_further();
     }
     status = uniform(status);

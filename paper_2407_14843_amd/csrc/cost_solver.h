@@ -252,6 +252,12 @@ struct Solver {
         p.ratio = p.h.lam * p.bh.rM;
     }
 
+    // Whether every pair has one core count, and with it one candidate.
+    __device__ __forceinline__ bool one_each() const
+    {
+        return ROLE == PINNED || a.c_fixed || a.c_all || a.c_max == 1;
+    }
+
     // Reciprocals of the core counts, for loops over them: lane l holds that of l + 1, a
     // lane fetches the one it needs (three instructions instead of nine).
     struct Recips {
@@ -450,11 +456,11 @@ struct Solver {
         return ((uint32_t)ev.lt << INDEX_BITS) | k;
     }
 
-    // Forward over the models, with the table of W <= 64 cells per model: the smallest
-    // index among the candidates that continue an optimum of x cells over base and
-    // `ticks`.  rest(s, y): cell y of row s + 1.
+    // Forward over the models, with the table of W <= 64 cells per model, `stride` from one
+    // model to the next: the smallest index among the candidates that continue an optimum of
+    // x cells over base and `ticks`.  rest(s, y): cell y of row s + 1.
     template <int W, typename F>
-    __device__ __forceinline__ int read_out(uint32_t total, uint32_t ticks, int x, F rest) const
+    __device__ __forceinline__ int read_out(uint32_t total, uint32_t ticks, int x, int stride, F rest) const
     {
         constexpr uint32_t INDEX = (1u << INDEX_BITS) - 1u;
         const uint32_t* const tab = lds + L.tab;
@@ -464,7 +470,7 @@ struct Solver {
         for (int s = 0; s < a.S; ++s) {
             const bool more_models = s + 1 < a.S;
             const uint32_t r = more_models ? rest(s, x >= d ? x - d : 0) : 0u;
-            const uint32_t e_next = more_models ? tab[(s + 1) * W + d] : 0u;
+            const uint32_t e_next = more_models ? tab[(s + 1) * stride + d] : 0u;
             unsigned long long who = __ballot(d <= x && (e >> INDEX_BITS) + r == t);
             if (W < 64) who &= (1ull << (W & 63)) - 1ull;
             if (who == 0ull) {  // never expected
@@ -491,15 +497,16 @@ struct Solver {
     // The recurrence over 16 cells.  Every row of sixteen lanes holds g[s+1][0..15]; row r
     // takes the table's costs 4 q + r, so its copy is first shifted by r and then by 4 q,
     // both operand modifiers, and the four rows' minima are combined.  (What does not beat
-    // everything cheaper does no harm.)  `base_sum`: the sum of the models' least costs.
-    __device__ __forceinline__ int solve_sixteen(uint32_t base_sum) const
+    // everything cheaper does no harm.)  `base_sum`: the sum of the models' least costs;
+    // `stride`: words of the table per model.
+    __device__ __forceinline__ int solve_sixteen(uint32_t base_sum, int stride) const
     {
         const uint32_t* const tab = lds + L.tab;
         uint32_t* const rows = lds + L.tab + 64 * a.S;
         uint32_t g = 0u;  // g[S]: nothing left to run
         const int at = lane >> 4;
         for (int s = a.S - 1; s >= 0; --s) {
-            const uint32_t* const mine = tab + s * 16 + at;
+            const uint32_t* const mine = tab + s * stride + at;
             uint32_t v[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) v[q] = mine[4 * q] >> INDEX_BITS;  // EMPTY: 2^19 - 1
@@ -520,7 +527,7 @@ struct Solver {
         const int x = __builtin_ctz(m);
         const uint32_t ticks = lane_value(g, x);
         wave_lds_fence();
-        return read_out<16>(base_sum + (uint32_t)x, ticks, x,
+        return read_out<16>(base_sum + (uint32_t)x, ticks, x, stride,
                             [&](int s, int y) { return rows[(s + 1) * 16 + y]; });
     }
 
@@ -1504,7 +1511,7 @@ struct Solver {
         if (m == 0ull) return UNFINISHED;
         const int x = __builtin_ctzll(m);
         const uint32_t my_base = lane < a.S ? keys()[lane] >> 15 : 0u;
-        return read_out<64>(sum_models(my_base) + (uint32_t)x, lane_value(acc, x), x,
+        return read_out<64>(sum_models(my_base) + (uint32_t)x, lane_value(acc, x), x, 64,
                             [&](int s, int y) { return (uint32_t)row_of(s + 1)[y]; });
     }
 

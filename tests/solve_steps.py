@@ -17,10 +17,14 @@ def steps_of(p, workspace):
     return np.where(status & 0xFF, -1, status >> 8)
 
 
-def steps_by_rule(w, oracle, want):
+def steps_by_rule(w, oracle, want, cores=None):
     """The step that csrc/cost_front.h's rule (Front::reach_of) and the answers `want` make it,
-    per instance; "" where there is no answer, or it lies beyond the 64 cells of step C."""
+    per instance; "" where there is no answer, or it lies beyond the 64 cells of step C.
+    cores: those of the horizontal solve."""
     lt, cost, _ = oracle.candidates(w)
+    if cores is not None:
+        mine = np.arange(lt.shape[-1]) // len(w.batch_sizes) + 1 == cores[..., None]
+        lt = np.where(mine, lt, -1)
     cost = np.where(lt >= 0, cost, 1 << 20)
     base = cost.min(axis=2)
     ticks = np.where((lt >= 0) & (cost == base[..., None]), lt, 1 << 20).min(axis=2).sum(axis=1)
@@ -28,10 +32,10 @@ def steps_by_rule(w, oracle, want):
     T = w.slo_us // w.tick_us
     x = want[1] - base.sum(axis=1)
     late, gain = (ticks - T) * 40, ticks - least
-    given = w.r_fixed is not None
+    given, one = w.r_fixed is not None, cores is not None or w.c_max == 1
     steps = []
     for i in range(w.n_inst):
-        cells = (4 if not given and late[i] <= 12 * gain[i] else
+        cells = (8 if one and late[i] <= 26 * gain[i] else 16 if one else 4 if not given and late[i] <= 12 * gain[i] else
                  8 if late[i] <= (14 if given else 26) * gain[i] else
                  16 if late[i] <= (26 if given else 31) * gain[i] else 64)
         steps.append("" if want[0][i] != 0 else "A" if late[i] <= 0 else

@@ -57,12 +57,13 @@ def test_layouts(T, oracle, S, n_batch, queue):
     assert (want[0] == 0).any()
 
 
-@pytest.mark.parametrize("given", [False, True])
-def test_window_edges(T, oracle, given):
+@pytest.mark.parametrize("kind", ["derived", "given", "one core"])
+def test_window_edges(T, oracle, kind):
     """Answers 0 to 17 over the least cost, all in one batch and each in one of its own, and the
     step that finds each of them."""
-    w = (family(21, 4000, 6, 16, [1, 2, 4, 8, 16], 5, 250, 700_000, (10, 400), r_fixed=5) if given
-         else families(4000)["three models"])
+    w = {"derived": lambda: family(22, 4000, 6, 16, [1, 2, 4, 8, 16], 30, 250, 500_000, (10, 900)),
+         "given": lambda: family(21, 4000, 6, 16, [1, 2, 4, 8, 16], 5, 250, 700_000, (10, 400), r_fixed=5),
+         "one core": lambda: families(4000)["three models"]}[kind]()
     want = oracle.solve(w, threads=8)
     at = np.nonzero(want[0] == 0)[0]
     over = over_base(w, oracle, want)
@@ -80,7 +81,28 @@ def test_window_edges(T, oracle, given):
             assert (steps == rule).all(), list(zip(steps, rule))
             met |= {(s, n) for s, n in zip(steps, over_base(v, oracle, x).tolist())}
     # each window up to its last cells, and step C where it found what step B was not asked for
-    assert {("B8", 7), ("B16", 15), ("B16", 8), ("C", 15), ("C", 16)} <= met, sorted(met)
+    if kind == "one core":
+        assert {("B8", 7), ("B16", 8), ("B16", 15), ("C", 16)} <= met, sorted(met)
+        assert not any(s == "C" and n < 16 for s, n in met), sorted(met)
+    else:
+        assert {("B8", 7), ("B16", 15), ("B16", 8), ("C", 15), ("C", 16)} <= met, sorted(met)
+
+
+@pytest.mark.parametrize("S,n_batch", [(4, 7), (8, 8), (7, 9), (9, 9)])
+def test_one_core_count(T, oracle, S, n_batch):
+    """With one candidate per model and batch size an answer below sixteen cells is step B's."""
+    rng = np.random.default_rng([S, n_batch])
+    w = family([S, n_batch, 7], 600, S, 7, list(range(1, n_batch + 1)), 32767 // (S * 7), 250,
+               S * 60_000, (10, 5000))
+    for cores in (np.ones((w.n_inst, S), np.int32), rng.integers(1, 8, (w.n_inst, S)).astype(np.int32)):
+        want = oracle.solve(w, threads=8, c_fixed=cores)
+        b = T.DeviceBatch(w)
+        b.solve_horizontal(cores)
+        same(b.results(), want)
+        rule = steps_by_rule(w, oracle, want, cores)
+        steps = np.array(STEPS + ("",))[steps_of(b.p, b.workspace)]
+        assert ((steps == rule) | (rule == "")).all(), list(zip(steps, rule))
+        assert {"A", "B8", "B16", "C"} <= set(rule), set(rule)
 
 
 @pytest.mark.parametrize("n_batch", [7, 13])
