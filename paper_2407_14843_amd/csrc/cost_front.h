@@ -542,18 +542,25 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
             return THEMIS_SOLVED;
         }
         const bool one = this->one_each();
-        uint32_t least_ticks = 0u;
+        uint32_t least_ticks = 0u, fast = 0u;
         for_pairs(first, [&](const Pair& p) {
             // (where it is the lane's only candidate step A has met it)
             const uint32_t f = ONE && one ? fastest_of(p, mine.own) : fastest_of<SMALL>(p);
             least_ticks += sum_of_models(p, f >> 15);
+            fast = f;
             if (leads(p)) {
                 this->fastest()[p.s] = f;
                 if (ONE) this->keys()[p.s] = mine.key;
             }
         });
         if (least_ticks > (uint32_t)T) return THEMIS_INFEASIBLE;
-        const int reach = reach_of(ticks, least_ticks);
+        if (!ONE) wave_lds_fence();
+        const int reach = reach_of(ticks, least_ticks, one, [&] {
+            const uint32_t cost =
+                ONE ? sum_of_models(first, fast & 0x7FFFu)
+                    : this->sum_models(lane < a.S ? this->fastest()[lane] & 0x7FFFu : 0u);
+            return cost - base_sum;
+        });
         // (one candidate each: what there is to enter is at hand, for all windows at once)
         if (one) fill_one_each<SMALL>(first, mine);
         if (reach <= 8) {
@@ -562,30 +569,38 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
             if (status != UNFINISHED) return status;
             wave_lds_fence();
         }
-        if (one || reach <= 16) {
+        if (reach <= 16) {
             if (!one) fill<SMALL>(first, mine, best, 16, 16);
             const int status = this->solve_sixteen(base_sum, one ? 64 : 16);
+            if (status != UNFINISHED) return status;
             wave_lds_fence();
-            if (one || status != UNFINISHED) return status;
         }
-        if (!this->shares_pairs()) fill<SMALL>(first, mine, best, 64, 64);
+        if (!one && !this->shares_pairs()) fill<SMALL>(first, mine, best, 64, 64);
         return UNFINISHED;
     }
-    // How many cells it takes, by how much the cheapest assignment is late, as a part of
-    // what the fastest gains on it.  By the oracle's answers for 1500 instances of each of
-    // the timed shapes, and of drawn ones: where the replicas are derived, up to three tenths
-    // of it is made up for within four cells, with next to no exception; beyond five eighths
-    // it mostly takes more than eight, beyond three quarters more than sixteen.  With the
-    // replicas given the gains are spread more evenly.  (Where an answer lies beyond these
-    // cells, or they are more than it takes, it is found all the same: at 4099 x 5 in the
-    // stability test sixteen cells ahead of every sixty-four take 21.8 us, none beyond three
-    // quarters 19.2.)
-    __device__ __forceinline__ int reach_of(uint32_t ticks, uint32_t least_ticks) const
+    // How many cells it takes, by how late the cheapest assignment is (`late`), what the fastest
+    // gains on it (`gain`) and how much more that one costs (span()).  The answers' cells over
+    // base grow as late / (1.1 gain - late) times the fourth root of the span: of the answers of
+    // 700 shapes drawn over 1 to 10 models, 4 to 32 cores, every list of batch sizes and
+    // objective, and of 6000 instances each of the numbered workloads, it is what a fit gives,
+    // and the bounds are where a step too small costs what a step too large does (24000
+    // instances of one class: eight cells 28 us, sixteen 47, sixty-four 69 beyond steps A and
+    // F; a single wavefront 1.6, 3.4 and 6.4).  Where the replicas are derived and up to three
+    // tenths of the gain is needed, four cells do, with next to no exception.  Where every pair
+    // has one candidate a table serves all windows, and sixteen cells cost least: they
+    // are left out only where nine in ten have more.  (By late / gain alone, at 26 and 31 of 40, or 14 and 26 with the replicas given, 43
+    // and 24 % of those sent to sixty-four had fewer than sixteen: 134 x 10 11.7 us instead of
+    // 9.6, 2 x 10 12.5 instead of 10.9, 13359 x 5 17.7 instead of 16.4; 16193 x 7 81.2 instead
+    // of 82.5.)
+    template <typename F>
+    __device__ __forceinline__ int reach_of(uint32_t ticks, uint32_t least_ticks, bool one, F span) const
     {
-        const uint32_t late = (ticks - (uint32_t)T) * 40u, gain = ticks - least_ticks;
-        if (DERIVE && late <= gain * 12u) return 4;
-        if (late <= gain * (DERIVE ? 26u : 14u)) return 8;
-        return late <= gain * (DERIVE ? 31u : 26u) ? 16 : 64;
+        const float late = (float)(ticks - (uint32_t)T), gain = (float)(ticks - least_ticks);
+        if (DERIVE && late <= 0.3f * gain) return 4;
+        const float have = late * __builtin_amdgcn_sqrtf(__builtin_amdgcn_sqrtf((float)span()));
+        const float need = 1.1f * gain - late;
+        if (have <= need * (DERIVE && !one ? 4.5f : 2.6f)) return 8;
+        return have <= need * (one ? 16.0f : DERIVE ? 11.0f : 7.0f) ? 16 : 64;
     }
     // The table of `cells` cells per model.  mine, best: what step A found, see solve_valid().
     template <bool SMALL>
