@@ -587,8 +587,8 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
     // instances of one class: eight cells 28 us, sixteen 47, sixty-four 69 beyond steps A and
     // F; a single wavefront 1.6, 3.4 and 6.4).  Where the replicas are derived and up to three
     // tenths of the gain is needed, four cells do, with next to no exception.  Where every pair
-    // has one candidate a table serves all windows, and sixteen cells cost least: they
-    // are left out only where nine in ten have more.  (By late / gain alone, at 26 and 31 of 40, or 14 and 26 with the replicas given, 43
+    // has one candidate a table serves all windows, and sixteen cells are always asked first:
+    // in vain they cost 1 us of 12 to 17, left out in vain 2.5 of 10.  (By late / gain alone, at 26 and 31 of 40, or 14 and 26 with the replicas given, 43
     // and 24 % of those sent to sixty-four had fewer than sixteen: 134 x 10 11.7 us instead of
     // 9.6, 2 x 10 12.5 instead of 10.9, 13359 x 5 17.7 instead of 16.4; 16193 x 7 81.2 instead
     // of 82.5.)
@@ -600,7 +600,7 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
         const float have = late * __builtin_amdgcn_sqrtf(__builtin_amdgcn_sqrtf((float)span()));
         const float need = 1.1f * gain - late;
         if (have <= need * (DERIVE && !one ? 4.5f : 2.6f)) return 8;
-        return have <= need * (one ? 16.0f : DERIVE ? 11.0f : 7.0f) ? 16 : 64;
+        return one || have <= need * (DERIVE ? 11.0f : 7.0f) ? 16 : 64;
     }
     // The table of `cells` cells per model.  mine, best: what step A found, see solve_valid().
     template <bool SMALL>

@@ -41,14 +41,14 @@ def steps_by_rule(w, oracle, want, cores=None):
     late_f, gain_f = late.astype(np.float32), gain.astype(np.float32)
     have = late_f * np.sqrt(np.sqrt((fast - base).sum(axis=1).clip(0).astype(np.float32)))
     need = np.float32(1.1) * gain_f - late_f
-    bounds = (2.6, 16.0) if one else (2.6, 7.0) if given else (4.5, 11.0)
+    bounds = (2.6, np.inf) if one else (2.6, 7.0) if given else (4.5, 11.0)
     # (the square roots of the two sides may differ in the last bits)
-    near = np.any([np.abs(have - b * need) <= 1e-5 * have for b in bounds], axis=0)
+    near = np.any([np.abs(have - b * need) <= 1e-5 * have for b in bounds if b < np.inf], axis=0)
     near |= np.abs(late_f - 0.3 * gain_f) <= 1e-5 * gain_f if not given else False
     steps = []
     for i in range(w.n_inst):
         cells = (4 if not given and late[i] <= 0.3 * gain[i] else
-                 8 if have[i] <= bounds[0] * need[i] else 16 if have[i] <= bounds[1] * need[i] else 64)
+                 8 if have[i] <= bounds[0] * need[i] else 16 if one or have[i] <= bounds[1] * need[i] else 64)
         cells = 8 if one and cells == 4 else cells
         steps.append("" if want[0][i] != 0 or near[i] else "A" if late[i] <= 0 else
                      "B8" if x[i] < cells <= 8 else "B16" if x[i] < 16 and cells <= 16 else

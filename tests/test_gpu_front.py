@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 
 from cost_families import families, family, over_base
+from paper_2407_14843_amd import workloads as wl
 from solve_steps import STEPS, steps_by_rule, steps_of
 from test_gpu_cost_solve import T, same  # noqa: F401
 
@@ -47,7 +48,7 @@ def every_call(T, oracle, w, r_most):
     (1, 1), (16, 4), (3, 3), (8, 8), (8, 5), (1, 16), (4, 16), (4, 9),
     (10, 6), (12, 5), (7, 9), (9, 7), (5, 12), (32, 2),
     (17, 4), (9, 8), (7, 12), (5, 16), (33, 2), (9, 9), (10, 10)])
-@pytest.mark.parametrize("queue", [0, 1])
+@pytest.mark.parametrize("queue", [0, 1, 2])
 def test_layouts(T, oracle, S, n_batch, queue):
     r_max = min(40, 32767 // (S * 7))
     w = family([S, n_batch], 96, S, 7, list(range(1, n_batch + 1)), r_max, 250, S * 60_000, (10, 900))
@@ -83,6 +84,7 @@ def test_window_edges(T, oracle, kind):
     # each window up to its last cells, and step C where it found what step B was not asked for
     if kind == "one core":
         assert {("B8", 7), ("B16", 8), ("B16", 15), ("C", 16)} <= met, sorted(met)
+        assert not any(s == "C" and n < 16 for s, n in met), sorted(met)
     else:
         assert {("B8", 7), ("B16", 15), ("B16", 8), ("C", 16)} <= met, sorted(met)
         assert any(s == "C" and n < 16 for s, n in met), sorted(met)
@@ -105,15 +107,34 @@ def test_one_core_count(T, oracle, S, n_batch):
         assert {"A", "B8", "B16", "C"} <= set(rule), set(rule)
 
 
-@pytest.mark.parametrize("n_batch", [7, 13])
-def test_products_beyond_42_bits(T, oracle, n_batch):
+@pytest.mark.parametrize("n_batch,queue", [(7, 0), (13, 0), (7, 2)])
+def test_products_beyond_42_bits(T, oracle, n_batch, queue):
     """Rates times objectives on both sides of 2^42."""
     w = family(9, 300, 3, 1, [2 ** j if n_batch == 7 else j + 1 for j in range(n_batch)], 10_000,
-               1000, 30_000_000, (50_000, 1_000_000))
+               1000, 30_000_000, (50_000, 1_000_000)).with_model(queue, None)
     large = w.lam.astype(np.int64) * w.slo_us >= 1 << 42
     assert large.any() and not large.all()
+    print(f"[case] beyond 2^42, three models, {n_batch} batch sizes, queue {queue}", flush=True)
     want = every_call(T, oracle, w, 10_000)
     assert (want[0][large] == 0).any()
+
+
+# rounds of models with gaps and without, more than eight models
+@pytest.mark.parametrize("S,n_batch,c_max,queue", [(10, 10, 1, 0), (17, 5, 1, 0), (17, 5, 1, 2), (9, 9, 2, 0)])
+def test_products_beyond_42_bits_in_rounds(T, oracle, S, n_batch, c_max, queue):
+    """Answers of every window at rates times objectives beyond 2^42, models in several rounds."""
+    rng, n = np.random.default_rng([42, S, n_batch]), 300
+    coef = wl._draw_coef(rng, (n, S), a=(1000, 40000), k=(100, 700), q=(0, 0), p=(1, c_max), o=(1, 2000))
+    sizes = sorted({int(x) for x in np.rint(np.geomspace(2, 1024, n_batch))})
+    r_max = 32767 // (S * c_max)
+    w = wl.Workload("large", wl.JOINT, n, S, c_max, sizes, r_max, 1000, 30_000_000, False, coef,
+                    rng.integers(100_000, 1_048_577, n).astype(np.int32),
+                    rng.integers(1_000_000, 30_000_000, n).astype(np.int32)).with_model(queue, None)
+    large = w.lam.astype(np.int64) * w.slo_us >= 1 << 42
+    print(f"[case] beyond 2^42, {S} models, {n_batch} batch sizes, queue {queue}", flush=True)
+    want = every_call(T, oracle, w, r_max)
+    met = set(steps_by_rule(w, oracle, want)[large])
+    assert {"A", "B16", "C"} <= met, met
 
 
 @pytest.mark.parametrize("S,n_batch", [(8, 8), (16, 4), (4, 16), (7, 9), (9, 9)])
