@@ -8,10 +8,10 @@
 // that goes through a scalar register.  So: minima per model in registers, bounds in
 // single precision ahead of evaluations, no loop over the models in step B, one call at the
 // very end.  Against evaluating every core count that the real-valued bound allows, with
-// LDS atomics per model and sixteen cells one model after the other, in microseconds:
-// 512 x 5 9.5 -> 7.1, 4096 x 5 13.3 -> 11.1, 3001 x 7 17.3 -> 13.0, stability 4099 x 5
-// 23.3 -> 19.5, 16384 x 8 with replicas given 26.2 -> 24.2, 86400 x 6 51.7 -> 39.7,
-// 65536 x 8 98.1 -> 76.3, fallback 16384 x 8 65 -> 29.3.
+// LDS atomics per model and sixteen cells for every instance, in microseconds:
+// 512 x 5 9.5 -> 7.0, 4096 x 5 13.3 -> 10.8, 3001 x 7 17.3 -> 12.8, stability 4099 x 5
+// 23.4 -> 17.4, 16384 x 8 with replicas given 26.3 -> 22.5, 86400 x 6 51.8 -> 39.7,
+// 65536 x 8 98.1 -> 76.3, fallback 16384 x 8 65 -> 28.5.
 #pragma once
 
 #include "cost_solver.h"
@@ -31,7 +31,7 @@ namespace {
 constexpr int PACKED = WIDTH_PACKED;
 template <int QUEUE, bool DERIVE, int ROLE>
 __device__ __attribute__((noinline)) int solve_rest(uint64_t args, int i, int T, int32_t lam,
-                                                    int32_t slo, bool none);
+                                                    int32_t slo);
 
 template <int QUEUE, bool DERIVE, int WIDTH, int ROLE = PLAIN>
 struct Front : Solver<QUEUE, DERIVE, ROLE> {
@@ -702,17 +702,16 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
             status = solve_valid<true>(first);
         return __builtin_amdgcn_readfirstlane(status);
     }
-    // What is left to do after that; `none`: also to write the results of an instance
-    // without an answer.
-    __device__ __forceinline__ int finish(int status, bool none) const
+    // What is left to do after that, and the results of an instance without an answer.
+    __device__ __forceinline__ int finish(int status) const
     {
         if (status == THEMIS_SOLVED) return status;
         if (status != UNFINISHED && status != LARGE) {
-            if (none) this->put_none(status);
+            this->put_none(status);
             return status;
         }
         return __builtin_amdgcn_readfirstlane(solve_rest<QUEUE, DERIVE, ROLE>(
-            (uint64_t)(uintptr_t)afresh(args), i, T, lam, slo, none));
+            (uint64_t)(uintptr_t)afresh(args), i, T, lam, slo));
     }
     // The same pointer, to arguments that the compiler hasn't loaded yet.
     static __device__ __forceinline__ ArgsPtr afresh(ArgsPtr p)
@@ -747,7 +746,7 @@ __device__ __attribute__((noinline)) int32_t rate_of_large(uint64_t args, int i,
 // from here 4096 x 5 took 12.4 us instead of 11.2.)
 template <int QUEUE, bool DERIVE, int ROLE>
 __device__ __attribute__((noinline)) int solve_rest(uint64_t args, int i, int T, int32_t lam,
-                                                    int32_t slo, bool none)
+                                                    int32_t slo)
 {
     auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
     const uint64_t lo = (uint32_t)uniform((int)(uint32_t)args);
@@ -761,7 +760,7 @@ __device__ __attribute__((noinline)) int solve_rest(uint64_t args, int i, int T,
         status = sv.solve_further();
     }
     status = uniform(status);
-    if (uniform((int)none) && (status == THEMIS_INVALID || status == THEMIS_INFEASIBLE)) sv.put_none(status);
+    if (status == THEMIS_INVALID || status == THEMIS_INFEASIBLE) sv.put_none(status);
     return status;
 }
 
@@ -773,7 +772,7 @@ __device__ __forceinline__ int solve_instance(ArgsPtr args, int inst, const int3
     Front<QUEUE, DERIVE, WIDTH, ROLE> sv(args, lane);
     bool valid;
     const auto first = sv.begin(inst, rates, valid);
-    return sv.finish(sv.solve(first, valid), true);
+    return sv.finish(sv.solve(first, valid));
 }
 
 }  // namespace

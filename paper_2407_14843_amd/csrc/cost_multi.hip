@@ -20,7 +20,7 @@
 // kernel around one-wavefront solves, eight launches and three, they took 250 and 28 us
 // at 16384 x 8 and 4099 x 5; as one launch each 65 and 23, with a solve at lambda ahead of
 // the search, an evaluation from the start for each of its midpoints and some sixty registers
-// spilled; now 30 and 19.  Pipelines of more than 64 models still go the other way, over the
+// spilled; now 28.5 and 17.4.  Pipelines of more than 64 models still go the other way, over the
 // three stages.
 #include "cost_front.h"
 
@@ -51,7 +51,7 @@ __device__ __forceinline__ void fallback_instance(ArgsPtr args, int i)
             sv.lam = rate = __builtin_amdgcn_readfirstlane(rate);
             first = sv.at_rate(first);
         }
-        status = sv.finish(sv.solve(first, valid), true);
+        status = sv.finish(sv.solve(first, valid));
     }
     const bool solved = status == THEMIS_SOLVED;
     args = Front<QUEUE, false, WIDTH, QUIET>::afresh(args);
@@ -77,7 +77,7 @@ __device__ __forceinline__ void fallback_instance(ArgsPtr args, int i)
     }
     bool valid;
     const auto first = nw.begin(i, rest, valid);
-    nw.finish(nw.solve(first, valid), true);
+    nw.finish(nw.solve(first, valid));
 }
 
 template <int QUEUE, int WIDTH>

@@ -58,7 +58,7 @@
 // against 0.3 KB of inputs and outputs; nothing but those touches HBM.  Whole solves
 // by the three stages (dense / with dominated candidates pruned) against this one, in
 // microseconds: 65536 x 8 models 25800 / 3880 -> 76, 16384 x 8 with replicas given
-// 3370 -> 24, 86400 x 6 2790 -> 40, 4096 x 5 177 -> 11.1, 64 x 3 27.2 -> 6.1.
+// 3370 -> 22.5, 86400 x 6 2790 -> 40, 4096 x 5 177 -> 10.8, 64 x 3 27.2 -> 6.5.
 #include "cost_front.h"
 
 namespace themis {

@@ -21,7 +21,7 @@ constexpr uint32_t SAME = 0xFFFFFFFFu;       // for a choice: the one of the sol
 struct __attribute__((aligned(16))) BatchConst {
     double rM, w;
     float M, both;
-    int32_t size, unused;
+    int32_t size;
 };
 
 // What every instance needs.
@@ -57,9 +57,9 @@ struct CostArgs : HotArgs {
 };
 
 // LDS words of one wavefront.  From `tab` on, steps B and C take a table of up to 64 words
-// per model and S + 1 rows: of 32-bit cells behind as many guard cells, or of 16-bit cells,
-// each with a guard cell (and one of padding) in front; wider windows a table of one model
-// and such rows.
+// per model and S + 1 rows: of eight 32-bit cells behind as many guard cells, of sixteen
+// without, or of 64 16-bit cells, each row with a guard cell (and one of padding) in front;
+// wider windows a table of one model and such rows.
 struct CostLds {
     int best, key, fast, pin, tab, rows, words;
 };
@@ -155,8 +155,10 @@ struct Solver {
         : args(p), a(hot_args(p)), lds(cost_smem), L(cost_lds(p->S, p->window)), lane(l)
     {
     }
+    // (member by member: the address space has no copies of whole structures)
     static __device__ __forceinline__ HotArgs hot_args(ArgsPtr p)
     {
+        static_assert(sizeof(HotArgs) == 200, "a member was added: copy it below");
         HotArgs h;
         h.coef = p->coef, h.lambda = p->lambda, h.slo_us = p->slo_us;
         h.r_fixed = p->r_fixed, h.c_fixed = p->c_fixed;
@@ -1986,11 +1988,10 @@ inline CostArgs cost_args(const themis_problem_t& p, const Layout& L, const int3
     }
     a.keep = opts.inspectable ? (int32_t*)(ws + L.step_off) : nullptr;
     a.n_batch = p.n_batch;
-    for (int j = 0; j < p.n_batch; ++j)
-{
+    for (int j = 0; j < p.n_batch; ++j) {
         const double b = (double)p.batch_sizes[j];
         a.bc[j] = {(1.0 / (1.0e6 * b)) * (1.0 - 0x1p-45), 1.0e6 * (b - 1.0), (float)(1.0e6 * b),
-                   (float)(b / (2.0 * b - 1.0)), p.batch_sizes[j], 0};
+                   (float)(b / (2.0 * b - 1.0)), p.batch_sizes[j]};
     }
     while (1 << a.width_log < p.n_batch) ++a.width_log;
     if (a.width_log < 2 && L.S <= 16) a.width_log = 2;
@@ -2021,9 +2022,9 @@ inline CostArgs cost_args(const themis_problem_t& p, const Layout& L, const int3
 }
 
 // The arguments with the arrays of all instances but the first n, for the launches after
-// the first one of a large batch: offsets in the kernels would cost every solve (the
-// fallback at 16384 x 8 62.8 us instead of 61.8, 65536 x 8 99.5 instead of 98.8).  (Each
-// of these launches marks the workspace again, with the same words.)
+// the first one of a large batch: offsets in the kernels would cost every solve (when it was
+// measured, the fallback at 16384 x 8 62.8 us instead of 61.8, 65536 x 8 99.5 instead of
+// 98.8).  (Each of these launches marks the workspace again, with the same words.)
 inline CostArgs past(CostArgs a, size_t n)
 {
     auto skip = [](auto*& array, size_t elements) {
