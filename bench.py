@@ -41,13 +41,13 @@ VALU_PEAK_GOPS = N_CU * 64 * CLOCK_GHZ                          # 39322 G lane-o
 # the counters were taken on, fingerprint of the kernel sources at that time).
 # `roofline.traffic` is null unless both still match this run.
 K2_HBM_TRAFFIC = {
-    "w1-joint-4096x5": (116367746, 5247396664, "24f8a557aa636b2c"),
-    "w3-joint-65536x8": (11106687523, 1422380424686, "24f8a557aa636b2c"),
+    "w1-joint-4096x5": (116324009, 5247396664, "a86600b4f43d6885"),
+    "w3-joint-65536x8": (11100893315, 1422380424686, "a86600b4f43d6885"),
 }
 # the same for stage 1 (input check + candidate kernel): workload -> (bytes, fingerprint)
 K1_HBM_TRAFFIC = {
-    "w1-joint-4096x5": (20099780, "24f8a557aa636b2c"),
-    "w3-joint-65536x8": (1064619748, "24f8a557aa636b2c"),
+    "w1-joint-4096x5": (20103389, "a86600b4f43d6885"),
+    "w3-joint-65536x8": (1064513773, "a86600b4f43d6885"),
 }
 KERNEL_SOURCES = ("k1_candidates.hip", "candidate_eval.h", "wave_ops.h", "k2_minplus.hip",
                   "instance_queue.h", "themis_internal.h")
@@ -56,8 +56,8 @@ KERNEL_SOURCES = ("k1_candidates.hip", "candidate_eval.h", "wave_ops.h", "k2_min
 # vector instructions of the timed whole solve per instance (the pipe counters in
 # profiles/*_kernel_trace.txt): workload -> (instructions, fingerprint of its sources)
 SOLVE_VALU = {
-    "w1-joint-4096x5": (383.3, "512d5256f5297d7b"),
-    "w3-joint-65536x8": (465.3, "512d5256f5297d7b"),
+    "w1-joint-4096x5": (382.7, "4caef5e6f9167590"),
+    "w3-joint-65536x8": (467.9, "4caef5e6f9167590"),
 }
 SOLVE_SOURCES = ("cost_solve.hip", "cost_front.h", "cost_solver.h", "candidate_eval.h",
                  "wave_ops.h", "themis_internal.h")
