@@ -58,8 +58,10 @@ struct CostArgs : HotArgs {
 
 // LDS words of one wavefront.  From `tab` on, steps B and C take a table of up to 64 words
 // per model and S + 1 rows: of eight 32-bit cells behind as many guard cells, of sixteen
-// without, or of 64 16-bit cells, each row with a guard cell (and one of padding) in front;
-// wider windows a table of one model and such rows.
+// without, or of 64 16-bit cells, behind which step C has its entries twice, a second copy of
+// the row at hand and that copy's guard cells; wider windows a table of one model and 16-bit
+// rows with a guard cell (and one of padding) in front of each.
+constexpr int STEP_C_WORDS = 2 * 64 + 32 + 33;
 struct CostLds {
     int best, key, fast, pin, tab, rows, words;
 };
@@ -72,8 +74,9 @@ __host__ __device__ inline CostLds cost_lds(int S, int window)
     l.pin = l.fast + S;
     l.tab = (l.pin + S + 3) & ~3;
     l.rows = l.tab + window;
-    const int c = l.rows + (S + 1) * (window + 2) / 2, b = l.tab + 64 * S + (S + 1) * 33;
-    l.words = ((c > b ? c : b) + 3) & ~3;
+    const int w = l.rows + (S + 1) * (window + 2) / 2;
+    const int b = l.tab + 64 * S + 8 + 16 * (S + 1), c = l.tab + 64 * S + 32 * (S + 1) + STEP_C_WORDS;
+    l.words = ((w > b ? w > c ? w : c : b > c ? b : c) + 3) & ~3;
     return l;
 }
 
@@ -460,21 +463,27 @@ struct Solver {
 
     // Forward over the models, with the table of W <= 64 cells per model, `stride` from one
     // model to the next: the smallest index among the candidates that continue an optimum of
-    // x cells over base and `ticks`.  rest(s, y): cell y of row s + 1.
-    template <int W, typename F>
-    __device__ __forceinline__ int read_out(uint32_t total, uint32_t ticks, int x, int stride, F rest) const
+    // x cells over base and `ticks`.  rows: W cells each, of models 0 to S - 1 and of nothing
+    // left to run.
+    //
+    // What bounds it is the chain from one model to the next: a read of LDS, a comparison, a
+    // scan of its bits and a lane's value.  So nothing else is in it: a lane whose cost is
+    // beyond x reads of the row before and is masked.
+    template <int W, typename R>
+    __device__ __forceinline__ int read_out(uint32_t total, uint32_t ticks, int x, int stride,
+                                            const R* rows) const
     {
         constexpr uint32_t INDEX = (1u << INDEX_BITS) - 1u;
         const uint32_t* const tab = lds + L.tab;
-        uint32_t t = ticks, my_k = 0, my_cost = lane < a.S ? keys()[lane] >> 15 : 0u;
+        uint32_t t = ticks, my_k = 0, my_over = 0;
         const int d = lane & (W - 1);
+        const R* row = rows + W - d;
         uint32_t e = tab[d];
         for (int s = 0; s < a.S; ++s) {
-            const bool more_models = s + 1 < a.S;
-            const uint32_t r = more_models ? rest(s, x >= d ? x - d : 0) : 0u;
-            const uint32_t e_next = more_models ? tab[(s + 1) * stride + d] : 0u;
-            unsigned long long who = __ballot(d <= x && (e >> INDEX_BITS) + r == t);
-            if (W < 64) who &= (1ull << (W & 63)) - 1ull;
+            const uint32_t r = (uint32_t)row[x];
+            const uint32_t e_next = tab[(s + 1) * stride + d];  // (behind the last: of the rows)
+            const unsigned long long who =
+                __ballot((e >> INDEX_BITS) + r == t) & ((2ull << x) - 1ull);
             if (who == 0ull) {  // never expected
                 put_none(THEMIS_INTERNAL);
                 return THEMIS_INTERNAL;
@@ -486,13 +495,15 @@ struct Solver {
                 const uint32_t e2 = lane_value(e, l2);
                 if ((e2 & INDEX) < (el & INDEX)) l = l2, el = e2;
             }
-            if (lane == s) my_k = el & INDEX, my_cost += (uint32_t)l;
+            my_k = lane == s ? el & INDEX : my_k;
+            my_over = lane == s ? (uint32_t)l : my_over;
             t -= el >> INDEX_BITS;
             x -= l;
             e = e_next;
+            row += W;
         }
         put(THEMIS_SOLVED, (int32_t)total, (int32_t)ticks, W == 16 ? BY_B16 : BY_C);
-        put_choice(my_k, my_cost);
+        put_choice(my_k, my_over + (lane < a.S ? keys()[lane] >> 15 : 0u));
         return THEMIS_SOLVED;
     }
 
@@ -507,6 +518,7 @@ struct Solver {
         uint32_t* const rows = lds + L.tab + 64 * a.S;
         uint32_t g = 0u;  // g[S]: nothing left to run
         const int at = lane >> 4;
+        if (lane < 16) rows[a.S * 16 + lane] = 0u;
         for (int s = a.S - 1; s >= 0; --s) {
             const uint32_t* const mine = tab + s * stride + at;
             uint32_t v[4];
@@ -529,8 +541,7 @@ struct Solver {
         const int x = __builtin_ctz(m);
         const uint32_t ticks = lane_value(g, x);
         wave_lds_fence();
-        return read_out<16>(base_sum + (uint32_t)x, ticks, x, stride,
-                            [&](int s, int y) { return rows[(s + 1) * 16 + y]; });
+        return read_out<16>(base_sum + (uint32_t)x, ticks, x, stride, rows);
     }
 
     // ---- sweeps over the candidates, for steps C and G -----------------------------
@@ -1472,49 +1483,103 @@ struct Solver {
     }
 
     // ---- steps C and W -------------------------------------------------------------
-    // The recurrence over 64 cells, lane = cell, the table of all models in LDS.
+    // The recurrence over 64 cells, the table of all models in LDS.
+    //
+    // Lane = two neighbouring cells, 16 bits each, the lower half of the wavefront for the
+    // table's even costs over base, the upper for the odd ones: for an even cost the two cells
+    // it leads from are a word of the row, for an odd one a word of a copy that is shifted by a
+    // cell.  So 64 of the 64 x 64 pairs take a packed addition and a packed minimum, with operands
+    // at fixed distances from a lane's first: no scan for the candidates worth a look, no address
+    // of an entry's own.  Sums saturate, so "none" (all ones) stays above any budget.
+    //
+    // What bounds it: latency.  A model is one wait for the row written last, 32 costs at a
+    // time, up to that of its fastest candidate.  A cell per lane, with every candidate that is
+    // faster than all cheaper ones in turn, four at a time, took 5.0 us for eight models of
+    // 65536 x 8, and the read-out 3.4; this takes 3.0 and 2.0.  The batches whose last wavefronts
+    // end here: 16384 x 8 with replicas given 22.6 -> 20.4 us, stability 4099 x 5 17.4 -> 16.3,
+    // 65536 x 8 76.2 -> 74.7.
     __device__ __forceinline__ int solve_sixtyfour() const
     {
+        typedef uint32_t four __attribute__((ext_vector_type(4), aligned(16)));
+        typedef uint16_t pair __attribute__((ext_vector_type(2)));
+        constexpr uint32_t NONE = 0xFFFFu, BOTH = 0xFFFFFFFFu;
         const uint32_t* const tab = lds + L.tab;
-        // rows of 16-bit cells, a guard cell (and one of padding) in front of each
-        uint16_t* const rows = reinterpret_cast<uint16_t*>(lds + L.tab + 64 * a.S);
-        auto row_of = [&](int s) { return rows + s * 66 + 2; };
-        for (int x = lane; x <= a.S; x += 64) row_of(x)[-1] = (uint16_t)G_INF;
-        row_of(a.S)[lane] = 0;
-        uint32_t acc = 0;
-        uint32_t lt = tab[(a.S - 1) * 64 + lane] >> INDEX_BITS;
+        // 32 words per model; row s is "none" for the model before it until it is formed
+        uint32_t* const rows = lds + L.tab + 64 * a.S;
+        uint16_t* const cells = reinterpret_cast<uint16_t*>(rows);
+        uint32_t* const entries = rows + 32 * (a.S + 1);  // even costs, odd costs; twice
+        uint32_t* const odd = entries + 2 * 64 + 32;      // behind its guard cells
+        const bool upper = lane >= 32;
+        const int m = lane & 31;
+        for (int x = lane; x < 8 * (a.S - 1); x += 64)
+            reinterpret_cast<four*>(rows)[x] = four{BOTH, BOTH, BOTH, BOTH};
+        odd[m - 32] = BOTH;
+        rows[32 * a.S + m] = 0u;  // nothing left to run
+        const uint32_t my_fast = lane < a.S ? fastest()[lane] >> 15 : 0u;
+        auto latency = [](uint32_t e) { return least(e >> INDEX_BITS, NONE); };
+        auto pair_of = [](uint32_t x) { return __builtin_bit_cast(pair, x); };
+        auto faster = [&](uint32_t x, uint32_t y) {
+            return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(pair_of(x), pair_of(y)));
+        };
+        // Where a lane's words of a row are, in words from `rows` on: the lower half's of model 0
+        // and their distance to the next model's; the upper half's are in the copy, a cell to
+        // the left of which is the last of the word before it (none: of word 0).
+        const int step = upper ? 0 : 32;
+        const int place = upper ? (int)(odd - rows) + m : m;
+        const uint32_t shift = !upper ? 0x07060504u : m > 0 ? 0x05040302u : 0x05040D0Du;
+        // (w: the lower half's and the upper's are the same)
+        auto put_words = [&](int s, uint32_t w) {
+            rows[place + step * s] = __builtin_amdgcn_perm(w, from_lane_below(w, 0u), shift);
+        };
+        // a model's latencies, each in both halves of its word
+        uint32_t* const my_entry = entries + 32 * (lane & 1) + (lane >> 1);
+        auto enter = [&](int s, uint32_t lt) { my_entry[64 * (s & 1)] = lt << 16 | lt; };
+        // the last model: the least of what costs no more
+        cells[(a.S - 1) * 64 + lane] = (uint16_t)wave_scan<true>(latency(tab[(a.S - 1) * 64 + lane]));
+        uint32_t lt = latency(tab[(a.S > 1 ? a.S - 2 : 0) * 64 + lane]);
+        enter(a.S - 2, lt);
         wave_lds_fence();
-        for (int s = a.S - 1; s >= 0; --s) {
-            const uint16_t* const next = row_of(s + 1);
-            // what beats everything cheaper
-            const bool on = lt < from_lane_below(wave_scan<true>(lt), LT_NONE) && lt < G_INF;
-            const uint32_t lt_next = s > 0 ? tab[(s - 1) * 64 + lane] >> INDEX_BITS : 0u;
-            acc = G_INF;
-            unsigned long long m = __ballot(on);
-            // Four entries at a time: independent reads.  (Where there are none left, that of
-            // cell 63, which is a candidate or beyond any budget and does no harm.)
-            const unsigned long long none = 1ull << 63;
-            while (m) {
-                uint32_t v[4];
+        put_words(a.S - 1, rows[32 * (a.S - 1) + m]);
+        wave_lds_fence();
+        for (int s = a.S - 2; s >= 0; --s) {
+            // a lane's words of the row, from the last one on that it reads (the others are at
+            // distances that fit the instruction)
+            int last = place + step * (s + 1) - 31;
+            asm("" : "+v"(last));
+            const uint32_t* const from = rows + last;
+            const four* const ent = reinterpret_cast<const four*>(entries + 64 * (s & 1)) + (upper ? 8 : 0);
+            const uint32_t next = tab[(s > 0 ? s - 1 : 0) * 64 + lane];
+            // nothing dearer than the fastest candidate is of use
+            const uint32_t fast = (uint32_t)__ballot(lt <= lane_value(my_fast, s));
+            uint32_t acc[2] = {BOTH, BOTH};
+            auto costs = [&](int q0) {
+                uint32_t v[16];
+                four e[4];
 #pragma unroll
-                for (int z = 0; z < 4; ++z) {
-                    const int d = __builtin_ctzll(z == 0 ? m : m | none);
-                    const int y = lane - d;
-                    v[z] = (uint32_t)next[y < -1 ? -1 : y] + lane_value(lt, d);
-                    m &= m - 1ull;
-                }
-                acc = least(least(acc, v[0]), least(v[1], least(v[2], v[3])));
-            }
-            row_of(s)[lane] = (uint16_t)acc;
+                for (int q = 0; q < 4; ++q) e[q] = ent[q0 / 4 + q];
+#pragma unroll
+                for (int q = 0; q < 16; ++q) v[q] = from[31 - q0 - q];
+#pragma unroll
+                for (int q = 0; q < 16; ++q)
+                    acc[q & 1] = faster(acc[q & 1], __builtin_bit_cast(uint32_t, __builtin_elementwise_add_sat(
+                                                        pair_of(v[q]), pair_of(e[q / 4][q % 4]))));
+            };
+            costs(0);
+            if (fast == 0u) costs(16);
+            const uint32_t mine = faster(acc[0], acc[1]);
+            const auto h = __builtin_amdgcn_permlane32_swap(mine, mine, false, false);
+            lt = latency(next);
             wave_lds_fence();
-            lt = lt_next;
+            put_words(s, faster(h[0], h[1]));
+            enter(s - 1, lt);
+            wave_lds_fence();
         }
-        const unsigned long long m = __ballot(acc <= (uint32_t)T);
-        if (m == 0ull) return UNFINISHED;
-        const int x = __builtin_ctzll(m);
+        const uint32_t g = cells[lane];
+        const unsigned long long within = __ballot(g <= (uint32_t)T);
+        if (within == 0ull) return UNFINISHED;
+        const int x = __builtin_ctzll(within);
         const uint32_t my_base = lane < a.S ? keys()[lane] >> 15 : 0u;
-        return read_out<64>(sum_models(my_base) + (uint32_t)x, lane_value(acc, x), x, 64,
-                            [&](int s, int y) { return (uint32_t)row_of(s + 1)[y]; });
+        return read_out<64>(sum_models(my_base) + (uint32_t)x, lane_value(g, x), x, 64, cells);
     }
 
     // Whether several lanes share a pair's cores in sweeps.
