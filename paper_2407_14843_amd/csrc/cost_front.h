@@ -14,6 +14,8 @@
 // 65536 x 8 98.1 -> 76.3, fallback 16384 x 8 65 -> 28.5.
 #pragma once
 
+#include <type_traits>
+
 #include "cost_solver.h"
 
 namespace themis {
@@ -25,9 +27,15 @@ namespace {
 // atomics took an initial value, a wait for each atomic and a read (some 200 cycles).
 // WIDTH: that width, where all models fit the wavefront that way (every lane keeps its pair
 // from step A on); PACKED: where they fit it only without gaps between the models, and
-// minima go through LDS; 0: the models in rounds of a.per_round, in 1 << width_log lanes each
-// or, where that takes fewer rounds (width_log < 0), without gaps, and what is found
-// about them in LDS.  (One kernel for the widths 4, 8 and 16, with the width an argument:
+// minima go through LDS; 0: where there are more pairs than lanes, the lanes of a model with its
+// batch sizes in turns (a power of two of lanes, or where that takes fewer turns as many as all
+// models leave room for, with minima through LDS).  A lane then keeps its model, and is done
+// with all of its batch sizes before minima and sums are formed.  (The models in turns, in lanes
+// for all of their batch sizes, with their inputs asked for again and minima and sums formed in
+// each: 3001 x 7 models with twelve batch sizes 11.8 us instead of 10.4, 59755 x 7 with fourteen
+// and replicas given 246 instead of 203, fallback 13320 x 9 with fifteen 105 instead of 59, of 50
+// shapes drawn 1.12 times as long in the mean; 186 x 10 with seven 30.6 instead of 32.4.)
+// (One kernel for the widths 4, 8 and 16, with the width an argument:
 // 86400 x 6 43.6 us instead of 39.8, fallback 16384 x 8 30.8 instead of 28.5, 65536 x 8 79.5
 // instead of 76.4, 512 x 5 7.4 instead of 7.0.)
 constexpr int PACKED = WIDTH_PACKED;
@@ -38,6 +46,7 @@ __device__ __attribute__((noinline)) int solve_rest(uint64_t args, int i, int T,
 template <int QUEUE, bool DERIVE, int WIDTH, int ROLE = PLAIN>
 struct Front : Solver<QUEUE, DERIVE, ROLE> {
     using Base = Solver<QUEUE, DERIVE, ROLE>;
+    using typename Base::Model;
     using typename Base::Pair;
     using Base::a, Base::args, Base::i, Base::L, Base::lam, Base::lane, Base::lds, Base::slo, Base::T;
     static constexpr bool ONE = WIDTH != 0;
@@ -48,39 +57,72 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
     {
         return WIDTH == 16 ? 4 : WIDTH == 8 ? 3 : WIDTH == 4 ? 2 : a.width_log;
     }
-    // this lane's pair of the round that starts with model s0
-    __device__ __forceinline__ Pair pair_of_round(int s0) const
+    // What a lane starts from: its pair, or (not ONE) its model and which of its lanes it is.
+    struct Own {
+        Model m;
+        uint32_t s, part;
+        bool there, valid, in;
+        int32_t size;
+    };
+    typedef typename std::conditional<ONE, Pair, Own>::type Start;
+    __device__ __forceinline__ Start start() const
     {
-        uint32_t s, j;
-        if (packed()) {
-            s = index_quotient((uint32_t)lane, a.magic);
-            j = (uint32_t)lane - s * (uint32_t)a.n_batch;
+        if constexpr (ONE) {
+            uint32_t s, j;
+            if (packed()) {
+                s = index_quotient((uint32_t)lane, a.magic);
+                j = (uint32_t)lane - s * (uint32_t)a.n_batch;
+            } else {
+                s = (uint32_t)lane >> width_log();
+                j = (uint32_t)lane & ((1u << width_log()) - 1u);
+            }
+            const bool in = s < (uint32_t)a.S;
+            Pair p = this->pair_of(s, j, (int)in & (int)(j < (uint32_t)a.n_batch));
+            p.in = in, p.first = j == 0u;
+            return p;
         } else {
-            s = (uint32_t)lane >> width_log();
-            j = (uint32_t)lane & ((1u << width_log()) - 1u);
+            Own o;
+            const uint32_t lanes = (uint32_t)args->lanes;
+            o.s = index_quotient((uint32_t)lane, args->lane_magic);
+            o.part = (uint32_t)lane - o.s * lanes;
+            o.in = o.there = o.s < (uint32_t)a.S;
+            o.s = o.there ? o.s : 0u;
+            o.m = this->model_of(o.s);
+            o.valid = o.m.valid;
+            o.size = args->bc[lane < a.n_batch ? lane : 0].size;
+            return o;
         }
-        const bool mine = ONE || s < (uint32_t)a.per_round;
-        s = mine ? s + (uint32_t)s0 : (uint32_t)a.S;
-        return this->pair_of(s, j, (int)(s < (uint32_t)a.S) & (int)(j < (uint32_t)a.n_batch));
     }
-    // Calls f(pair) for this lane's pair of every round; lanes without one get a pair with
-    // `there` unset.  `mine`: the pair, where there is one round only.
-    template <typename F>
-    __device__ __forceinline__ void for_pairs(const Pair& mine, F f) const
+    // Calls f(pair) for this lane's pair, or each of its pairs; lanes without one get a pair
+    // with `there` unset.  The lanes of a model take batch sizes next to one another, so that
+    // they have about the same work; SPREAD: each from its own part of the list, so that the first
+    // ones met are of all sizes.
+    template <bool SPREAD = false, typename F>
+    __device__ __forceinline__ void for_pairs(const Start& mine, F f) const
     {
         if constexpr (ONE) {
             f(mine);
         } else {
-            for (int s0 = 0; s0 < a.S; s0 += a.per_round) f(pair_of_round(s0));
+            const uint32_t nb = (uint32_t)a.n_batch, turns = (uint32_t)args->turns;
+            const uint32_t first = SPREAD ? mine.part * turns : mine.part;
+            const uint32_t step = SPREAD ? 1u : (uint32_t)args->lanes;
+            for (uint32_t t = 0u, j = first; t < turns; ++t, j += step) {
+                const bool there = mine.there && j < nb;
+                Pair p;
+                this->batch_size(p, there ? j : 0u);
+                this->of_model(p, mine.m, mine.s);
+                p.there = there, p.in = mine.in, p.first = mine.part == 0u;
+                f(p);
+            }
         }
     }
+    // whether this lane is the first of its model's
+    static __device__ __forceinline__ bool leads(const Pair& p) { return (int)p.in & (int)p.first; }
+    static __device__ __forceinline__ bool leads(const Own& o) { return (int)o.in & (int)(o.part == 0u); }
     __device__ __forceinline__ bool packed() const
     {
         return WIDTH == PACKED || (WIDTH == 0 && a.width_log < 0);
     }
-    // whether this lane is the first of its model's
-    static __device__ __forceinline__ bool leads(const Pair& p) { return (int)p.in & (int)p.first; }
-
     static __device__ __forceinline__ bool any(bool x) { return __builtin_amdgcn_ballot_w64(x) != 0ull; }
 
     // The least of a model's lanes, in all of them.
@@ -89,7 +131,8 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
     {
         return least(x, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)x, CTRL, 0xF, 0xF, false));
     }
-    __device__ __forceinline__ uint32_t model_least(const Pair& p, uint32_t x) const
+    template <typename P>
+    __device__ __forceinline__ uint32_t model_least(const P& p, uint32_t x) const
     {
         if (packed()) {
             // (a wavefront's LDS operations complete in order)
@@ -115,7 +158,8 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
     {
         return x + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, false);
     }
-    __device__ __forceinline__ uint32_t sum_of_models(const Pair& p, uint32_t x) const
+    template <typename P>
+    __device__ __forceinline__ uint32_t sum_of_models(const P& p, uint32_t x) const
     {
         if constexpr (ONE && WIDTH != PACKED) {
             x = p.in ? x : 0u;
@@ -129,10 +173,11 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
 
     // What step A finds about a model, the same in all its lanes: cost << 15 | lt of the best
     // candidate (EMPTY: none is feasible) and its index.  c0: the lane's first_core().
-    // mine: this lane's own best is the one, with that many cores.
+    // mine: this lane's own best is the one, with that many cores and that batch size.
     // own: the lane's own best's.
     struct Best {
         uint32_t key, k, c0, c, own;
+        int32_t size;
         bool mine;
     };
 
@@ -279,39 +324,84 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
         b.c0 = c0;
         const uint32_t mine = __umul24(best_c - 1u, (uint32_t)a.n_batch) + p.j;
         b.k = model_least(p, best == model ? mine : EMPTY);
-        b.c = best_c, b.own = best;
+        b.c = best_c, b.own = best, b.size = p.size;
         b.mine = p.there && best == model && mine == b.k;
         return b;
     }
+    // The same where a lane has several pairs, one after the other: of a pair only what can
+    // still matter after those before it is evaluated.  (own, c, size, k: of the lane's own best;
+    // key: the model's, in all of its lanes.)
+    template <bool SMALL>
+    __device__ __forceinline__ void improve(Best& b, const Pair& p) const
+    {
+        const uint32_t c0 = this->first_core(p);
+        bool go = p.there && c0 <= p.last;
+        auto offer = [&](uint32_t c, bool is) {
+            const uint32_t key = meet<SMALL>(p, c);
+            const uint32_t k = __umul24(c - 1u, (uint32_t)a.n_batch) + p.j;
+            if (is && key != EMPTY && (key < b.own || (key == b.own && k < b.k)))
+                b.own = key, b.k = k, b.c = c, b.size = p.size;
+            return key;
+        };
+        if (DERIVE && this->one_each()) {
+            if (any(go)) offer(go ? c0 : p.lo, go);
+        } else if (DERIVE) {
+            uint32_t from = c0;
+            if (any(go && b.key == EMPTY)) {
+                const bool is = go && b.key == EMPTY;
+                offer(is ? c0 : p.lo, is);
+                from = is ? c0 + 1u : c0;
+                b.key = model_least(p, b.own);
+            }
+            if (!any(go)) return;
+            const Bounds bound = bounds_of(p);
+            for (;;) {
+                const float limit = (float)(b.key >> 15);
+                const float most = go ? most_cores(p, bound, limit) : -1.0f;
+                go = go && (float)from <= most;
+                if (!any(go)) break;
+                uint32_t mask = promising<false>(bound, from, go ? most : -1.0f, limit, 0.0f);
+                while (any(mask != 0u)) {
+                    const bool is = mask != 0u;
+                    const uint32_t z = (uint32_t)__builtin_clz(mask | 1u);
+                    mask &= ~(0x80000000u >> z);
+                    offer(is ? from + z : p.lo, is);
+                }
+                b.key = model_least(p, b.own);
+                from += 32u;
+            }
+        } else {
+            // the cost grows with every core: a lane is done with its first feasible count
+            for (uint32_t c = c0;; ++c) {
+                go = go && c <= p.last && (double)c * p.h.n_given <= (double)(b.key >> 15);
+                if (!any(go)) break;
+                const uint32_t key = offer(go ? c : p.lo, go);
+                go = go && key == EMPTY;
+                b.key = model_least(p, b.own);
+            }
+        }
+    }
 
     // ---- step F ------------------------------------------------------------------
-    // lt << 15 | cost of the fastest candidate of the lanes' models, EMPTY where there is none.
-    // fastest: the lane's own, where it is known.
-    template <bool SMALL>
-    __device__ __forceinline__ uint32_t fastest_of(const Pair& p) const
+    // lt << 15 | cost of a candidate, EMPTY where there is none (of equal latencies any cost
+    // will do).
+    static __device__ __forceinline__ uint32_t turned(const Pair& p, uint32_t key)
     {
-        return fastest_of(p, meet<SMALL>(p, p.last));
+        return key == EMPTY || !p.there ? EMPTY : (key & 0x7FFFu) << 15 | key >> 15;
     }
-    __device__ __forceinline__ uint32_t fastest_of(const Pair& p, uint32_t key) const
+    // That of the fastest candidate of the lanes' models.
+    template <bool SMALL>
+    __device__ __forceinline__ uint32_t fastest_of(const Start& first) const
     {
-        // (of equal latencies any cost will do)
-        const uint32_t turned = key == EMPTY || !p.there ? EMPTY : (key & 0x7FFFu) << 15 | key >> 15;
-        return model_least(p, turned);
+        uint32_t fast = EMPTY;
+        for_pairs(first, [&](const Pair& p) { fast = least(fast, turned(p, meet<SMALL>(p, p.last))); });
+        return model_least(first, fast);
     }
     // Sum of the models' least latencies, beyond any budget where one has no candidate.
     template <bool SMALL>
-    __device__ __forceinline__ uint32_t fastest_ticks(const Pair& first) const
+    __device__ __forceinline__ uint32_t fastest_ticks(const Start& first) const
     {
-        if constexpr (ONE) {
-            return sum_of_models(first, fastest_of<SMALL>(first) >> 15);
-        } else {
-            uint32_t sum = 0u;
-            for_pairs(first, [&](const Pair& p) {
-                const uint32_t f = fastest_of<SMALL>(p);
-                sum += sum_of_models(p, f >> 15);
-            });
-            return sum;
-        }
+        return sum_of_models(first, fastest_of<SMALL>(first) >> 15);
     }
 
     // ---- the tables of steps B and C ----------------------------------------------
@@ -473,17 +563,16 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
     // the budget exists exactly when the fastest candidates of all models fit it together, and
     // with the replicas given those are the ones at the core cap, whatever the rate.
     template <bool SMALL>
-    __device__ __forceinline__ int32_t search_rate(const Pair& first)
+    __device__ __forceinline__ int32_t search_rate(const Start& first)
     {
         constexpr bool KEPT = ONE && SMALL && QUEUE != THEMIS_QUEUE_WORST_CASE;
         const int32_t lambda = lam;
         int32_t lo = 1, hi = lambda;
-        const double proc =
-            KEPT ? ceil_div_small(first.num, recip_below((double)this->speed(first, first.last))) +
-                       first.fixed
-                 : 0.0;
-        const double wait =
-            QUEUE == THEMIS_QUEUE_PER_REPLICA ? first.bh.w * first.h.n_given : first.bh.w;
+        double proc = 0.0, wait = 0.0;
+        if constexpr (KEPT) {
+            proc = ceil_div_small(first.num, recip_below((double)this->speed(first, first.last))) + first.fixed;
+            wait = QUEUE == THEMIS_QUEUE_PER_REPLICA ? first.bh.w * first.h.n_given : first.bh.w;
+        }
         while (hi - lo > 1) {
             lam = lo + ((hi - lo) >> 1);
             uint32_t ticks;
@@ -510,74 +599,53 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
 
     // Steps A, F and B of a valid instance.
     template <bool SMALL>
-    __device__ __forceinline__ int solve_valid(const Pair& first) const
+    __device__ __forceinline__ int solve_valid(const Start& first) const
     {
-        Best mine{EMPTY, 0u, 0u, 0u, EMPTY, false};
-        uint32_t ticks = 0u;
-        for_pairs(first, [&](const Pair& p) {
-            const Best b = best_of<SMALL>(p);
-            if (ONE) mine = b;
-            ticks += sum_of_models(p, b.key == EMPTY ? LT_NONE : b.key & 0x7FFFu);
-            if (!ONE && leads(p)) {
-                this->keys()[p.s] = b.key;
-                this->bests()[p.s] = (unsigned long long)b.key << INDEX_BITS | b.k;
-            }
-        });
-        if (ticks >= LT_NONE) return THEMIS_INFEASIBLE;
-        uint32_t base_sum;
-        unsigned long long best = 0ull;  // not ONE: lane s: that of model s
+        Best mine{EMPTY, EMPTY, 0u, 1u, EMPTY, 0, false};
         if constexpr (ONE) {
-            base_sum = sum_of_models(first, mine.key >> 15);
+            mine = best_of<SMALL>(first);
         } else {
-            wave_lds_fence();
-            if (lane < a.S) best = this->bests()[lane];
-            base_sum = this->sum_models((uint32_t)(best >> (INDEX_BITS + 15)));
+            for_pairs<DERIVE>(first, [&](const Pair& p) { improve<SMALL>(mine, p); });
+            mine.key = model_least(first, mine.own);
+            const uint32_t k = mine.own == mine.key ? mine.k : EMPTY;
+            mine.k = model_least(first, k);
+            mine.mine = first.there && mine.own != EMPTY && k == mine.k;
         }
+        const uint32_t ticks = sum_of_models(first, mine.key == EMPTY ? LT_NONE : mine.key & 0x7FFFu);
+        if (ticks >= LT_NONE) return THEMIS_INFEASIBLE;
+        const uint32_t base_sum = sum_of_models(first, mine.key >> 15);
         if (ticks <= (uint32_t)T) {
             this->put(THEMIS_SOLVED, (int32_t)base_sum, (int32_t)ticks);
-            if constexpr (ONE) {
-                this->put_row(mine.mine, first.s, mine.c, first.size, mine.k, mine.key >> 15);
-            } else {
-                this->put_choice((uint32_t)best & ((1u << INDEX_BITS) - 1u),
-                                 (uint32_t)(best >> (INDEX_BITS + 15)));
-            }
+            this->put_row(mine.mine, first.s, mine.c, ONE ? first.size : mine.size, mine.k, mine.key >> 15);
             return THEMIS_SOLVED;
         }
         const bool one = this->one_each();
-        uint32_t least_ticks = 0u, fast = 0u;
-        for_pairs(first, [&](const Pair& p) {
-            // (where it is the lane's only candidate step A has met it)
-            const uint32_t f = ONE && one ? fastest_of(p, mine.own) : fastest_of<SMALL>(p);
-            least_ticks += sum_of_models(p, f >> 15);
-            fast = f;
-            if (leads(p)) {
-                this->fastest()[p.s] = f;
-                if (ONE) this->keys()[p.s] = mine.key;
-            }
-        });
+        // (where it is the lane's only candidate step A has met it)
+        uint32_t fast;
+        if constexpr (ONE)
+            fast = one ? model_least(first, turned(first, mine.own)) : fastest_of<SMALL>(first);
+        else
+            fast = fastest_of<SMALL>(first);
+        const uint32_t least_ticks = sum_of_models(first, fast >> 15);
+        if (leads(first)) this->fastest()[first.s] = fast, this->keys()[first.s] = mine.key;
         if (least_ticks > (uint32_t)T) return THEMIS_INFEASIBLE;
-        if (!ONE) wave_lds_fence();
-        const int reach = reach_of(ticks, least_ticks, one, [&] {
-            const uint32_t cost =
-                ONE ? sum_of_models(first, fast & 0x7FFFu)
-                    : this->sum_models(lane < a.S ? this->fastest()[lane] & 0x7FFFu : 0u);
-            return cost - base_sum;
-        });
+        const int reach = reach_of(ticks, least_ticks, one,
+                                   [&] { return sum_of_models(first, fast & 0x7FFFu) - base_sum; });
         // (one candidate each: what there is to enter is at hand, for all windows at once)
         if (one) fill_one_each<SMALL>(first, mine);
         if (reach <= 8) {
-            if (!one) fill<SMALL>(first, mine, best, 8, reach);
+            if (!one) fill<SMALL>(first, mine, 8, reach);
             const int status = solve_eight(base_sum, one ? 8 : reach, one ? 6u : 3u);
             if (status != UNFINISHED) return status;
             wave_lds_fence();
         }
         if (reach <= 16) {
-            if (!one) fill<SMALL>(first, mine, best, 16, 16);
+            if (!one) fill<SMALL>(first, mine, 16, 16);
             const int status = this->solve_sixteen(base_sum, one ? 64 : 16);
             if (status != UNFINISHED) return status;
             wave_lds_fence();
         }
-        if (!one && !this->shares_pairs()) fill<SMALL>(first, mine, best, 64, 64);
+        if (!one && !this->shares_pairs()) fill<SMALL>(first, mine, 64, 64);
         return UNFINISHED;
     }
     // How many cells it takes, by how late the cheapest assignment is (`late`), what the fastest
@@ -604,38 +672,30 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
         if (have <= need * (DERIVE && !one ? 4.5f : 2.6f)) return 8;
         return one || have <= need * (DERIVE ? 11.0f : 7.0f) ? 16 : 64;
     }
-    // The table of `cells` cells per model.  mine, best: what step A found, see solve_valid().
+    // The table of `cells` cells per model.  mine: what step A found.
     template <bool SMALL>
-    __device__ __forceinline__ void fill(const Pair& first, const Best& mine, unsigned long long best,
-                                         int cells, int span) const
+    __device__ __forceinline__ void fill(const Start& first, const Best& mine, int cells, int span) const
     {
         uint32_t* const tab = lds + L.tab;
         for (int y = lane; y < cells * a.S; y += 64) tab[y] = EMPTY;
         wave_lds_fence();
-        if constexpr (ONE) {
-            if (leads(first)) tab[first.s * cells] = (mine.key & 0x7FFFu) << INDEX_BITS | mine.k;
-        } else {
-            if (lane < a.S) tab[lane * cells] = (uint32_t)best & ((1u << (INDEX_BITS + 15)) - 1u);
-        }
+        if (leads(first)) tab[first.s * cells] = (mine.key & 0x7FFFu) << INDEX_BITS | mine.k;
         wave_lds_fence();
         for_pairs(first, [&](const Pair& p) {
-            if constexpr (ONE)
-                enter<SMALL>(p, mine.c0, mine.key, (uint32_t)cells, (uint32_t)span);
-            else
-                enter<SMALL>(p, this->first_core(p), this->keys()[p.s], (uint32_t)cells, (uint32_t)span);
+            enter<SMALL>(p, ONE ? mine.c0 : this->first_core(p), mine.key, (uint32_t)cells, (uint32_t)span);
         });
         wave_lds_fence();
     }
     // The table of 64 cells per model where every pair has one candidate.
     template <bool SMALL>
-    __device__ __forceinline__ void fill_one_each(const Pair& first, const Best& mine) const
+    __device__ __forceinline__ void fill_one_each(const Start& first, const Best& mine) const
     {
         uint32_t* const tab = lds + L.tab;
         for (int y = lane; y < 64 * a.S; y += 64) tab[y] = EMPTY;
         wave_lds_fence();
         for_pairs(first, [&](const Pair& p) {
             const uint32_t key = ONE ? mine.own : meet<SMALL>(p, p.last);
-            const uint32_t base = (ONE ? mine.key : this->keys()[p.s]) >> 15, d = (key >> 15) - base;
+            const uint32_t d = (key >> 15) - (mine.key >> 15);
             // (EMPTY is beyond any cell)
             const bool use = (int)p.there & (int)(d < 64u);
             atomicMin(&tab[use ? 64u * p.s + d : (uint32_t)lane],
@@ -650,12 +710,12 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
     // The arguments this takes are held in scalar registers from the start: where the
     // compiler is free to load each where it is used, there are a dozen waits of 50 to 200
     // cycles, and the coefficients are asked for only after the rate has come.
-    __device__ __forceinline__ Pair begin(int inst, const int32_t* rates, bool& valid)
+    __device__ __forceinline__ Start begin(int inst, const int32_t* rates, bool& valid)
     {
         asm volatile("" ::"s"(rates));
         return begin(inst, constant(rates)[inst], valid);
     }
-    __device__ __forceinline__ Pair begin(int inst, int32_t rate, bool& valid)
+    __device__ __forceinline__ Start begin(int inst, int32_t rate, bool& valid)
     {
         i = inst;
         // (asked for, and not changed, here)
@@ -671,10 +731,10 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
         int32_t word = 0;
         const bool keeps = (ROLE == PLAIN || ROLE == PINNED) && a.keep && a.coef_stride;
         if (keeps && lane < a.S * a.cs) word = (a.coef + (size_t)i * (uint32_t)a.coef_stride)[lane];
-        Pair first = pair_of_round(0);
+        const Start first = start();
         this->lane_b = first.size;  // (the first lanes have the first model's pairs)
         int fine = (int)in_range(lam, 1, THEMIS_VALUE_MAX) & (int)in_range(slo, 0, a.slo_max);
-        for_pairs(first, [&](const Pair& p) { fine &= (int)!p.there | (int)p.valid; });
+        fine &= (int)!first.there | (int)first.valid;
         valid = !any(!fine);
         this->keep_inputs(valid, word);
         if (this->records() && lane == 0) a.tmeta[i] = valid ? T : -1;
@@ -682,11 +742,9 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
     }
     // The pair kept from another rate at the rate `lam` (where pairs are not kept they are
     // formed at that rate anyway).
-    __device__ __forceinline__ Pair at_rate(Pair p) const
+    __device__ __forceinline__ Start at_rate(Start p) const
     {
-        if (ONE) {
-            this->set_rate(p);
-        }
+        if constexpr (ONE) this->set_rate(p);
         return p;
     }
 
@@ -697,7 +755,7 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
     }
     // Steps A, F and B of the instance that was begun, at the rate `lam`, with the results
     // where these suffice.
-    __device__ __forceinline__ int solve(const Pair& first, bool valid) const
+    __device__ __forceinline__ int solve(const Start& first, bool valid) const
     {
         int status = valid ? LARGE : THEMIS_INVALID;
         if (valid && is_small())
@@ -734,7 +792,7 @@ __device__ __attribute__((noinline)) int32_t rate_of_large(uint64_t args, int i,
     const uint64_t hi = (uint32_t)uniform((int)(uint32_t)(args >> 32));
     Front<QUEUE, false, 0, QUIET> sv((ArgsPtr)(uintptr_t)(hi << 32 | lo));
     sv.instance(uniform(i), uniform(T), uniform(lam), uniform(slo));
-    const auto first = sv.pair_of_round(0);
+    const auto first = sv.start();
     return uniform(sv.template fastest_ticks<false>(first) <= (uint32_t)sv.T
                        ? sv.lam
                        : sv.template search_rate<false>(first));
@@ -757,7 +815,7 @@ __device__ __attribute__((noinline)) int solve_rest(uint64_t args, int i, int T,
     sv.instance(uniform(i), uniform(T), uniform(lam), uniform(slo));
     int status;
     if (sv.is_small() ||
-        (status = uniform(sv.template solve_valid<false>(sv.pair_of_round(0)))) == UNFINISHED) {
+        (status = uniform(sv.template solve_valid<false>(sv.start()))) == UNFINISHED) {
         if (sv.shares_pairs() && !sv.one_each()) sv.fill_sixtyfour();
         status = sv.solve_further();
     }

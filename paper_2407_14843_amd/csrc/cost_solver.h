@@ -27,7 +27,7 @@ struct __attribute__((aligned(16))) BatchConst {
 // What every instance needs.
 struct HotArgs {
     const int32_t *coef, *lambda, *slo_us, *r_fixed, *c_fixed;
-    int32_t S, cs, n_batch, width_log, per_round;  // see Front
+    int32_t S, cs, n_batch, width_log;  // see Front
     int32_t c_max, r_max, tick, slo_max;
     int32_t coef_stride;  // words of an instance's coefficients (shared: 0)
     int32_t c_all;
@@ -53,6 +53,8 @@ struct CostArgs : HotArgs {
     int32_t row_stride;
     int32_t window_hbm;   // like `window`, in HBM (no larger than the other: none)
     uint32_t parts, pair_magic;  // lanes per (model, batch size) pair of a sweep, see sweep()
+    int32_t lanes, turns;  // lanes per model, and the batch sizes of each, see Front
+    uint32_t lane_magic;   // index_magic() of them
     BatchConst bc[THEMIS_MAX_BATCH];
 };
 
@@ -161,11 +163,11 @@ struct Solver {
     // (member by member: the address space has no copies of whole structures)
     static __device__ __forceinline__ HotArgs hot_args(ArgsPtr p)
     {
-        static_assert(sizeof(HotArgs) == 200, "a member was added: copy it below");
+        static_assert(sizeof(HotArgs) == 192, "a member was added: copy it below");
         HotArgs h;
         h.coef = p->coef, h.lambda = p->lambda, h.slo_us = p->slo_us;
         h.r_fixed = p->r_fixed, h.c_fixed = p->c_fixed;
-        h.S = p->S, h.cs = p->cs, h.n_batch = p->n_batch, h.width_log = p->width_log, h.per_round = p->per_round;
+        h.S = p->S, h.cs = p->cs, h.n_batch = p->n_batch, h.width_log = p->width_log;
         h.c_max = p->c_max, h.r_max = p->r_max, h.tick = p->tick, h.slo_max = p->slo_max;
         h.coef_stride = p->coef_stride, h.c_all = p->c_all, h.magic = p->magic;
         h.window = p->window, h.rtick = p->rtick, h.tick_d = p->tick_d, h.r_max_d = p->r_max_d;
@@ -188,62 +190,82 @@ struct Solver {
         int32_t size;
         uint32_t s, j, lo, last, pcap;
         bool there, valid;  // there: the lane has a pair
-        bool in, first;     // its model exists; it is the model's first
+        bool in, first;     // its model exists; the lane is the model's first (see Front)
     };
 
-    __device__ __forceinline__ Pair pair_of(uint32_t s, uint32_t j, bool there) const
+    // One model as the caller's arrays have it.
+    struct Model {
+        words4 c4;
+        int32_t v4, v5, given;
+        uint32_t lo, hi;  // the cores: all, or one count for all models, or one for each
+        bool valid;
+    };
+    __device__ __forceinline__ Model model_of(uint32_t s) const
     {
-        Pair p;
-        p.there = there;
-        p.s = there ? s : 0u;
-        p.j = there ? j : 0u;
-        p.in = s < (uint32_t)a.S;
-        p.first = j == 0u;
-        const auto& bc = args->bc[p.j];
+        Model m;
+        const size_t row0 = (size_t)i * a.S;
+        const int32_t* const cf = a.coef + (size_t)i * (uint32_t)a.coef_stride + s * (uint32_t)a.cs;
+        m.c4 = *reinterpret_cast<const words4*>(cf);
+        m.v4 = cf[4];
+        m.v5 = 0;
+        if (a.cs == 6) m.v5 = cf[5];
+        m.given = DERIVE ? 0 : (a.r_fixed + row0)[s];
+        // a, k, q, d in 0 .. max, p >= 1, o in 1 .. max
+        uint32_t top = (uint32_t)m.c4.x > (uint32_t)m.c4.y ? (uint32_t)m.c4.x : (uint32_t)m.c4.y;
+        top = (uint32_t)m.c4.z > top ? (uint32_t)m.c4.z : top;
+        top = (uint32_t)m.v5 > top ? (uint32_t)m.v5 : top;
+        m.valid = (int)(top <= (uint32_t)THEMIS_VALUE_MAX) & (int)(m.c4.w >= 1) &
+                  (int)in_range(m.v4, 1, THEMIS_VALUE_MAX);
+        if (!DERIVE) m.valid &= (int)in_range(m.given, 1, a.r_max);
+        m.lo = a.c_all > 0 ? (uint32_t)a.c_all : 1u;
+        m.hi = a.c_all > 0 ? (uint32_t)a.c_all : (uint32_t)a.c_max;
+        if (ROLE == PINNED) {
+            m.lo = m.hi = lds[L.pin + s];
+        } else if (a.c_fixed) {
+            const int32_t only = (a.c_fixed + row0)[s];
+            m.valid &= (int)in_range(only, 1, a.c_max);
+            m.lo = m.hi = only > 0 ? (uint32_t)only : 1u;
+        }
+        return m;
+    }
+    // A pair's parts.
+    __device__ __forceinline__ void batch_size(Pair& p, uint32_t j) const
+    {
+        const auto& bc = args->bc[j];
+        p.j = j;
         p.bh.rM = bc.rM, p.bh.w = bc.w;
         p.M = bc.M, p.both = bc.both, p.size = bc.size;
         p.bh.b = (double)p.size;
         p.bh.b2 = p.bh.b * p.bh.b;
         p.bh.M = p.bh.b * 1.0e6;
         p.w = (float)p.bh.w;
-        const size_t row0 = (size_t)i * a.S;
-        const int32_t* const cf = a.coef + (size_t)i * (uint32_t)a.coef_stride + p.s * (uint32_t)a.cs;
-        const words4 c4 = *reinterpret_cast<const words4*>(cf);
-        const int32_t v4 = cf[4];
-        int32_t v5 = 0;
-        const bool eq1 = a.cs == 6;
-        if (eq1) v5 = cf[5];
-        const int32_t given = DERIVE ? 0 : (a.r_fixed + row0)[p.s];
-        // a, k, q, d in 0 .. max, p >= 1, o in 1 .. max
-        uint32_t top = (uint32_t)c4.x > (uint32_t)c4.y ? (uint32_t)c4.x : (uint32_t)c4.y;
-        top = (uint32_t)c4.z > top ? (uint32_t)c4.z : top;
-        top = (uint32_t)v5 > top ? (uint32_t)v5 : top;
-        p.valid = (int)(top <= (uint32_t)THEMIS_VALUE_MAX) & (int)(c4.w >= 1) &
-                  (int)in_range(v4, 1, THEMIS_VALUE_MAX);
-        if (!DERIVE) p.valid &= (int)in_range(given, 1, a.r_max);
-        // the cores: all, or one count for all models, or one for each
-        p.lo = a.c_all > 0 ? (uint32_t)a.c_all : 1u;
-        uint32_t hi = a.c_all > 0 ? (uint32_t)a.c_all : (uint32_t)a.c_max;
-        if (ROLE == PINNED) {
-            p.lo = hi = lds[L.pin + p.s];
-        } else if (a.c_fixed) {
-            const int32_t only = (a.c_fixed + row0)[p.s];
-            p.valid &= (int)in_range(only, 1, a.c_max);
-            p.lo = hi = only > 0 ? (uint32_t)only : 1u;
-        }
-        p.pcap = (uint32_t)c4.w;
+    }
+    __device__ __forceinline__ void of_model(Pair& p, const Model& m, uint32_t s) const
+    {
+        p.s = s;
+        p.valid = m.valid;
+        p.lo = m.lo;
+        p.pcap = (uint32_t)m.c4.w;
         // beyond the cap a candidate has the cap's latency and costs more
         const uint32_t reach = p.pcap > p.lo ? p.pcap : p.lo;
-        p.last = hi < reach ? hi : reach;
-        p.h.a = (double)c4.x, p.h.k = (double)c4.y, p.h.q = (double)c4.z, p.h.o = (double)v4;
-        p.h.d = (double)v5;
-        p.h.p = (double)c4.w;
+        p.last = m.hi < reach ? m.hi : reach;
+        p.h.a = (double)m.c4.x, p.h.k = (double)m.c4.y, p.h.q = (double)m.c4.z, p.h.o = (double)m.v4;
+        p.h.d = (double)m.v5;
+        p.h.p = (double)m.c4.w;
         p.h.slo = (double)slo, p.h.T = (double)T;
-        p.h.n_given = (double)given;
+        p.h.n_given = (double)m.given;
         p.num = __builtin_fma(p.h.q, p.bh.b2, __builtin_fma(p.h.k, p.bh.b, p.h.a));
         p.fixed = p.h.o;
-        if (eq1) p.fixed = __builtin_fma(p.h.d, p.bh.b, p.fixed);
+        if (a.cs == 6) p.fixed = __builtin_fma(p.h.d, p.bh.b, p.fixed);
         set_rate(p);
+    }
+    __device__ __forceinline__ Pair pair_of(uint32_t s, uint32_t j, bool there) const
+    {
+        s = there ? s : 0u, j = there ? j : 0u;
+        Pair p;
+        batch_size(p, j);
+        of_model(p, model_of(s), s);
+        p.there = there;
         return p;
     }
 
@@ -2060,10 +2082,16 @@ inline CostArgs cost_args(const themis_problem_t& p, const Layout& L, const int3
     }
     while (1 << a.width_log < p.n_batch) ++a.width_log;
     if (a.width_log < 2 && L.S <= 16) a.width_log = 2;
-    a.per_round = 64 >> a.width_log;
-    auto rounds = [&](int models) { return (L.S + models - 1) / models; };
-    if (L.S > a.per_round && rounds(64 / p.n_batch) < rounds(a.per_round))
-        a.per_round = 64 / p.n_batch, a.width_log = -1;
+    // Lanes per model: a power of two, or where that takes more turns (or doesn't fit) as many as
+    // there are batch sizes or all models leave room for (9 x 14: seven and two turns, not four
+    // and four).
+    while (L.S << a.width_log > 64) --a.width_log;
+    a.lanes = 1 << a.width_log;
+    const int fit = 64 / L.S < p.n_batch ? 64 / L.S : p.n_batch;
+    auto turns = [&](int lanes) { return (p.n_batch + lanes - 1) / lanes; };
+    if (turns(fit) < turns(a.lanes)) a.lanes = fit, a.width_log = -1;
+    a.turns = turns(a.lanes);
+    a.lane_magic = index_magic((uint32_t)a.lanes);
     a.S = L.S;
     a.cs = p.profile_form == THEMIS_PROFILE_EQ1 ? 6 : 5;
     a.c_max = p.c_max;
@@ -2143,8 +2171,8 @@ hipError_t launch_per_instance(const themis_problem_t& p, const Layout& L, CostA
     const int room = lds.words - lds.tab;
     a.window_hbm = (fit < room ? fit : room) & ~63;
     // (at most 40 KB of LDS, which a kernel may have without asking)
-    const bool one = L.S <= a.per_round;
-    const CostKernel k = kernel(!one ? 0 : a.width_log < 2 ? WIDTH_PACKED : 1 << a.width_log);
+    const int width = a.turns > 1 ? 0 : a.width_log >= 2 ? 1 << a.width_log : WIDTH_PACKED;
+    const CostKernel k = kernel(width);
     hipError_t e = hipSuccess;
     in_launches(grid, [&](int first, int count) {
         if (e != hipSuccess) return;
