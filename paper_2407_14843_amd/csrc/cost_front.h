@@ -51,7 +51,14 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
     using Base::a, Base::args, Base::i, Base::L, Base::lam, Base::lane, Base::lds, Base::slo, Base::T;
     static constexpr bool ONE = WIDTH != 0;
 
-    __device__ __forceinline__ explicit Front(ArgsPtr p, int l = (int)threadIdx.x) : Base(p, l) {}
+    __device__ __forceinline__ explicit Front(ArgsPtr p, int l = (int)threadIdx.x, uint32_t offset = 0u)
+        : Base(p, l, offset)
+    {
+    }
+    static __device__ __forceinline__ Front of_wave(ArgsPtr p)
+    {
+        return Front(p, (int)threadIdx.x & 63, wave_number() * p->wave_words);
+    }
 
     __device__ __forceinline__ int width_log() const
     {
@@ -811,7 +818,7 @@ __device__ __attribute__((noinline)) int solve_rest(uint64_t args, int i, int T,
     auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
     const uint64_t lo = (uint32_t)uniform((int)(uint32_t)args);
     const uint64_t hi = (uint32_t)uniform((int)(uint32_t)(args >> 32));
-    Front<QUEUE, DERIVE, 0, ROLE> sv((ArgsPtr)(uintptr_t)(hi << 32 | lo));
+    auto sv = Front<QUEUE, DERIVE, 0, ROLE>::of_wave((ArgsPtr)(uintptr_t)(hi << 32 | lo));
     sv.instance(uniform(i), uniform(T), uniform(lam), uniform(slo));
     int status;
     if (sv.is_small() ||
@@ -827,9 +834,9 @@ __device__ __attribute__((noinline)) int solve_rest(uint64_t args, int i, int T,
 // One whole solve of instance `inst` at the rate rates[inst].
 template <int QUEUE, bool DERIVE, int WIDTH, int ROLE>
 __device__ __forceinline__ int solve_instance(ArgsPtr args, int inst, const int32_t* rates,
-                                              int lane = (int)threadIdx.x)
+                                              int lane = (int)threadIdx.x, uint32_t offset = 0u)
 {
-    Front<QUEUE, DERIVE, WIDTH, ROLE> sv(args, lane);
+    Front<QUEUE, DERIVE, WIDTH, ROLE> sv(args, lane, offset);
     bool valid;
     const auto first = sv.begin(inst, rates, valid);
     return sv.finish(sv.solve(first, valid));

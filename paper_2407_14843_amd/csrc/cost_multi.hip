@@ -1,13 +1,14 @@
 // The entry points that solve an instance more than once, each with all of an
-// instance's solves in one wavefront (cost_solver.h), one after the other:
+// instance's solves in one launch (cost_solver.h), one after the other but for kc_stability:
 //
 //   kc_fallback   Algorithm 1 with its fallback (Section 4.4): whether the replicas given
 //                 can meet the SLO at lambda; where they cannot, the binary search on the
 //                 rate; the vertical solve at lambda or the rate found, and the horizontal
 //                 solve of the rest with the cores just chosen.
 //   kc_stability  the stability test of Section 5.1.3: the horizontal solve at the
-//                 current and, where that succeeds and the rate differs, at the
-//                 predicted rate, and whether the configurations agree.
+//                 current and, where the rate differs, at the predicted rate, and whether
+//                 the configurations agree; by a wavefront each where the batch leaves
+//                 room for that, else (where the first succeeds) one after the other.
 //
 // The search needs no recurrence: a configuration within the budget exists exactly
 // when the fastest feasible candidates of all models fit it together, and with the
@@ -20,7 +21,7 @@
 // kernel around one-wavefront solves, eight launches and three, they took 250 and 28 us
 // at 16384 x 8 and 4099 x 5; as one launch each 65 and 23, with a solve at lambda ahead of
 // the search, an evaluation from the start for each of its midpoints and some sixty registers
-// spilled; now 28.5 and 17.4.  Pipelines of more than 64 models still go the other way, over the
+// spilled; now 26.7 and 11.8.  Pipelines of more than 64 models still go the other way, over the
 // three stages.
 #include "cost_front.h"
 
@@ -110,11 +111,58 @@ __device__ __forceinline__ void stability_instance(ArgsPtr args, int i)
     if (threadIdx.x == 0) args->stable[i] = stable ? 1 : 0;
 }
 
+// The same with a wavefront for each of the two rates.  Two barriers each: the first one's first
+// is when its solve is done, the second one's before it uses the instance's rows in HBM or, if
+// it has no use for them, after its solve; then both have their results.
 template <int QUEUE, int WIDTH>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6, 6))) void kc_stability(CostArgs)
+__device__ __forceinline__ void stability_pair(ArgsPtr args, int i)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    const bool later = wave_number() == 1u;
+    const bool moves = constant(args->lambda)[i] != constant(args->lambda2)[i];
+    int status = THEMIS_SOLVED;
+    if (!later) {
+        status = solve_instance<QUEUE, true, WIDTH, PLAIN>(args, i, args->lambda, (int)lane);
+        __syncthreads();
+    } else {
+        {
+            const CostLds L = cost_lds(args->S, args->window);
+            uint32_t* const mine = cost_smem + args->wave_words;
+            // (there is no choice of a solve before for put_row() to find)
+            if (lane < (uint32_t)args->S) mine[L.pin + lane] = SAME;
+            if (lane == 0u) mine[L.words] = 0u;
+            wave_lds_fence();
+        }
+        if (moves)
+            status = solve_instance<QUEUE, true, WIDTH, SECOND>(args, i, args->lambda2, (int)lane,
+                                                                args->wave_words);
+        args = Front<QUEUE, true, WIDTH>::afresh(args);
+        const CostLds L = cost_lds(args->S, args->window);
+        uint32_t* const mine = cost_smem + args->wave_words;
+        wave_lds_fence();
+        if (__builtin_amdgcn_readfirstlane((int)mine[L.words]) == 0) __syncthreads();
+        if (lane == 0u) mine[L.words] = status == THEMIS_SOLVED ? 1u : 0u;
+    }
+    __syncthreads();
+    if (later) return;
+    args = Front<QUEUE, true, WIDTH>::afresh(args);
+    const CostLds L = cost_lds(args->S, args->window);
+    // what put_row() left of the choices of both
+    const uint32_t *const first = cost_smem, *const second = cost_smem + args->wave_words;
+    const bool same = !moves || lane >= (uint32_t)args->S || first[L.pin + lane] == second[L.pin + lane];
+    const bool stable = status == THEMIS_SOLVED && second[L.words] && __ballot(!same) == 0ull;
+    if (lane == 0u) args->stable[i] = stable ? 1 : 0;
+}
+
+// TWO: a workgroup of two wavefronts per instance.
+template <int QUEUE, int WIDTH, bool TWO>
+__global__ __launch_bounds__(TWO ? 128 : 64) __attribute__((amdgpu_waves_per_eu(6, 6))) void kc_stability(CostArgs)
 {
     const ArgsPtr args = kernel_args();
-    stability_instance<QUEUE, WIDTH>(args, (int)blockIdx.x);
+    if (TWO)
+        stability_pair<QUEUE, WIDTH>(args, (int)blockIdx.x);
+    else
+        stability_instance<QUEUE, WIDTH>(args, (int)blockIdx.x);
     mark_workspace(args, STATE_KEPT | (args->c_fixed ? STATE_ONLY : 0) |
                              args->c_all << STATE_C_ALL);
 }
@@ -131,16 +179,21 @@ CostKernel fallback_kernel(int width)
     }
 }
 
-template <int QUEUE>
+template <int QUEUE, bool TWO>
 CostKernel stability_kernel(int width)
 {
     switch (width) {
-    case WIDTH_PACKED: return &kc_stability<QUEUE, PACKED>;
-    case 4: return &kc_stability<QUEUE, 4>;
-    case 8: return &kc_stability<QUEUE, 8>;
-    case 16: return &kc_stability<QUEUE, 16>;
-    default: return &kc_stability<QUEUE, 0>;
+    case WIDTH_PACKED: return &kc_stability<QUEUE, PACKED, TWO>;
+    case 4: return &kc_stability<QUEUE, 4, TWO>;
+    case 8: return &kc_stability<QUEUE, 8, TWO>;
+    case 16: return &kc_stability<QUEUE, 16, TWO>;
+    default: return &kc_stability<QUEUE, 0, TWO>;
     }
+}
+template <int QUEUE>
+CostKernel stability_kernel(int width, bool two)
+{
+    return two ? stability_kernel<QUEUE, true>(width) : stability_kernel<QUEUE, false>(width);
 }
 
 }  // namespace
@@ -181,13 +234,19 @@ hipError_t launch_cost_stability(const themis_problem_t& p, const Layout& L,
     a.cost2 = (int32_t*)(ws + B.cost_off);
     a.ticks2 = (int32_t*)(ws + B.ticks_off);
     a.cfg2 = (int32_t*)(ws + B.cfg_off);
+    // Two wavefronts for an instance halve its chain, where all are in flight at once and there
+    // is one (a single model is done with step A).  The second one's solve is in vain where
+    // the first finds nothing, so with more instances than that it depends on what they are:
+    // 4099 x 5 16.3 -> 11.8 us, 145 x 8 16.8 -> 9.7; 15061 x 4 48.8 -> 40.3, but 9782 x 2
+    // 9.4 -> 10.0 and 32841 x 3 24.5 -> 30.4; 6434 x 1 7.45 -> 7.62.
+    const bool two = L.S > 1 && L.N <= RESIDENT_PER_CU * compute_units();
     return launch_per_instance(p, L, a, st, false, [&](int width) {
         switch (p.queue_model) {
-        case THEMIS_QUEUE_SHARED: return stability_kernel<THEMIS_QUEUE_SHARED>(width);
-        case THEMIS_QUEUE_WORST_CASE: return stability_kernel<THEMIS_QUEUE_WORST_CASE>(width);
-        default: return stability_kernel<THEMIS_QUEUE_PER_REPLICA>(width);
+        case THEMIS_QUEUE_SHARED: return stability_kernel<THEMIS_QUEUE_SHARED>(width, two);
+        case THEMIS_QUEUE_WORST_CASE: return stability_kernel<THEMIS_QUEUE_WORST_CASE>(width, two);
+        default: return stability_kernel<THEMIS_QUEUE_PER_REPLICA>(width, two);
         }
-    });
+    }, two ? 2 : 1);
 }
 
 }  // namespace themis

@@ -52,6 +52,7 @@ struct CostArgs : HotArgs {
     int32_t hrow_stride;  // cells of hrow per instance
     int32_t row_stride;
     int32_t window_hbm;   // like `window`, in HBM (no larger than the other: none)
+    uint32_t wave_words;  // LDS words of each wavefront of a workgroup (0: there is one)
     uint32_t parts, pair_magic;  // lanes per (model, batch size) pair of a sweep, see sweep()
     int32_t lanes, turns;  // lanes per model, and the batch sizes of each, see Front
     uint32_t lane_magic;   // index_magic() of them
@@ -104,6 +105,12 @@ __device__ __forceinline__ const __attribute__((address_space(4))) T* constant(c
 
 extern __shared__ uint32_t cost_smem[];
 
+// which of its workgroup's wavefronts this is
+__device__ __forceinline__ uint32_t wave_number()
+{
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)threadIdx.x) >> 6;
+}
+
 // The value D lanes down within the rows of sixteen that `ROWS` names; `fill` where
 // there is none, x itself in the other rows.
 template <int D, int ROWS = 0xF>
@@ -147,7 +154,7 @@ template <int QUEUE, bool DERIVE, int ROLE>
 struct Solver {
     const ArgsPtr args;
     HotArgs a;
-    uint32_t* const lds;  // the wavefront's words: a workgroup is one wavefront
+    uint32_t* const lds;  // the wavefront's words
     const CostLds L;
     const int lane;
 
@@ -156,9 +163,15 @@ struct Solver {
     int32_t lam, slo;
     int32_t lane_b;  // lane j: batch size j
 
-    __device__ __forceinline__ explicit Solver(ArgsPtr p, int l = (int)threadIdx.x)
-        : args(p), a(hot_args(p)), lds(cost_smem), L(cost_lds(p->S, p->window)), lane(l)
+    // `offset`: of the wavefront's words
+    __device__ __forceinline__ explicit Solver(ArgsPtr p, int l = (int)threadIdx.x, uint32_t offset = 0u)
+        : args(p), a(hot_args(p)), lds(cost_smem + offset), L(cost_lds(p->S, p->window)), lane(l)
     {
+    }
+    // (out of line, where a workgroup may have several wavefronts)
+    static __device__ __forceinline__ Solver of_wave(ArgsPtr p)
+    {
+        return Solver(p, (int)threadIdx.x & 63, wave_number() * p->wave_words);
     }
     // (member by member: the address space has no copies of whole structures)
     static __device__ __forceinline__ HotArgs hot_args(ArgsPtr p)
@@ -1929,6 +1942,19 @@ struct Solver {
         return status == UNFINISHED ? out_of_line<PART_LIST>() : status;
     }
 
+    // Rows in HBM are the instance's.  Where both of its solves have a wavefront, the second one
+    // waits with them until the first is done (which it says with a barrier as its last step).
+    // The word behind its others tells whether it has.
+    __device__ __forceinline__ void wait_for_rows() const
+    {
+        if (ROLE != SECOND || !args->wave_words) return;
+        uint32_t* const waited = lds + L.words;
+        if (__builtin_amdgcn_readfirstlane((int)*waited)) return;
+        __syncthreads();
+        if (lane == 0) *waited = 1u;
+        wave_lds_fence();
+    }
+
     // Steps C, G, W and D.
     __device__ __forceinline__ int solve_further() const
     {
@@ -1946,10 +1972,15 @@ struct Solver {
             const bool in_lds = cells / 2 <= l.free_words;
             status = most ? out_of_line<PART_TRIAL>(most) : UNFINISHED;
             if (status == UNFINISHED && in_lds) status = out_of_line<PART_ROWS>(W);
-            else if (status == UNFINISHED && cells <= args->hrow_stride) status = out_of_line<PART_ROWS_HBM>(W);
+            else if (status == UNFINISHED && cells <= args->hrow_stride) {
+                wait_for_rows();
+                status = out_of_line<PART_ROWS_HBM>(W);
+            }
             if (status == UNFINISHED) status = out_of_line<PART_TRIAL>(MOST_TRIALS);
         }
-        return status == UNFINISHED ? out_of_line<PART_WD>() : status;
+        if (status != UNFINISHED) return status;
+        wait_for_rows();
+        return out_of_line<PART_WD>();
     }
 
     // Steps W and D.
@@ -2004,7 +2035,7 @@ __device__ __attribute__((noinline)) int solve_part(uint64_t args, int i, int T,
     auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
     const uint64_t lo = (uint32_t)uniform((int)(uint32_t)args);
     const uint64_t hi = (uint32_t)uniform((int)(uint32_t)(args >> 32));
-    Solver<QUEUE, DERIVE, ROLE> sv((ArgsPtr)(uintptr_t)(hi << 32 | lo));
+    auto sv = Solver<QUEUE, DERIVE, ROLE>::of_wave((ArgsPtr)(uintptr_t)(hi << 32 | lo));
     return uniform(
         sv.template part<PART>(uniform(i), uniform(T), uniform(lam), uniform(slo), uniform(x)));
 }
@@ -2146,7 +2177,7 @@ inline CostArgs past(CostArgs a, size_t n)
 // compute unit allows have their rows in HBM instead.
 template <typename K>
 hipError_t launch_per_instance(const themis_problem_t& p, const Layout& L, CostArgs& a,
-                               hipStream_t st, bool listed, K kernel)
+                               hipStream_t st, bool listed, K kernel, int waves = 1)
 {
     const int cus = compute_units();
     const int grid = listed && L.N > RESIDENT_PER_CU * cus ? RESIDENT_PER_CU * cus : L.N;
@@ -2154,11 +2185,11 @@ hipError_t launch_per_instance(const themis_problem_t& p, const Layout& L, CostA
     // larger than the costs of a pipeline can spread.  With room for just the mean of a compute
     // unit, the last ones wait until one of their unit's ends, as they are not dealt out evenly:
     // a quarter more (3001 x 7, twelve of a unit: 12.75 us without, 11.84 with it or with half).
-    int per_cu = (int)(((long long)grid + cus - 1) / cus);
+    int per_cu = (int)(((long long)grid * waves + cus - 1) / cus);
     per_cu += (per_cu + 3) / 4;
     per_cu = per_cu < 4 ? 4 : per_cu > RESIDENT_PER_CU ? RESIDENT_PER_CU : per_cu;
     auto lds_for = [&](int window) {
-        return (size_t)cost_lds(L.S, window).words * sizeof(uint32_t);
+        return (size_t)(cost_lds(L.S, window).words + (waves > 1 ? 4 : 0)) * sizeof(uint32_t);
     };
     const int spread = L.S * p.r_max * p.c_max;
     a.window = 64;
@@ -2169,6 +2200,7 @@ hipError_t launch_per_instance(const themis_problem_t& p, const Layout& L, CostA
     const CostLds lds = cost_lds(L.S, a.window);
     const int fit = a.hrow_stride / (L.S + 1) - 2;
     const int room = lds.words - lds.tab;
+    a.wave_words = waves > 1 ? (uint32_t)(lds_for(a.window) / sizeof(uint32_t)) : 0u;
     a.window_hbm = (fit < room ? fit : room) & ~63;
     // (at most 40 KB of LDS, which a kernel may have without asking)
     const int width = a.turns > 1 ? 0 : a.width_log >= 2 ? 1 << a.width_log : WIDTH_PACKED;
@@ -2176,11 +2208,11 @@ hipError_t launch_per_instance(const themis_problem_t& p, const Layout& L, CostA
     hipError_t e = hipSuccess;
     in_launches(grid, [&](int first, int count) {
         if (e != hipSuccess) return;
-        const dim3 groups((unsigned)count);
+        const dim3 groups((unsigned)count), lanes(64 * waves);
         if (first == 0)
-            hipLaunchKernelGGL(k, groups, dim3(64), lds_for(a.window), st, a);
+            hipLaunchKernelGGL(k, groups, lanes, waves * lds_for(a.window), st, a);
         else
-            hipLaunchKernelGGL(k, groups, dim3(64), lds_for(a.window), st, past(a, (size_t)first));
+            hipLaunchKernelGGL(k, groups, lanes, waves * lds_for(a.window), st, past(a, (size_t)first));
         e = hipGetLastError();
     });
     return e;
