@@ -331,8 +331,9 @@ size_t themis_memo_workspace_bytes(const themis_problem_t *p);
  * unless shared), one instance per group is solved, and
  * the others receive its results.  Outputs are those of themis_solve_joint /
  * themis_solve_vertical on the same arguments, word for word, invalid
- * instances included; only the work differs.  The measured hot path does not
- * use it: there every instance is solved.
+ * instances included; only the work differs (a batch of up to an instance per
+ * SIMD, 1024 on a whole MI355X, is solved as it is, which is sooner done).  The
+ * measured hot path does not use it: there every instance is solved.
  * d_workspace holds themis_memo_workspace_bytes(p) bytes.
  */
 int themis_solve_distinct(const themis_problem_t *p, const int32_t *d_coef,

@@ -117,6 +117,10 @@ CostKernel solve_kernel(bool listed, int width)
 }  // namespace
 
 bool cost_solve_serves(const Layout& L) { return L.S <= COST_MAX_STAGES; }
+bool cost_solve_side_by_side(const Layout& L)
+{
+    return cost_solve_serves(L) && L.N <= SIMDS_PER_CU * compute_units();
+}
 
 hipError_t launch_cost_solve(const themis_problem_t& p, const Layout& L, const int32_t* d_coef,
                              const int32_t* d_lambda, const int32_t* d_slo_us,

@@ -2073,7 +2073,7 @@ constexpr int MAX_WINDOW = 8192;
 // are in flight on average, and the room of the others lets step G list more candidates
 // (measured while it could only list all of them: at 16384 x 8 with a twelfth of the
 // objectives 32 / 28 / 24 / 20 took 579 / 122 / 121 / 129 us, at 86400 x 6 51 / 51 / 55 / 60).
-constexpr int RESIDENT_PER_CU = 28;
+constexpr int RESIDENT_PER_CU = 28, SIMDS_PER_CU = 4;
 
 // What does not depend on the entry point.
 inline CostArgs cost_args(const themis_problem_t& p, const Layout& L, const int32_t* d_coef,

@@ -15,6 +15,7 @@
 //               representative, a thread per word.
 // Which index of a tuple becomes the representative depends on the order the
 // threads arrive in; the outputs do not, since equal inputs have one answer.
+// (Batches of up to an instance per SIMD don't come here, see themis_solve_distinct.)
 //
 // What bounds it: the launches (four, some four microseconds each) and, before the
 // workgroups sorted out their own duplicates, the compare-and-swaps, which serialise

@@ -256,6 +256,13 @@ int themis_solve_distinct(const themis_problem_t* p, const int32_t* d_coef,
         return THEMIS_ERR_WORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(stream);
     char* w = static_cast<char*>(d_workspace);
+    // Up to a wavefront per SIMD the instances that recur take nothing away from the others, and to
+    // find them and hand out their results (three launches more) only adds to the time: 3 x 2
+    // 16.2 us by way of it and 7.3 without, 451 x 1 16.8 and 7.9, 979 x 8 18.8 and 7.8.  With
+    // more it depends on what they are: 10446 x 2 19.0 and 8.2, 18297 x 6 37.6 and 59.5.
+    if (cost_solve_side_by_side(L))
+        return pass(*p, L, d_coef, d_lambda, d_slo_us, d_r_fixed, d_status, d_cost, d_ticks, d_cfg,
+                    w, st, PassOpts());
     if (launch_memo_dedupe(*p, L, M, d_coef, d_lambda, d_slo_us, d_r_fixed, d_status, d_cost,
                            d_ticks, d_cfg, w, st) != hipSuccess)
         return THEMIS_ERR_LAUNCH;
