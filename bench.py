@@ -56,8 +56,8 @@ KERNEL_SOURCES = ("k1_candidates.hip", "candidate_eval.h", "wave_ops.h", "k2_min
 # vector instructions of the timed whole solve per instance (the pipe counters in
 # profiles/*_kernel_trace.txt): workload -> (instructions, fingerprint of its sources)
 SOLVE_VALU = {
-    "w1-joint-4096x5": (382.7, "95ee8bd443a9d697"),
-    "w3-joint-65536x8": (467.9, "95ee8bd443a9d697"),
+    "w1-joint-4096x5": (383.2, "417d2880813c0c4a"),
+    "w3-joint-65536x8": (465.7, "417d2880813c0c4a"),
 }
 SOLVE_SOURCES = ("cost_solve.hip", "cost_front.h", "cost_solver.h", "candidate_eval.h",
                  "wave_ops.h", "themis_internal.h")

@@ -5,6 +5,11 @@
 
 #include <mutex>
 
+namespace themis {
+// Whether the wavefront of every instance of such a batch has a SIMD to itself (cost_solve.hip).
+bool cost_solve_side_by_side(const Layout& L);
+}  // namespace themis
+
 using namespace themis;
 
 // Workspace of themis_solve_joint_static: one array per GPU, held from the

@@ -283,8 +283,6 @@ struct PassOpts {
 // The one-wavefront solve: three stages' worth of results in one launch.
 constexpr int COST_MAX_STAGES = 64;  // a lane per model
 bool cost_solve_serves(const Layout& L);
-// Whether the wavefront of every instance of such a batch has a SIMD to itself.
-bool cost_solve_side_by_side(const Layout& L);
 // A launch has a wavefront per instance, and HIP takes fewer than 2^32 work-items, so
 // larger batches (of up to 2^28 instances) take several: launch(first, count) for each.
 constexpr int MAX_PER_LAUNCH = 1 << 25;
