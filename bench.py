@@ -59,8 +59,8 @@ SOLVE_VALU = {
     "w1-joint-4096x5": (383.2, "417d2880813c0c4a"),
     "w3-joint-65536x8": (465.7, "417d2880813c0c4a"),
 }
-SOLVE_SOURCES = ("cost_solve.hip", "cost_front.h", "cost_solver.h", "candidate_eval.h",
-                 "wave_ops.h", "themis_internal.h")
+SOLVE_SOURCES = ("cost_solve.hip", "cost_front.h", "cost_solver.h", "cost_plan.h",
+                 "candidate_eval.h", "wave_ops.h", "themis_internal.h")
 
 
 def kernel_fingerprint(sources=KERNEL_SOURCES):

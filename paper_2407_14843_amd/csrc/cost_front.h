@@ -27,19 +27,22 @@ namespace {
 // atomics took an initial value, a wait for each atomic and a read (some 200 cycles).
 // WIDTH: that width, where all models fit the wavefront that way (every lane keeps its pair
 // from step A on); PACKED: where they fit it only without gaps between the models, and
-// minima go through LDS; 0: where there are more pairs than lanes, the lanes of a model with its
-// batch sizes in turns (a power of two of lanes, or where that takes fewer turns as many as all
-// models leave room for, with minima through LDS).  A lane then keeps its model, and is done
-// with all of its batch sizes before minima and sums are formed.  (The models in turns, in lanes
-// for all of their batch sizes, with their inputs asked for again and minima and sums formed in
-// each: 3001 x 7 models with twelve batch sizes 11.8 us instead of 10.4, 59755 x 7 with fourteen
-// and replicas given 246 instead of 203, fallback 13320 x 9 with fifteen 105 instead of 59, of 50
-// shapes drawn 1.12 times as long in the mean; 186 x 10 with seven 30.6 instead of 32.4.)
+// minima go through LDS; TURNS: where there are more pairs than lanes, the lanes of a model with
+// its batch sizes in turns (a power of two of lanes, or where that takes fewer turns as many as
+// all models leave room for, with minima through LDS).  A lane then keeps its model, and is done
+// with all of its batch sizes before minima and sums are formed.  ROUNDS: where that leaves too
+// many lanes idle (front_layout() has the rule), the models in rounds of args->per_round, in
+// lanes for all of their batch sizes (round_log below zero: without gaps), with their inputs
+// asked for again, minima and sums formed in each, and what is found about them in LDS.  (That
+// way 3001 x 7 models with twelve batch sizes take 11.8 us and in turns 10.4, 59755 x 7 with
+// fourteen and replicas given 246 and 203, fallback 13320 x 9 with fifteen 105 and 59, 186 x 10
+// with seven 30.6 and 32.4, 50 shapes drawn from one to ten models 1.12 times as long in the mean.)
 // (One kernel for the widths 4, 8 and 16, with the width an argument:
 // 86400 x 6 43.6 us instead of 39.8, fallback 16384 x 8 30.8 instead of 28.5, 65536 x 8 79.5
 // instead of 76.4, 512 x 5 7.4 instead of 7.0.)
-constexpr int PACKED = WIDTH_PACKED;
-template <int QUEUE, bool DERIVE, int ROLE>
+constexpr int TURNS = WIDTH_TURNS, PACKED = WIDTH_PACKED, ROUNDS = WIDTH_ROUNDS;
+// MANY: TURNS or, where the instance's steps are taken that way, ROUNDS
+template <int QUEUE, bool DERIVE, int ROLE, int MANY>
 __device__ __attribute__((noinline)) int solve_rest(uint64_t args, int i, int T, int32_t lam,
                                                     int32_t slo);
 
@@ -49,7 +52,9 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
     using typename Base::Model;
     using typename Base::Pair;
     using Base::a, Base::args, Base::i, Base::L, Base::lam, Base::lane, Base::lds, Base::slo, Base::T;
-    static constexpr bool ONE = WIDTH != 0;
+    // a pair, or a model, for every lane from the start
+    static constexpr bool ONE = WIDTH != TURNS && WIDTH != ROUNDS, OWN = WIDTH == TURNS;
+    static constexpr int MANY = WIDTH == ROUNDS ? ROUNDS : TURNS;
 
     __device__ __forceinline__ explicit Front(ArgsPtr p, int l = (int)threadIdx.x, uint32_t offset = 0u)
         : Base(p, l, offset)
@@ -62,31 +67,37 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
 
     __device__ __forceinline__ int width_log() const
     {
-        return WIDTH == 16 ? 4 : WIDTH == 8 ? 3 : WIDTH == 4 ? 2 : a.width_log;
+        return WIDTH == 16 ? 4 : WIDTH == 8 ? 3 : WIDTH == 4 ? 2 : WIDTH == ROUNDS ? args->round_log : a.width_log;
     }
-    // What a lane starts from: its pair, or (not ONE) its model and which of its lanes it is.
+    // this lane's pair (ROUNDS: of the round that starts with model s0)
+    __device__ __forceinline__ Pair lanes_pair(int s0 = 0) const
+    {
+        uint32_t s, j;
+        if (packed()) {
+            s = index_quotient((uint32_t)lane, a.magic);
+            j = (uint32_t)lane - s * (uint32_t)a.n_batch;
+        } else {
+            s = (uint32_t)lane >> width_log();
+            j = (uint32_t)lane & ((1u << width_log()) - 1u);
+        }
+        if (WIDTH == ROUNDS) s = s < (uint32_t)args->per_round ? s + (uint32_t)s0 : (uint32_t)a.S;
+        const bool in = s < (uint32_t)a.S;
+        Pair p = this->pair_of(s, j, (int)in & (int)(j < (uint32_t)a.n_batch));
+        p.in = in, p.first = j == 0u;
+        return p;
+    }
+    // What a lane starts from: its pair, or (OWN) its model and which of its lanes it is.
     struct Own {
         Model m;
         uint32_t s, part;
         bool there, valid, in;
         int32_t size;
     };
-    typedef typename std::conditional<ONE, Pair, Own>::type Start;
+    typedef typename std::conditional<OWN, Own, Pair>::type Start;
     __device__ __forceinline__ Start start() const
     {
-        if constexpr (ONE) {
-            uint32_t s, j;
-            if (packed()) {
-                s = index_quotient((uint32_t)lane, a.magic);
-                j = (uint32_t)lane - s * (uint32_t)a.n_batch;
-            } else {
-                s = (uint32_t)lane >> width_log();
-                j = (uint32_t)lane & ((1u << width_log()) - 1u);
-            }
-            const bool in = s < (uint32_t)a.S;
-            Pair p = this->pair_of(s, j, (int)in & (int)(j < (uint32_t)a.n_batch));
-            p.in = in, p.first = j == 0u;
-            return p;
+        if constexpr (!OWN) {
+            return lanes_pair();
         } else {
             Own o;
             const uint32_t lanes = (uint32_t)args->lanes;
@@ -109,6 +120,8 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
     {
         if constexpr (ONE) {
             f(mine);
+        } else if constexpr (!OWN) {
+            for (int s0 = 0; s0 < a.S; s0 += args->per_round) f(lanes_pair(s0));
         } else {
             const uint32_t nb = (uint32_t)a.n_batch, turns = (uint32_t)args->turns;
             const uint32_t first = SPREAD ? mine.part * turns : mine.part;
@@ -128,7 +141,7 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
     static __device__ __forceinline__ bool leads(const Own& o) { return (int)o.in & (int)(o.part == 0u); }
     __device__ __forceinline__ bool packed() const
     {
-        return WIDTH == PACKED || (WIDTH == 0 && a.width_log < 0);
+        return WIDTH == PACKED || (!ONE && width_log() < 0);
     }
     static __device__ __forceinline__ bool any(bool x) { return __builtin_amdgcn_ballot_w64(x) != 0ull; }
 
@@ -400,6 +413,7 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
     template <bool SMALL>
     __device__ __forceinline__ uint32_t fastest_of(const Start& first) const
     {
+        static_assert(WIDTH != ROUNDS, "a lane has several models");
         uint32_t fast = EMPTY;
         for_pairs(first, [&](const Pair& p) { fast = least(fast, turned(p, meet<SMALL>(p, p.last))); });
         return model_least(first, fast);
@@ -408,7 +422,15 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
     template <bool SMALL>
     __device__ __forceinline__ uint32_t fastest_ticks(const Start& first) const
     {
-        return sum_of_models(first, fastest_of<SMALL>(first) >> 15);
+        if constexpr (WIDTH == ROUNDS) {
+            uint32_t sum = 0u;
+            for_pairs(first, [&](const Pair& p) {
+                sum += sum_of_models(p, model_least(p, turned(p, meet<SMALL>(p, p.last))) >> 15);
+            });
+            return sum;
+        } else {
+            return sum_of_models(first, fastest_of<SMALL>(first) >> 15);
+        }
     }
 
     // ---- the tables of steps B and C ----------------------------------------------
@@ -609,35 +631,71 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
     __device__ __forceinline__ int solve_valid(const Start& first) const
     {
         Best mine{EMPTY, EMPTY, 0u, 1u, EMPTY, 0, false};
-        if constexpr (ONE) {
-            mine = best_of<SMALL>(first);
+        uint32_t ticks = 0u, base_sum;
+        if constexpr (WIDTH == ROUNDS) {
+            for_pairs(first, [&](const Pair& p) {
+                const Best b = best_of<SMALL>(p);
+                ticks += sum_of_models(p, b.key == EMPTY ? LT_NONE : b.key & 0x7FFFu);
+                if (leads(p)) {
+                    this->keys()[p.s] = b.key;
+                    this->bests()[p.s] = (unsigned long long)b.key << INDEX_BITS | b.k;
+                }
+            });
         } else {
-            for_pairs<DERIVE>(first, [&](const Pair& p) { improve<SMALL>(mine, p); });
-            mine.key = model_least(first, mine.own);
-            const uint32_t k = mine.own == mine.key ? mine.k : EMPTY;
-            mine.k = model_least(first, k);
-            mine.mine = first.there && mine.own != EMPTY && k == mine.k;
+            if constexpr (ONE) {
+                mine = best_of<SMALL>(first);
+            } else {
+                for_pairs<DERIVE>(first, [&](const Pair& p) { improve<SMALL>(mine, p); });
+                mine.key = model_least(first, mine.own);
+                const uint32_t k = mine.own == mine.key ? mine.k : EMPTY;
+                mine.k = model_least(first, k);
+                mine.mine = first.there && mine.own != EMPTY && k == mine.k;
+            }
+            ticks = sum_of_models(first, mine.key == EMPTY ? LT_NONE : mine.key & 0x7FFFu);
         }
-        const uint32_t ticks = sum_of_models(first, mine.key == EMPTY ? LT_NONE : mine.key & 0x7FFFu);
         if (ticks >= LT_NONE) return THEMIS_INFEASIBLE;
-        const uint32_t base_sum = sum_of_models(first, mine.key >> 15);
+        if constexpr (WIDTH == ROUNDS) {
+            // from here on lane s has what was found about model s
+            wave_lds_fence();
+            const unsigned long long best = lane < a.S ? this->bests()[lane] : 0ull;
+            mine.key = (uint32_t)(best >> INDEX_BITS);
+            mine.k = (uint32_t)best & ((1u << INDEX_BITS) - 1u);
+            base_sum = this->sum_models(mine.key >> 15);
+        } else {
+            base_sum = sum_of_models(first, mine.key >> 15);
+        }
         if (ticks <= (uint32_t)T) {
             this->put(THEMIS_SOLVED, (int32_t)base_sum, (int32_t)ticks);
-            this->put_row(mine.mine, first.s, mine.c, ONE ? first.size : mine.size, mine.k, mine.key >> 15);
+            if constexpr (WIDTH == ROUNDS)
+                this->put_choice(mine.k, mine.key >> 15);
+            else
+                this->put_row(mine.mine, first.s, mine.c, ONE ? first.size : mine.size, mine.k, mine.key >> 15);
             return THEMIS_SOLVED;
         }
         const bool one = this->one_each();
-        // (where it is the lane's only candidate step A has met it)
-        uint32_t fast;
-        if constexpr (ONE)
-            fast = one ? model_least(first, turned(first, mine.own)) : fastest_of<SMALL>(first);
-        else
-            fast = fastest_of<SMALL>(first);
-        const uint32_t least_ticks = sum_of_models(first, fast >> 15);
-        if (leads(first)) this->fastest()[first.s] = fast, this->keys()[first.s] = mine.key;
+        uint32_t fast = 0u, least_ticks = 0u;
+        if constexpr (WIDTH == ROUNDS) {
+            for_pairs(first, [&](const Pair& p) {
+                const uint32_t f = model_least(p, turned(p, meet<SMALL>(p, p.last)));
+                least_ticks += sum_of_models(p, f >> 15);
+                if (leads(p)) this->fastest()[p.s] = f;
+            });
+            wave_lds_fence();
+            fast = lane < a.S ? this->fastest()[lane] : 0u;
+        } else {
+            // (where it is the lane's only candidate step A has met it)
+            if constexpr (ONE)
+                fast = one ? model_least(first, turned(first, mine.own)) : fastest_of<SMALL>(first);
+            else
+                fast = fastest_of<SMALL>(first);
+            least_ticks = sum_of_models(first, fast >> 15);
+            if (leads(first)) this->fastest()[first.s] = fast, this->keys()[first.s] = mine.key;
+        }
         if (least_ticks > (uint32_t)T) return THEMIS_INFEASIBLE;
-        const int reach = reach_of(ticks, least_ticks, one,
-                                   [&] { return sum_of_models(first, fast & 0x7FFFu) - base_sum; });
+        const int reach = reach_of(ticks, least_ticks, one, [&] {
+            return (WIDTH == ROUNDS ? this->sum_models(fast & 0x7FFFu) : sum_of_models(first, fast & 0x7FFFu)) -
+                   base_sum;
+        });
         // (one candidate each: what there is to enter is at hand, for all windows at once)
         if (one) fill_one_each<SMALL>(first, mine);
         if (reach <= 8) {
@@ -686,10 +744,12 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
         uint32_t* const tab = lds + L.tab;
         for (int y = lane; y < cells * a.S; y += 64) tab[y] = EMPTY;
         wave_lds_fence();
-        if (leads(first)) tab[first.s * cells] = (mine.key & 0x7FFFu) << INDEX_BITS | mine.k;
+        if (WIDTH == ROUNDS ? lane < a.S : leads(first))
+            tab[(WIDTH == ROUNDS ? (uint32_t)lane : first.s) * cells] = (mine.key & 0x7FFFu) << INDEX_BITS | mine.k;
         wave_lds_fence();
         for_pairs(first, [&](const Pair& p) {
-            enter<SMALL>(p, ONE ? mine.c0 : this->first_core(p), mine.key, (uint32_t)cells, (uint32_t)span);
+            enter<SMALL>(p, ONE ? mine.c0 : this->first_core(p), WIDTH == ROUNDS ? this->keys()[p.s] : mine.key,
+                         (uint32_t)cells, (uint32_t)span);
         });
         wave_lds_fence();
     }
@@ -702,7 +762,7 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
         wave_lds_fence();
         for_pairs(first, [&](const Pair& p) {
             const uint32_t key = ONE ? mine.own : meet<SMALL>(p, p.last);
-            const uint32_t d = (key >> 15) - (mine.key >> 15);
+            const uint32_t d = (key >> 15) - ((WIDTH == ROUNDS ? this->keys()[p.s] : mine.key) >> 15);
             // (EMPTY is beyond any cell)
             const bool use = (int)p.there & (int)(d < 64u);
             atomicMin(&tab[use ? 64u * p.s + d : (uint32_t)lane],
@@ -741,7 +801,10 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
         const Start first = start();
         this->lane_b = first.size;  // (the first lanes have the first model's pairs)
         int fine = (int)in_range(lam, 1, THEMIS_VALUE_MAX) & (int)in_range(slo, 0, a.slo_max);
-        fine &= (int)!first.there | (int)first.valid;
+        if constexpr (WIDTH == ROUNDS)
+            for_pairs(first, [&](const Pair& p) { fine &= (int)!p.there | (int)p.valid; });
+        else
+            fine &= (int)!first.there | (int)first.valid;
         valid = !any(!fine);
         this->keep_inputs(valid, word);
         if (this->records() && lane == 0) a.tmeta[i] = valid ? T : -1;
@@ -777,7 +840,7 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
             this->put_none(status);
             return status;
         }
-        return __builtin_amdgcn_readfirstlane(solve_rest<QUEUE, DERIVE, ROLE>(
+        return __builtin_amdgcn_readfirstlane(solve_rest<QUEUE, DERIVE, ROLE, MANY>(
             (uint64_t)(uintptr_t)afresh(args), i, T, lam, slo));
     }
     // The same pointer, to arguments that the compiler hasn't loaded yet.
@@ -790,14 +853,14 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
 
 // The rate the given replicas of an instance are solved at (see Front::search_rate()), where
 // products exceed 2^42.
-template <int QUEUE>
+template <int QUEUE, int MANY>
 __device__ __attribute__((noinline)) int32_t rate_of_large(uint64_t args, int i, int T, int32_t lam,
                                                            int32_t slo)
 {
     auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
     const uint64_t lo = (uint32_t)uniform((int)(uint32_t)args);
     const uint64_t hi = (uint32_t)uniform((int)(uint32_t)(args >> 32));
-    Front<QUEUE, false, 0, QUIET> sv((ArgsPtr)(uintptr_t)(hi << 32 | lo));
+    Front<QUEUE, false, MANY, QUIET> sv((ArgsPtr)(uintptr_t)(hi << 32 | lo));
     sv.instance(uniform(i), uniform(T), uniform(lam), uniform(slo));
     const auto first = sv.start();
     return uniform(sv.template fastest_ticks<false>(first) <= (uint32_t)sv.T
@@ -811,14 +874,14 @@ __device__ __attribute__((noinline)) int32_t rate_of_large(uint64_t args, int i,
 // and B where products exceed 2^42, with rates times objectives beyond those of any of the
 // numbered workloads by a factor of 200.  (Step B's sixteen cells stay with the others:
 // from here 4096 x 5 took 12.4 us instead of 11.2.)
-template <int QUEUE, bool DERIVE, int ROLE>
+template <int QUEUE, bool DERIVE, int ROLE, int MANY>
 __device__ __attribute__((noinline)) int solve_rest(uint64_t args, int i, int T, int32_t lam,
                                                     int32_t slo)
 {
     auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
     const uint64_t lo = (uint32_t)uniform((int)(uint32_t)args);
     const uint64_t hi = (uint32_t)uniform((int)(uint32_t)(args >> 32));
-    auto sv = Front<QUEUE, DERIVE, 0, ROLE>::of_wave((ArgsPtr)(uintptr_t)(hi << 32 | lo));
+    auto sv = Front<QUEUE, DERIVE, MANY, ROLE>::of_wave((ArgsPtr)(uintptr_t)(hi << 32 | lo));
     sv.instance(uniform(i), uniform(T), uniform(lam), uniform(slo));
     int status;
     if (sv.is_small() ||

@@ -48,7 +48,7 @@ __device__ __forceinline__ void fallback_instance(ArgsPtr args, int i)
                 first = sv.at_rate(first);
             }
         } else if (valid) {
-            rate = rate_of_large<QUEUE>((uint64_t)(uintptr_t)args, i, sv.T, lambda, sv.slo);
+            rate = rate_of_large<QUEUE, decltype(sv)::MANY>((uint64_t)(uintptr_t)args, i, sv.T, lambda, sv.slo);
             sv.lam = rate = __builtin_amdgcn_readfirstlane(rate);
             first = sv.at_rate(first);
         }
@@ -172,10 +172,11 @@ CostKernel fallback_kernel(int width)
 {
     switch (width) {
     case WIDTH_PACKED: return &kc_fallback<QUEUE, PACKED>;
+    case WIDTH_ROUNDS: return &kc_fallback<QUEUE, ROUNDS>;
     case 4: return &kc_fallback<QUEUE, 4>;
     case 8: return &kc_fallback<QUEUE, 8>;
     case 16: return &kc_fallback<QUEUE, 16>;
-    default: return &kc_fallback<QUEUE, 0>;
+    default: return &kc_fallback<QUEUE, TURNS>;
     }
 }
 
@@ -184,10 +185,11 @@ CostKernel stability_kernel(int width)
 {
     switch (width) {
     case WIDTH_PACKED: return &kc_stability<QUEUE, PACKED, TWO>;
+    case WIDTH_ROUNDS: return &kc_stability<QUEUE, ROUNDS, TWO>;
     case 4: return &kc_stability<QUEUE, 4, TWO>;
     case 8: return &kc_stability<QUEUE, 8, TWO>;
     case 16: return &kc_stability<QUEUE, 16, TWO>;
-    default: return &kc_stability<QUEUE, 0, TWO>;
+    default: return &kc_stability<QUEUE, TURNS, TWO>;
     }
 }
 template <int QUEUE>

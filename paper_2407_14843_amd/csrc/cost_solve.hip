@@ -101,10 +101,11 @@ CostKernel solve_kernel(int width)
 {
     switch (width) {
     case WIDTH_PACKED: return &kc_solve<QUEUE, DERIVE, PACKED, LISTED>;
+    case WIDTH_ROUNDS: return &kc_solve<QUEUE, DERIVE, ROUNDS, LISTED>;
     case 4: return &kc_solve<QUEUE, DERIVE, 4, LISTED>;
     case 8: return &kc_solve<QUEUE, DERIVE, 8, LISTED>;
     case 16: return &kc_solve<QUEUE, DERIVE, 16, LISTED>;
-    default: return &kc_solve<QUEUE, DERIVE, 0, LISTED>;
+    default: return &kc_solve<QUEUE, DERIVE, TURNS, LISTED>;
     }
 }
 

@@ -3,6 +3,7 @@
 #pragma once
 
 #include "candidate_eval.h"
+#include "cost_plan.h"
 #include "themis_internal.h"
 #include "wave_ops.h"
 
@@ -56,6 +57,7 @@ struct CostArgs : HotArgs {
     uint32_t parts, pair_magic;  // lanes per (model, batch size) pair of a sweep, see sweep()
     int32_t lanes, turns;  // lanes per model, and the batch sizes of each, see Front
     uint32_t lane_magic;   // index_magic() of them
+    int32_t round_log, per_round;  // see FrontLayout
     BatchConst bc[THEMIS_MAX_BATCH];
 };
 
@@ -2065,7 +2067,6 @@ __device__ __forceinline__ ArgsPtr kernel_args()
 namespace {
 
 typedef void (*CostKernel)(CostArgs);
-constexpr int WIDTH_PACKED = 1;  // see Front
 
 constexpr size_t LDS_PER_CU = 160 * 1024;
 constexpr int MAX_WINDOW = 8192;
@@ -2111,17 +2112,12 @@ inline CostArgs cost_args(const themis_problem_t& p, const Layout& L, const int3
         a.bc[j] = {(1.0 / (1.0e6 * b)) * (1.0 - 0x1p-45), 1.0e6 * (b - 1.0), (float)(1.0e6 * b),
                    (float)(b / (2.0 * b - 1.0)), p.batch_sizes[j]};
     }
-    while (1 << a.width_log < p.n_batch) ++a.width_log;
-    if (a.width_log < 2 && L.S <= 16) a.width_log = 2;
-    // Lanes per model: a power of two, or where that takes more turns (or doesn't fit) as many as
-    // there are batch sizes or all models leave room for (9 x 14: seven and two turns, not four
-    // and four).
-    while (L.S << a.width_log > 64) --a.width_log;
-    a.lanes = 1 << a.width_log;
-    const int fit = 64 / L.S < p.n_batch ? 64 / L.S : p.n_batch;
-    auto turns = [&](int lanes) { return (p.n_batch + lanes - 1) / lanes; };
-    if (turns(fit) < turns(a.lanes)) a.lanes = fit, a.width_log = -1;
-    a.turns = turns(a.lanes);
+    const FrontLayout front = front_layout(L.S, p.n_batch);
+    a.width_log = front.width_log;
+    a.lanes = front.lanes;
+    a.turns = front.turns;
+    a.round_log = front.round_log;
+    a.per_round = front.per_round;
     a.lane_magic = index_magic((uint32_t)a.lanes);
     a.S = L.S;
     a.cs = p.profile_form == THEMIS_PROFILE_EQ1 ? 6 : 5;
@@ -2203,8 +2199,7 @@ hipError_t launch_per_instance(const themis_problem_t& p, const Layout& L, CostA
     a.wave_words = waves > 1 ? (uint32_t)(lds_for(a.window) / sizeof(uint32_t)) : 0u;
     a.window_hbm = (fit < room ? fit : room) & ~63;
     // (at most 40 KB of LDS, which a kernel may have without asking)
-    const int width = a.turns > 1 ? 0 : a.width_log >= 2 ? 1 << a.width_log : WIDTH_PACKED;
-    const CostKernel k = kernel(width);
+    const CostKernel k = kernel(front_layout(L.S, p.n_batch).width);
     hipError_t e = hipSuccess;
     in_launches(grid, [&](int first, int count) {
         if (e != hipSuccess) return;

@@ -43,7 +43,8 @@ def every_call(T, oracle, w, r_most):
 
 
 # lanes per model 4, 8 and 16, the fewest and the most models and batch sizes that fit; pairs
-# that fit only without gaps; rounds of models with gaps, and without where that takes fewer
+# that fit only without gaps; more of them than lanes, in turns with gaps and without, and
+# (33 x 2) in rounds of models
 @pytest.mark.parametrize("S,n_batch", [
     (1, 1), (16, 4), (3, 3), (8, 8), (8, 5), (1, 16), (4, 16), (4, 9),
     (10, 6), (12, 5), (7, 9), (9, 7), (5, 12), (32, 2),
@@ -119,10 +120,11 @@ def test_products_beyond_42_bits(T, oracle, n_batch, queue):
     assert (want[0][large] == 0).any()
 
 
-# rounds of models with gaps and without, more than eight models
-@pytest.mark.parametrize("S,n_batch,c_max,queue", [(10, 10, 1, 0), (17, 5, 1, 0), (17, 5, 1, 2), (9, 9, 2, 0)])
+# turns without gaps, more than eight models; rounds of ten, seven and twelve models
+@pytest.mark.parametrize("S,n_batch,c_max,queue", [(10, 10, 1, 0), (17, 5, 1, 0), (17, 5, 1, 2), (9, 9, 2, 0),
+                                                   (33, 6, 1, 2), (23, 9, 1, 0), (33, 5, 1, 0)])
 def test_products_beyond_42_bits_in_rounds(T, oracle, S, n_batch, c_max, queue):
-    """Answers of every window at rates times objectives beyond 2^42, models in several rounds."""
+    """Answers of every window at rates times objectives beyond 2^42, with more pairs than lanes."""
     rng, n = np.random.default_rng([42, S, n_batch]), 300
     coef = wl._draw_coef(rng, (n, S), a=(1000, 40000), k=(100, 700), q=(0, 0), p=(1, c_max), o=(1, 2000))
     sizes = sorted({int(x) for x in np.rint(np.geomspace(2, 1024, n_batch))})
