@@ -101,7 +101,7 @@ __device__ __forceinline__ void stability_instance(ArgsPtr args, int i)
         args = Front<QUEUE, true, WIDTH>::afresh(args);
         if (stable) {
             wave_lds_fence();
-            const CostLds L = cost_lds(args->S, args->window);
+            const CostLds L = cost_lds(args->S, args->window, args->lds_words);
             // what put_row() made of the choices of both
             const bool same =
                 (int)threadIdx.x >= args->S || cost_smem[L.pin + threadIdx.x] == SAME;
@@ -126,7 +126,7 @@ __device__ __forceinline__ void stability_pair(ArgsPtr args, int i)
         __syncthreads();
     } else {
         {
-            const CostLds L = cost_lds(args->S, args->window);
+            const CostLds L = cost_lds(args->S, args->window, args->lds_words);
             uint32_t* const mine = cost_smem + args->wave_words;
             // (there is no choice of a solve before for put_row() to find)
             if (lane < (uint32_t)args->S) mine[L.pin + lane] = SAME;
@@ -137,7 +137,7 @@ __device__ __forceinline__ void stability_pair(ArgsPtr args, int i)
             status = solve_instance<QUEUE, true, WIDTH, SECOND>(args, i, args->lambda2, (int)lane,
                                                                 args->wave_words);
         args = Front<QUEUE, true, WIDTH>::afresh(args);
-        const CostLds L = cost_lds(args->S, args->window);
+        const CostLds L = cost_lds(args->S, args->window, args->lds_words);
         uint32_t* const mine = cost_smem + args->wave_words;
         wave_lds_fence();
         if (__builtin_amdgcn_readfirstlane((int)mine[L.words]) == 0) __syncthreads();
@@ -146,7 +146,7 @@ __device__ __forceinline__ void stability_pair(ArgsPtr args, int i)
     __syncthreads();
     if (later) return;
     args = Front<QUEUE, true, WIDTH>::afresh(args);
-    const CostLds L = cost_lds(args->S, args->window);
+    const CostLds L = cost_lds(args->S, args->window, args->lds_words);
     // what put_row() left of the choices of both
     const uint32_t *const first = cost_smem, *const second = cost_smem + args->wave_words;
     const bool same = !moves || lane >= (uint32_t)args->S || first[L.pin + lane] == second[L.pin + lane];

@@ -1,5 +1,5 @@
-// How the one-wavefront solve lies in lanes: host arithmetic that its launches follow
-// (cost_solver.h).
+// How the one-wavefront solve lies in lanes and in LDS: whole-number arithmetic that its launches
+// and its kernels follow (cost_solver.h).
 #pragma once
 
 namespace themis {
@@ -46,6 +46,95 @@ inline FrontLayout front_layout(int S, int n_batch)
     else
         f.width = f.width_log >= 2 ? 1 << f.width_log : WIDTH_PACKED;
     return f;
+}
+
+// LDS words of one wavefront, of which there are `words` (at least `least`).  From `tab` on, steps
+// B and C take a table of up to 64 words per model and S + 1 rows: of eight 32-bit cells behind as
+// many guard cells, of sixteen without, or of 64 16-bit cells (see StepCLds); wider windows a
+// table of one model and 16-bit rows with a guard cell (and one of padding) in front of each;
+// step G lists as long as there are words.
+struct CostLds {
+    int best, key, fast, pin, tab, rows, least, words;
+};
+// Step C: rows of 32 words, the last one that of nothing left to run; a model's latencies at
+// even and at odd costs, 32 words each; a copy of the row at hand behind 32 guard words.  Of
+// pipelines of many models a compute unit has room for few wavefronts, so the latencies go
+// where nothing is meanwhile: those at even costs in the last row, which is filled when the
+// rows are complete, those at odd ones (from 16 models on) in the words of the best candidates,
+// which steps A and G use.  (With words of their own for both, twice over, 7000 x 56 models with
+// three batch sizes took 38.1 us and take 33.8, six wavefronts of a compute unit and seven;
+// 20000 x 14 50.6 and 48.8, 20000 x 20 80.8 and 78.2.)
+struct StepCLds {
+    int rows, even, odd, copy, words;
+};
+constexpr StepCLds step_c_lds(int S, int tab)
+{
+    StepCLds c{};
+    c.rows = tab + 64 * S;
+    c.even = c.rows + 32 * S;
+    const int behind = c.even + 32;
+    c.odd = S >= 16 ? 0 : behind;
+    c.copy = (S >= 16 ? behind : behind + 32) + 32;
+    c.words = c.copy + 32;
+    return c;
+}
+constexpr CostLds cost_lds(int S, int window, int words = 0)
+{
+    CostLds l{};
+    l.best = 0;  // two words per model
+    l.key = 2 * S;
+    l.fast = l.key + S;
+    l.pin = l.fast + S;
+    l.tab = (l.pin + S + 3) & ~3;
+    l.rows = l.tab + window;
+    const int w = l.rows + (S + 1) * (window + 2) / 2;
+    const int b = l.tab + 64 * S + 8 + 16 * (S + 1), c = step_c_lds(S, l.tab).words;
+    l.least = ((w > b ? w > c ? w : c : b > c ? b : c) + 3) & ~3;
+    l.words = words;
+    return l;
+}
+
+// A launch's window (cells of the largest one with rows in LDS) and LDS.
+constexpr int LDS_PER_CU = 160 * 1024, LDS_UNIT = 1280;  // bytes; LDS is granted in whole units
+constexpr int MAX_WINDOW = 8192;
+// Wavefronts whose LDS a compute unit has room for.  Registers allow 32, but some twenty
+// are in flight on average, and the room of the others lets step G list more candidates
+// (measured while it could only list all of them: at 16384 x 8 with a twelfth of the
+// objectives 32 / 28 / 24 / 20 took 579 / 122 / 121 / 129 us, at 86400 x 6 51 / 51 / 55 / 60).
+// As LDS is granted in units, what 28 leave each other is five of these at up to eleven models,
+// and 25 wavefronts are resident.
+constexpr int RESIDENT_PER_CU = 28, SIMDS_PER_CU = 4;
+struct LdsPlan {
+    int window, words;  // words: of one wavefront, and WAVE_FLAGS behind them where there are two
+    int bytes;          // of a workgroup
+};
+constexpr int WAVE_FLAGS = 4;
+// groups: workgroups of the launch, of `waves` wavefronts; spread: of a pipeline's costs
+inline LdsPlan lds_plan(int S, int spread, int groups, int waves, int cus)
+{
+    const int flags = waves > 1 ? WAVE_FLAGS : 0;
+    // The largest window that leaves the wavefronts that can be resident their LDS, no
+    // larger than the costs of a pipeline can spread.  With room for just the mean of a compute
+    // unit, the last ones wait until one of their unit's ends, as they are not dealt out evenly:
+    // a quarter more (3001 x 7, twelve of a unit: 12.75 us without, 11.84 with it or with half).
+    int per_cu = (int)(((long long)groups * waves + cus - 1) / cus);
+    per_cu += (per_cu + 3) / 4;
+    per_cu = per_cu < 4 ? 4 : per_cu > RESIDENT_PER_CU ? RESIDENT_PER_CU : per_cu;
+    auto words_for = [&](int window) { return cost_lds(S, window).least + flags; };
+    LdsPlan p{};
+    p.window = 64;
+    while (p.window + 64 <= MAX_WINDOW && p.window < spread && 4 * words_for(p.window + 64) <= LDS_PER_CU / per_cu)
+        p.window += 64;
+    p.words = words_for(p.window) - flags;
+    if (p.window == 64) {
+        // the least there is to have: what no further workgroup of the compute unit could have
+        // is there for the lists (stability test of 4096 x 16 models 56.6 us without, 43.1 with it)
+        const int needed = (4 * waves * words_for(64) + LDS_UNIT - 1) / LDS_UNIT;
+        const int all = LDS_PER_CU / LDS_UNIT, units = all / (all / needed);
+        p.words = (units * LDS_UNIT / 4 / waves & ~3) - flags;
+    }
+    p.bytes = 4 * waves * (p.words + flags);
+    return p;
 }
 
 }  // namespace themis

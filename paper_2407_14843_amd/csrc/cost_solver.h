@@ -53,6 +53,7 @@ struct CostArgs : HotArgs {
     int32_t hrow_stride;  // cells of hrow per instance
     int32_t row_stride;
     int32_t window_hbm;   // like `window`, in HBM (no larger than the other: none)
+    int32_t lds_words;    // of one wavefront, see CostLds
     uint32_t wave_words;  // LDS words of each wavefront of a workgroup (0: there is one)
     uint32_t parts, pair_magic;  // lanes per (model, batch size) pair of a sweep, see sweep()
     int32_t lanes, turns;  // lanes per model, and the batch sizes of each, see Front
@@ -60,30 +61,6 @@ struct CostArgs : HotArgs {
     int32_t round_log, per_round;  // see FrontLayout
     BatchConst bc[THEMIS_MAX_BATCH];
 };
-
-// LDS words of one wavefront.  From `tab` on, steps B and C take a table of up to 64 words
-// per model and S + 1 rows: of eight 32-bit cells behind as many guard cells, of sixteen
-// without, or of 64 16-bit cells, behind which step C has its entries twice, a second copy of
-// the row at hand and that copy's guard cells; wider windows a table of one model and 16-bit
-// rows with a guard cell (and one of padding) in front of each.
-constexpr int STEP_C_WORDS = 2 * 64 + 32 + 33;
-struct CostLds {
-    int best, key, fast, pin, tab, rows, words;
-};
-__host__ __device__ inline CostLds cost_lds(int S, int window)
-{
-    CostLds l;
-    l.best = 0;  // two words per model
-    l.key = 2 * S;
-    l.fast = l.key + S;
-    l.pin = l.fast + S;
-    l.tab = (l.pin + S + 3) & ~3;
-    l.rows = l.tab + window;
-    const int w = l.rows + (S + 1) * (window + 2) / 2;
-    const int b = l.tab + 64 * S + 8 + 16 * (S + 1), c = l.tab + 64 * S + 32 * (S + 1) + STEP_C_WORDS;
-    l.words = ((w > b ? w > c ? w : c : b > c ? b : c) + 3) & ~3;
-    return l;
-}
 
 // lo <= v <= hi, 0 <= lo
 __device__ __forceinline__ bool in_range(int32_t v, int32_t lo, int32_t hi)
@@ -167,7 +144,7 @@ struct Solver {
 
     // `offset`: of the wavefront's words
     __device__ __forceinline__ explicit Solver(ArgsPtr p, int l = (int)threadIdx.x, uint32_t offset = 0u)
-        : args(p), a(hot_args(p)), lds(cost_smem + offset), L(cost_lds(p->S, p->window)), lane(l)
+        : args(p), a(hot_args(p)), lds(cost_smem + offset), L(cost_lds(p->S, p->window, p->lds_words)), lane(l)
     {
     }
     // (out of line, where a workgroup may have several wavefronts)
@@ -1541,17 +1518,16 @@ struct Solver {
         typedef uint16_t pair __attribute__((ext_vector_type(2)));
         constexpr uint32_t NONE = 0xFFFFu, BOTH = 0xFFFFFFFFu;
         const uint32_t* const tab = lds + L.tab;
+        const StepCLds at = step_c_lds(a.S, L.tab);
         // 32 words per model; row s is "none" for the model before it until it is formed
-        uint32_t* const rows = lds + L.tab + 64 * a.S;
+        uint32_t* const rows = lds + at.rows;
         uint16_t* const cells = reinterpret_cast<uint16_t*>(rows);
-        uint32_t* const entries = rows + 32 * (a.S + 1);  // even costs, odd costs; twice
-        uint32_t* const odd = entries + 2 * 64 + 32;      // behind its guard cells
+        uint32_t* const odd = lds + at.copy;
         const bool upper = lane >= 32;
         const int m = lane & 31;
         for (int x = lane; x < 8 * (a.S - 1); x += 64)
             reinterpret_cast<four*>(rows)[x] = four{BOTH, BOTH, BOTH, BOTH};
         odd[m - 32] = BOTH;
-        rows[32 * a.S + m] = 0u;  // nothing left to run
         const uint32_t my_fast = lane < a.S ? fastest()[lane] >> 15 : 0u;
         auto latency = [](uint32_t e) { return least(e >> INDEX_BITS, NONE); };
         auto pair_of = [](uint32_t x) { return __builtin_bit_cast(pair, x); };
@@ -1569,12 +1545,13 @@ struct Solver {
             rows[place + step * s] = __builtin_amdgcn_perm(w, from_lane_below(w, 0u), shift);
         };
         // a model's latencies, each in both halves of its word
-        uint32_t* const my_entry = entries + 32 * (lane & 1) + (lane >> 1);
-        auto enter = [&](int s, uint32_t lt) { my_entry[64 * (s & 1)] = lt << 16 | lt; };
+        uint32_t* const my_entry = lds + (lane & 1 ? at.odd : at.even) + (lane >> 1);
+        auto enter = [&](uint32_t lt) { *my_entry = lt << 16 | lt; };
+        const four* const ent = reinterpret_cast<const four*>(lds + (upper ? at.odd : at.even));
         // the last model: the least of what costs no more
         cells[(a.S - 1) * 64 + lane] = (uint16_t)wave_scan<true>(latency(tab[(a.S - 1) * 64 + lane]));
         uint32_t lt = latency(tab[(a.S > 1 ? a.S - 2 : 0) * 64 + lane]);
-        enter(a.S - 2, lt);
+        enter(lt);
         wave_lds_fence();
         put_words(a.S - 1, rows[32 * (a.S - 1) + m]);
         wave_lds_fence();
@@ -1584,7 +1561,6 @@ struct Solver {
             int last = place + step * (s + 1) - 31;
             asm("" : "+v"(last));
             const uint32_t* const from = rows + last;
-            const four* const ent = reinterpret_cast<const four*>(entries + 64 * (s & 1)) + (upper ? 8 : 0);
             const uint32_t next = tab[(s > 0 ? s - 1 : 0) * 64 + lane];
             // nothing dearer than the fastest candidate is of use
             const uint32_t fast = (uint32_t)__ballot(lt <= lane_value(my_fast, s));
@@ -1608,9 +1584,11 @@ struct Solver {
             lt = latency(next);
             wave_lds_fence();
             put_words(s, faster(h[0], h[1]));
-            enter(s - 1, lt);
+            enter(lt);
             wave_lds_fence();
         }
+        rows[32 * a.S + m] = 0u;  // nothing left to run
+        wave_lds_fence();
         const uint32_t g = cells[lane];
         const unsigned long long within = __ballot(g <= (uint32_t)T);
         if (within == 0ull) return UNFINISHED;
@@ -2068,14 +2046,6 @@ namespace {
 
 typedef void (*CostKernel)(CostArgs);
 
-constexpr size_t LDS_PER_CU = 160 * 1024;
-constexpr int MAX_WINDOW = 8192;
-// Wavefronts whose LDS a compute unit has room for.  Registers allow 32, but some twenty
-// are in flight on average, and the room of the others lets step G list more candidates
-// (measured while it could only list all of them: at 16384 x 8 with a twelfth of the
-// objectives 32 / 28 / 24 / 20 took 579 / 122 / 121 / 129 us, at 86400 x 6 51 / 51 / 55 / 60).
-constexpr int RESIDENT_PER_CU = 28, SIMDS_PER_CU = 4;
-
 // What does not depend on the entry point.
 inline CostArgs cost_args(const themis_problem_t& p, const Layout& L, const int32_t* d_coef,
                           const int32_t* d_lambda, const int32_t* d_slo_us,
@@ -2177,27 +2147,14 @@ hipError_t launch_per_instance(const themis_problem_t& p, const Layout& L, CostA
 {
     const int cus = compute_units();
     const int grid = listed && L.N > RESIDENT_PER_CU * cus ? RESIDENT_PER_CU * cus : L.N;
-    // The largest window that leaves the wavefronts that can be resident their LDS, no
-    // larger than the costs of a pipeline can spread.  With room for just the mean of a compute
-    // unit, the last ones wait until one of their unit's ends, as they are not dealt out evenly:
-    // a quarter more (3001 x 7, twelve of a unit: 12.75 us without, 11.84 with it or with half).
-    int per_cu = (int)(((long long)grid * waves + cus - 1) / cus);
-    per_cu += (per_cu + 3) / 4;
-    per_cu = per_cu < 4 ? 4 : per_cu > RESIDENT_PER_CU ? RESIDENT_PER_CU : per_cu;
-    auto lds_for = [&](int window) {
-        return (size_t)(cost_lds(L.S, window).words + (waves > 1 ? 4 : 0)) * sizeof(uint32_t);
-    };
-    const int spread = L.S * p.r_max * p.c_max;
-    a.window = 64;
-    while (a.window + 64 <= MAX_WINDOW && a.window < spread &&
-           lds_for(a.window + 64) <= LDS_PER_CU / per_cu)
-        a.window += 64;
+    const LdsPlan lds = lds_plan(L.S, L.S * p.r_max * p.c_max, grid, waves, cus);
+    a.window = lds.window;
+    a.lds_words = lds.words;
     // rows in HBM: S + 1 of them, and the table of a model still in LDS
-    const CostLds lds = cost_lds(L.S, a.window);
     const int fit = a.hrow_stride / (L.S + 1) - 2;
-    const int room = lds.words - lds.tab;
-    a.wave_words = waves > 1 ? (uint32_t)(lds_for(a.window) / sizeof(uint32_t)) : 0u;
+    const int room = lds.words - cost_lds(L.S, a.window).tab;
     a.window_hbm = (fit < room ? fit : room) & ~63;
+    a.wave_words = waves > 1 ? (uint32_t)(lds.words + WAVE_FLAGS) : 0u;
     // (at most 40 KB of LDS, which a kernel may have without asking)
     const CostKernel k = kernel(front_layout(L.S, p.n_batch).width);
     hipError_t e = hipSuccess;
@@ -2205,9 +2162,9 @@ hipError_t launch_per_instance(const themis_problem_t& p, const Layout& L, CostA
         if (e != hipSuccess) return;
         const dim3 groups((unsigned)count), lanes(64 * waves);
         if (first == 0)
-            hipLaunchKernelGGL(k, groups, lanes, waves * lds_for(a.window), st, a);
+            hipLaunchKernelGGL(k, groups, lanes, lds.bytes, st, a);
         else
-            hipLaunchKernelGGL(k, groups, lanes, waves * lds_for(a.window), st, past(a, (size_t)first));
+            hipLaunchKernelGGL(k, groups, lanes, lds.bytes, st, past(a, (size_t)first));
         e = hipGetLastError();
     });
     return e;

@@ -1,9 +1,13 @@
-// Host-side check of how the one-wavefront solve lies in lanes.  Built and run by
+// Host-side check of how the one-wavefront solve lies in lanes and in LDS.  Built and run by
 // tests/test_host_plan.py (no GPU needed).  The properties are stated from what the kernels do
 // with the layout, not from the formulas under test:
 //   every (model, batch size) pair is taken once, by a lane of the wavefront;
 //   where there are more pairs than lanes, no more of them one after the other than whole
-//   models side by side would take, with or without gaps between them.
+//   models side by side would take, with or without gaps between them;
+//   what step C has in LDS at one time lies apart and inside the wavefront's words, and takes
+//   no more of them than its table, rows and the copy of one, or below 16 models 32 more;
+//   the lists of step G have room for fourteen candidates of a model;
+//   a launch asks for what its wavefronts have, and no compute unit has fewer of them for it.
 #include <cstdio>
 #include <vector>
 
@@ -69,8 +73,50 @@ static void check_lanes(int S, int nb)
     CHECK(f.lanes >= 1 && f.turns * f.lanes >= nb && S * f.lanes <= 64, "%d x %d", S, nb);
 }
 
+static void check_step_c(int S)
+{
+    const CostLds l = cost_lds(S, 64);
+    const int least = l.least;
+    const StepCLds c = step_c_lds(S, l.tab);
+    std::vector<int> owner(least + 64, 0);
+    auto own = [&](int first, int words) {
+        CHECK(first >= 0 && first + words <= least, "%d models: %d words from %d of %d", S, words, first, least);
+        for (int x = first; x < first + words && x < (int)owner.size(); ++x) CHECK(++owner[x] == 1, "%d models: word %d", S, x);
+    };
+    own(l.key, S), own(l.fast, S), own(l.pin, S);
+    own(l.tab, 64 * S);
+    own(c.rows, 32 * S);
+    own(c.even, 32), own(c.odd, 32);
+    own(c.copy - 32, 64);
+    // read four words at a time
+    CHECK(c.rows % 4 == 0 && c.even % 4 == 0 && c.odd % 4 == 0 && least % 4 == 0, "%d models", S);
+    // the row of nothing left to run is behind the others, and nothing else is in it by then
+    CHECK(c.rows + 32 * S + 32 <= least && (c.odd < c.rows || c.odd >= c.rows + 32 * (S + 1)), "%d models", S);
+    CHECK(least <= l.tab + 64 * S + 32 * (S + 1) + 64 + (S < 16 ? 32 : 0), "%d models: %d words", S, least);
+}
+
+static void check_launch(int S, int spread, int groups, int waves)
+{
+    const LdsPlan p = lds_plan(S, spread, groups, waves, 256);
+    const CostLds l = cost_lds(S, p.window);
+    const int flags = waves > 1 ? WAVE_FLAGS : 0, all = 4 * waves * (p.words + flags);
+    CHECK(p.window >= 64 && p.window % 64 == 0, "%d models, %d groups", S, groups);
+    CHECK(p.words >= l.least && (p.words + flags) % 4 == 0, "%d models, %d groups", S, groups);
+    CHECK(p.words - l.tab - 67 * S - 2 >= 2 * 14 * S, "%d models, %d groups: %d words", S, groups, p.words);
+    CHECK(all == p.bytes, "%d models, %d groups: %d of %d", S, groups, all, p.bytes);
+    // no fewer workgroups of a compute unit than with the least (LDS is granted by 1280 bytes)
+    auto resident = [](int bytes) { return 128 / ((bytes + 1279) / 1280); };
+    CHECK(resident(p.bytes) == resident(4 * waves * (l.least + flags)), "%d models, %d groups", S, groups);
+    CHECK(p.bytes <= 160 * 1024, "%d models, %d groups", S, groups);
+}
+
 int main()
 {
+    for (int S = 1; S <= 64; ++S)
+        for (int waves = 1; waves <= 2; ++waves)
+            for (int groups : {1, 255, 256, 257, 512, 1024, 3001, 4099, 7168, 86400})
+                for (int spread : {1, 100, 32767}) check_launch(S, spread, groups, waves);
+    for (int S = 1; S <= 64; ++S) check_step_c(S);
     for (int S = 1; S <= 64; ++S)
         for (int nb = 1; nb <= 16; ++nb) check_lanes(S, nb);
     if (failures) {

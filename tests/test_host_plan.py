@@ -1,4 +1,4 @@
-"""How the one-wavefront solve lies in lanes (csrc/cost_plan.h), by a small host program,
+"""How the one-wavefront solve lies in lanes and in LDS (csrc/cost_plan.h), by a small host program,
 tests/host/plan_check.cpp: whole numbers, no GPU."""
 
 import os
