@@ -221,6 +221,8 @@ hipError_t launch_cost_fallback(const themis_problem_t& p, const Layout& L, cons
     });
 }
 
+constexpr int PAIRS_PER_CU = 28;
+
 hipError_t launch_cost_stability(const themis_problem_t& p, const Layout& L,
                                  const StabilityLayout& B, const int32_t* d_coef,
                                  const int32_t* d_lambda_now, const int32_t* d_lambda_pred,
@@ -241,7 +243,7 @@ hipError_t launch_cost_stability(const themis_problem_t& p, const Layout& L,
     // the first finds nothing, so with more instances than that it depends on what they are:
     // 4099 x 5 16.3 -> 11.8 us, 145 x 8 16.8 -> 9.7; 15061 x 4 48.8 -> 40.3, but 9782 x 2
     // 9.4 -> 10.0 and 32841 x 3 24.5 -> 30.4; 6434 x 1 7.45 -> 7.62.
-    const bool two = L.S > 1 && L.N <= RESIDENT_PER_CU * compute_units();
+    const bool two = L.S > 1 && L.N <= PAIRS_PER_CU * compute_units();
     return launch_per_instance(p, L, a, st, false, [&](int width) {
         switch (p.queue_model) {
         case THEMIS_QUEUE_SHARED: return stability_kernel<THEMIS_QUEUE_SHARED>(width, two);

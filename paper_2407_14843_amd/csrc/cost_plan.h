@@ -97,13 +97,12 @@ constexpr CostLds cost_lds(int S, int window, int words = 0)
 // A launch's window (cells of the largest one with rows in LDS) and LDS.
 constexpr int LDS_PER_CU = 160 * 1024, LDS_UNIT = 1280;  // bytes; LDS is granted in whole units
 constexpr int MAX_WINDOW = 8192;
-// Wavefronts whose LDS a compute unit has room for.  Registers allow 32, but some twenty
-// are in flight on average, and the room of the others lets step G list more candidates
-// (measured while it could only list all of them: at 16384 x 8 with a twelfth of the
-// objectives 32 / 28 / 24 / 20 took 579 / 122 / 121 / 129 us, at 86400 x 6 51 / 51 / 55 / 60).
-// As LDS is granted in units, what 28 leave each other is five of these at up to eleven models,
-// and 25 wavefronts are resident.
-constexpr int RESIDENT_PER_CU = 28, SIMDS_PER_CU = 4;
+// Wavefronts of a compute unit that share its LDS, and how many of them are resident then, as
+// what 28 leave each other is five units.  Registers allow 32, but some twenty are in flight on
+// average, and the room of the others lets step G list more candidates (measured while it
+// could only list all of them: at 16384 x 8 with a twelfth of the objectives 32 / 28 / 24 / 20
+// took 579 / 122 / 121 / 129 us, at 86400 x 6 51 / 51 / 55 / 60).
+constexpr int SHARED_PER_CU = 28, RESIDENT_PER_CU = 25, SIMDS_PER_CU = 4;
 struct LdsPlan {
     int window, words;  // words: of one wavefront, and WAVE_FLAGS behind them where there are two
     int bytes;          // of a workgroup
@@ -113,26 +112,34 @@ constexpr int WAVE_FLAGS = 4;
 inline LdsPlan lds_plan(int S, int spread, int groups, int waves, int cus)
 {
     const int flags = waves > 1 ? WAVE_FLAGS : 0;
-    // The largest window that leaves the wavefronts that can be resident their LDS, no
-    // larger than the costs of a pipeline can spread.  With room for just the mean of a compute
-    // unit, the last ones wait until one of their unit's ends, as they are not dealt out evenly:
-    // a quarter more (3001 x 7, twelve of a unit: 12.75 us without, 11.84 with it or with half).
-    int per_cu = (int)(((long long)groups * waves + cus - 1) / cus);
-    per_cu += (per_cu + 3) / 4;
-    per_cu = per_cu < 4 ? 4 : per_cu > RESIDENT_PER_CU ? RESIDENT_PER_CU : per_cu;
-    auto words_for = [&](int window) { return cost_lds(S, window).least + flags; };
+    auto bytes_for = [&](int window) { return 4 * waves * (cost_lds(S, window).least + flags); };
+    // what leaves room for as many workgroups
+    auto filled = [](int bytes) {
+        const int units = (bytes + LDS_UNIT - 1) / LDS_UNIT, all = LDS_PER_CU / LDS_UNIT;
+        return all / (all / units) * LDS_UNIT;
+    };
+    // Where all workgroups can be resident, what those of a compute unit leave each other in
+    // whole units, all of it: of a quotient of bytes the last unit is granted too, and the
+    // compute unit has one workgroup fewer, that waits until another ends (3001 x 7 models,
+    // twelve and room for eleven: 12.75 us, with room 11.84).  With a quarter more of them to be on
+    // the safe side the lists of step G run out of words: 5000 x 7 models, 256 candidates each,
+    // 126 us, 92 without.
+    const int per_cu = (groups + cus - 1) / cus, few = 4 / waves, most = SHARED_PER_CU / waves;
+    const bool all = per_cu <= RESIDENT_PER_CU / waves;
+    int bytes = all ? LDS_PER_CU / LDS_UNIT / (per_cu < few ? few : per_cu) * LDS_UNIT
+                    : LDS_PER_CU / (per_cu > most ? most : per_cu);
+    // (the least there is to have, and what no further workgroup could have: stability test of
+    // 4096 x 16 models 56.6 us without that, 43.1 with it)
+    const int least = filled(bytes_for(64));
+    const bool tight = bytes < bytes_for(64);
+    if (tight) bytes = least;
     LdsPlan p{};
     p.window = 64;
-    while (p.window + 64 <= MAX_WINDOW && p.window < spread && 4 * words_for(p.window + 64) <= LDS_PER_CU / per_cu)
-        p.window += 64;
-    p.words = words_for(p.window) - flags;
-    if (p.window == 64) {
-        // the least there is to have: what no further workgroup of the compute unit could have
-        // is there for the lists (stability test of 4096 x 16 models 56.6 us without, 43.1 with it)
-        const int needed = (4 * waves * words_for(64) + LDS_UNIT - 1) / LDS_UNIT;
-        const int all = LDS_PER_CU / LDS_UNIT, units = all / (all / needed);
-        p.words = (units * LDS_UNIT / 4 / waves & ~3) - flags;
-    }
+    while (p.window + 64 <= MAX_WINDOW && p.window < spread && bytes_for(p.window + 64) <= bytes) p.window += 64;
+    if (!all && !tight) bytes = p.window > 64 ? bytes_for(p.window) : least;
+    // no more than the costs of a pipeline can spread over need
+    if (p.window >= spread && filled(bytes_for(p.window)) < bytes) bytes = filled(bytes_for(p.window));
+    p.words = (bytes / 4 / waves & ~3) - flags;
     p.bytes = 4 * waves * (p.words + flags);
     return p;
 }

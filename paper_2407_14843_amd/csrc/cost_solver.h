@@ -2146,7 +2146,7 @@ hipError_t launch_per_instance(const themis_problem_t& p, const Layout& L, CostA
                                hipStream_t st, bool listed, K kernel, int waves = 1)
 {
     const int cus = compute_units();
-    const int grid = listed && L.N > RESIDENT_PER_CU * cus ? RESIDENT_PER_CU * cus : L.N;
+    const int grid = listed && L.N > SHARED_PER_CU * cus ? SHARED_PER_CU * cus : L.N;
     const LdsPlan lds = lds_plan(L.S, L.S * p.r_max * p.c_max, grid, waves, cus);
     a.window = lds.window;
     a.lds_words = lds.words;

@@ -7,7 +7,8 @@
 //   what step C has in LDS at one time lies apart and inside the wavefront's words, and takes
 //   no more of them than its table, rows and the copy of one, or below 16 models 32 more;
 //   the lists of step G have room for fourteen candidates of a model;
-//   a launch asks for what its wavefronts have, and no compute unit has fewer of them for it.
+//   a launch asks for what its wavefronts have, with room for those that a compute unit has at a
+//   time, and for all of what that leaves each of them.
 #include <cstdio>
 #include <vector>
 
@@ -104,9 +105,22 @@ static void check_launch(int S, int spread, int groups, int waves)
     CHECK(p.words >= l.least && (p.words + flags) % 4 == 0, "%d models, %d groups", S, groups);
     CHECK(p.words - l.tab - 67 * S - 2 >= 2 * 14 * S, "%d models, %d groups: %d words", S, groups, p.words);
     CHECK(all == p.bytes, "%d models, %d groups: %d of %d", S, groups, all, p.bytes);
-    // no fewer workgroups of a compute unit than with the least (LDS is granted by 1280 bytes)
+    // A compute unit has room for the workgroups that it has at a time, or, if that is less, for
+    // as many as with the least request (LDS is granted by 1280 bytes).
     auto resident = [](int bytes) { return 128 / ((bytes + 1279) / 1280); };
-    CHECK(resident(p.bytes) == resident(4 * waves * (l.least + flags)), "%d models, %d groups", S, groups);
+    const int mean = (groups + 255) / 256, most = 25 / waves;
+    const int wanted = mean < 4 / waves ? 4 / waves : mean > most ? most : mean;
+    const int by_least = resident(4 * waves * (cost_lds(S, 64).least + flags));
+    const int room = wanted < by_least ? wanted : by_least;
+    CHECK(resident(p.bytes) >= room, "%d models, %d groups of %d: %d for %d", S, groups, waves, resident(p.bytes), room);
+    // and, where all can be resident and the window doesn't hold all that a pipeline's costs
+    // can spread over, what is granted is in use, and no more could be
+    if (p.window < spread && mean <= most) {
+        const int granted = 128 / resident(p.bytes) * 1280;
+        CHECK(granted - p.bytes < 16 * waves, "%d models, %d groups of %d: %d of %d", S, groups, waves, p.bytes, granted);
+        CHECK(resident(granted + 1280) < room || resident(p.bytes) == by_least, "%d models, %d groups of %d: %d",
+              S, groups, waves, p.bytes);
+    }
     CHECK(p.bytes <= 160 * 1024, "%d models, %d groups", S, groups);
 }
 
