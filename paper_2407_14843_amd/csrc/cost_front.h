@@ -632,8 +632,14 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
     {
         Best mine{EMPTY, EMPTY, 0u, 1u, EMPTY, 0, false};
         uint32_t ticks = 0u, base_sum;
+        bool vain = false;  // (asked ahead of each of several pairs)
+        auto go_on = [&] {
+            vain = vain || this->in_vain();
+            return !vain;
+        };
         if constexpr (WIDTH == ROUNDS) {
             for_pairs(first, [&](const Pair& p) {
+                if (!go_on()) return;
                 const Best b = best_of<SMALL>(p);
                 ticks += sum_of_models(p, b.key == EMPTY ? LT_NONE : b.key & 0x7FFFu);
                 if (leads(p)) {
@@ -645,7 +651,9 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
             if constexpr (ONE) {
                 mine = best_of<SMALL>(first);
             } else {
-                for_pairs<DERIVE>(first, [&](const Pair& p) { improve<SMALL>(mine, p); });
+                for_pairs<DERIVE>(first, [&](const Pair& p) {
+                    if (go_on()) improve<SMALL>(mine, p);
+                });
                 mine.key = model_least(first, mine.own);
                 const uint32_t k = mine.own == mine.key ? mine.k : EMPTY;
                 mine.k = model_least(first, k);
@@ -653,7 +661,7 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
             }
             ticks = sum_of_models(first, mine.key == EMPTY ? LT_NONE : mine.key & 0x7FFFu);
         }
-        if (ticks >= LT_NONE) return THEMIS_INFEASIBLE;
+        if (ticks >= LT_NONE || vain) return THEMIS_INFEASIBLE;
         if constexpr (WIDTH == ROUNDS) {
             // from here on lane s has what was found about model s
             wave_lds_fence();
@@ -672,10 +680,12 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
                 this->put_row(mine.mine, first.s, mine.c, ONE ? first.size : mine.size, mine.k, mine.key >> 15);
             return THEMIS_SOLVED;
         }
+        const uint32_t word = this->vain_word();
         const bool one = this->one_each();
         uint32_t fast = 0u, least_ticks = 0u;
         if constexpr (WIDTH == ROUNDS) {
             for_pairs(first, [&](const Pair& p) {
+                if (!go_on()) return;
                 const uint32_t f = model_least(p, turned(p, meet<SMALL>(p, p.last)));
                 least_ticks += sum_of_models(p, f >> 15);
                 if (leads(p)) this->fastest()[p.s] = f;
@@ -691,7 +701,7 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
             least_ticks = sum_of_models(first, fast >> 15);
             if (leads(first)) this->fastest()[first.s] = fast, this->keys()[first.s] = mine.key;
         }
-        if (least_ticks > (uint32_t)T) return THEMIS_INFEASIBLE;
+        if (least_ticks > (uint32_t)T || vain || this->in_vain(word)) return THEMIS_INFEASIBLE;
         const int reach = reach_of(ticks, least_ticks, one, [&] {
             return (WIDTH == ROUNDS ? this->sum_models(fast & 0x7FFFu) : sum_of_models(first, fast & 0x7FFFu)) -
                    base_sum;
@@ -704,6 +714,7 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
             if (status != UNFINISHED) return status;
             wave_lds_fence();
         }
+        if (this->in_vain()) return THEMIS_INFEASIBLE;
         if (reach <= 16) {
             if (!one) fill<SMALL>(first, mine, 16, 16);
             const int status = this->solve_sixteen(base_sum, one ? 64 : 16);

@@ -123,6 +123,14 @@ __device__ __forceinline__ void stability_pair(ArgsPtr args, int i)
     int status = THEMIS_SOLVED;
     if (!later) {
         status = solve_instance<QUEUE, true, WIDTH, PLAIN>(args, i, args->lambda, (int)lane);
+        if (status != THEMIS_SOLVED) {
+            // (where that is before the other one has made its words ready, it isn't told)
+            args = Front<QUEUE, true, WIDTH>::afresh(args);
+            const CostLds L = cost_lds(args->S, args->window, args->lds_words);
+            if (lane == 0u)
+                __hip_atomic_store(cost_smem + args->wave_words + L.words + 1, 1u, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
         __syncthreads();
     } else {
         {
@@ -130,7 +138,7 @@ __device__ __forceinline__ void stability_pair(ArgsPtr args, int i)
             uint32_t* const mine = cost_smem + args->wave_words;
             // (there is no choice of a solve before for put_row() to find)
             if (lane < (uint32_t)args->S) mine[L.pin + lane] = SAME;
-            if (lane == 0u) mine[L.words] = 0u;
+            if (lane < 2u) mine[L.words + lane] = 0u;
             wave_lds_fence();
         }
         if (moves)
@@ -221,8 +229,6 @@ hipError_t launch_cost_fallback(const themis_problem_t& p, const Layout& L, cons
     });
 }
 
-constexpr int PAIRS_PER_CU = 28;
-
 hipError_t launch_cost_stability(const themis_problem_t& p, const Layout& L,
                                  const StabilityLayout& B, const int32_t* d_coef,
                                  const int32_t* d_lambda_now, const int32_t* d_lambda_pred,
@@ -238,12 +244,7 @@ hipError_t launch_cost_stability(const themis_problem_t& p, const Layout& L,
     a.cost2 = (int32_t*)(ws + B.cost_off);
     a.ticks2 = (int32_t*)(ws + B.ticks_off);
     a.cfg2 = (int32_t*)(ws + B.cfg_off);
-    // Two wavefronts for an instance halve its chain, where all are in flight at once and there
-    // is one (a single model is done with step A).  The second one's solve is in vain where
-    // the first finds nothing, so with more instances than that it depends on what they are:
-    // 4099 x 5 16.3 -> 11.8 us, 145 x 8 16.8 -> 9.7; 15061 x 4 48.8 -> 40.3, but 9782 x 2
-    // 9.4 -> 10.0 and 32841 x 3 24.5 -> 30.4; 6434 x 1 7.45 -> 7.62.
-    const bool two = L.S > 1 && L.N <= PAIRS_PER_CU * compute_units();
+    const bool two = stability_in_pairs(L.S, L.N, compute_units());
     return launch_per_instance(p, L, a, st, false, [&](int width) {
         switch (p.queue_model) {
         case THEMIS_QUEUE_SHARED: return stability_kernel<THEMIS_QUEUE_SHARED>(width, two);

@@ -1922,6 +1922,20 @@ struct Solver {
         return status == UNFINISHED ? out_of_line<PART_LIST>() : status;
     }
 
+    // Whether the first of an instance's two wavefronts has found that there is no solution, and
+    // what the second one is still about to find is not asked for: the second word behind its
+    // others.  It looks between its steps (vain_word() ahead of one, in_vain() of it behind).
+    __device__ __forceinline__ uint32_t vain_word() const
+    {
+        if (ROLE != SECOND || !args->wave_words) return 0u;
+        return __hip_atomic_load(lds + L.words + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __device__ __forceinline__ bool in_vain(uint32_t word) const
+    {
+        return ROLE == SECOND && __builtin_amdgcn_readfirstlane((int)word) != 0;
+    }
+    __device__ __forceinline__ bool in_vain() const { return in_vain(vain_word()); }
+
     // Rows in HBM are the instance's.  Where both of its solves have a wavefront, the second one
     // waits with them until the first is done (which it says with a barrier as its last step).
     // The word behind its others tells whether it has.
@@ -1938,13 +1952,19 @@ struct Solver {
     // Steps C, G, W and D.
     __device__ __forceinline__ int solve_further() const
     {
+        if (in_vain()) return THEMIS_INFEASIBLE;
         int status = solve_c();
         if (status == TOO_MANY) {
+            if (in_vain()) return THEMIS_INFEASIBLE;
             out_of_line<PART_PRICE>();
             status = out_of_line<PART_NARROW>();
         }
-        if (status == ARE_LISTED) status = out_of_line<PART_GAP>();
         if (status == ARE_LISTED) {
+            if (in_vain()) return THEMIS_INFEASIBLE;
+            status = out_of_line<PART_GAP>();
+        }
+        if (status == ARE_LISTED) {
+            if (in_vain()) return THEMIS_INFEASIBLE;
             const Survivors l = survivors();
             const int W = __builtin_amdgcn_readfirstlane((int)l.plan[0]);
             const int most = __builtin_amdgcn_readfirstlane((int)l.plan[1]);
@@ -1954,12 +1974,14 @@ struct Solver {
             if (status == UNFINISHED && in_lds) status = out_of_line<PART_ROWS>(W);
             else if (status == UNFINISHED && cells <= args->hrow_stride) {
                 wait_for_rows();
+                if (in_vain()) return THEMIS_INFEASIBLE;
                 status = out_of_line<PART_ROWS_HBM>(W);
             }
             if (status == UNFINISHED) status = out_of_line<PART_TRIAL>(MOST_TRIALS);
         }
         if (status != UNFINISHED) return status;
         wait_for_rows();
+        if (in_vain()) return THEMIS_INFEASIBLE;
         return out_of_line<PART_WD>();
     }
 
