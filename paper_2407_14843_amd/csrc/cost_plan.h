@@ -95,7 +95,9 @@ constexpr CostLds cost_lds(int S, int window, int words = 0)
 }
 
 // A launch's window (cells of the largest one with rows in LDS) and LDS.
-constexpr int LDS_PER_CU = 160 * 1024, LDS_UNIT = 1280;  // bytes; LDS is granted in whole units
+// bytes; LDS is granted in whole units, and a kernel that may have more than LDS_UNASKED needs an
+// attribute set, which takes the host 0.14 us
+constexpr int LDS_PER_CU = 160 * 1024, LDS_UNIT = 1280, LDS_UNASKED = 64 * 1024, LDS_MOST = LDS_PER_CU / 2;
 constexpr int MAX_WINDOW = 8192;
 // Wavefronts of a compute unit that share its LDS, and how many of them are resident then, as
 // what 28 leave each other is five units.  Registers allow 32, but some twenty are in flight on
@@ -128,6 +130,9 @@ inline LdsPlan lds_plan(int S, int spread, int groups, int waves, int cus)
     const bool all = per_cu <= RESIDENT_PER_CU / waves;
     int bytes = all ? LDS_PER_CU / LDS_UNIT / (per_cu < few ? few : per_cu) * LDS_UNIT
                     : LDS_PER_CU / (per_cu > most ? most : per_cu);
+    // (60 x 64 models whose rows by cost are in HBM with less than is unasked take 163 us instead
+    // of 109, up to 16 models nothing does)
+    if (S <= 16 && bytes > LDS_UNASKED) bytes = LDS_UNASKED / LDS_UNIT * LDS_UNIT;
     // (the least there is to have, and what no further workgroup could have: stability test of
     // 4096 x 16 models 56.6 us without that, 43.1 with it)
     const int least = filled(bytes_for(64));

@@ -2177,9 +2177,10 @@ hipError_t launch_per_instance(const themis_problem_t& p, const Layout& L, CostA
     const int room = lds.words - cost_lds(L.S, a.window).tab;
     a.window_hbm = (fit < room ? fit : room) & ~63;
     a.wave_words = waves > 1 ? (uint32_t)(lds.words + WAVE_FLAGS) : 0u;
-    // (at most 40 KB of LDS, which a kernel may have without asking)
     const CostKernel k = kernel(front_layout(L.S, p.n_batch).width);
     hipError_t e = hipSuccess;
+    if (lds.bytes > LDS_UNASKED)
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_MOST);
     in_launches(grid, [&](int first, int count) {
         if (e != hipSuccess) return;
         const dim3 groups((unsigned)count), lanes(64 * waves);
