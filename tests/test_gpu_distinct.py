@@ -1,11 +1,16 @@
 """GPU parity for the solve that handles every distinct instance once: its
 outputs must equal the CPU checker's on the whole batch, duplicates and invalid
-instances included, and equal those of the plain solve.  Integer work: every
+instances included, and equal those of the plain solve, for batches that are solved as they are
+and for the same instances again and again in one beyond that.  Integer work: every
 output must be equal."""
+
+from dataclasses import replace
 
 import numpy as np
 import pytest
 
+from cost_families import family
+from distinct_calls import distinct, side_by_side
 from paper_2407_14843_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
@@ -49,6 +54,7 @@ def test_joint_with_recurring_instances(T, oracle, idx, pool, n):
     same(got, oracle.solve(w))
     b.solve()
     same(b.results(), got)
+    distinct(T, w, got)
 
 
 def test_vertical_with_recurring_replicas(T, oracle):
@@ -58,7 +64,9 @@ def test_vertical_with_recurring_replicas(T, oracle):
     w.r_fixed[::3] = np.maximum(1, w.r_fixed[::3] - 1)
     b = T.DeviceBatch(w)
     b.solve_distinct()
-    same(b.results(), oracle.solve(w))
+    want = oracle.solve(w)
+    same(b.results(), want)
+    distinct(T, w, want)
 
 
 def test_trace_sweep_shares_everything_but_the_rate(T, oracle):
@@ -93,6 +101,7 @@ def test_invalid_instances_and_their_copies(T, oracle):
     got = b.results()
     same(got, oracle.solve(w))
     assert (got[0][[5, 6, 7, 8, 9]] == 2).all()
+    distinct(T, w, got)
 
 
 def test_all_distinct_and_single_instance(T, oracle):
@@ -104,7 +113,13 @@ def test_all_distinct_and_single_instance(T, oracle):
             w.slo_us = (w.slo_us % (w.slo_max_us + 1)).astype(np.int32)
         b = T.DeviceBatch(w)
         b.solve_distinct()
-        same(b.results(), oracle.solve(w))
+        want = oracle.solve(w)
+        same(b.results(), want)
+        distinct(T, w, want)
+    # no instance twice, and more of them than are solved as they are
+    w = wl.workload(1, side_by_side() + 200)
+    assert len(np.unique(w.coef.reshape(w.n_inst, -1), axis=0)) == w.n_inst
+    distinct(T, w, oracle.solve(w, threads=8))
 
 
 def test_tiny_random_with_repeats_and_options(T, oracle):
@@ -118,9 +133,12 @@ def test_tiny_random_with_repeats_and_options(T, oracle):
             base.slo_us = (base.slo_us % (base.slo_max_us + 1)).astype(np.int32)
         w = with_repeats(base, rng, int(rng.integers(1, 80)))
         w = w.with_model(queue_model=int(rng.integers(0, 3)))
-        b = T.DeviceBatch(w, prune=int(rng.integers(0, 4)))
+        prune = int(rng.integers(0, 4))
+        b = T.DeviceBatch(w, prune=prune)
         b.solve_distinct()
-        same(b.results(), oracle.solve(w))
+        want = oracle.solve(w)
+        same(b.results(), want)
+        distinct(T, w, want, prune)
 
 
 def test_twice_on_one_workspace_and_on_a_stream(T, oracle):
@@ -137,6 +155,27 @@ def test_twice_on_one_workspace_and_on_a_stream(T, oracle):
     b.status.fill_(77)
     b.solve_distinct()
     same(b.results(), want)
+    distinct(T, w, want, stream=st)
+
+
+# Lanes per model 4, 8 and 16, pairs without gaps, in turns and in rounds of models; each with every
+# queue model, both profiles, replicas derived and given, coefficients of its own or shared.
+@pytest.mark.parametrize("S,n_batch", [(16, 4), (8, 7), (4, 16), (7, 9), (9, 9), (33, 2)])
+@pytest.mark.parametrize("queue", [0, 1, 2])
+def test_listed_in_every_form(T, oracle, S, n_batch, queue):
+    rng = np.random.default_rng([S, n_batch, queue])
+    w = family([S, n_batch, 11], 90, S, 7, list(range(1, n_batch + 1)), min(40, 32767 // (S * 7)), 250,
+               S * 60_000, (10, 900)).take(rng.integers(0, 90, 120))
+    shared = replace(w, coef_shared=True, coef=np.ascontiguousarray(w.coef[0]))
+    for base in (w, shared):
+        # a profile that differs in the sixth coefficient only is another one
+        delta = rng.integers(0, 300, base.coef.shape[:-1])
+        for v in (base.with_model(queue, None), base.with_model(queue, delta)):
+            given = v.with_r_fixed(rng.integers(1, 3, (v.n_inst, S)))
+            for x in (v, given):
+                print(f"[case] distinct {S} models, {n_batch} batch sizes, queue {queue}, profile "
+                      f"{x.profile_form}, given {x.r_fixed is not None}, shared {x.coef_shared}", flush=True)
+                distinct(T, x, oracle.solve(x, threads=8), sizes=("beyond",))
 
 
 def test_argument_checks(T):

@@ -5,31 +5,11 @@ from other calls.  Integer work: every output must be equal."""
 import numpy as np
 import pytest
 
+from distinct_calls import NAMES, side_by_side
 from paper_2407_14843_amd import workloads as wl
+from test_gpu_cost_solve import T  # noqa: F401
 
 pytestmark = pytest.mark.gpu
-
-NAMES = ("status", "cost", "ticks", "cfg")
-
-
-@pytest.fixture(scope="module")
-def T():
-    import torch
-    assert torch.cuda.is_available(), "these tests need the GPU"
-    from paper_2407_14843_amd import themis
-    themis.lib()
-    return themis
-
-
-@pytest.fixture(scope="module")
-def oracle():
-    from oracle import oracle as o
-    return o
-
-
-def side_by_side():
-    import torch
-    return 4 * torch.cuda.get_device_properties(0).multi_processor_count
 
 
 def batch(oracle, idx, pool, n, seed, shared=False):

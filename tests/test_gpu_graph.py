@@ -6,6 +6,7 @@ library between the replays."""
 import numpy as np
 import pytest
 
+from distinct_calls import side_by_side
 from paper_2407_14843_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
@@ -74,12 +75,16 @@ def test_captured_fallback_replays(T, oracle):
             assert np.array_equal(got[k], want[k]), f"replay {rep}: {k} differs"
 
 
-def test_captured_distinct_solve_replays(T, oracle):
+# one launch, or (beyond an instance per SIMD) four that depend on one another
+@pytest.mark.parametrize("n", [400, 1700])
+def test_captured_distinct_solve_replays(T, oracle, n):
     import torch
     rng = np.random.default_rng(5)
     base = wl.workload(1, 40)
-    w = base.take(rng.integers(0, base.n_inst, 400))   # most inputs recur
-    want = oracle.solve(w, threads=8)
+    pick = rng.integers(0, base.n_inst, n)             # most inputs recur
+    w = base.take(pick)
+    want = tuple(x[pick] for x in oracle.solve(base, threads=8))
+    assert (n > side_by_side()) == (n > 400)
     print("[case] graph capture distinct-instance solve", flush=True)
     b = T.DeviceBatch(w)
     s = torch.cuda.Stream()

@@ -5,6 +5,7 @@ Whole numbers: no tolerance."""
 import numpy as np
 import pytest
 
+from distinct_calls import distinct
 from paper_2407_14843_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
@@ -77,7 +78,9 @@ def test_given_cores_and_the_rest(T, oracle, batch_sizes):
     assert (stable.cpu().numpy() == want[0]).all()
     same(b.results(), want[1:])
     b.solve_distinct()
-    same(b.results(), oracle.solve(w, threads=8))
+    want = oracle.solve(w, threads=8)
+    same(b.results(), want)
+    distinct(T, w, want, sizes=("beyond",))
     v = w.with_r_fixed(np.ones((w.n_inst, 2), np.int32))
     v.lam = (v.lam * 5).astype(np.int32)
     b = T.DeviceBatch(v)

@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 
 from cost_families import families, family, over_base
+from distinct_calls import distinct
 from paper_2407_14843_amd import workloads as wl
 from solve_steps import STEPS, steps_by_rule, steps_of
 from test_gpu_cost_solve import T, same  # noqa: F401
@@ -112,7 +113,9 @@ def test_every_form(T, oracle, name, queue, delta):
     solved(T, oracle, w)
     b = T.DeviceBatch(w)
     b.solve_distinct()
-    same(b.results(), oracle.solve(w, threads=8))
+    want = oracle.solve(w, threads=8)
+    same(b.results(), want)
+    distinct(T, w, want, sizes=("beyond",))
     for cores in (None, rng.integers(1, w.c_max + 1, (w.n_inst, w.n_stage)).astype(np.int32)):
         b.solve_horizontal(cores)
         same(b.results(), oracle.solve(w, threads=8, c_fixed=cores if cores is not None
