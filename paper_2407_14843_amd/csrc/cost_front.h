@@ -31,12 +31,13 @@ namespace {
 // its batch sizes in turns (a power of two of lanes, or where that takes fewer turns as many as
 // all models leave room for, with minima through LDS).  A lane then keeps its model, and is done
 // with all of its batch sizes before minima and sums are formed.  ROUNDS: where that leaves too
-// many lanes idle (front_layout() has the rule), the models in rounds of args->per_round, in
-// lanes for all of their batch sizes (round_log below zero: without gaps), with their inputs
-// asked for again, minima and sums formed in each, and what is found about them in LDS.  (That
-// way 3001 x 7 models with twelve batch sizes take 11.8 us and in turns 10.4, 59755 x 7 with
+// many lanes idle (front_layout() has the rule; single solves only), the models in rounds of
+// args->per_round, in lanes for all of their batch sizes (round_log below zero: without gaps),
+// with their inputs asked for again, minima and sums formed in each, and what is found about
+// them in LDS.  (That way 3001 x 7 models with twelve batch sizes take 11.8 us and in turns 10.4, 59755 x 7 with
 // fourteen and replicas given 246 and 203, fallback 13320 x 9 with fifteen 105 and 59, 186 x 10
-// with seven 30.6 and 32.4, 50 shapes drawn from one to ten models 1.12 times as long in the mean.)
+// with seven 30.6 and 32.4, on other inputs 6.48 and 6.53; 43 shapes of five to ten models, four calls and three batches each, are
+// in turns done in 0.84 of the time in the mean and 1.02 at most.)
 // (One kernel for the widths 4, 8 and 16, with the width an argument:
 // 86400 x 6 43.6 us instead of 39.8, fallback 16384 x 8 30.8 instead of 28.5, 65536 x 8 79.5
 // instead of 76.4, 512 x 5 7.4 instead of 7.0.)
@@ -422,15 +423,7 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
     template <bool SMALL>
     __device__ __forceinline__ uint32_t fastest_ticks(const Start& first) const
     {
-        if constexpr (WIDTH == ROUNDS) {
-            uint32_t sum = 0u;
-            for_pairs(first, [&](const Pair& p) {
-                sum += sum_of_models(p, model_least(p, turned(p, meet<SMALL>(p, p.last))) >> 15);
-            });
-            return sum;
-        } else {
-            return sum_of_models(first, fastest_of<SMALL>(first) >> 15);
-        }
+        return sum_of_models(first, fastest_of<SMALL>(first) >> 15);
     }
 
     // ---- the tables of steps B and C ----------------------------------------------
@@ -632,14 +625,9 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
     {
         Best mine{EMPTY, EMPTY, 0u, 1u, EMPTY, 0, false};
         uint32_t ticks = 0u, base_sum;
-        bool vain = false;  // (asked ahead of each of several pairs)
-        auto go_on = [&] {
-            vain = vain || this->in_vain();
-            return !vain;
-        };
+        bool vain = false;
         if constexpr (WIDTH == ROUNDS) {
             for_pairs(first, [&](const Pair& p) {
-                if (!go_on()) return;
                 const Best b = best_of<SMALL>(p);
                 ticks += sum_of_models(p, b.key == EMPTY ? LT_NONE : b.key & 0x7FFFu);
                 if (leads(p)) {
@@ -652,7 +640,8 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
                 mine = best_of<SMALL>(first);
             } else {
                 for_pairs<DERIVE>(first, [&](const Pair& p) {
-                    if (go_on()) improve<SMALL>(mine, p);
+                    vain = vain || this->in_vain();
+                    if (!vain) improve<SMALL>(mine, p);
                 });
                 mine.key = model_least(first, mine.own);
                 const uint32_t k = mine.own == mine.key ? mine.k : EMPTY;
@@ -685,7 +674,6 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
         uint32_t fast = 0u, least_ticks = 0u;
         if constexpr (WIDTH == ROUNDS) {
             for_pairs(first, [&](const Pair& p) {
-                if (!go_on()) return;
                 const uint32_t f = model_least(p, turned(p, meet<SMALL>(p, p.last)));
                 least_ticks += sum_of_models(p, f >> 15);
                 if (leads(p)) this->fastest()[p.s] = f;
@@ -864,14 +852,14 @@ struct Front : Solver<QUEUE, DERIVE, ROLE> {
 
 // The rate the given replicas of an instance are solved at (see Front::search_rate()), where
 // products exceed 2^42.
-template <int QUEUE, int MANY>
+template <int QUEUE>
 __device__ __attribute__((noinline)) int32_t rate_of_large(uint64_t args, int i, int T, int32_t lam,
                                                            int32_t slo)
 {
     auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
     const uint64_t lo = (uint32_t)uniform((int)(uint32_t)args);
     const uint64_t hi = (uint32_t)uniform((int)(uint32_t)(args >> 32));
-    Front<QUEUE, false, MANY, QUIET> sv((ArgsPtr)(uintptr_t)(hi << 32 | lo));
+    Front<QUEUE, false, TURNS, QUIET> sv((ArgsPtr)(uintptr_t)(hi << 32 | lo));
     sv.instance(uniform(i), uniform(T), uniform(lam), uniform(slo));
     const auto first = sv.start();
     return uniform(sv.template fastest_ticks<false>(first) <= (uint32_t)sv.T

@@ -48,7 +48,7 @@ __device__ __forceinline__ void fallback_instance(ArgsPtr args, int i)
                 first = sv.at_rate(first);
             }
         } else if (valid) {
-            rate = rate_of_large<QUEUE, decltype(sv)::MANY>((uint64_t)(uintptr_t)args, i, sv.T, lambda, sv.slo);
+            rate = rate_of_large<QUEUE>((uint64_t)(uintptr_t)args, i, sv.T, lambda, sv.slo);
             sv.lam = rate = __builtin_amdgcn_readfirstlane(rate);
             first = sv.at_rate(first);
         }
@@ -180,7 +180,6 @@ CostKernel fallback_kernel(int width)
 {
     switch (width) {
     case WIDTH_PACKED: return &kc_fallback<QUEUE, PACKED>;
-    case WIDTH_ROUNDS: return &kc_fallback<QUEUE, ROUNDS>;
     case 4: return &kc_fallback<QUEUE, 4>;
     case 8: return &kc_fallback<QUEUE, 8>;
     case 16: return &kc_fallback<QUEUE, 16>;
@@ -193,7 +192,6 @@ CostKernel stability_kernel(int width)
 {
     switch (width) {
     case WIDTH_PACKED: return &kc_stability<QUEUE, PACKED, TWO>;
-    case WIDTH_ROUNDS: return &kc_stability<QUEUE, ROUNDS, TWO>;
     case 4: return &kc_stability<QUEUE, 4, TWO>;
     case 8: return &kc_stability<QUEUE, 8, TWO>;
     case 16: return &kc_stability<QUEUE, 16, TWO>;
@@ -214,7 +212,7 @@ hipError_t launch_cost_fallback(const themis_problem_t& p, const Layout& L, cons
                                 hipStream_t st)
 {
     CostArgs a = cost_args(p, L, d_coef, d_lambda, d_slo_us, d_r_fixed, out.status, out.cost,
-                           out.ticks, out.cfg, ws, PassOpts());
+                           out.ticks, out.cfg, ws, PassOpts(), WORK_FEW);
     a.status2 = out.status_h;
     a.cost2 = out.cost_h;
     a.ticks2 = out.ticks_h;
@@ -237,7 +235,7 @@ hipError_t launch_cost_stability(const themis_problem_t& p, const Layout& L,
                                  hipStream_t st, const PassOpts& opts)
 {
     CostArgs a = cost_args(p, L, d_coef, d_lambda_now, d_slo_us, nullptr, d_status, d_cost, d_ticks,
-                           d_cfg, ws, opts);
+                           d_cfg, ws, opts, WORK_FEW);
     a.lambda2 = d_lambda_pred;
     a.stable = d_stable;
     a.status2 = (int32_t*)(ws + B.status_off);

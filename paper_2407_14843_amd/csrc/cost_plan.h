@@ -15,18 +15,22 @@ struct FrontLayout {
     int round_log, per_round;    // the same of a round of whole models, and the models of one
 };
 
+// What is sought of a (model, batch size) pair: of many candidates with the replicas derived, of
+// those with the replicas given, or of one (one core count), or that of the fallback besides.
+enum FrontWork { WORK_DERIVED, WORK_GIVEN, WORK_FEW };
+
 // Lanes per model: a power of two, or where that takes more turns (or doesn't fit) as many as
 // there are batch sizes or all models leave room for (9 x 14: seven and two turns, not four
 // and four).
 //
-// Where there are more pairs than lanes: in turns if that takes no more of them than whole models
-// take rounds, with two lanes per model or more.  Turns leave lanes idle where the models don't
-// divide the wavefront: 12 x 16 in four turns 39.3 us, in three rounds 34.1 (7000 pipelines);
-// 22 x 16, eight and six: 87.1 and 73.8; 300 x 33 x 16, sixteen and nine: 112 and 69.  A single
-// lane per model has no other's candidates to go by: 300 x 63 x 3, three of either, 10.8 and
-// 8.4.  With as many of either, and two lanes, turns take 0.84 to 0.99 of the time in the mean
-// of a shape.
-inline FrontLayout front_layout(int S, int n_batch)
+// Where there are more pairs than lanes: in turns, but where they leave lanes idle that whole models
+// in rounds put to use, as the models don't divide the wavefront, and what the pairs still have
+// to do then counts.  Turns against rounds in the time of 150 shapes of 11 to 64 models, at 300
+// and 7000 pipelines: derived with as few turns as rounds 0.85 to 1.05 (mean 0.97), with more 1.02
+// to 1.50 (12 x 16 1.09, 33 x 16 1.47), and as many of either but a single lane per model, which
+// has no other's candidates to go by, 0.97 to 1.11; given 0.77 to 1.02, but with more turns and a
+// single lane 0.93 to 1.20; one candidate 0.81 to 1.00; fallback 0.65 to 1.00.
+inline FrontLayout front_layout(int S, int n_batch, FrontWork work)
 {
     FrontLayout f{};
     while (1 << f.width_log < n_batch) ++f.width_log;
@@ -41,8 +45,12 @@ inline FrontLayout front_layout(int S, int n_batch)
     auto turns = [&](int lanes) { return (n_batch + lanes - 1) / lanes; };
     if (turns(fit) < turns(f.lanes)) f.lanes = fit, f.width_log = -1;
     f.turns = turns(f.lanes);
+    const int most = rounds(f.per_round);
+    const bool fewer = work == WORK_DERIVED ? f.turns < most + (f.lanes > 1)
+                       : work == WORK_GIVEN ? f.turns <= most || f.lanes > 1
+                                            : true;
     if (f.turns > 1)
-        f.width = f.lanes > 1 && f.turns <= rounds(f.per_round) ? WIDTH_TURNS : WIDTH_ROUNDS;
+        f.width = fewer ? WIDTH_TURNS : WIDTH_ROUNDS;
     else
         f.width = f.width_log >= 2 ? 1 << f.width_log : WIDTH_PACKED;
     return f;

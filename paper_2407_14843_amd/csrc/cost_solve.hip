@@ -41,7 +41,8 @@
 //   B  else the recurrence over the first 8 or 16 cells: one table of (lt, index) by
 //      model and cost over base in LDS, lane = (model, cell), rows of neighbouring models
 //      combined in turns.  How late the candidates of step A are says which it takes.
-//   C  else over 64 cells, rows in LDS, lane = cell;
+//   C  else over 64 cells, rows in LDS, lane = two cells, the halves of the wavefront for the even
+//      and the odd costs over base;
 //   G  else lists of the candidates (of all, or where those do not fit of those that
 //      Lagrangian bounds leave), those that the bounds show to be in no answer dropped, and
 //      every combination of what is left, a few candidates per model; or the recurrence
@@ -130,7 +131,10 @@ hipError_t launch_cost_solve(const themis_problem_t& p, const Layout& L, const i
                              const PassOpts& opts)
 {
     CostArgs a = cost_args(p, L, d_coef, d_lambda, d_slo_us, d_r_fixed, d_status, d_cost, d_ticks,
-                           d_cfg, ws, opts);
+                           d_cfg, ws, opts,
+                           d_r_fixed                                           ? WORK_GIVEN
+                           : opts.c_fixed || opts.c_all > 0 || p.c_max == 1 ? WORK_FEW
+                                                                               : WORK_DERIVED);
     const bool listed = opts.list != nullptr;
     return launch_per_instance(p, L, a, st, listed, [&](int width) {
         switch (p.queue_model) {

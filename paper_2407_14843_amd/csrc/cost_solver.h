@@ -56,6 +56,7 @@ struct CostArgs : HotArgs {
     int32_t lds_words;    // of one wavefront, see CostLds
     uint32_t wave_words;  // LDS words of each wavefront of a workgroup (0: there is one)
     uint32_t parts, pair_magic;  // lanes per (model, batch size) pair of a sweep, see sweep()
+    int32_t width;         // how the pairs lie in the wavefront, see Front
     int32_t lanes, turns;  // lanes per model, and the batch sizes of each, see Front
     uint32_t lane_magic;   // index_magic() of them
     int32_t round_log, per_round;  // see FrontLayout
@@ -2072,7 +2073,8 @@ typedef void (*CostKernel)(CostArgs);
 inline CostArgs cost_args(const themis_problem_t& p, const Layout& L, const int32_t* d_coef,
                           const int32_t* d_lambda, const int32_t* d_slo_us,
                           const int32_t* d_r_fixed, int32_t* d_status, int32_t* d_cost,
-                          int32_t* d_ticks, int32_t* d_cfg, char* ws, const PassOpts& opts)
+                          int32_t* d_ticks, int32_t* d_cfg, char* ws, const PassOpts& opts,
+                          FrontWork work)
 {
     CostArgs a{};
     a.coef = d_coef;
@@ -2104,7 +2106,8 @@ inline CostArgs cost_args(const themis_problem_t& p, const Layout& L, const int3
         a.bc[j] = {(1.0 / (1.0e6 * b)) * (1.0 - 0x1p-45), 1.0e6 * (b - 1.0), (float)(1.0e6 * b),
                    (float)(b / (2.0 * b - 1.0)), p.batch_sizes[j]};
     }
-    const FrontLayout front = front_layout(L.S, p.n_batch);
+    const FrontLayout front = front_layout(L.S, p.n_batch, work);
+    a.width = front.width;
     a.width_log = front.width_log;
     a.lanes = front.lanes;
     a.turns = front.turns;
@@ -2177,7 +2180,7 @@ hipError_t launch_per_instance(const themis_problem_t& p, const Layout& L, CostA
     const int room = lds.words - cost_lds(L.S, a.window).tab;
     a.window_hbm = (fit < room ? fit : room) & ~63;
     a.wave_words = waves > 1 ? (uint32_t)(lds.words + WAVE_FLAGS) : 0u;
-    const CostKernel k = kernel(front_layout(L.S, p.n_batch).width);
+    const CostKernel k = kernel(a.width);
     hipError_t e = hipSuccess;
     if (lds.bytes > LDS_UNASKED)
         e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_MOST);

@@ -5,11 +5,6 @@
 
 #include <mutex>
 
-namespace themis {
-// Whether the wavefront of every instance of such a batch has a SIMD to itself (cost_solve.hip).
-bool cost_solve_side_by_side(const Layout& L);
-}  // namespace themis
-
 using namespace themis;
 
 // Workspace of themis_solve_joint_static: one array per GPU, held from the
@@ -261,10 +256,13 @@ int themis_solve_distinct(const themis_problem_t* p, const int32_t* d_coef,
         return THEMIS_ERR_WORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(stream);
     char* w = static_cast<char*>(d_workspace);
-    // Up to a wavefront per SIMD the instances that recur take nothing away from the others, and to
-    // find them and hand out their results (three launches more) only adds to the time: 3 x 2
-    // 16.2 us by way of it and 7.3 without, 451 x 1 16.8 and 7.9, 979 x 8 18.8 and 7.8.  With
-    // more it depends on what they are: 10446 x 2 19.0 and 8.2, 18297 x 6 37.6 and 59.5.
+    // Up to a wavefront per SIMD the instances that recur take next to nothing away from the
+    // others, and to find them and hand out their results (three launches more) adds to the time:
+    // 3 x 2 16.2 us by way of it and 7.3 without, 979 x 8 18.8 and 7.8, 1000 x 3 of the longest
+    // lists 104 and 82, 1024 x 32 with rows in HBM 296 and 73; only with rows over the budget
+    // (step D) in all of them it is the other way round, 1024 x 4 889 and 950.  With more
+    // it depends on what they are: 2000 was faster without in 60 calls out of 60, but 4000 of the
+    // long lists 81 and 109, 7000 x 3 34 and 45; 10446 x 2 19.0 and 8.2, 18297 x 6 37.6 and 59.5.
     if (cost_solve_side_by_side(L))
         return pass(*p, L, d_coef, d_lambda, d_slo_us, d_r_fixed, d_status, d_cost, d_ticks, d_cfg,
                     w, st, PassOpts());

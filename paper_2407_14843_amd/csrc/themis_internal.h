@@ -283,6 +283,8 @@ struct PassOpts {
 // The one-wavefront solve: three stages' worth of results in one launch.
 constexpr int COST_MAX_STAGES = 64;  // a lane per model
 bool cost_solve_serves(const Layout& L);
+// Whether the wavefront of every instance of such a batch has a SIMD to itself.
+bool cost_solve_side_by_side(const Layout& L);
 // A launch has a wavefront per instance, and HIP takes fewer than 2^32 work-items, so
 // larger batches (of up to 2^28 instances) take several: launch(first, count) for each.
 constexpr int MAX_PER_LAUNCH = 1 << 25;
@@ -403,8 +405,8 @@ inline StabilityLayout make_stability_layout(const Layout& L)
     return B;
 }
 
-// The entry points that solve an instance more than once, an instance's solves by one
-// wavefront (cost_multi.hip); for problems that cost_solve_serves().
+// The entry points that solve an instance more than once, all of an instance's solves in one
+// launch (cost_multi.hip); for problems that cost_solve_serves().
 hipError_t launch_cost_fallback(const themis_problem_t& p, const Layout& L, const int32_t* d_coef,
                                 const int32_t* d_lambda, const int32_t* d_slo_us,
                                 const int32_t* d_r_fixed, const FallbackOut& out, char* ws,

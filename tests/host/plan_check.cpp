@@ -3,7 +3,8 @@
 // with the layout, not from the formulas under test:
 //   every (model, batch size) pair is taken once, by a lane of the wavefront;
 //   where there are more pairs than lanes, no more of them one after the other than whole
-//   models side by side would take, with or without gaps between them;
+//   models side by side would take, with or without gaps between them, if there is a choice
+//   among many candidates, or the lane has no other's to go by;
 //   what step C has in LDS at one time lies apart and inside the wavefront's words, and takes
 //   no more of them than its table, rows and the copy of one, or below 16 models 32 more;
 //   the lists of step G have room for fourteen candidates of a model;
@@ -31,9 +32,9 @@ static int failures = 0;
 
 static int up(int a, int b) { return (a + b - 1) / b; }
 
-static void check_lanes(int S, int nb)
+static void check_lanes(int S, int nb, FrontWork work)
 {
-    const FrontLayout f = front_layout(S, nb);
+    const FrontLayout f = front_layout(S, nb, work);
     for (int spread = 0; spread < 2; ++spread) {
         std::vector<int> taken(S * nb, 0);
         int steps = 0;
@@ -43,7 +44,6 @@ static void check_lanes(int S, int nb)
         if (f.width == WIDTH_TURNS) {
             steps = f.turns;
             CHECK(f.width_log < 0 || f.lanes == 1 << f.width_log, "%d x %d", S, nb);
-            CHECK(f.lanes > 1, "%d x %d", S, nb);
             for (int lane = 0; lane < 64; ++lane)
                 for (int t = 0; t < f.turns; ++t) {
                     const int part = lane % f.lanes;
@@ -67,8 +67,15 @@ static void check_lanes(int S, int nb)
         int width = S <= 16 ? 4 : 1;
         while (width < nb) width *= 2;
         const int with_gaps = up(S, 64 / width), without = up(S, 64 / nb);
-        CHECK(steps <= (with_gaps < without ? with_gaps : without), "%d x %d, width %d: %d steps", S, nb,
-              f.width, steps);
+        const int rounds = with_gaps < without ? with_gaps : without;
+        // where the pairs' candidates count, or a lane has the model to itself
+        if (work == WORK_DERIVED || (work == WORK_GIVEN && f.lanes == 1))
+            CHECK(steps <= rounds, "%d x %d, width %d: %d steps", S, nb, f.width, steps);
+        if (work == WORK_DERIVED && f.width == WIDTH_TURNS && f.lanes == 1)
+            CHECK(steps < rounds, "%d x %d: %d steps", S, nb, steps);
+        // and else turns
+        if (work == WORK_FEW || (work == WORK_GIVEN && f.lanes > 1))
+            CHECK(f.width != WIDTH_ROUNDS, "%d x %d, width %d", S, nb, f.width);
     }
     // what is sought per model goes by these in code shared between the layouts
     CHECK(f.lanes >= 1 && f.turns * f.lanes >= nb && S * f.lanes <= 64, "%d x %d", S, nb);
@@ -133,7 +140,8 @@ int main()
                 for (int spread : {1, 100, 32767}) check_launch(S, spread, groups, waves);
     for (int S = 1; S <= 64; ++S) check_step_c(S);
     for (int S = 1; S <= 64; ++S)
-        for (int nb = 1; nb <= 16; ++nb) check_lanes(S, nb);
+        for (int nb = 1; nb <= 16; ++nb)
+            for (FrontWork work : {WORK_DERIVED, WORK_GIVEN, WORK_FEW}) check_lanes(S, nb, work);
     if (failures) {
         std::printf("%d failures\n", failures);
         return 1;
