@@ -41,13 +41,13 @@ VALU_PEAK_GOPS = N_CU * 64 * CLOCK_GHZ                          # 39322 G lane-o
 # the counters were taken on, fingerprint of the kernel sources at that time).
 # `roofline.traffic` is null unless both still match this run.
 K2_HBM_TRAFFIC = {
-    "w1-joint-4096x5": (116324009, 5247396664, "a86600b4f43d6885"),
-    "w3-joint-65536x8": (11100893315, 1422380424686, "a86600b4f43d6885"),
+    "w1-joint-4096x5": (116199040, 5247396664, "7766d1a6dab2edbb"),
+    "w3-joint-65536x8": (11101167744, 1422380424686, "7766d1a6dab2edbb"),
 }
 # the same for stage 1 (input check + candidate kernel): workload -> (bytes, fingerprint)
 K1_HBM_TRAFFIC = {
-    "w1-joint-4096x5": (20103389, "a86600b4f43d6885"),
-    "w3-joint-65536x8": (1064513773, "a86600b4f43d6885"),
+    "w1-joint-4096x5": (20041664, "7766d1a6dab2edbb"),
+    "w3-joint-65536x8": (1057004832, "7766d1a6dab2edbb"),
 }
 KERNEL_SOURCES = ("k1_candidates.hip", "candidate_eval.h", "wave_ops.h", "k2_minplus.hip",
                   "instance_queue.h", "themis_internal.h")
@@ -56,8 +56,8 @@ KERNEL_SOURCES = ("k1_candidates.hip", "candidate_eval.h", "wave_ops.h", "k2_min
 # vector instructions of the timed whole solve per instance (the pipe counters in
 # profiles/*_kernel_trace.txt): workload -> (instructions, fingerprint of its sources)
 SOLVE_VALU = {
-    "w1-joint-4096x5": (383.2, "417d2880813c0c4a"),
-    "w3-joint-65536x8": (465.7, "417d2880813c0c4a"),
+    "w1-joint-4096x5": (383.2, "8d45e123c5d9106a"),
+    "w3-joint-65536x8": (465.3, "8d45e123c5d9106a"),
 }
 SOLVE_SOURCES = ("cost_solve.hip", "cost_front.h", "cost_solver.h", "cost_plan.h",
                  "candidate_eval.h", "wave_ops.h", "themis_internal.h")

@@ -34,10 +34,11 @@ namespace {
 // many lanes idle (front_layout() has the rule; single solves only), the models in rounds of
 // args->per_round, in lanes for all of their batch sizes (round_log below zero: without gaps),
 // with their inputs asked for again, minima and sums formed in each, and what is found about
-// them in LDS.  (That way 3001 x 7 models with twelve batch sizes take 11.8 us and in turns 10.4, 59755 x 7 with
-// fourteen and replicas given 246 and 203, fallback 13320 x 9 with fifteen 105 and 59, 186 x 10
-// with seven 30.6 and 32.4, on other inputs 6.48 and 6.53; 43 shapes of five to ten models, four calls and three batches each, are
-// in turns done in 0.84 of the time in the mean and 1.02 at most.)
+// them in LDS.  (That way 3001 x 7 models with twelve batch sizes take 11.8 us and in turns 10.4,
+// 59755 x 7 with fourteen and replicas given 246 and 203, fallback 13320 x 9 with fifteen 105 and
+// 59, 186 x 10 with seven 30.6 and 32.4, on other inputs 6.48 and 6.53; 43 shapes of five to ten
+// models, four calls and three batches each, are in turns done in 0.84 of the time in the mean
+// and 1.02 at most.)
 // (One kernel for the widths 4, 8 and 16, with the width an argument:
 // 86400 x 6 43.6 us instead of 39.8, fallback 16384 x 8 30.8 instead of 28.5, 65536 x 8 79.5
 // instead of 76.4, 512 x 5 7.4 instead of 7.0.)

@@ -21,7 +21,7 @@
 // kernel around one-wavefront solves, eight launches and three, they took 250 and 28 us
 // at 16384 x 8 and 4099 x 5; as one launch each 65 and 23, with a solve at lambda ahead of
 // the search, an evaluation from the start for each of its midpoints and some sixty registers
-// spilled; now 26.7 and 11.8.  Pipelines of more than 64 models still go the other way, over the
+// spilled; now 27 and 12.  Pipelines of more than 64 models still go the other way, over the
 // three stages.
 #include "cost_front.h"
 
@@ -113,7 +113,8 @@ __device__ __forceinline__ void stability_instance(ArgsPtr args, int i)
 
 // The same with a wavefront for each of the two rates.  Two barriers each: the first one's first
 // is when its solve is done, the second one's before it uses the instance's rows in HBM or, if
-// it has no use for them, after its solve; then both have their results.
+// it has no use for them, after its solve; then both have their results.  A first one without a
+// solution says so ahead of its barrier, for the second to end its solve early (in_vain()).
 template <int QUEUE, int WIDTH>
 __device__ __forceinline__ void stability_pair(ArgsPtr args, int i)
 {

@@ -58,8 +58,8 @@
 // with the candidate tables and the rate search, so that all agree bit for bit),
 // against 0.3 KB of inputs and outputs; nothing but those touches HBM.  Whole solves
 // by the three stages (dense / with dominated candidates pruned) against this one, in
-// microseconds: 65536 x 8 models 25800 / 3880 -> 76, 16384 x 8 with replicas given
-// 3370 -> 22.5, 86400 x 6 2790 -> 40, 4096 x 5 177 -> 10.8, 64 x 3 27.2 -> 6.5.
+// microseconds: 65536 x 8 models 25800 / 3880 -> 72, 16384 x 8 with replicas given
+// 3370 -> 20, 86400 x 6 2790 -> 39, 4096 x 5 177 -> 10.0, 64 x 3 27.2 -> 6.3.
 #include "cost_front.h"
 
 namespace themis {
