@@ -56,8 +56,8 @@ KERNEL_SOURCES = ("k1_candidates.hip", "candidate_eval.h", "wave_ops.h", "k2_min
 # vector instructions of the timed whole solve per instance (the pipe counters in
 # profiles/*_kernel_trace.txt): workload -> (instructions, fingerprint of its sources)
 SOLVE_VALU = {
-    "w1-joint-4096x5": (383.2, "8d45e123c5d9106a"),
-    "w3-joint-65536x8": (465.3, "8d45e123c5d9106a"),
+    "w1-joint-4096x5": (383.2, "894a525917c435c6"),
+    "w3-joint-65536x8": (465.3, "894a525917c435c6"),
 }
 SOLVE_SOURCES = ("cost_solve.hip", "cost_front.h", "cost_solver.h", "cost_plan.h",
                  "candidate_eval.h", "wave_ops.h", "themis_internal.h")

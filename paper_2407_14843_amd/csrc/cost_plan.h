@@ -159,20 +159,21 @@ inline LdsPlan lds_plan(int S, int spread, int groups, int waves, int cus)
 
 // Whether an instance's two solves of the stability test get a wavefront each.
 //
-// That halves its chain where there is one (a single model is done with step A), and where most
-// instances have one it is the sooner done of the two ways far beyond the twelve pairs per
-// compute unit that can be in flight.  Where next to all are done with step A, it is the launch of
-// twice the wavefronts that shows from 20 per compute unit on, the less the more models there
-// are; beyond 24 models few pairs are resident.  Microseconds in one wavefront and two, instances
-// that need steps B and C / that don't: 4099 x 5 models 35.5, 20.6 / 7.3, 7.0; 5000 x 3 16.4, 13.0 /
-// 6.9, 6.9; 6000 x 4 24.3, 21.9 / 7.3, 8.0; 7000 x 8 44.1, 28.1 / 11.6, 10.5; 9000 x 5 31.6, 30.8 /
-// 10.2, 10.8; 5000 x 33 216, 202 / 86, 78; 7000 x 33 255, 276 / 116, 112.
+// That halves its chain where there is one (a single model is done with step A), which shows far
+// beyond the twelve pairs per compute unit that can be in flight: of seven mixes of rates and
+// objectives, with half of the rates predicted to stay or none, pairs are the sooner done in most
+// up to 9000 instances of 2 to 33 models, at 15000 with few models no longer.  What they cost is
+// the launch of twice the wavefronts, where next to all instances are done with step A.
+// Microseconds in one wavefront and two, instances that need steps B and C / that don't: 4099 x 5
+// models 35.7, 20.7 / 7.3, 7.0; 7000 x 2 14.5, 13.3 / 7.9, 8.3; 6000 x 4 24.3, 21.9 / 7.3, 8.0;
+// 7000 x 8 47.0, 32.5 / 11.6, 10.5; 7000 x 33 271, 239 / 116, 112; 9000 x 3 21.7, 19.5 / 9.3, 9.9;
+// 15000 x 3 26.3, 26.7 / 12.7, 14.6; 15000 x 8 58.4, 46.9 / 16.5, 17.0.
 // The second wavefront's work is in vain where the first finds no solution, and it stops when it is
 // told.  If that is so for every instance of the batch: 2000 x 5 6.9, 6.9; 4099 x 5 6.8, 9.7;
 // 7000 x 5 6.9, 13.0; 4099 x 24 10.3, 23.8 (for half of them 15.4, 12.9; 18.7, 16.9; 113, 76).
 inline bool stability_in_pairs(int S, int instances, int cus)
 {
-    return S > 1 && instances <= (S >= 5 && S <= 24 ? 28 : 20) * cus;
+    return S > 1 && instances <= 28 * cus;
 }
 
 }  // namespace themis

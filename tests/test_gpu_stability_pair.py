@@ -1,7 +1,7 @@
 """The stability test with a wavefront for each of its two solves, on both sides of the batch
-size up to which it has them (20 instances per compute unit, 28 for 5 to 24 models), with one
-model and several, and with predicted rates that are the current one, differ, or are not valid.
-Whole numbers, so the oracle's answers word for word: no tolerance."""
+size up to which it has them (28 instances per compute unit), with one model and several, and
+with predicted rates that are the current one, differ, or are not valid.  Whole numbers, so the
+oracle's answers word for word: no tolerance."""
 
 import numpy as np
 import pytest
@@ -13,10 +13,10 @@ from test_gpu_cost_solve import T, same  # noqa: F401
 pytestmark = pytest.mark.gpu
 
 
-def in_pairs(S):
+def in_pairs():
     """The most instances that have two wavefronts each."""
     import torch
-    return (28 if 5 <= S <= 24 else 20) * torch.cuda.get_device_properties(0).multi_processor_count
+    return 28 * torch.cuda.get_device_properties(0).multi_processor_count
 
 
 # (beyond the bound the queue models: each has a kernel of its own)
@@ -30,7 +30,7 @@ def test_two_solves(T, oracle, name, more, queue):
     pred = np.where(rng.random(300) < 0.4, w.lam, w.lam + rng.integers(-3, 40, 300)).astype(np.int32)
     pred[11] = 0
     cores = rng.integers(1, w.c_max + 1, (300, w.n_stage)).astype(np.int32)
-    n = 300 if more is None else in_pairs(w.n_stage) + more
+    n = 300 if more is None else in_pairs() + more
     again = np.arange(n) % 300
     b = T.DeviceBatch(w.take(again))
     print(f"[case] stability {name}, {n} instances, queue {queue}", flush=True)
@@ -51,7 +51,7 @@ def test_one_wavefront(T, oracle, S, n_batch):
                S * 60_000, (10, 900))
     pred = np.maximum(1, w.lam + np.random.default_rng(S).integers(-3, 4, 240)).astype(np.int32)
     want = oracle.stability(w, pred)
-    again = np.arange(in_pairs(S) + 1) % 240
+    again = np.arange(in_pairs() + 1) % 240
     print(f"[case] stability {S} models, {n_batch} batch sizes, {again.size} instances", flush=True)
     b = T.DeviceBatch(w.take(again))
     stable = b.check_stability(pred[again])
